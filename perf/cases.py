@@ -224,6 +224,68 @@ def work(case):
     return {"bytes": bytes_, "flops": flops}
 
 
+def _gates(wl, logits, topk):
+    """Gate weights [T,k] of the selected experts; differentiable in the logits."""
+    chosen = logits.gather(1, topk)
+    if wl.gate_mode == W.GATE_SOFTMAX_RENORM:
+        return chosen.softmax(dim=1)
+    if wl.gate_mode == W.GATE_SIGMOID_RENORM:
+        s = chosen.sigmoid()
+        return s / s.sum(dim=1, keepdim=True)
+    return logits.softmax(dim=1).gather(1, topk)
+
+
+def exact(case, seed):
+    """The same outputs in float64 from torch's own products, one expert after the other; nothing for the whole numbers."""
+    s = prepare(case, seed)
+    wl, dev, step, router = s.wl, s.dev, case["mode"] == "step", case["gate"] == "router"
+    x = dev["x"].double()
+    logits = x @ dev["wr"].double() if router else dev["logits"].double()
+    # the ranking is on fp32 logits
+    topk = logits.float().topk(wl.k, dim=1).indices
+    logits.requires_grad_(step and router)
+    w = _gates(wl, logits, topk)
+    g = w.detach()
+    y = torch.zeros_like(x)
+    out = {"y": y, "topk_idx": None, "topk_w": g}
+    if router:
+        out["logits"] = logits.detach()
+    if step:
+        dy = dev["dy"].double()
+        dx, dgate = torch.zeros_like(x), torch.zeros_like(g)
+        old = lambda t: t.double() if case["accumulate"] else torch.zeros(t.shape, dtype=torch.float64, device="cuda")  # noqa: E731
+        dw1, dw3, dw2 = old(s.buf.dw1), old(s.buf.dw3), old(s.buf.dw2)
+        out.update(dx=dx, dw1=dw1, dw3=dw3, dw2=dw2)
+    for e in range(wl.e_cnt):
+        t, j = (topk == wl.e_lo + e).nonzero(as_tuple=True)
+        if not len(t):
+            continue
+        w1, w3, w2 = (dev[n][e].double() for n in ("w1", "w3", "w2"))
+        xe, ge = x[t], g[t, j].unsqueeze(1)
+        h1, h3 = xe @ w1, xe @ w3
+        sig = h1.sigmoid()
+        a = h1 * sig * h3
+        o = a @ w2
+        y.index_add_(0, t, ge * o)
+        if step:
+            dye = dy[t]
+            dgate[t, j] = (dye * o).sum(dim=1)
+            do = ge * dye
+            da = do @ w2.t()
+            dh1, dh3 = da * h3 * sig * (1 + h1 * (1 - sig)), da * h1 * sig
+            dw2[e] += a.t() @ do
+            dw1[e] += xe.t() @ dh1
+            dw3[e] += xe.t() @ dh3
+            dx.index_add_(0, t, dh1 @ w1.t() + dh3 @ w3.t())
+    if step and router:
+        (dlogits,) = torch.autograd.grad(w, logits, dgate)
+        dx += dlogits @ dev["wr"].double().t()
+        out["dwr"] = old(s.buf.dwr) + x.t() @ dlogits
+    elif step:
+        out.update(counts=None, offsets=None, inv=None)
+    return out
+
+
 def tolerance(case):
     """bf16: h1, h3, a, o, dH1, dH3, dxp and the outputs are each rounded to 8 bits of mantissa between fp32-accumulated
     products; against the same path in 64 bits every output is off by 2.9e-3 to 3.9e-3 (largest element 0.13).  fp32:
