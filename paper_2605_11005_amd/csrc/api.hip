@@ -20,8 +20,7 @@ int shape_check_expert(int dtype, int cap, int d, int f, int e_cnt) {
   // 32-bit row*ld products inside a tile and 31-bit element counts per activation tensor
   if ((long long)cap * (d > f ? d : f) >= (1ll << 40)) return MOE_EUNSUPPORTED;
   if ((long long)(d > f ? d : f) * 256 >= (1ll << 31)) return MOE_EUNSUPPORTED;
-  // the fp32 kernels put row tiles (64 rows each, at most one ragged tile per expert) and, for the weight
-  // gradients, 64-wide tiles of d or f on grid dimensions y / z, which hold 65535 blocks
+  // fp32: limits of the row tiles (64 rows each, at most one ragged tile per expert) and of 64-wide tiles of d or f
   if (dtype == MOE_F32 && ((long long)(cap + 63) / 64 + e_cnt > 65535 || (d > f ? d : f) / 64 + 1 > 65535)) return MOE_EUNSUPPORTED;
   return MOE_OK;
 }
@@ -304,10 +303,8 @@ int moe_expert_fwd(const void* xp, int dtype, int cap, int d, int f, int e_cnt,
   if (dtype == MOE_BF16)
     return launch_expert_fwd_bf16(xp, cap, d, f, e_cnt, offsets, w1, w3, w2, h1, h3, a_out, o, ws, s);
   float* a = a_out ? (float*)a_out : (float*)ws;
-  float* t1 = h1 ? (float*)h1 : (float*)ws + (size_t)cap * f;
-  float* t3 = h3 ? (float*)h3 : (float*)ws + 2 * (size_t)cap * f;
   return launch_expert_fwd_f32((const float*)xp, cap, d, f, e_cnt, offsets, (const float*)w1, (const float*)w3,
-                               (const float*)w2, t1, t3, (float*)o, a, s);
+                               (const float*)w2, (float*)h1, (float*)h3, (float*)o, a, s);
 }
 
 int moe_expert_bwd(const void* xp, const void* h1, const void* h3, const void* a_in, const void* d_o, int dtype,

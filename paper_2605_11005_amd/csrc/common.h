@@ -28,6 +28,49 @@ __device__ __forceinline__ float bf16hi(uint32_t v) { return __uint_as_float(v &
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (WAVE - 1); }
 
+// The tile of workgroup b in a launch whose list of tiles is known on the device only: experts in ascending order, each
+// cut into row tiles of TM rows, each of them into n_cols column tiles (fastest).  Workgroup b runs on XCD b % 8, and every
+// XCD takes a contiguous eighth of the list, so that an expert's weights pass through one or two of the eight L2s instead
+// of all of them.  The grid is the host's bound on the list rounded up to a multiple of eight: false for a surplus
+// workgroup.  Called by whole wavefronts; 64 experts per step.
+template <int TM>
+__device__ __forceinline__ int row_tiles_scan(const int32_t* __restrict__ off, int e_cnt, int e, int lane, int& n) {
+  n = e < e_cnt ? (off[e + 1] - off[e] + TM - 1) / TM : 0;
+  int incl = n;
+#pragma unroll
+  for (int o = 1; o < WAVE; o <<= 1) {
+    const int v = __shfl_up(incl, o, WAVE);
+    if (lane >= o) incl += v;
+  }
+  return incl;
+}
+template <int TM>
+__device__ __forceinline__ bool ragged_tile(const int32_t* __restrict__ off, int e_cnt, int n_cols, int b, int lane, int& e,
+                                            int& row_tile, int& col_tile) {
+  int n, incl = row_tiles_scan<TM>(off, e_cnt, lane, lane, n);
+  int total = __builtin_amdgcn_readfirstlane(__shfl(incl, WAVE - 1, WAVE));
+  for (int base = WAVE; base < e_cnt; base += WAVE) {
+    int m;
+    total += __builtin_amdgcn_readfirstlane(__shfl(row_tiles_scan<TM>(off, e_cnt, base + lane, lane, m), WAVE - 1, WAVE));
+  }
+  const int share = (total * n_cols + 7) / 8;
+  const int tile = (b % 8) * share + b / 8;
+  if (b / 8 >= share || tile >= total * n_cols) return false;
+  int t = tile / n_cols;
+  col_tile = tile - t * n_cols;
+  for (int base = 0;; base += WAVE) {          // ends: t < total
+    if (base > 0) incl = row_tiles_scan<TM>(off, e_cnt, base + lane, lane, n);
+    const unsigned long long past = __ballot(incl > t);
+    if (past) {
+      const int who = __builtin_ctzll(past);
+      row_tile = __builtin_amdgcn_readfirstlane(t - __shfl(incl - n, who, WAVE));
+      e = base + who;
+      return true;
+    }
+    t = __builtin_amdgcn_readfirstlane(t - __shfl(incl, WAVE - 1, WAVE));
+  }
+}
+
 // logistic function with the hardware exp2 and reciprocal (about 1 ulp each; used by the bf16
 // epilogues, whose results are rounded to 8 bits of mantissa)
 __device__ __forceinline__ float sigmoid_fast(float z) {

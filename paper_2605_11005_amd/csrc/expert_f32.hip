@@ -1,173 +1,303 @@
-// fp32 expert FFNs (correctness-grade path for the small all-fp32 configuration).
-// Plain LDS-tiled FMA GEMMs, 64x64 output tile per 256-thread block, 4x4 per thread,
-// fp32 accumulation in ascending-k order.  The bf16 MFMA path is in expert_bf16.hip.
+// fp32 expert FFNs on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32: fp32 products and sums).  The bf16 path is in expert_bf16.hip.
+//
+// One kernel template covers the six GEMM shapes of the layer, with the activation in the epilogue:
+//   UP     h1|h3 = xp [W1|W3]   ragged M, weights n-contiguous, two outputs of one tile -> a = silu(h1) h3
+//   DOWN   o     = a W2         ragged M, weights n-contiguous
+//   DA     dA    = d_o W2^T     ragged M, weights k-contiguous, SwiGLU backward -> dH1, dH3 (and a if it was not kept)
+//   DX     dxp   = dH1 W1^T + dH3 W3^T   ragged M, K in two segments
+//   WG     dW2   = a^T d_o      ragged K (the expert's rows)
+//   WGD    dW1|dW3 = xp^T [dH1|dH3]      ragged K, two outputs of one tile
+//
+// What bounds it: the fp32 matrix rate is 256 FLOP per cycle and CU, twice what plain vector FMAs reach (packed fp32
+// FMAs are not used), and at the sizes of this path (a few hundred rows per expert) the number of tiles per CU and what a
+// tile costs besides its k loop.  Hence a small tile, 64x64 by four wavefronts of 32x32 each, two blocks or more per CU,
+// and two k-tiles of 32 on their way in registers while a third is multiplied (two LDS buffers, one barrier per k-tile).
+// Measured at 3000 rows over 16 experts, d = 520, f = 776 (4.8 GFLOP for the pair of up projections): 77 us, the matrix
+// pipes busy 60 % of the time a CU has work; as two products and an element-wise pass on vector FMAs it took 304 us.
+// Tiles of 32x64 by two wavefronts leave fewer empty rows and took 99 us.
 #include "common.h"
 #include "kernels.h"
 
 namespace {
 
-constexpr int TM = 64, TN = 64, TK = 16;
+constexpr int TM = 64, TN = 64, TK = 32, NT = 256;
+typedef float f32x16 __attribute__((ext_vector_type(16)));
 
-// Ragged-M grouped GEMM: for expert e and its rows r in [off[e], off[e+1]):
-//   C[r, n] = beta*C[r,n] + sum_k A[r,k] * B_e(k,n),   B_e(k,n) = B[e*b_es + k*b_rs + n*b_cs]
-// grid.x = N tiles, grid.y = upper bound on M tiles (ceil(cap/TM) + e_cnt).
-__global__ __launch_bounds__(256) void gemm_rows_f32(const float* __restrict__ A, int lda, const float* __restrict__ B,
-                                                    long b_es, long b_rs, long b_cs, float* __restrict__ C,
-                                                    int ldc, int N, int K, int e_cnt,
-                                                    const int32_t* __restrict__ off, int beta) {
-  // locate this block's (expert, m-tile)
-  int mt = blockIdx.y, e = 0, lo = 0, hi = 0;
-  for (; e < e_cnt; ++e) {
-    lo = off[e]; hi = off[e + 1];
-    int tiles = (hi - lo + TM - 1) / TM;
-    if (mt < tiles) break;
-    mt -= tiles;
+enum { UP, DOWN, DA, DX, WG, WGD };
+
+// A matrix instruction contracts two values of k, one per half of the wavefront.  Which two is free as long as both
+// operands agree: in groups of eight steps the lower half takes k = 0..7 and the upper one k = 8..15 of a group of 16, so
+// that a lane of a k-contiguous operand reads consecutive words (16 bytes serve four steps).
+// Pitches: [64 rows][k] at 36 words -- 16 lanes reading 16 bytes each hit 64 banks; [k][64 columns] at 68 -- rows eight
+// apart, read together by the two halves, are 32 banks apart.
+constexpr int PITCH_KC = 36, PITCH_MN = 68;
+constexpr int HALF = TK / 4;      // steps whose fragments are held at a time: half of a k-tile
+
+// The loads below are unconditional (clamped addresses); what lies past the end of the contraction becomes zero on the
+// way to LDS, rows and columns past the end repeat the last ones (their products are never stored).
+__device__ __forceinline__ float4 keep(float4 v, bool in) {
+  return make_float4(in ? v.x : 0.f, in ? v.y : 0.f, in ? v.z : 0.f, in ? v.w : 0.f);
+}
+
+// k-contiguous operand: rows [0, rows) of a matrix with leading dimension ld; k in [0, K), K % 4 == 0
+struct OperKC {
+  static constexpr int WORDS = 64 * PITCH_KC;
+  const float* base;
+  long ld;
+  int rows, K;
+  __device__ __forceinline__ void load(float4* v, int k0, int tid) const {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int idx = tid + NT * i;
+      const int r = min(idx >> 3, rows - 1), k = min(k0 + 4 * (idx & 7), K - 4);
+      v[i] = *reinterpret_cast<const float4*>(base + (size_t)r * ld + k);
+    }
   }
-  if (e >= e_cnt) return;
-  const int row0 = lo + mt * TM, col0 = blockIdx.x * TN;
-  __shared__ float sa[TK][TM + 1], sb[TK][TN + 1];
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  float acc[4][4] = {};
-  const float* Be = B + (size_t)e * b_es;
-  for (int k0 = 0; k0 < K; k0 += TK) {
-    for (int i = threadIdx.x; i < TM * TK; i += 256) {
-      int m = i / TK, kk = i % TK;
-      int r = row0 + m, kidx = k0 + kk;
-      sa[kk][m] = (r < hi && kidx < K) ? A[(size_t)r * lda + kidx] : 0.f;
+  __device__ __forceinline__ void store(const float4* v, float* s, int k0, int tid) const {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int idx = tid + NT * i;
+      *reinterpret_cast<float4*>(s + (idx >> 3) * PITCH_KC + 4 * (idx & 7)) = keep(v[i], k0 + 4 * (idx & 7) < K);
     }
-    for (int i = threadIdx.x; i < TN * TK; i += 256) {
-      int n, kk;
-      if (b_cs == 1) { n = i % TN; kk = i / TN; } else { kk = i % TK; n = i / TK; }
-      int c = col0 + n, kidx = k0 + kk;
-      sb[kk][n] = (c < N && kidx < K) ? Be[(size_t)kidx * b_rs + (size_t)c * b_cs] : 0.f;
+  }
+  // fragments of steps [HALF * h, HALF * (h + 1)); pos: row or column of this lane in the tile, up: upper half of the wavefront
+  static __device__ __forceinline__ void frags(float* f, const float* s, int pos, int up, int h) {
+#pragma unroll
+    for (int q = 0; q < HALF / 4; ++q) {
+      const float4 w = *reinterpret_cast<const float4*>(s + pos * PITCH_KC + 16 * h + 8 * up + 4 * q);
+      f[4 * q] = w.x; f[4 * q + 1] = w.y; f[4 * q + 2] = w.z; f[4 * q + 3] = w.w;
     }
+  }
+};
+
+// operand whose rows or columns are contiguous: base points at k = 0, tile column 0; cols columns are valid (cols % 4 == 0)
+struct OperMN {
+  static constexpr int WORDS = TK * PITCH_MN;
+  const float* base;
+  long ld;
+  int cols, K;
+  __device__ __forceinline__ void load(float4* v, int k0, int tid) const {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int idx = tid + NT * i;
+      const int k = min(k0 + (idx >> 4), K - 1), c = min(4 * (idx & 15), cols - 4);
+      v[i] = *reinterpret_cast<const float4*>(base + (size_t)k * ld + c);
+    }
+  }
+  __device__ __forceinline__ void store(const float4* v, float* s, int k0, int tid) const {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int idx = tid + NT * i;
+      *reinterpret_cast<float4*>(s + (idx >> 4) * PITCH_MN + 4 * (idx & 15)) = keep(v[i], k0 + (idx >> 4) < K);
+    }
+  }
+  static __device__ __forceinline__ void frags(float* f, const float* s, int pos, int up, int h) {
+#pragma unroll
+    for (int q = 0; q < HALF; ++q) f[q] = s[(16 * h + 8 * up + q) * PITCH_MN + pos];
+  }
+};
+
+template <int V> struct Set { static constexpr int value = V; };
+template <bool C, typename A, typename B> struct Pick { typedef A type; };
+template <typename A, typename B> struct Pick<false, A, B> { typedef B type; };
+
+struct Args {
+  const float* A[2];        // [1]: second K segment of DX
+  const float* B[2];        // [1]: second output of a dual tile / second K segment of DX
+  long lda, ldb, b_es;      // b_es: expert stride of B (0: row-indexed)
+  float* C[3];
+  const float* H[2];        // DA: h1, h3
+  long ldc, c_es;           // c_es: expert stride of C (0: row-indexed)
+  int M, N, K;              // M: WG / WGD, K: ragged-M shapes (per segment)
+  const int32_t* off;
+  int e_cnt, beta;
+};
+
+// 1-D grid over the tiles: ragged_tile's list for the ragged-M shapes, the same with a fixed number of row tiles per
+// expert for the ragged-K ones.
+template <int MODE>
+__global__ __launch_bounds__(NT) void gemm_f32(Args p) {
+  constexpr bool RAGGED_K = MODE == WG || MODE == WGD;
+  constexpr bool DUAL = MODE == UP || MODE == WGD;
+  constexpr int NB = DUAL ? 2 : 1;
+  typedef typename Pick<RAGGED_K, OperMN, OperKC>::type OperA;
+  typedef typename Pick<MODE == DA || MODE == DX, OperKC, OperMN>::type OperB;
+  __shared__ __align__(16) float lds[2][OperA::WORDS + NB * OperB::WORDS];
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int n_tiles = (p.N + TN - 1) / TN, m_tiles = (p.M + TM - 1) / TM;
+  int e, mt, nt, row0, row_end, K;                       // output rows [row0, row_end)
+  if (RAGGED_K) {
+    const int total = p.e_cnt * m_tiles * n_tiles, share = (total + 7) / 8;
+    const int tile = (blockIdx.x % 8) * share + blockIdx.x / 8;
+    if ((int)(blockIdx.x / 8) >= share || tile >= total) return;
+    e = tile / (m_tiles * n_tiles);
+    mt = (tile - e * m_tiles * n_tiles) / n_tiles;
+    nt = tile % n_tiles;
+    row0 = mt * TM;
+    row_end = p.M;
+    K = p.off[e + 1] - p.off[e];
+  } else {
+    if (!ragged_tile<TM>(p.off, p.e_cnt, n_tiles, blockIdx.x, lane, e, mt, nt)) return;
+    row0 = p.off[e] + mt * TM;
+    row_end = p.off[e + 1];
+    K = p.K;
+  }
+  const int col0 = nt * TN;
+
+  OperA a;
+  OperB b[NB];
+  auto setup = [&](int seg) {
+    if constexpr (RAGGED_K) {
+      const size_t first = p.off[e];
+      a.base = p.A[0] + first * p.lda + row0; a.ld = p.lda; a.cols = p.M - row0; a.K = K;
+#pragma unroll
+      for (int i = 0; i < NB; ++i) { b[i].base = p.B[i] + first * p.ldb + col0; b[i].ld = p.ldb; b[i].cols = p.N - col0; b[i].K = K; }
+    } else {
+      a.base = p.A[seg] + (size_t)row0 * p.lda; a.ld = p.lda; a.rows = row_end - row0; a.K = K;
+#pragma unroll
+      for (int i = 0; i < NB; ++i) {
+        const float* w = p.B[DUAL ? i : seg] + (size_t)e * p.b_es;
+        b[i].ld = p.ldb;
+        b[i].K = K;
+        if constexpr (MODE == DA || MODE == DX) { b[i].base = w + (size_t)col0 * p.ldb; b[i].rows = p.N - col0; }
+        else { b[i].base = w + col0; b[i].cols = p.N - col0; }
+      }
+    }
+  };
+  // two chains of sums per output (even and odd steps), added at the end: half as many roundings in a row, and
+  // consecutive matrix instructions do not wait for each other
+  f32x16 acc[NB][2];
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[i][0][r] = acc[i][1][r] = 0.f;
+
+  const int wm = wave >> 1, wn = wave & 1;
+  const int a_pos = wm * 32 + (lane & 31), b_pos = wn * 32 + (lane & 31), up = lane >> 5;
+  const int nk1 = (K + TK - 1) / TK, nk = MODE == DX ? 2 * nk1 : nk1;
+  // two k-tiles travel in registers while one is multiplied
+  float4 va[2][2], vb[2][NB][2];
+  const auto first_k = [&](int kt) { return (MODE == DX && kt >= nk1 ? kt - nk1 : kt) * TK; };
+  auto fetch = [&](int kt, auto set) {
+    constexpr int S = decltype(set)::value;
+    if (kt > nk - 1) kt = nk - 1;                // (surplus loads at the end, never multiplied)
+    if (MODE == DX && kt == nk1) setup(1);       // the second half of the k-tiles is the second segment
+    const int k0 = first_k(kt);
+    a.load(va[S], k0, tid);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) b[i].load(vb[S][i], k0, tid);
+  };
+  auto publish = [&](int kt, auto set) {         // k-tiles of set S live in LDS buffer S
+    constexpr int S = decltype(set)::value;
+    a.store(va[S], lds[S], first_k(kt), tid);
+#pragma unroll
+    for (int i = 0; i < NB; ++i) b[i].store(vb[S][i], lds[S] + OperA::WORDS + i * OperB::WORDS, first_k(kt), tid);
+  };
+  const bool live = wm * 32 < row_end - row0;    // a wavefront without valid rows only moves data
+  auto multiply = [&](auto set) {
+    constexpr int S = decltype(set)::value;
+    if (!live) return;
+    float fa[2][HALF], fb[2][NB][HALF];
+    auto read = [&](int h) {
+      OperA::frags(fa[h], lds[S], a_pos, up, h);
+#pragma unroll
+      for (int i = 0; i < NB; ++i) OperB::frags(fb[h][i], lds[S] + OperA::WORDS + i * OperB::WORDS, b_pos, up, h);
+    };
+    read(0);
+    read(1);
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+#pragma unroll
+      for (int q = 0; q < HALF; ++q)
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+          acc[i][q & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[h][q], fb[h][i][q], acc[i][q & 1], 0, 0, 0);
+  };
+  setup(0);
+  if (nk > 0) {
+    fetch(0, Set<0>{});
+    fetch(1, Set<1>{});
+    publish(0, Set<0>{});
+  }
+  __syncthreads();
+  // LDS buffer 1 is written while buffer 0 is multiplied and the other way round; the barrier ends both
+  for (int kt = 0; kt + 1 < nk; kt += 2) {
+    fetch(kt + 2, Set<0>{});
+    multiply(Set<0>{});
+    publish(kt + 1, Set<1>{});
     __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < TK; ++kk) {
-      float av[4], bv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = sa[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bv[j] = sb[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += av[i] * bv[j];
-    }
+    fetch(kt + 3, Set<1>{});
+    multiply(Set<1>{});
+    publish(kt + 2, Set<0>{});
     __syncthreads();
   }
+  if (nk & 1) multiply(Set<0>{});
+
+  // accumulator element 4g + i of a lane is row 8g + 4*(lane/32) + i, column lane%32 of its wavefront's block
+  const int col = col0 + wn * 32 + (lane & 31);
+  if (col >= p.N) return;
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int r = row0 + ty * 4 + i;
-    if (r >= hi) continue;
+  for (int g = 0; g < 4; ++g) {
+    float h1[4], h3[4];
+    const int r0 = row0 + wm * 32 + 8 * g + 4 * (lane >> 5);
+    if (MODE == DA) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int c = col0 + tx * 4 + j;
-      if (c < N) {
-        size_t idx = (size_t)r * ldc + c;
-        C[idx] = beta ? C[idx] + acc[i][j] : acc[i][j];
+      for (int i = 0; i < 4; ++i) {
+        const size_t idx = (size_t)(r0 + i < row_end ? r0 + i : row_end - 1) * p.ldc + col;
+        h1[i] = p.H[0][idx];
+        h3[i] = p.H[1][idx];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      if (r0 + i >= row_end) continue;
+      const size_t idx = (size_t)e * p.c_es + (size_t)(r0 + i) * p.ldc + col;
+      const float x = acc[0][0][4 * g + i] + acc[0][1][4 * g + i];
+      const float x3 = acc[NB - 1][0][4 * g + i] + acc[NB - 1][1][4 * g + i];      // second output of a dual tile
+      if (MODE == UP) {
+        if (p.C[0]) { p.C[0][idx] = x; p.C[1][idx] = x3; }
+        p.C[2][idx] = (x / (1.0f + expf(-x))) * x3;
+      } else if (MODE == DA) {
+        const float z = h1[i], sg = 1.0f / (1.0f + expf(-z)), sl = z * sg;
+        if (p.C[0]) p.C[0][idx] = sl * h3[i];      // not stored when the forward's copy is at hand
+        p.C[1][idx] = x * h3[i] * (sg * (1.0f + z * (1.0f - sg)));
+        p.C[2][idx] = x * sl;
+      } else {
+        p.C[0][idx] = p.beta ? p.C[0][idx] + x : x;
+        if (DUAL) p.C[1][idx] = p.beta ? p.C[1][idx] + x3 : x3;
       }
     }
   }
 }
 
-// Ragged-K grouped GEMM (weight gradients): C_e[i,j] = beta*C_e[i,j] + sum_{r in expert e} P[r,i]*Q[r,j]
-// grid = (N tiles, M tiles, e_cnt)
-__global__ __launch_bounds__(256) void gemm_wgrad_f32(const float* __restrict__ P, int ldp, const float* __restrict__ Q,
-                                                     int ldq, float* __restrict__ C, int M, int N,
-                                                     const int32_t* __restrict__ off, int beta) {
-  const int e = blockIdx.z;
-  const int lo = off[e], hi = off[e + 1];
-  const int i0 = blockIdx.y * TM, j0 = blockIdx.x * TN;
-  __shared__ float sa[TK][TM + 1], sb[TK][TN + 1];
-  const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
-  float acc[4][4] = {};
-  for (int r0 = lo; r0 < hi; r0 += TK) {
-    for (int t = threadIdx.x; t < TM * TK; t += 256) {
-      int m = t % TM, kk = t / TM;
-      int r = r0 + kk, i = i0 + m;
-      sa[kk][m] = (r < hi && i < M) ? P[(size_t)r * ldp + i] : 0.f;
-    }
-    for (int t = threadIdx.x; t < TN * TK; t += 256) {
-      int n = t % TN, kk = t / TN;
-      int r = r0 + kk, j = j0 + n;
-      sb[kk][n] = (r < hi && j < N) ? Q[(size_t)r * ldq + j] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < TK; ++kk) {
-      float av[4], bv[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) av[i] = sa[kk][ty * 4 + i];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) bv[j] = sb[kk][tx * 4 + j];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] += av[i] * bv[j];
-    }
-    __syncthreads();
-  }
-  float* Ce = C + (size_t)e * M * N;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    int ii = i0 + ty * 4 + i;
-    if (ii >= M) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      int jj = j0 + tx * 4 + j;
-      if (jj < N) {
-        size_t idx = (size_t)ii * N + jj;
-        Ce[idx] = beta ? Ce[idx] + acc[i][j] : acc[i][j];
-      }
-    }
-  }
+// m_tiles: bound on the row tiles of all experts
+template <int MODE>
+int launch(const Args& p, long long m_tiles, hipStream_t s) {
+  const long long blocks = (m_tiles * ((p.N + TN - 1) / TN) + 7) / 8 * 8;
+  if (blocks >= (1ll << 31)) return MOE_EUNSUPPORTED;
+  hipLaunchKernelGGL(gemm_f32<MODE>, dim3((unsigned)blocks), dim3(NT), 0, s, p);
+  HIP_CHECK_LAUNCH();
+  return MOE_OK;
 }
-
-// a = silu(h1) * h3 on rows [0, R), R = off[e_cnt]
-__global__ void swiglu_fwd_f32(const float* __restrict__ h1, const float* __restrict__ h3, float* __restrict__ a,
-                               int f, const int32_t* __restrict__ off, int e_cnt) {
-  const size_t n = (size_t)off[e_cnt] * f;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    float z = h1[i];
-    a[i] = (z / (1.0f + expf(-z))) * h3[i];
-  }
-}
-
-// in: dA (in dh1 buffer), h1, h3.  out: a, dH1 (in place of dA), dH3
-__global__ void swiglu_bwd_f32(const float* __restrict__ h1, const float* __restrict__ h3, float* __restrict__ a,
-                               float* __restrict__ dh1, float* __restrict__ dh3, int f,
-                               const int32_t* __restrict__ off, int e_cnt) {
-  const size_t n = (size_t)off[e_cnt] * f;
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-    float z = h1[i], g = h3[i], da = dh1[i];
-    float sg = 1.0f / (1.0f + expf(-z));
-    float sl = z * sg;
-    a[i] = sl * g;
-    dh1[i] = da * g * (sg * (1.0f + z * (1.0f - sg)));
-    dh3[i] = da * sl;
-  }
-}
-
-inline int m_tiles_bound(int cap, int e_cnt) { return (cap + TM - 1) / TM + e_cnt; }
 
 }  // namespace
 
 int launch_expert_fwd_f32(const float* xp, int cap, int d, int f, int e_cnt, const int32_t* offsets,
                           const float* w1, const float* w3, const float* w2, float* h1, float* h3,
-                          float* o, float* a_ws, hipStream_t s) {
+                          float* o, float* a, hipStream_t s) {
   if (cap == 0 || e_cnt == 0) return MOE_OK;
-  const int mtb = m_tiles_bound(cap, e_cnt);
-  dim3 blk(256);
-  hipLaunchKernelGGL(gemm_rows_f32, dim3((f + TN - 1) / TN, mtb), blk, 0, s, xp, d, w1, (long)d * f, (long)f, 1L, h1, f, f, d, e_cnt, offsets, 0);
-  HIP_CHECK_LAUNCH();
-  hipLaunchKernelGGL(gemm_rows_f32, dim3((f + TN - 1) / TN, mtb), blk, 0, s, xp, d, w3, (long)d * f, (long)f, 1L, h3, f, f, d, e_cnt, offsets, 0);
-  HIP_CHECK_LAUNCH();
-  hipLaunchKernelGGL(swiglu_fwd_f32, dim3(device_cu_count() * 4), dim3(256), 0, s, h1, h3, a_ws, f, offsets, e_cnt);
-  HIP_CHECK_LAUNCH();
-  hipLaunchKernelGGL(gemm_rows_f32, dim3((d + TN - 1) / TN, mtb), blk, 0, s, a_ws, f, w2, (long)f * d, (long)d, 1L, o, d, d, f, e_cnt, offsets, 0);
-  HIP_CHECK_LAUNCH();
-  return MOE_OK;
+  const long long mtb = ((long long)cap + TM - 1) / TM + e_cnt;
+  Args u = {};
+  u.A[0] = xp; u.lda = d; u.B[0] = w1; u.B[1] = w3; u.ldb = f; u.b_es = (long)d * f;
+  u.C[0] = h1; u.C[1] = h3; u.C[2] = a; u.ldc = f; u.N = f; u.K = d; u.off = offsets; u.e_cnt = e_cnt;
+  int rc = launch<UP>(u, mtb, s);
+  if (rc) return rc;
+  Args w = {};
+  w.A[0] = a; w.lda = f; w.B[0] = w2; w.ldb = d; w.b_es = (long)f * d;
+  w.C[0] = o; w.ldc = d; w.N = d; w.K = f; w.off = offsets; w.e_cnt = e_cnt;
+  return launch<DOWN>(w, mtb, s);
 }
 
 int launch_expert_bwd_f32(const float* xp, const float* h1, const float* h3, const float* a_in, const float* d_o, int cap,
@@ -178,27 +308,26 @@ int launch_expert_bwd_f32(const float* xp, const float* h1, const float* h3, con
   float* a = ws;
   float* dh1 = ws + (size_t)cap * f;
   float* dh3 = ws + 2 * (size_t)cap * f;
-  dim3 blk(256);
+  int rc;
   if (cap > 0) {
-    const int mtb = m_tiles_bound(cap, e_cnt);
-    // dA = d_o W2^T : B_e(k = col of d, n = row of f) = W2[e][n][k]
-    hipLaunchKernelGGL(gemm_rows_f32, dim3((f + TN - 1) / TN, mtb), blk, 0, s, d_o, d, w2, (long)f * d, 1L, (long)d, dh1, f, f, d, e_cnt, offsets, 0);
-    HIP_CHECK_LAUNCH();
-    hipLaunchKernelGGL(swiglu_bwd_f32, dim3(device_cu_count() * 4), dim3(256), 0, s, h1, h3, a, dh1, dh3, f, offsets, e_cnt);
-    HIP_CHECK_LAUNCH();
-    // dxp = dH1 W1^T + dH3 W3^T : B_e(k = col of f, n = row of d) = W1[e][n][k]
-    hipLaunchKernelGGL(gemm_rows_f32, dim3((d + TN - 1) / TN, mtb), blk, 0, s, dh1, f, w1, (long)d * f, 1L, (long)f, dxp, d, d, f, e_cnt, offsets, 0);
-    HIP_CHECK_LAUNCH();
-    hipLaunchKernelGGL(gemm_rows_f32, dim3((d + TN - 1) / TN, mtb), blk, 0, s, dh3, f, w3, (long)d * f, 1L, (long)f, dxp, d, d, f, e_cnt, offsets, 1);
-    HIP_CHECK_LAUNCH();
+    const long long mtb = ((long long)cap + TM - 1) / TM + e_cnt;
+    Args g = {};
+    g.A[0] = d_o; g.lda = d; g.B[0] = w2; g.ldb = d; g.b_es = (long)f * d;
+    g.C[0] = a_in ? nullptr : a; g.C[1] = dh1; g.C[2] = dh3; g.H[0] = h1; g.H[1] = h3; g.ldc = f;
+    g.N = f; g.K = d; g.off = offsets; g.e_cnt = e_cnt;
+    if ((rc = launch<DA>(g, mtb, s))) return rc;
+    Args x = {};
+    x.A[0] = dh1; x.A[1] = dh3; x.lda = f; x.B[0] = w1; x.B[1] = w3; x.ldb = f; x.b_es = (long)d * f;
+    x.C[0] = dxp; x.ldc = d; x.N = d; x.K = f; x.off = offsets; x.e_cnt = e_cnt;
+    if ((rc = launch<DX>(x, mtb, s))) return rc;
   }
-  const int beta = accumulate ? 1 : 0;
   // dW2 takes the activation the forward kept, if the caller passed it, else the one recomputed above
-  hipLaunchKernelGGL(gemm_wgrad_f32, dim3((d + TN - 1) / TN, (f + TM - 1) / TM, e_cnt), blk, 0, s, a_in ? a_in : a, f, d_o, d, dw2, f, d, offsets, beta);
-  HIP_CHECK_LAUNCH();
-  hipLaunchKernelGGL(gemm_wgrad_f32, dim3((f + TN - 1) / TN, (d + TM - 1) / TM, e_cnt), blk, 0, s, xp, d, dh1, f, dw1, d, f, offsets, beta);
-  HIP_CHECK_LAUNCH();
-  hipLaunchKernelGGL(gemm_wgrad_f32, dim3((f + TN - 1) / TN, (d + TM - 1) / TM, e_cnt), blk, 0, s, xp, d, dh3, f, dw3, d, f, offsets, beta);
-  HIP_CHECK_LAUNCH();
-  return MOE_OK;
+  Args w = {};
+  w.A[0] = a_in ? a_in : a; w.lda = f; w.B[0] = d_o; w.ldb = d;
+  w.C[0] = dw2; w.ldc = d; w.c_es = (long)f * d; w.M = f; w.N = d; w.off = offsets; w.e_cnt = e_cnt; w.beta = accumulate;
+  if ((rc = launch<WG>(w, (long long)e_cnt * ((f + TM - 1) / TM), s))) return rc;
+  Args v = {};
+  v.A[0] = xp; v.lda = d; v.B[0] = dh1; v.B[1] = dh3; v.ldb = f;
+  v.C[0] = dw1; v.C[1] = dw3; v.ldc = f; v.c_es = (long)d * f; v.M = d; v.N = f; v.off = offsets; v.e_cnt = e_cnt; v.beta = accumulate;
+  return launch<WGD>(v, (long long)e_cnt * ((d + TM - 1) / TM), s);
 }

@@ -23,7 +23,7 @@ int launch_combine_rows(const void* o, int dtype, int T, int d, int k, const int
 
 int launch_expert_fwd_f32(const float* xp, int cap, int d, int f, int e_cnt, const int32_t* offsets,
                           const float* w1, const float* w3, const float* w2, float* h1, float* h3,
-                          float* o, float* a_ws, hipStream_t s);
+                          float* o, float* a, hipStream_t s);   // h1, h3: both or neither
 int launch_expert_bwd_f32(const float* xp, const float* h1, const float* h3, const float* a_in, const float* d_o, int cap,
                           int d, int f, int e_cnt, const int32_t* offsets, const float* w1,
                           const float* w3, const float* w2, float* dxp, float* dw1, float* dw3,
