@@ -162,12 +162,13 @@ __device__ __forceinline__ float from_ordered_bits(uint32_t o) {
 }
 
 template <int NV>   // NV = number of 4-expert vectors per lane = ceil(E / 64)
-__global__ __launch_bounds__(256) void route_kernel_q(const float* __restrict__ logits, int T, int E, int k, int mode,
+__global__ __launch_bounds__(512) void route_kernel_q(const float* __restrict__ logits, int T, int E, int k, int mode,
                                                       int e_lo, int e_cnt, int32_t* __restrict__ topk_idx,
                                                       float* __restrict__ topk_w, int32_t* __restrict__ counts) {
   extern __shared__ int32_t hist[];
   for (int i = threadIdx.x; i < e_cnt; i += blockDim.x) hist[i] = 0;
   __syncthreads();
+  const bool alone = gridDim.x == 1;                     // the only block stores its counts: nobody cleared them
   const int s = threadIdx.x & 15;
   const int group = threadIdx.x >> 4;                    // 16 tokens per block
   const int groups = blockDim.x >> 4;
@@ -244,7 +245,8 @@ __global__ __launch_bounds__(256) void route_kernel_q(const float* __restrict__ 
   __syncthreads();
   for (int i = threadIdx.x; i < e_cnt; i += blockDim.x) {
     const int c = hist[i];
-    if (c) atomicAdd(&counts[i], c);
+    if (alone) counts[i] = c;
+    else if (c) atomicAdd(&counts[i], c);
   }
 }
 
@@ -252,21 +254,25 @@ __global__ __launch_bounds__(256) void route_kernel_q(const float* __restrict__ 
 
 int launch_route(const float* logits, int T, int E, int k, int gate_mode, int e_lo, int e_cnt,
                  int32_t* topk_idx, float* topk_w, int32_t* counts, hipStream_t s) {
-  if (e_cnt > 0) {
+  const bool quarter = T > 0 && E <= 256 && k <= 16 && E % 4 == 0 && ((uintptr_t)logits & 15) == 0;      // 16 lanes per token
+  // up to 32 tokens: one block, which needs no cleared counts (a launch less; at 128 tokens one CU takes 20 us for the
+  // selection rounds that eight blocks finish in 7)
+  const bool alone = quarter && T <= 32;
+  if (e_cnt > 0 && !alone) {
     hipLaunchKernelGGL(zero_i32, dim3((e_cnt + 255) / 256), dim3(256), 0, s, counts, e_cnt);
     HIP_CHECK_LAUNCH();
   }
   if (T == 0) return MOE_OK;
   ProfScope prof(MOE_K_ROUTE, s);
   size_t shm_q = (size_t)(e_cnt > 0 ? e_cnt : 1) * sizeof(int32_t);
-  if (E <= 256 && k <= 16 && E % 4 == 0 && ((uintptr_t)logits & 15) == 0) {
-    // 16 lanes per token
-    int qb = (T + 15) / 16;
+  if (quarter) {
+    int qb = alone ? 1 : (T + 15) / 16;
+    const int qt = alone ? (T + 3) / 4 * WAVE : 256;
     const int qmax = device_cu_count() * 8;
     if (qb > qmax) qb = qmax;
     const int nv = (E + 63) / 64;
 #define ROUTE_Q(V)                                                                                     \
-  hipLaunchKernelGGL(route_kernel_q<V>, dim3(qb), dim3(256), shm_q, s, logits, T, E, k, gate_mode, e_lo, \
+  hipLaunchKernelGGL(route_kernel_q<V>, dim3(qb), dim3(qt), shm_q, s, logits, T, E, k, gate_mode, e_lo, \
                      e_cnt, topk_idx, topk_w, counts)
     if (nv <= 1) ROUTE_Q(1);
     else if (nv <= 2) ROUTE_Q(2);

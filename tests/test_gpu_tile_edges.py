@@ -1,7 +1,10 @@
 """GPU parity at the edges of the expert kernels' tiles, against the CPU oracle."""
+import numpy as np
 import pytest
 import torch
 
+from oracle import moe_oracle as O
+from paper_2605_11005_amd import binding as B
 from paper_2605_11005_amd import workloads as W
 from paper_2605_11005_amd.layer import run_backward
 from tests.gpu_util import TOL, check_layer, gpu_layer, host, make_inputs, oracle_layer, rel_err
@@ -22,3 +25,47 @@ def test_fp32_experts_at_tile_edges(T, d, f):
     torch.cuda.synchronize()
     for got, ref in ((buf.dw1, bw["dw1"]), (buf.dw3, bw["dw3"]), (buf.dw2, bw["dw2"])):
         assert rel_err(host(got), 2.0 * ref) < TOL["f32"]
+
+
+# kernels for few rows: 16, 32 or 64 rows per block, wavefronts without a piece of the contraction (d = 64), columns past the end
+@pytest.mark.parametrize("T,d,f", [(1, 64, 64), (16, 192, 320), (17, 1088, 64), (33, 64, 192), (64, 320, 128), (65, 128, 448), (127, 256, 64)])
+def test_bf16_forward_with_few_rows(T, d, f):
+    wl = W.QWEN.scaled(name=f"few-rows-{T}-{d}-{f}", T=T, d=d, f=f, E=1, e_cnt=1, k=1)
+    print(f"case {wl.name}", flush=True)
+    inp = make_inputs(wl)
+    fw, bw = oracle_layer(wl, inp)
+    dev, buf = gpu_layer(wl, inp)
+    check_layer(wl, inp, fw, bw, buf)
+
+
+# router logits: E = 8 n with column blocks of 128, row blocks of 16 to 64, contraction whole or cut into ranges.
+# fp32 sums of bf16 products: n products of N(0, 1/n) terms in any order are off by less than 1e-5 of the largest
+@pytest.mark.parametrize("T,d,E", [(1, 64, 8), (15, 448, 24), (17, 4096, 128), (300, 2880, 136), (4100, 128, 192), (16500, 64, 64)])
+def test_router_logits_at_block_edges(T, d, E):
+    print(f"case router-{T}-{d}-{E}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T + d + E)
+    x = torch.randn((T, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    wr = torch.randn((d, E), generator=g, device="cuda", dtype=torch.bfloat16).mul_(d ** -0.5)
+    logits = torch.full((T, E), float("nan"), device="cuda")
+    ws = torch.empty(B.moe_workspace_bytes(B.WS_ROUTER, B.MOE_BF16, T, 1, d, 0, E, 0), dtype=torch.uint8, device="cuda")
+    B.moe_router_fwd(x, wr, logits, ws)
+    assert rel_err(host(logits), host(x) @ host(wr)) < 1e-5
+
+
+# one block plans up to 8192 slots of up to 900 local experts; beyond either the plan is three launches
+@pytest.mark.parametrize("T,k,e_cnt", [(1, 1, 1), (63, 1, 3), (64, 16, 64), (1024, 8, 7), (1025, 8, 7), (300, 4, 900), (300, 4, 901), (40, 2, 0)])
+def test_plan_in_one_block_and_in_three_launches(T, k, e_cnt):
+    print(f"case plan-{T}-{k}-{e_cnt}", flush=True)
+    E, e_lo = 1024, 5
+    ids = np.random.default_rng(T).permuted(np.tile(np.arange(E if e_cnt > 100 else 80), (T, 1)), axis=1)[:, :k].astype(np.int32)
+    off_ref, perm_ref, inv_ref = O.plan(ids, e_lo, e_cnt)[:3]
+    x = torch.zeros((T, 8), dtype=torch.bfloat16, device="cuda")
+    idx = torch.from_numpy(ids).cuda()
+    cap = T * k
+    i32 = dict(dtype=torch.int32, device="cuda")
+    off, perm, inv = torch.full((e_cnt + 1,), -7, **i32), torch.full((cap,), -7, **i32), torch.full((T, k), -7, **i32)
+    ws = torch.empty(B.moe_workspace_bytes(B.WS_DISPATCH, B.MOE_BF16, T, k, 8, 8, e_cnt, cap), dtype=torch.uint8, device="cuda")
+    B.moe_dispatch(x, k, idx, None, e_lo, e_cnt, off, perm, inv, False, torch.empty((cap, 8), dtype=torch.bfloat16, device="cuda"), ws)
+    R = int(off_ref[-1])
+    assert (host(off) == off_ref).all() and (host(inv) == inv_ref).all() and (host(perm)[:R] == perm_ref).all()
+    assert int(ws[:4].view(torch.int32).item()) == 0
