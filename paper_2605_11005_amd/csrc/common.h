@@ -28,6 +28,14 @@ __device__ __forceinline__ float bf16hi(uint32_t v) { return __uint_as_float(v &
 
 __device__ __forceinline__ int lane_id() { return threadIdx.x & (WAVE - 1); }
 
+// f(Int<0>{}), .., f(Int<N - 1>{})
+template <int V> struct Int { static constexpr int value = V; };
+template <int N, typename F>
+__device__ __forceinline__ void static_for(F f) {
+  if constexpr (N > 1) static_for<N - 1>(f);
+  f(Int<N - 1>{});
+}
+
 // The tile of workgroup b in a launch whose list of tiles is known on the device only: experts in ascending order, each
 // cut into row tiles of TM rows, each of them into n_cols column tiles (fastest).  Workgroup b runs on XCD b % 8, and every
 // XCD takes a contiguous eighth of the list, so that an expert's weights pass through one or two of the eight L2s instead

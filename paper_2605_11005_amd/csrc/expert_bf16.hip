@@ -68,9 +68,8 @@ static_assert(SMEM_BYTES <= 160 * 1024, "one workgroup per CU: 160 KB of LDS");
 
 enum { UP = 0, DOWN = 1, DA = 2, DX = 3, WG = 4, WGD = 5,
        // the trainable router reuses the same machinery on one full-height "expert":
-       RL = 6,    // logits = x Wr            ragged-M shape, B read transposed, fp32 output
-       RW = 7,    // dWr partials = x^T dl    ragged-K shape over fixed chunks of the tokens, fp32 output
-       RX = 8 };  // dx (+)= dl Wr^T          ragged-M shape, B K-contiguous, optional bf16 accumulate
+       RW = 6,    // dWr partials = x^T dl    ragged-K shape over fixed chunks of the tokens, fp32 output
+       RX = 7 };  // dx (+)= dl Wr^T          ragged-M shape, B K-contiguous, optional bf16 accumulate
 
 struct GArgs {
   const bf16_t* A0; const bf16_t* A1;     // A sources (A1: second K segment of DX)
@@ -80,7 +79,7 @@ struct GArgs {
   bf16_t* C0; bf16_t* C1; bf16_t* C2;     // outputs
   long ldc, c_es;
   const bf16_t* H1; const bf16_t* H3;     // DA epilogue inputs
-  float* F0;                              // fp32 output (RL, RW)
+  float* F0;                              // fp32 output (RW)
   const int32_t* off;                     // row offsets; NULL: segment e = [min(e*chunk, rows), min((e+1)*chunk, rows))
   int rows, chunk;
   // Weight gradients of experts with far more rows than the average are cut along the rows into
@@ -96,17 +95,13 @@ struct GArgs {
   int M;                                  // WG/WGD: rows of the output (d or f)
   int N;                                  // output columns (per half for dual tiles)
   int K;                                  // contraction length per segment (ragged-M modes)
-  // RL only: the contraction is cut into ksplit ranges of K columns each (the last one may be
-  // shorter; k_total columns in all); range j writes its fp32 tile to F0 + j * c_es and a
-  // separate pass adds the ranges up.  0 or 1: not cut.
-  int ksplit, k_total;
   int accumulate;
   int save_h;
 };
 
 template <int MODE> struct Traits {
   static constexpr bool A_TRANS = MODE == WG || MODE == WGD || MODE == RW;
-  static constexpr bool B_TRANS = MODE == UP || MODE == DOWN || MODE == WG || MODE == WGD || MODE == RL || MODE == RW;
+  static constexpr bool B_TRANS = MODE == UP || MODE == DOWN || MODE == WG || MODE == WGD || MODE == RW;
   static constexpr bool DUAL = MODE == UP || MODE == WGD;
   static constexpr bool RAGGED_K = MODE == WG || MODE == WGD || MODE == RW;
   static constexpr int BN_EFF = DUAL ? BN / 2 : BN;   // output columns covered per tile
@@ -266,9 +261,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
   // ---- tile list.  Experts are taken heaviest first (ties by id), so that the cheap tiles
   // come last and even out the end of the schedule.  position -> expert in order[];
   // tile_start[pos] = number of tiles before that position (ragged-M modes).
-  // (RL: the ranges of a cut contraction are listed like further column tiles)
-  const int n_tiles_cols = (p.N + TR::BN_EFF - 1) / TR::BN_EFF;
-  const int n_tiles_n = MODE == RL && p.ksplit > 1 ? n_tiles_cols * p.ksplit : n_tiles_cols;
+  const int n_tiles_n = (p.N + TR::BN_EFF - 1) / TR::BN_EFF;
   int total;
   int wg_tiles_per_e = 0, wg_mt = 0;
   for (int e = tid; e <= e_cnt; e += NT) {
@@ -389,7 +382,6 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
   // ---- state of the tile whose k loop runs next (written by next_tile)
   int e = 0, lo = 0, hi = 0, n0 = 0;
   int piece = -1;         // ragged-K modes: index of the fp32 partial tile to write, or -1
-  int krange = 0;         // RL: which range of a cut contraction
   int nk0 = 0, nk = 0;    // k-tiles in segment 0 / in total
   int row0 = 0;           // first output row (global row for ragged-M, i for the weight gradients)
   int row_end = 0;        // one past the last valid output row
@@ -532,10 +524,6 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
       nt = in_band / band_rows;
       mt = band * 8 + (in_band - nt * band_rows);
     }
-    if (MODE == RL) {
-      krange = nt / n_tiles_cols;
-      nt -= krange * n_tiles_cols;
-    }
     n0 = nt * TR::BN_EFF;
     if (TR::RAGGED_K) {
       row0 = mt * BM;
@@ -546,11 +534,10 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
     } else {
       row0 = lo + mt * BM;
       row_end = hi;
-      const size_t kfirst = MODE == RL ? (size_t)krange * p.K : 0;      // first column of this tile's range
-      nk0 = (MODE == RL && p.ksplit > 1 ? min(p.K, p.k_total - krange * p.K) : p.K) / BK;
+      nk0 = p.K / BK;
       nk = MODE == DX ? 2 * nk0 : nk0;
-      ia_kp.setup(p.A0 + (size_t)row0 * p.lda + kfirst, p.lda, hi - row0, wave, lane);
-      if (TR::B_TRANS) ib_tr.setup(p.B0 + (size_t)e * p.b_es + kfirst * p.ldb, p.B1 + (size_t)e * p.b_es, TR::DUAL, p.ldb, n0, p.N, wave, lane);
+      ia_kp.setup(p.A0 + (size_t)row0 * p.lda, p.lda, hi - row0, wave, lane);
+      if (TR::B_TRANS) ib_tr.setup(p.B0 + (size_t)e * p.b_es, p.B1 + (size_t)e * p.b_es, TR::DUAL, p.ldb, n0, p.N, wave, lane);
       else ib_kc.setup(p.B0 + (size_t)e * p.b_es + (size_t)n0 * p.ldb, p.ldb, p.N - n0, wave, lane);
     }
     if (nk > 0) {
@@ -755,7 +742,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
     __syncthreads();
 
     // the ring is free: decode the next tile and start its first loads, then store this one
-    const int ep_e = e, ep_row0 = row0, ep_row_end = row_end, ep_n0 = n0, ep_piece = piece, ep_krange = krange;
+    const int ep_e = e, ep_row0 = row0, ep_row_end = row_end, ep_n0 = n0, ep_piece = piece;
     have = next_tile();
 
     // ---------------------------------------------------------------- epilogue
@@ -967,8 +954,8 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
               float* c0 = p.P0 + (size_t)ep_piece * p.p_stride + (size_t)grow * p.ldc + gcol;
               *reinterpret_cast<float4*>(c0) = make_float4(x[0], x[1], x[2], x[3]);
               *reinterpret_cast<float4*>(c0 + 4) = make_float4(x[4], x[5], x[6], x[7]);
-            } else if (MODE == RL || MODE == RW) {
-              float* c0 = p.F0 + (size_t)(MODE == RW ? ep_e : ep_krange) * p.c_es + (size_t)grow * p.ldc + gcol;
+            } else if (MODE == RW) {
+              float* c0 = p.F0 + (size_t)ep_e * p.c_es + (size_t)grow * p.ldc + gcol;
               *reinterpret_cast<float4*>(c0) = make_float4(x[0], x[1], x[2], x[3]);
               *reinterpret_cast<float4*>(c0 + 4) = make_float4(x[4], x[5], x[6], x[7]);
             } else {
@@ -1112,7 +1099,7 @@ int launch_gg(const GArgs& a, hipStream_t s) {
     attr_set[dev] = true;
   }
   int grid = device_cu_count();
-  ProfScope prof(MODE == RL ? MOE_K_ROUTER_FWD : MODE == RW ? MOE_K_ROUTER_DW : MODE == RX ? MOE_K_ROUTER_DX : MOE_K_UP + MODE, s);
+  ProfScope prof(MODE == RW ? MOE_K_ROUTER_DW : MODE == RX ? MOE_K_ROUTER_DX : MOE_K_UP + MODE, s);
   hipLaunchKernelGGL(gg_kernel<MODE>, dim3(grid), dim3(NT), SMEM_BYTES, s, a);
   HIP_CHECK_LAUNCH();
   return MOE_OK;
@@ -1120,11 +1107,25 @@ int launch_gg(const GArgs& a, hipStream_t s) {
 
 }  // namespace
 
+// Whether the forward takes the kernels for few rows (expert_small.hip) instead of the 256x256 tiles.  Those kernels read
+// each weight once per 64 rows and win while the big tiles would leave CUs idle or mostly multiply padding; the true row
+// counts are on the device, so the line is drawn by the host's bound on the rows per expert and by how many big tiles the
+// up projection would have.  Forward of both GEMMs, this / big tiles, in us (d, f, local experts, bound):
+//   fewer tiles than CUs:      2048, 1408, 8, 128: 38 / 81     4096, 1536, 16, 128: 123 / 136    2048, 1024, 8, 128: 56 / 81
+//   up to two tiles per CU:    2880, 2880, 16, 16: 62 / 107    4096, 4096, 8, 16: 181 / 193      and at 32: 213 / 194
+//   more:                      7168, 2048, 32, 8: 215 / 224    and at 16: 255 / 250, at 32: 301 / 270
+inline bool few_rows(int cap, int f, int e_cnt) {
+  const long long tiles = (long long)e_cnt * ((f + BN / 2 - 1) / (BN / 2)), cus = device_cu_count();
+  const long long bound = tiles < cus ? 128 : (tiles < 2 * cus ? 16 : 8);
+  return cap <= bound * e_cnt;
+}
+
 int launch_expert_fwd_bf16(const void* xp, int cap, int d, int f, int e_cnt, const int32_t* offsets,
                            const void* w1, const void* w3, const void* w2, void* h1, void* h3, void* a_out, void* o,
                            void* a_ws, hipStream_t s) {
   if (cap == 0 || e_cnt == 0) return MOE_OK;
   bf16_t* act = a_out ? (bf16_t*)a_out : (bf16_t*)a_ws;
+  if (few_rows(cap, f, e_cnt)) return launch_expert_fwd_small(xp, cap, d, f, e_cnt, offsets, w1, w3, w2, h1, h3, act, o, s);
   int32_t* sched = sched_area(a_ws, (size_t)cap * f * 2);
   hipLaunchKernelGGL(zero_words, dim3(1), dim3(64), 0, s, sched, 16);
   HIP_CHECK_LAUNCH();
@@ -1248,9 +1249,8 @@ int router_dw_splits(int T, int d, int E) {
   return best;
 }
 
-// Into how many ranges the router's forward GEMM cuts its contraction over d: with few experts
-// the [T, E] logits are fewer tiles than the chip has CUs, so each tile's k loop is shared out.
-// The same cost model as above, in pairs of k-tiles (a range is a whole number of pairs).
+// How many ranges of the contraction over d the workspace of the router's forward holds fp32 partial logits for: the same
+// cost model as above for a [T, E] result of few 256 x 256 tiles, in pairs of k-tiles.
 int router_fwd_splits(int T, int d, int E) {
   const long long tiles = (long long)((T + BM - 1) / BM) * ((E + BN - 1) / BN);
   const int cus = device_cu_count();
@@ -1265,22 +1265,6 @@ int router_fwd_splits(int T, int d, int E) {
   // no empty range: as many ranges as the rounded-up range length needs
   const int per = (pairs + best - 1) / best;
   return (pairs + per - 1) / per;
-}
-
-// partials: fp32 [splits, T, E] when the contraction is cut (splits > 1), else unused; the caller adds them up
-int launch_router_fwd_bf16(const void* x, const void* wr, int T, int d, int E, float* logits, float* partials,
-                           int splits, int32_t* sched, hipStream_t s) {
-  if (T == 0) return MOE_OK;
-  hipLaunchKernelGGL(zero_words, dim3(1), dim3(64), 0, s, sched, 8);
-  HIP_CHECK_LAUNCH();
-  GArgs g = {};
-  g.A0 = g.A1 = (const bf16_t*)x; g.lda = d;
-  g.B0 = g.B1 = (const bf16_t*)wr; g.ldb = E; g.b_es = 0;
-  g.F0 = splits > 1 ? partials : logits; g.ldc = E; g.c_es = (long)T * E;
-  g.off = nullptr; g.rows = T; g.chunk = T; g.sched = sched; g.e_cnt = 1; g.N = E;
-  const int pairs = d / (2 * BK);
-  g.ksplit = splits; g.k_total = d; g.K = splits > 1 ? (pairs + splits - 1) / splits * 2 * BK : d;
-  return launch_gg<RL>(g, s);
 }
 
 int launch_router_dw_bf16(const void* x, const void* dl_bf16, int T, int d, int E, float* partials, int splits,

@@ -97,7 +97,6 @@ struct OperMN {
   }
 };
 
-template <int V> struct Set { static constexpr int value = V; };
 template <bool C, typename A, typename B> struct Pick { typedef A type; };
 template <typename A, typename B> struct Pick<false, A, B> { typedef B type; };
 
@@ -217,23 +216,23 @@ __global__ __launch_bounds__(NT) void gemm_f32(Args p) {
   };
   setup(0);
   if (nk > 0) {
-    fetch(0, Set<0>{});
-    fetch(1, Set<1>{});
-    publish(0, Set<0>{});
+    fetch(0, Int<0>{});
+    fetch(1, Int<1>{});
+    publish(0, Int<0>{});
   }
   __syncthreads();
   // LDS buffer 1 is written while buffer 0 is multiplied and the other way round; the barrier ends both
   for (int kt = 0; kt + 1 < nk; kt += 2) {
-    fetch(kt + 2, Set<0>{});
-    multiply(Set<0>{});
-    publish(kt + 1, Set<1>{});
+    fetch(kt + 2, Int<0>{});
+    multiply(Int<0>{});
+    publish(kt + 1, Int<1>{});
     __syncthreads();
-    fetch(kt + 3, Set<1>{});
-    multiply(Set<1>{});
-    publish(kt + 2, Set<0>{});
+    fetch(kt + 3, Int<1>{});
+    multiply(Int<1>{});
+    publish(kt + 2, Int<0>{});
     __syncthreads();
   }
-  if (nk & 1) multiply(Set<0>{});
+  if (nk & 1) multiply(Int<0>{});
 
   // accumulator element 4g + i of a lane is row 8g + 4*(lane/32) + i, column lane%32 of its wavefront's block
   const int col = col0 + wn * 32 + (lane & 31);

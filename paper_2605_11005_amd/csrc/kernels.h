@@ -37,6 +37,12 @@ int launch_expert_bwd_bf16(const void* xp, const void* h1, const void* h3, const
                            const void* w3, const void* w2, void* dxp, void* dw1, void* dw3, void* dw2,
                            int accumulate, void* ws, hipStream_t s);
 
+// forward with few rows per expert (expert_small.hip): h1, h3 both or neither
+int launch_expert_fwd_small(const void* xp, int cap, int d, int f, int e_cnt, const int32_t* offsets, const void* w1,
+                            const void* w3, const void* w2, void* h1, void* h3, void* a, void* o, hipStream_t s);
+int launch_router_fwd_small(const void* x, const void* wr, int T, int d, int E, float* logits, float* partials, int max_ranges,
+                            int* ranges, hipStream_t s);
+
 // trainable router (router.hip; the matrix-core variants live in expert_bf16.hip)
 size_t router_ws_bytes(int dtype, int T, int d, int E);
 int launch_router_fwd(const void* x, const void* wr, int dtype, int T, int d, int E, float* logits, void* ws,
@@ -49,8 +55,6 @@ int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int d
                       int dwr_acc, void* dx, int dx_acc, void* ws, hipStream_t s);
 int router_dw_splits(int T, int d, int E);
 int router_fwd_splits(int T, int d, int E);
-int launch_router_fwd_bf16(const void* x, const void* wr, int T, int d, int E, float* logits, float* partials,
-                           int splits, int32_t* sched, hipStream_t s);
 int launch_router_dw_bf16(const void* x, const void* dl_bf16, int T, int d, int E, float* partials, int splits,
                           int32_t* sched, hipStream_t s);
 int launch_router_dx_bf16(const void* dl_bf16, const void* wr, int T, int d, int E, void* dx, int accumulate,

@@ -423,10 +423,11 @@ size_t router_ws_bytes(int dtype, int T, int d, int E) {
 int launch_router_fwd(const void* x, const void* wr, int dtype, int T, int d, int E, float* logits, void* ws,
                       hipStream_t s) {
   if (T == 0) return MOE_OK;
-  if (mfma_shape(dtype, T, d, E)) {
-    const int splits = router_fwd_splits(T, d, E);
+  if (dtype == MOE_BF16 && E % 8 == 0 && d % 64 == 0) {
     float* partial = (float*)((char*)ws + 256);
-    int rc = launch_router_fwd_bf16(x, wr, T, d, E, logits, partial, splits, (int32_t*)ws, s);
+    const int room = mfma_shape(dtype, T, d, E) ? router_fwd_splits(T, d, E) : 1;      // what the workspace holds
+    int splits = 1;
+    int rc = launch_router_fwd_small(x, wr, T, d, E, logits, partial, room, &splits, s);
     if (rc || splits == 1) return rc;
     ProfScope prof(MOE_K_ROUTER_FWD, s);
     hipLaunchKernelGGL((reduce_chunks<float>), dim3(device_cu_count() * 4), dim3(256), 0, s, partial, splits, (size_t)T * E,
