@@ -1288,12 +1288,6 @@ int launch_router_dx_bf16(const void* dl_bf16, const void* wr, int T, int d, int
   return launch_gg<RX>(g, s);
 }
 
-int launch_zero_words(int32_t* p, int n, hipStream_t s) {
-  hipLaunchKernelGGL(zero_words, dim3(1), dim3(64), 0, s, p, n);
-  HIP_CHECK_LAUNCH();
-  return MOE_OK;
-}
-
 // fp32 partial tiles for weight gradients cut along the rows: room for up to 32 pieces of the
 // larger (two-output) gradient, at most 512 MB
 size_t wgrad_split_bytes(int d, int f) {

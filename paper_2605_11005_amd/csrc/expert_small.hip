@@ -3,6 +3,8 @@
 //   UP     h1|h3 = xp [W1|W3] -> a = silu(h1) h3     per expert, up to 64 rows at a time
 //   DOWN   o     = a W2
 //   RL     logits = x Wr (fp32)                       one "expert" of T rows
+//   RW     dWr = x^T dlogits (fp32 partial sums)      x streams in the weights' place, the contraction runs over the tokens
+//                                                     and the rows are the experts (launch_router_dw_small)
 //
 // What bounds it: reading the weights once (a row of a decode step multiplies each of them once or a few times), so the
 // kernel is a stream of weights with the matrix instruction at its end.  256x256 tiles leave most of the chip idle here (four
@@ -25,7 +27,7 @@ typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-enum { UP, DOWN, RL };
+enum { UP, DOWN, RL, RW };
 
 constexpr int COLS = 128;                 // columns of a block (UP: 64 of W1 and the same 64 of W3)
 constexpr int ROWS = 64;                  // rows of a block at most
@@ -41,7 +43,9 @@ struct SArgs {
   long ldc;
   const int32_t* off;                     // NULL (RL): one expert of `rows` rows
   int rows, e_cnt, N, K;
-  int range;                              // RL: pieces of the contraction per range (grid z); range z's sums go to F + z * rows * N
+  long xstep;                             // elements from a row's piece to its next piece
+  int n_experts;                          // RW: rows are (plane, expert), expert fastest
+  int range;                              // RL, RW: pieces of the contraction per range (grid z); range z's sums go to F + z * rows * N
 };
 
 // Loads go through a buffer descriptor: a wave-uniform base and a 32-bit byte offset per lane.  With 64-bit addresses per
@@ -122,9 +126,10 @@ __device__ __forceinline__ void tile(const SArgs& p, float* red, int e, int row0
     auto load = [&](auto slot, int idx) {
       constexpr int S = decltype(slot)::value;
       const bool in = idx < n;
-      const long k = in ? (long)(first + wave + NW * idx) * KP : 0;
+      const long piece = in ? first + wave + NW * idx : 0;
+      const long k = MODE == RW ? min(piece * KP, (long)p.K - KP) : piece * KP;      // RW: the last piece ends at the last token
       w[S].load(b0 + k * p.ldb, b1 + k * p.ldb, in, 2 * (int)p.ldb, woff);
-      const __amdgpu_buffer_rsrc_t dx = descriptor(xrow + k, in);
+      const __amdgpu_buffer_rsrc_t dx = descriptor(xrow + piece * p.xstep, in);
 #pragma unroll
       for (int t = 0; t < TG; ++t) x[S][t] = __builtin_bit_cast(bf16x8, __builtin_amdgcn_raw_buffer_load_b128(dx, xoff[t], 0, 0));
       __builtin_amdgcn_sched_barrier(0);  // pieces stay in order: waiting for one must not wait for the next
@@ -158,6 +163,20 @@ __device__ __forceinline__ void tile(const SArgs& p, float* red, int e, int row0
         *reinterpret_cast<f32x4*>(mine + (DUAL ? 64 * h + 4 * (4 * g + r) : 8 * (4 * g + r) + 4 * h)) =
             f32x4{acc[t][4 * h][r], acc[t][4 * h + 1][r], acc[t][4 * h + 2][r], acc[t][4 * h + 3][r]};
     __syncthreads();
+    if (MODE == RW) {                                           // [column][expert], one plane after the other; rows fastest
+      const int r = tid & 15, row = row0 + 16 * t + r;
+      if (row < row_end) {
+        const int plane = row / p.n_experts;
+        float* out = p.F + (size_t)plane * p.N * p.n_experts + (row - plane * p.n_experts);
+        for (int c = tid >> 4; c < COLS && n0 + c < p.N; c += NW * WAVE / 16) {
+          float v = 0.f;
+#pragma unroll
+          for (int wv = 0; wv < NW; ++wv) v += red[(wv * 16 + r) * RPITCH + c];
+          out[(size_t)(n0 + c) * p.n_experts] = v;
+        }
+      }
+      continue;
+    }
     const int rr = tid / (COLS / PER), c = tid % (COLS / PER);  // row of the group, column group
     const int row = row0 + 16 * t + rr;
     // this thread's columns: PER / 2 from each half of a row (UP: h1 | h3), or PER in a row
@@ -220,13 +239,13 @@ __global__ __launch_bounds__(NW_EXPERT * WAVE, 2) void small_rows(SArgs p) {
 }
 
 // grid = (row blocks of 16 * TG, column blocks, ranges of the contraction)
-template <int TG>
+template <int MODE, int TG>
 __global__ __launch_bounds__(NW_ROUTER * WAVE) void small_rows_router(SArgs p) {
   __shared__ __align__(16) float red[NW_ROUTER * 16 * RPITCH];
   const int row0 = blockIdx.x * 16 * TG, first = blockIdx.z * p.range;
   p.F += (size_t)blockIdx.z * p.rows * p.N;
-  tile<RL, TG, NW_ROUTER>(p, red, 0, row0, min(p.rows, row0 + 16 * TG), blockIdx.y * COLS, first,
-                          min(p.range, p.K / KP - first), threadIdx.x);
+  tile<MODE, TG, NW_ROUTER>(p, red, 0, row0, min(p.rows, row0 + 16 * TG), blockIdx.y * COLS, first,
+                            min(p.range, (p.K + KP - 1) / KP - first), threadIdx.x);
 }
 
 template <int MODE>
@@ -247,14 +266,14 @@ int launch_expert_fwd_small(const void* xp, int cap, int d, int f, int e_cnt, co
   SArgs u = {};
   u.A = (const bf16_t*)xp; u.lda = d;
   u.B0 = (const bf16_t*)w1; u.B1 = (const bf16_t*)w3; u.ldb = f; u.b_es = (long)d * f;
-  u.C0 = (bf16_t*)h1; u.C1 = (bf16_t*)h3; u.C2 = (bf16_t*)a; u.ldc = f;
+  u.C0 = (bf16_t*)h1; u.C1 = (bf16_t*)h3; u.C2 = (bf16_t*)a; u.ldc = f; u.xstep = KP;
   u.off = offsets; u.e_cnt = e_cnt; u.N = f; u.K = d;
   int rc = launch_small<UP>(u, cap, MOE_K_UP, s);
   if (rc) return rc;
   SArgs w = {};
   w.A = (const bf16_t*)a; w.lda = f;
   w.B0 = (const bf16_t*)w2; w.ldb = d; w.b_es = (long)f * d;
-  w.C0 = (bf16_t*)o; w.ldc = d;
+  w.C0 = (bf16_t*)o; w.ldc = d; w.xstep = KP;
   w.off = offsets; w.e_cnt = e_cnt; w.N = d; w.K = f;
   return launch_small<DOWN>(w, cap, MOE_K_DOWN, s);
 }
@@ -266,7 +285,7 @@ int launch_router_fwd_small(const void* x, const void* wr, int T, int d, int E, 
   SArgs p = {};
   p.A = (const bf16_t*)x; p.lda = d;
   p.B0 = (const bf16_t*)wr; p.ldb = E;
-  p.ldc = E; p.rows = T; p.e_cnt = 1; p.N = E; p.K = d;
+  p.ldc = E; p.rows = T; p.e_cnt = 1; p.N = E; p.K = d; p.xstep = KP;
   const int cols = (E + COLS - 1) / COLS, cus = device_cu_count(), pieces = d / KP;
   // as many rows per block as still leave a block for every CU: the weights are read once per block
   const int tg = (long long)(T + 63) / 64 * cols >= cus ? 4 : ((long long)(T + 31) / 32 * cols >= cus ? 2 : 1);
@@ -283,9 +302,37 @@ int launch_router_fwd_small(const void* x, const void* wr, int T, int d, int E, 
   *ranges = n;
   const dim3 grid(row_blocks, cols, n), block(NW_ROUTER * WAVE);
   ProfScope prof(MOE_K_ROUTER_FWD, s);
-  if (tg == 4) hipLaunchKernelGGL(small_rows_router<4>, grid, block, 0, s, p);
-  else if (tg == 2) hipLaunchKernelGGL(small_rows_router<2>, grid, block, 0, s, p);
-  else hipLaunchKernelGGL(small_rows_router<1>, grid, block, 0, s, p);
+  if (tg == 4) hipLaunchKernelGGL((small_rows_router<RL, 4>), grid, block, 0, s, p);
+  else if (tg == 2) hipLaunchKernelGGL((small_rows_router<RL, 2>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((small_rows_router<RL, 1>), grid, block, 0, s, p);
+  HIP_CHECK_LAUNCH();
+  return MOE_OK;
+}
+
+// dlogits as router_dw_operand lays them out: [pieces][planes * E][32].  Partial sums go to partials[ranges * planes][d][E]
+// (range by range, plane by plane); at most max_sums of them.  T >= 32.
+int launch_router_dw_small(const void* x, const void* dl_pieces, int planes, int T, int d, int E, float* partials, int max_sums,
+                           int* sums, hipStream_t s) {
+  SArgs p = {};
+  p.A = (const bf16_t*)dl_pieces; p.lda = KP; p.rows = planes * E; p.xstep = (long)planes * E * KP; p.n_experts = E;
+  p.B0 = (const bf16_t*)x; p.ldb = d;
+  p.F = partials; p.N = d; p.K = T;
+  const int cols = (d + COLS - 1) / COLS, pieces = (T + KP - 1) / KP;
+  const int tg = p.rows <= 16 ? 1 : (p.rows <= 32 ? 2 : 4);
+  const int row_blocks = (p.rows + 16 * tg - 1) / (16 * tg);
+  // a block for every CU, but at least two pieces per wavefront and no more sums than there is room for
+  int n = device_cu_count() / (cols * row_blocks);
+  if (n > max_sums / planes) n = max_sums / planes;
+  if (n > pieces / (2 * NW_ROUTER)) n = pieces / (2 * NW_ROUTER);
+  if (n < 1) n = 1;
+  p.range = (pieces + n - 1) / n;
+  n = (pieces + p.range - 1) / p.range;
+  *sums = n * planes;
+  const dim3 grid(row_blocks, cols, n), block(NW_ROUTER * WAVE);
+  ProfScope prof(MOE_K_ROUTER_DW, s);
+  if (tg == 4) hipLaunchKernelGGL((small_rows_router<RW, 4>), grid, block, 0, s, p);
+  else if (tg == 2) hipLaunchKernelGGL((small_rows_router<RW, 2>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((small_rows_router<RW, 1>), grid, block, 0, s, p);
   HIP_CHECK_LAUNCH();
   return MOE_OK;
 }

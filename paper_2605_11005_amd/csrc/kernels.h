@@ -42,6 +42,8 @@ int launch_expert_fwd_small(const void* xp, int cap, int d, int f, int e_cnt, co
                             const void* w3, const void* w2, void* h1, void* h3, void* a, void* o, hipStream_t s);
 int launch_router_fwd_small(const void* x, const void* wr, int T, int d, int E, float* logits, float* partials, int max_ranges,
                             int* ranges, hipStream_t s);
+int launch_router_dw_small(const void* x, const void* dl_pieces, int planes, int T, int d, int E, float* partials, int max_sums,
+                           int* sums, hipStream_t s);
 
 // trainable router (router.hip; the matrix-core variants live in expert_bf16.hip)
 size_t router_ws_bytes(int dtype, int T, int d, int E);
@@ -59,7 +61,6 @@ int launch_router_dw_bf16(const void* x, const void* dl_bf16, int T, int d, int 
                           int32_t* sched, hipStream_t s);
 int launch_router_dx_bf16(const void* dl_bf16, const void* wr, int T, int d, int E, void* dx, int accumulate,
                           int32_t* sched, hipStream_t s);
-int launch_zero_words(int32_t* p, int n, hipStream_t s);
 
 // bytes that launch_expert_bwd_bf16 uses after the three [cap,f] activation buffers
 size_t expert_bwd_extra_ws_bytes(int d, int f);

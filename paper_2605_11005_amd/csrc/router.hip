@@ -225,9 +225,100 @@ __global__ __launch_bounds__(256) void router_fwd_small_e(const TX* __restrict__
   }
 }
 
-__global__ void round_to_bf16(const float* __restrict__ in, bf16_t* __restrict__ out, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    out[i] = f32_to_bf16(in[i]);
+// dlogits for the matrix-core products, one block per 32 tokens (a piece of the contraction over the tokens):
+//   dlb     [T][E] bf16 (NULL: not wanted): operand of the input-gradient product
+//   pieces  [piece][plane][E][32] bf16 (NULL: not wanted): operand of the weight-gradient product, tokens contiguous.
+//           PLANES = 1: rounded once, the path whose dlogits are bf16.  PLANES = 3: three terms whose sum keeps all 24 bits,
+//           for shapes whose dlogits stay fp32.  The last piece ends at the last token, with zeros for the tokens that the
+//           piece before it has covered (T >= 32).
+// The first block also clears the ticket counters of the product that follows (n_words; a launch of its own otherwise).
+template <int PLANES>
+__global__ __launch_bounds__(256) void router_dl_operands(const float* __restrict__ dl, int T, int E, bf16_t* __restrict__ dlb,
+                                                         bf16_t* __restrict__ pieces, int32_t* __restrict__ words, int n_words) {
+  __shared__ float tile[32][65];
+  const int tid = threadIdx.x;
+  if (blockIdx.x == 0 && tid < n_words) words[tid] = 0;
+  const int t0 = blockIdx.x * 32, base = pieces && T - 32 < t0 ? T - 32 : t0;
+  for (int e0 = 0; e0 < E; e0 += 64) {
+    __syncthreads();
+    for (int i = tid; i < 32 * 64; i += 256) {
+      const int t = base + (i >> 6), e = e0 + (i & 63);
+      float v = 0.f;
+      if (t >= t0 && t < T && e < E) {
+        v = dl[(size_t)t * E + e];
+        if (dlb) dlb[(size_t)t * E + e] = f32_to_bf16(v);
+      }
+      tile[i >> 6][i & 63] = v;
+    }
+    __syncthreads();
+    const int e = e0 + (tid >> 2), k = 8 * (tid & 3);
+    if (pieces && e < E) {
+      float v[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) v[i] = tile[k + i][tid >> 2];
+#pragma unroll
+      for (int p = 0; p < PLANES; ++p) {
+        uint32_t w[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          w[i] = pack_bf16x2(v[2 * i], v[2 * i + 1]);
+          v[2 * i] -= bf16lo(w[i]);
+          v[2 * i + 1] -= bf16hi(w[i]);
+        }
+        *reinterpret_cast<uint4*>(pieces + (((size_t)blockIdx.x * PLANES + p) * E + e) * 32 + k) = make_uint4(w[0], w[1], w[2], w[3]);
+      }
+    }
+  }
+}
+
+// The router term of dx for E = 8 or 16 experts: a thread keeps the weights of its eight columns in registers and walks
+// DX_TOKENS tokens (their dlogits are uniform: scalar loads), so that what is left is the read-modify-write of dx, eight
+// tokens in flight.  With one block per token, which fetched the weights again for each, T = 16384, d = 4096, E = 8 took
+// 172 us.
+constexpr int DX_TOKENS = 32;
+
+template <int E>
+__global__ __launch_bounds__(256) void router_dx_columns(const float* __restrict__ dl, const bf16_t* __restrict__ wr,
+                                                        bf16_t* __restrict__ dx, int T, int d, int beta, int col_groups) {
+  const int tg = blockIdx.x / col_groups;
+  const int c0 = ((blockIdx.x - tg * col_groups) * 256 + threadIdx.x) * 8;
+  if (c0 >= d) return;
+  float w[8][E];
+#pragma unroll
+  for (int i = 0; i < 8; ++i)
+#pragma unroll
+    for (int e = 0; e < E; e += 8) {
+      const uint4 q = *reinterpret_cast<const uint4*>(wr + (size_t)(c0 + i) * E + e);
+      const uint32_t* u = reinterpret_cast<const uint32_t*>(&q);
+#pragma unroll
+      for (int j = 0; j < 4; ++j) { w[i][e + 2 * j] = bf16lo(u[j]); w[i][e + 2 * j + 1] = bf16hi(u[j]); }
+    }
+  constexpr int AHEAD = 8;
+  const int t_end = min(T, (tg + 1) * DX_TOKENS);
+  for (int t0 = tg * DX_TOKENS; t0 < t_end; t0 += AHEAD) {
+    u32x4 old[AHEAD];
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k) {
+      old[k] = u32x4{0u, 0u, 0u, 0u};
+      if (beta) old[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(dx + (size_t)min(t0 + k, t_end - 1) * d + c0));
+    }
+#pragma unroll
+    for (int k = 0; k < AHEAD; ++k) {
+      if (t0 + k >= t_end) break;
+      const float* row = dl + (size_t)(t0 + k) * E;
+      float acc[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc[i] = 0.f;
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) acc[i] += row[e] * w[i][e];
+      u32x4 out;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) out[i] = pack_bf16x2(bf16lo(old[k][i]) + acc[2 * i], bf16hi(old[k][i]) + acc[2 * i + 1]);
+      __builtin_nontemporal_store(out, reinterpret_cast<u32x4*>(dx + (size_t)(t0 + k) * d + c0));
+    }
+  }
 }
 
 // ---- fused backward of combine ------------------------------------------------------------
@@ -501,16 +592,39 @@ int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int d
   const size_t n_w = (size_t)d * E;
   const int red_blocks = device_cu_count() * 4;
   int rc;
-  if (mfma_shape(dtype, T, d, E)) {
+  // Weight gradient of up to 128 experts (two passes over x): the streaming kernel, if the workspace's partial sums leave
+  // room for its operand beside at least one sum per plane.  Its sums need no more bytes than the cut product's.
+  const bool mfma = mfma_shape(dtype, T, d, E);
+  const int planes = mfma ? 1 : 3;
+  const size_t sum_bytes = n_w * 4;
+  const size_t room = mfma ? align256((size_t)router_dw_splits(T, d, E) * sum_bytes) : align256((size_t)valu_splits(T, d, E) * sum_bytes);
+  const size_t piece_bytes = align256((size_t)((T + 31) / 32) * 32 * planes * E * 2);
+  const bool dw_small = dwr && dtype == MOE_BF16 && T >= 32 && d % 64 == 0 && planes * E <= 128 &&
+                        room >= piece_bytes + planes * sum_bytes;
+  const auto dw_operands = [&](bf16_t* dlb, bf16_t* pieces) -> int {
+    ProfScope prof(dwr ? MOE_K_ROUTER_DW : MOE_K_ROUTER_DX, s);
+    if (planes == 1)
+      hipLaunchKernelGGL(router_dl_operands<1>, dim3((T + 31) / 32), dim3(256), 0, s, dlogits, T, E, dlb, pieces, sched, 16);
+    else
+      hipLaunchKernelGGL(router_dl_operands<3>, dim3((T + 31) / 32), dim3(256), 0, s, dlogits, T, E, dlb, pieces, sched, 0);
+    return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
+  };
+  const auto dw_stream = [&](bf16_t* pieces) -> int {
+    float* sums = (float*)((char*)pieces + piece_bytes);
+    int n = 0;
+    const int rc2 = launch_router_dw_small(x, pieces, planes, T, d, E, sums, (int)((room - piece_bytes) / sum_bytes), &n, s);
+    if (rc2) return rc2;
+    ProfScope prof(MOE_K_ROUTER_DW, s);
+    hipLaunchKernelGGL((reduce_chunks<bf16_t>), dim3(red_blocks), dim3(256), 0, s, sums, n, n_w, (bf16_t*)dwr, dwr_acc);
+    return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
+  };
+  if (mfma) {
     bf16_t* dlb = (bf16_t*)base;
     float* partial = (float*)(base + align256((size_t)T * E * 2));
-    if ((rc = launch_zero_words(sched, 16, s))) return rc;
-    {
-      ProfScope prof(dwr ? MOE_K_ROUTER_DW : MOE_K_ROUTER_DX, s);
-      hipLaunchKernelGGL(round_to_bf16, dim3(red_blocks), dim3(256), 0, s, dlogits, dlb, (size_t)T * E);
-      HIP_CHECK_LAUNCH();
-    }
-    if (dwr) {
+    if ((rc = dw_operands(dlb, dw_small ? (bf16_t*)partial : nullptr))) return rc;
+    if (dw_small) {
+      if ((rc = dw_stream((bf16_t*)partial))) return rc;
+    } else if (dwr) {
       const int splits = router_dw_splits(T, d, E);
       if ((rc = launch_router_dw_bf16(x, dlb, T, d, E, partial, splits, sched, s))) return rc;
       ProfScope prof(MOE_K_ROUTER_DW, s);
@@ -522,7 +636,10 @@ int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int d
     return MOE_OK;
   }
   float* partial = (float*)base;
-  if (dwr) {
+  if (dw_small) {
+    if ((rc = dw_operands(nullptr, (bf16_t*)base))) return rc;
+    if ((rc = dw_stream((bf16_t*)base))) return rc;
+  } else if (dwr) {
     const int splits = T > 0 ? valu_splits(T, d, E) : 0;
     if (splits > 0) {
       ProfScope prof(MOE_K_ROUTER_DW, s);
@@ -542,7 +659,14 @@ int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int d
   }
   if (dx && T > 0) {
     ProfScope prof(MOE_K_ROUTER_DX, s);
-    if (E <= 64) {
+    if (dtype == MOE_BF16 && (E == 8 || E == 16)) {
+      const int col_groups = tiles(d, 2048);
+      dim3 grid((unsigned)col_groups * ((T + DX_TOKENS - 1) / DX_TOKENS)), blk(256);
+      if (E == 8)
+        hipLaunchKernelGGL(router_dx_columns<8>, grid, blk, 0, s, dlogits, (const bf16_t*)wr, (bf16_t*)dx, T, d, dx_acc, col_groups);
+      else
+        hipLaunchKernelGGL(router_dx_columns<16>, grid, blk, 0, s, dlogits, (const bf16_t*)wr, (bf16_t*)dx, T, d, dx_acc, col_groups);
+    } else if (E <= 64) {
       // a handful of experts: per-token dot products against contiguous weight rows
       const int col_groups = tiles(d, 1024);
       if ((long long)col_groups * T >= (1ll << 31)) return MOE_EUNSUPPORTED;

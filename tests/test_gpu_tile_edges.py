@@ -69,3 +69,25 @@ def test_plan_in_one_block_and_in_three_launches(T, k, e_cnt):
     R = int(off_ref[-1])
     assert (host(off) == off_ref).all() and (host(inv) == inv_ref).all() and (host(perm)[:R] == perm_ref).all()
     assert int(ws[:4].view(torch.int32).item()) == 0
+
+
+# router backward: the streaming weight gradient (32 tokens or more, planes * E <= 128; pieces of 32 tokens, the last one
+# overlapping the one before it), the input gradient of up to 16 experts, and the shapes just outside either.
+# bf16 dlogits (E % 64 == 0): one rounding, 2e-2 as everywhere; fp32 dlogits: bf16 stores only, 2**-8 of the largest
+@pytest.mark.parametrize("T,d,E", [(32, 64, 8), (33, 192, 8), (1000, 2048, 16), (31, 64, 8), (777, 320, 40), (500, 128, 48),
+                                   (2049, 448, 64), (4000, 128, 128), (300, 64, 192)])
+def test_router_backward_at_block_edges(T, d, E):
+    print(f"case router-bwd-{T}-{d}-{E}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T + d + E)
+    x = torch.randn((T, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    wr = torch.randn((d, E), generator=g, device="cuda", dtype=torch.bfloat16).mul_(d ** -0.5)
+    dl = torch.randn((T, E), generator=g, device="cuda")
+    dx = torch.randn((T, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    dx0 = host(dx)
+    dwr = torch.full((d, E), float("nan"), device="cuda", dtype=torch.bfloat16)
+    ws = torch.empty(B.moe_workspace_bytes(B.WS_ROUTER, B.MOE_BF16, T, 1, d, 0, E, 0), dtype=torch.uint8, device="cuda")
+    B.moe_router_bwd(x, wr, dl, dwr, False, dx, True, ws)
+    dwr_ref, dx_ref = O.router_bwd(host(x), host(wr), host(dl))
+    tol = TOL["bf16"] if E % 64 == 0 else 2.0 ** -8
+    assert rel_err(host(dwr), dwr_ref) < tol
+    assert rel_err(host(dx), dx0 + dx_ref) < tol
