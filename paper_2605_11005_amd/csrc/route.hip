@@ -266,10 +266,11 @@ int launch_route(const float* logits, int T, int E, int k, int gate_mode, int e_
   ProfScope prof(MOE_K_ROUTE, s);
   size_t shm_q = (size_t)(e_cnt > 0 ? e_cnt : 1) * sizeof(int32_t);
   if (quarter) {
+    // otherwise one block per CU at most: every block adds its counts to the same e_cnt words, and those adds queue up
+    // (T = 16384, E = 128, 16 local experts: 17.4 us with 1024 blocks, 12.3 with 256)
     int qb = alone ? 1 : (T + 15) / 16;
-    const int qt = alone ? (T + 3) / 4 * WAVE : 256;
-    const int qmax = device_cu_count() * 8;
-    if (qb > qmax) qb = qmax;
+    const int qt = alone ? (T + 3) / 4 * WAVE : (T > 16 * device_cu_count() ? 512 : 256);
+    if (qb > device_cu_count()) qb = device_cu_count();
     const int nv = (E + 63) / 64;
 #define ROUTE_Q(V)                                                                                     \
   hipLaunchKernelGGL(route_kernel_q<V>, dim3(qb), dim3(qt), shm_q, s, logits, T, E, k, gate_mode, e_lo, \
