@@ -68,8 +68,9 @@ static_assert(SMEM_BYTES <= 160 * 1024, "one workgroup per CU: 160 KB of LDS");
 
 enum { UP = 0, DOWN = 1, DA = 2, DX = 3, WG = 4, WGD = 5,
        // the trainable router reuses the same machinery on one full-height "expert":
-       RW = 6,    // dWr partials = x^T dl    ragged-K shape over fixed chunks of the tokens, fp32 output
-       RX = 7 };  // dx (+)= dl Wr^T          ragged-M shape, B K-contiguous, optional bf16 accumulate
+       RL = 6,    // logits = x Wr            ragged-M shape, B read transposed, fp32 output
+       RW = 7,    // dWr partials = x^T dl    ragged-K shape over fixed chunks of the tokens, fp32 output
+       RX = 8 };  // dx (+)= dl Wr^T          ragged-M shape, B K-contiguous, optional bf16 accumulate
 
 struct GArgs {
   const bf16_t* A0; const bf16_t* A1;     // A sources (A1: second K segment of DX)
@@ -79,7 +80,7 @@ struct GArgs {
   bf16_t* C0; bf16_t* C1; bf16_t* C2;     // outputs
   long ldc, c_es;
   const bf16_t* H1; const bf16_t* H3;     // DA epilogue inputs
-  float* F0;                              // fp32 output (RW)
+  float* F0;                              // fp32 output (RL, RW)
   const int32_t* off;                     // row offsets; NULL: segment e = [min(e*chunk, rows), min((e+1)*chunk, rows))
   int rows, chunk;
   // Weight gradients of experts with far more rows than the average are cut along the rows into
@@ -95,13 +96,17 @@ struct GArgs {
   int M;                                  // WG/WGD: rows of the output (d or f)
   int N;                                  // output columns (per half for dual tiles)
   int K;                                  // contraction length per segment (ragged-M modes)
+  // RL only: the contraction is cut into ksplit ranges of K columns each (the last one may be
+  // shorter; k_total columns in all); range j writes its fp32 tile to F0 + j * c_es and a
+  // separate pass adds the ranges up.  0 or 1: not cut.
+  int ksplit, k_total;
   int accumulate;
   int save_h;
 };
 
 template <int MODE> struct Traits {
   static constexpr bool A_TRANS = MODE == WG || MODE == WGD || MODE == RW;
-  static constexpr bool B_TRANS = MODE == UP || MODE == DOWN || MODE == WG || MODE == WGD || MODE == RW;
+  static constexpr bool B_TRANS = MODE == UP || MODE == DOWN || MODE == WG || MODE == WGD || MODE == RL || MODE == RW;
   static constexpr bool DUAL = MODE == UP || MODE == WGD;
   static constexpr bool RAGGED_K = MODE == WG || MODE == WGD || MODE == RW;
   static constexpr int BN_EFF = DUAL ? BN / 2 : BN;   // output columns covered per tile
@@ -261,7 +266,9 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
   // ---- tile list.  Experts are taken heaviest first (ties by id), so that the cheap tiles
   // come last and even out the end of the schedule.  position -> expert in order[];
   // tile_start[pos] = number of tiles before that position (ragged-M modes).
-  const int n_tiles_n = (p.N + TR::BN_EFF - 1) / TR::BN_EFF;
+  // (RL: the ranges of a cut contraction are listed like further column tiles)
+  const int n_tiles_cols = (p.N + TR::BN_EFF - 1) / TR::BN_EFF;
+  const int n_tiles_n = MODE == RL && p.ksplit > 1 ? n_tiles_cols * p.ksplit : n_tiles_cols;
   int total;
   int wg_tiles_per_e = 0, wg_mt = 0;
   for (int e = tid; e <= e_cnt; e += NT) {
@@ -386,6 +393,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
   // ---- state of the tile whose k loop runs next (written by next_tile)
   int e = 0, lo = 0, hi = 0, n0 = 0;
   int piece = -1;         // ragged-K modes: index of the fp32 partial tile to write, or -1
+  int krange = 0;         // RL: which range of a cut contraction
   int nk0 = 0, nk = 0;    // k-tiles in segment 0 / in total
   int row0 = 0;           // first output row (global row for ragged-M, i for the weight gradients)
   int row_end = 0;        // one past the last valid output row
@@ -528,6 +536,10 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
       nt = in_band / band_rows;
       mt = band * 8 + (in_band - nt * band_rows);
     }
+    if (MODE == RL) {
+      krange = nt / n_tiles_cols;
+      nt -= krange * n_tiles_cols;
+    }
     n0 = nt * TR::BN_EFF;
     if (TR::RAGGED_K) {
       row0 = mt * BM;
@@ -538,10 +550,11 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
     } else {
       row0 = lo + mt * BM;
       row_end = hi;
-      nk0 = p.K / BK;
+      const size_t kfirst = MODE == RL ? (size_t)krange * p.K : 0;      // first column of this tile's range
+      nk0 = (MODE == RL && p.ksplit > 1 ? min(p.K, p.k_total - krange * p.K) : p.K) / BK;
       nk = MODE == DX ? 2 * nk0 : nk0;
-      ia_kp.setup(p.A0 + (size_t)row0 * p.lda, p.lda, hi - row0, wave, lane);
-      if (TR::B_TRANS) ib_tr.setup(p.B0 + (size_t)e * p.b_es, p.B1 + (size_t)e * p.b_es, TR::DUAL, p.ldb, n0, p.N, wave, lane);
+      ia_kp.setup(p.A0 + (size_t)row0 * p.lda + kfirst, p.lda, hi - row0, wave, lane);
+      if (TR::B_TRANS) ib_tr.setup(p.B0 + (size_t)e * p.b_es + kfirst * p.ldb, p.B1 + (size_t)e * p.b_es, TR::DUAL, p.ldb, n0, p.N, wave, lane);
       else ib_kc.setup(p.B0 + (size_t)e * p.b_es + (size_t)n0 * p.ldb, p.ldb, p.N - n0, wave, lane);
     }
     if (nk > 0) {
@@ -746,7 +759,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
     __syncthreads();
 
     // the ring is free: decode the next tile and start its first loads, then store this one
-    const int ep_e = e, ep_row0 = row0, ep_row_end = row_end, ep_n0 = n0, ep_piece = piece;
+    const int ep_e = e, ep_row0 = row0, ep_row_end = row_end, ep_n0 = n0, ep_piece = piece, ep_krange = krange;
     have = next_tile();
 
     // ---------------------------------------------------------------- epilogue
@@ -958,8 +971,8 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
               float* c0 = p.P0 + (size_t)ep_piece * p.p_stride + (size_t)grow * p.ldc + gcol;
               *reinterpret_cast<float4*>(c0) = make_float4(x[0], x[1], x[2], x[3]);
               *reinterpret_cast<float4*>(c0 + 4) = make_float4(x[4], x[5], x[6], x[7]);
-            } else if (MODE == RW) {
-              float* c0 = p.F0 + (size_t)ep_e * p.c_es + (size_t)grow * p.ldc + gcol;
+            } else if (MODE == RL || MODE == RW) {
+              float* c0 = p.F0 + (size_t)(MODE == RW ? ep_e : ep_krange) * p.c_es + (size_t)grow * p.ldc + gcol;
               *reinterpret_cast<float4*>(c0) = make_float4(x[0], x[1], x[2], x[3]);
               *reinterpret_cast<float4*>(c0 + 4) = make_float4(x[4], x[5], x[6], x[7]);
             } else {
@@ -1103,7 +1116,7 @@ int launch_gg(const GArgs& a, hipStream_t s) {
     attr_set[dev] = true;
   }
   int grid = device_cu_count();
-  ProfScope prof(MODE == RW ? MOE_K_ROUTER_DW : MODE == RX ? MOE_K_ROUTER_DX : MOE_K_UP + MODE, s);
+  ProfScope prof(MODE == RL ? MOE_K_ROUTER_FWD : MODE == RW ? MOE_K_ROUTER_DW : MODE == RX ? MOE_K_ROUTER_DX : MOE_K_UP + MODE, s);
   hipLaunchKernelGGL(gg_kernel<MODE>, dim3(grid), dim3(NT), SMEM_BYTES, s, a);
   HIP_CHECK_LAUNCH();
   return MOE_OK;
@@ -1253,8 +1266,9 @@ int router_dw_splits(int T, int d, int E) {
   return best;
 }
 
-// How many ranges of the contraction over d the workspace of the router's forward holds fp32 partial logits for: the same
-// cost model as above for a [T, E] result of few 256 x 256 tiles, in pairs of k-tiles.
+// Into how many ranges the router's forward GEMM cuts its contraction over d: with few experts
+// the [T, E] logits are fewer tiles than the chip has CUs, so each tile's k loop is shared out.
+// The same cost model as above, in pairs of k-tiles (a range is a whole number of pairs).
 int router_fwd_splits(int T, int d, int E) {
   const long long tiles = (long long)((T + BM - 1) / BM) * ((E + BN - 1) / BN);
   const int cus = device_cu_count();
@@ -1269,6 +1283,22 @@ int router_fwd_splits(int T, int d, int E) {
   // no empty range: as many ranges as the rounded-up range length needs
   const int per = (pairs + best - 1) / best;
   return (pairs + per - 1) / per;
+}
+
+// partials: fp32 [splits, T, E] when the contraction is cut (splits > 1), else unused; the caller adds them up
+int launch_router_fwd_bf16(const void* x, const void* wr, int T, int d, int E, float* logits, float* partials,
+                           int splits, int32_t* sched, hipStream_t s) {
+  if (T == 0) return MOE_OK;
+  hipLaunchKernelGGL(zero_words, dim3(1), dim3(64), 0, s, sched, 8);
+  HIP_CHECK_LAUNCH();
+  GArgs g = {};
+  g.A0 = g.A1 = (const bf16_t*)x; g.lda = d;
+  g.B0 = g.B1 = (const bf16_t*)wr; g.ldb = E; g.b_es = 0;
+  g.F0 = splits > 1 ? partials : logits; g.ldc = E; g.c_es = (long)T * E;
+  g.off = nullptr; g.rows = T; g.chunk = T; g.sched = sched; g.e_cnt = 1; g.N = E;
+  const int pairs = d / (2 * BK);
+  g.ksplit = splits; g.k_total = d; g.K = splits > 1 ? (pairs + splits - 1) / splits * 2 * BK : d;
+  return launch_gg<RL>(g, s);
 }
 
 int launch_router_dw_bf16(const void* x, const void* dl_bf16, int T, int d, int E, float* partials, int splits,

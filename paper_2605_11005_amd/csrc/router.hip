@@ -2,9 +2,10 @@
 // gradient of the gate weights in one pass over dy), gradient through the gate weights to the
 // logits, and the router's backward GEMMs.
 //
-// Large bf16 shapes (E % 64 == 0, d % 64 == 0) run on the matrix cores through the grouped-GEMM
-// kernel of expert_bf16.hip; every other shape (fp32, or a handful of experts) takes the plain
-// LDS-tiled FMA kernels below, which accept any size.  The contraction over the tokens (dWr) is
+// bf16 runs on the matrix cores: the logits of E % 8 == 0 experts and the weight gradient of up to 128 (42 where the
+// dlogits stay fp32) through the streaming kernel of expert_small.hip, larger ones and the input gradient
+// of E % 64 == 0 through the grouped-GEMM kernel of expert_bf16.hip.  Every other shape (fp32, odd expert counts) takes
+// the plain LDS-tiled FMA kernels below, which accept any size.  The contraction over the tokens (dWr) is
 // always split into fixed chunks whose fp32 sums are added in ascending order, so the result
 // does not depend on scheduling.
 #include "common.h"
@@ -225,9 +226,16 @@ __global__ __launch_bounds__(256) void router_fwd_small_e(const TX* __restrict__
   }
 }
 
+// dlogits as bf16, where only their rows are wanted; the first block clears the ticket counters of the product that follows
+__global__ void round_to_bf16(const float* __restrict__ in, bf16_t* __restrict__ out, size_t n, int32_t* __restrict__ words, int n_words) {
+  if (blockIdx.x == 0 && (int)threadIdx.x < n_words) words[threadIdx.x] = 0;
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
+    out[i] = f32_to_bf16(in[i]);
+}
+
 // dlogits for the matrix-core products, one block per 32 tokens (a piece of the contraction over the tokens):
 //   dlb     [T][E] bf16 (NULL: not wanted): operand of the input-gradient product
-//   pieces  [piece][plane][E][32] bf16 (NULL: not wanted): operand of the weight-gradient product, tokens contiguous.
+//   pieces  [piece][plane][E][32] bf16: operand of the weight-gradient product, tokens contiguous.
 //           PLANES = 1: rounded once, the path whose dlogits are bf16.  PLANES = 3: three terms whose sum keeps all 24 bits,
 //           for shapes whose dlogits stay fp32.  The last piece ends at the last token, with zeros for the tokens that the
 //           piece before it has covered (T >= 32).
@@ -238,7 +246,7 @@ __global__ __launch_bounds__(256) void router_dl_operands(const float* __restric
   __shared__ float tile[32][65];
   const int tid = threadIdx.x;
   if (blockIdx.x == 0 && tid < n_words) words[tid] = 0;
-  const int t0 = blockIdx.x * 32, base = pieces && T - 32 < t0 ? T - 32 : t0;
+  const int t0 = blockIdx.x * 32, base = T - 32 < t0 ? T - 32 : t0;
   for (int e0 = 0; e0 < E; e0 += 64) {
     __syncthreads();
     for (int i = tid; i < 32 * 64; i += 256) {
@@ -252,7 +260,7 @@ __global__ __launch_bounds__(256) void router_dl_operands(const float* __restric
     }
     __syncthreads();
     const int e = e0 + (tid >> 2), k = 8 * (tid & 3);
-    if (pieces && e < E) {
+    if (e < E) {
       float v[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) v[i] = tile[k + i][tid >> 2];
@@ -518,7 +526,17 @@ int launch_router_fwd(const void* x, const void* wr, int dtype, int T, int d, in
     float* partial = (float*)((char*)ws + 256);
     const int room = mfma_shape(dtype, T, d, E) ? router_fwd_splits(T, d, E) : 1;      // what the workspace holds
     int splits = 1;
-    int rc = launch_router_fwd_small(x, wr, T, d, E, logits, partial, room, &splits, s);
+    // The streaming kernel reads the weights once per 64 tokens: it is the faster one up to a block of 64 tokens by 128
+    // experts per CU (T = 16384, d = 4096, E = 128: 41 us against 56), beyond that the big tiles are (T = 32768, d = 7168,
+    // E = 256: 180 us against 296).
+    const bool stream = !mfma_shape(dtype, T, d, E) || (long long)tiles(T, 64) * tiles(E, 128) <= device_cu_count();
+    int rc;
+    if (stream) {
+      rc = launch_router_fwd_small(x, wr, T, d, E, logits, partial, room, &splits, s);
+    } else {
+      splits = room;
+      rc = launch_router_fwd_bf16(x, wr, T, d, E, logits, partial, splits, (int32_t*)ws, s);
+    }
     if (rc || splits == 1) return rc;
     ProfScope prof(MOE_K_ROUTER_FWD, s);
     hipLaunchKernelGGL((reduce_chunks<float>), dim3(device_cu_count() * 4), dim3(256), 0, s, partial, splits, (size_t)T * E,
@@ -603,7 +621,9 @@ int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int d
                         room >= piece_bytes + planes * sum_bytes;
   const auto dw_operands = [&](bf16_t* dlb, bf16_t* pieces) -> int {
     ProfScope prof(dwr ? MOE_K_ROUTER_DW : MOE_K_ROUTER_DX, s);
-    if (planes == 1)
+    if (!pieces)
+      hipLaunchKernelGGL(round_to_bf16, dim3(red_blocks), dim3(256), 0, s, dlogits, dlb, (size_t)T * E, sched, 16);
+    else if (planes == 1)
       hipLaunchKernelGGL(router_dl_operands<1>, dim3((T + 31) / 32), dim3(256), 0, s, dlogits, T, E, dlb, pieces, sched, 16);
     else
       hipLaunchKernelGGL(router_dl_operands<3>, dim3((T + 31) / 32), dim3(256), 0, s, dlogits, T, E, dlb, pieces, sched, 0);
