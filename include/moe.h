@@ -141,6 +141,8 @@ int moe_dispatch_static(const void* x, int dtype, int T, int d, int k, const int
  *                  moe_workspace_bytes(MOE_WS_EXPERT_FWD, ...) bytes, 256-byte aligned
  * bf16 requires d % 64 == 0 and f % 64 == 0; fp32 requires d % 4 == 0 and f % 4 == 0
  * (EUNSUPPORTED otherwise).  offsets must be non-decreasing with offsets[e_cnt] <= cap.
+ * A row's results depend on that row and its expert's weights alone, bit for bit: not on cap (which picks the kernel),
+ * nor on the rows beside it.
  */
 int moe_expert_fwd(const void* xp, int dtype, int cap, int d, int f, int e_cnt,
                    const int32_t* offsets, const void* w1, const void* w3, const void* w2,

@@ -13,7 +13,7 @@ from tests.gpu_util import TOL, gpu_layer, host, make_inputs, oracle_layer, rel_
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n_chunks", [2, 4])
+@pytest.mark.parametrize("n_chunks", [2, 4, 8])     # chunks of 512 tokens take the kernel for few rows, the whole batch does not
 def test_chunked_schedule_matches_unchunked_and_oracle(n_chunks):
     wl = W.DSV3.scaled(name="dsv3-chunked", T=4096, d=512, f=256)
     print(f"case {wl.name} chunks={n_chunks}", flush=True)
