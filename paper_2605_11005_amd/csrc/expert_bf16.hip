@@ -1124,16 +1124,26 @@ int launch_gg(const GArgs& a, hipStream_t s) {
 
 }  // namespace
 
-// Whether the forward takes the kernels for few rows (expert_small.hip) instead of the 256x256 tiles.  Those kernels read
-// each weight once per 64 rows and win while the big tiles would leave CUs idle or mostly multiply padding; the true row
-// counts are on the device, so the line is drawn by the host's bound on the rows per expert and by how many big tiles the
-// up projection would have.  Forward of both GEMMs, this / big tiles, in us (d, f, local experts, bound):
-//   fewer tiles than CUs:      2048, 1408, 8, 128: 38 / 81     4096, 1536, 16, 128: 123 / 136    2048, 1024, 8, 128: 56 / 81
-//   up to two tiles per CU:    2880, 2880, 16, 16: 62 / 107    4096, 4096, 8, 16: 181 / 193      and at 32: 213 / 194
-//   more:                      7168, 2048, 32, 8: 215 / 224    and at 16: 255 / 250, at 32: 301 / 270
-inline bool few_rows(int cap, int f, int e_cnt) {
-  const long long tiles = (long long)e_cnt * ((f + BN / 2 - 1) / (BN / 2)), cus = device_cu_count();
-  const long long bound = tiles < cus ? 128 : (tiles < 2 * cus ? 16 : 8);
+// Whether the forward takes the kernels for few rows (expert_small.hip) instead of the 256x256 tiles; the results are the
+// same bit for bit.  Those kernels read an expert's weights once per 64 rows, the tiles once per 256 with 256 rows' worth of
+// work each.  The true row counts are on the device, so the line is drawn by the host's bound on the rows per expert, and it
+// has to hold when the bound is filled, evenly or not.  While all weights fit the Infinity Cache (256 MB) the tiles leave the
+// chip idle up to 128 rows; larger weights stream from HBM at nearly its rate either way, and reading them again for further
+// rows costs more than the tiles' padding.  Forward of both GEMMs, few rows / tiles, in us, with the bound filled evenly, by
+// 1/r (Zipf), by one expert alone, and to a tenth:
+//   weights  d, f, experts       bound   even         Zipf         one          a tenth
+//   138 MB   2048, 1408, 8       128     62 / 87      77 / 87      63 / 87      37 / 68
+//   151 MB   2048, 768, 16       128     68 / 78      79 / 82      67 / 85      38 / 65
+//   604 MB   4096, 1536, 16      16      129 / 143    158 / 146    62 / 116     122 / 143
+//                                128     249 / 155    295 / 177    204 / 155    147 / 145
+//   796 MB   2880, 2880, 16      16      154 / 189    188 / 185    60 / 122     145 / 185
+//                                64      198 / 193    268 / 195    152 / 146    153 / 183
+//   2.8 GB   7168, 2048, 32      8       502 / 526    544 / 529    94 / 176     337 / 400
+//                                16      514 / 527    656 / 532    125 / 191    493 / 527
+//   2.8 GB   4096, 14336, 8      8       509 / 603    528 / 601    207 / 298    439 / 558
+inline bool few_rows(int cap, int d, int f, int e_cnt) {
+  const long long mb = 6ll * d * f * e_cnt >> 20;
+  const long long bound = mb <= 256 ? 128 : (mb <= 1024 ? 16 : 8);
   return cap <= bound * e_cnt;
 }
 
@@ -1142,7 +1152,7 @@ int launch_expert_fwd_bf16(const void* xp, int cap, int d, int f, int e_cnt, con
                            void* a_ws, hipStream_t s) {
   if (cap == 0 || e_cnt == 0) return MOE_OK;
   bf16_t* act = a_out ? (bf16_t*)a_out : (bf16_t*)a_ws;
-  if (few_rows(cap, f, e_cnt)) return launch_expert_fwd_small(xp, cap, d, f, e_cnt, offsets, w1, w3, w2, h1, h3, act, o, s);
+  if (few_rows(cap, d, f, e_cnt)) return launch_expert_fwd_small(xp, cap, d, f, e_cnt, offsets, w1, w3, w2, h1, h3, act, o, s);
   int32_t* sched = sched_area(a_ws, (size_t)cap * f * 2);
   hipLaunchKernelGGL(zero_words, dim3(1), dim3(64), 0, s, sched, 16);
   HIP_CHECK_LAUNCH();
