@@ -266,11 +266,18 @@ int launch_route(const float* logits, int T, int E, int k, int gate_mode, int e_
   ProfScope prof(MOE_K_ROUTE, s);
   size_t shm_q = (size_t)(e_cnt > 0 ? e_cnt : 1) * sizeof(int32_t);
   if (quarter) {
-    // otherwise one block per CU at most: every block adds its counts to the same e_cnt words, and those adds queue up
-    // (T = 16384, E = 128, 16 local experts: 17.4 us with 1024 blocks, 12.3 with 256)
+    // Otherwise few blocks: every block adds its counts to the same e_cnt words, and those adds queue up.  More of them pay
+    // where the selection rounds of many tokens take longer than that.  k = 8, one / two / four / eight blocks per CU, us:
+    //   T = 16384:  E = 128, 16 local 12.6 / 12.7 / 16.6 / 16.6;  E = 256, 256 local 17.7 / 18.2 / 23.6 / 23.6
+    //   T = 65536:  E = 128, 16 local 31.5 / 26.8 / 24.4 / 33.1;  E = 256, 256 local 47.7 / 42.3 / 39.1 / 52.9
+    //   T = 262144: E = 128, 16 local 107 / 84 / 74 / 70;         E = 256, 256 local 179 / 133 / 117 / 110
+    // and with k = 1 and 128 local experts of 128 (less selection, more adds) 10.6 / 14.3 / 15.4, 16.9 / 18.1 / 25.8 and
+    // 48 / 35 / 38 / 51.
+    const int cus = device_cu_count();
     int qb = alone ? 1 : (T + 15) / 16;
-    const int qt = alone ? (T + 3) / 4 * WAVE : (T > 16 * device_cu_count() ? 512 : 256);
-    if (qb > device_cu_count()) qb = device_cu_count();
+    const int qt = alone ? (T + 3) / 4 * WAVE : (T > 16 * cus ? 512 : 256);
+    const int qmax = cus * (T <= 64 * cus ? 1 : (T <= 256 * cus ? 2 : 4));
+    if (qb > qmax) qb = qmax;
     const int nv = (E + 63) / 64;
 #define ROUTE_Q(V)                                                                                     \
   hipLaunchKernelGGL(route_kernel_q<V>, dim3(qb), dim3(qt), shm_q, s, logits, T, E, k, gate_mode, e_lo, \

@@ -91,3 +91,23 @@ def test_router_backward_at_block_edges(T, d, E):
     tol = TOL["bf16"] if E % 64 == 0 else 2.0 ** -8
     assert rel_err(host(dwr), dwr_ref) < tol
     assert rel_err(host(dx), dx0 + dx_ref) < tol
+
+
+# a token's selection and the counts, with one, two and four blocks per CU (the lines lie at 64 and 256 tokens per CU)
+@pytest.mark.parametrize("T", [16385, 65537])
+def test_route_of_many_tokens_equals_the_route_of_a_few(T):
+    print(f"case route-{T}", flush=True)
+    E, k, e_lo, e_cnt = 64, 4, 8, 24
+    logits = torch.randn((T, E), generator=torch.Generator(device="cuda").manual_seed(T), device="cuda")
+
+    def route(lg):
+        n = lg.shape[0]
+        idx, w = torch.full((n, k), -7, dtype=torch.int32, device="cuda"), torch.full((n, k), -7.0, device="cuda")
+        counts = torch.full((e_cnt,), -7, dtype=torch.int32, device="cuda")
+        B.moe_route(lg, k, W.GATE_SOFTMAX_RENORM, e_lo, e_cnt, idx, w, counts)
+        return idx, w, counts
+    idx, w, counts = route(logits)
+    for t0 in (0, 4096, T - 100):
+        idx2, w2, _ = route(logits[t0:t0 + 100].contiguous())
+        assert torch.equal(idx[t0:t0 + 100], idx2) and torch.equal(w[t0:t0 + 100], w2)
+    assert torch.equal(counts.long(), torch.bincount(idx.flatten().long(), minlength=E)[e_lo:e_lo + e_cnt])
