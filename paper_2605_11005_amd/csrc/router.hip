@@ -280,14 +280,12 @@ __global__ __launch_bounds__(256) void router_dl_operands(const float* __restric
 }
 
 // The router term of dx for E = 8 or 16 experts: a thread keeps the weights of its eight columns in registers and walks
-// DX_TOKENS tokens (their dlogits are uniform: scalar loads), so that what is left is the read-modify-write of dx, eight
+// `tokens` tokens (their dlogits are uniform: scalar loads), so that what is left is the read-modify-write of dx, eight
 // tokens in flight.  With one block per token, which fetched the weights again for each, T = 16384, d = 4096, E = 8 took
 // 172 us.
-constexpr int DX_TOKENS = 32;
-
 template <int E>
 __global__ __launch_bounds__(256) void router_dx_columns(const float* __restrict__ dl, const bf16_t* __restrict__ wr,
-                                                        bf16_t* __restrict__ dx, int T, int d, int beta, int col_groups) {
+                                                        bf16_t* __restrict__ dx, int T, int d, int beta, int tokens, int col_groups) {
   const int tg = blockIdx.x / col_groups;
   const int c0 = ((blockIdx.x - tg * col_groups) * 256 + threadIdx.x) * 8;
   if (c0 >= d) return;
@@ -302,8 +300,8 @@ __global__ __launch_bounds__(256) void router_dx_columns(const float* __restrict
       for (int j = 0; j < 4; ++j) { w[i][e + 2 * j] = bf16lo(u[j]); w[i][e + 2 * j + 1] = bf16hi(u[j]); }
     }
   constexpr int AHEAD = 8;
-  const int t_end = min(T, (tg + 1) * DX_TOKENS);
-  for (int t0 = tg * DX_TOKENS; t0 < t_end; t0 += AHEAD) {
+  const int t_end = min(T, (tg + 1) * tokens);
+  for (int t0 = tg * tokens; t0 < t_end; t0 += AHEAD) {
     u32x4 old[AHEAD];
 #pragma unroll
     for (int k = 0; k < AHEAD; ++k) {
@@ -679,13 +677,20 @@ int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int d
   }
   if (dx && T > 0) {
     ProfScope prof(MOE_K_ROUTER_DX, s);
-    if (dtype == MOE_BF16 && (E == 8 || E == 16)) {
+    if (dtype == MOE_BF16 && (E == 8 || E == 16) && (long long)T * d * E >= (1ll << 23)) {
+      // Below that a block per token is faster; walking tokens, the longer the fewer blocks there are, is what a small
+      // batch waits for.  A block per token / 8 / 16 / 32 tokens per block, us:
+      //   E = 8:  T = 64, d = 4096 3.8 / 4.7 / 6.6 / 10.7    512, 2048 4.9 / 4.9 / 6.8 / 11.0    2000, 4096 19 / 8.5 / 8.2 / 11.7
+      //           4096, 4096 35 / 15.5 / 13.9 / 15.1         9001, 7168 151 / 60 / 54 / 57       16384, 4096 128 / - / 53 / 52
+      //   E = 16: T = 64, d = 4096 4.7 / 6.6 / 9.8 / 16.5    512, 2048 7.5 / 6.8 / 10.0 / 16.7   2000, 4096 41 / 12.0 / 12.0 / 17.7
+      //           4096, 4096 81 / 20.5 / 18.4 / 20.4         9001, 7168 483 / 70 / 68 / 66       16384, 4096 318 / - / 65 / 58
+      const int tokens = (long long)T * d < (1ll << 23) ? 8 : ((long long)T * d < (1ll << 26) ? 16 : 32);
       const int col_groups = tiles(d, 2048);
-      dim3 grid((unsigned)col_groups * ((T + DX_TOKENS - 1) / DX_TOKENS)), blk(256);
+      dim3 grid((unsigned)col_groups * tiles(T, tokens)), blk(256);
       if (E == 8)
-        hipLaunchKernelGGL(router_dx_columns<8>, grid, blk, 0, s, dlogits, (const bf16_t*)wr, (bf16_t*)dx, T, d, dx_acc, col_groups);
+        hipLaunchKernelGGL(router_dx_columns<8>, grid, blk, 0, s, dlogits, (const bf16_t*)wr, (bf16_t*)dx, T, d, dx_acc, tokens, col_groups);
       else
-        hipLaunchKernelGGL(router_dx_columns<16>, grid, blk, 0, s, dlogits, (const bf16_t*)wr, (bf16_t*)dx, T, d, dx_acc, col_groups);
+        hipLaunchKernelGGL(router_dx_columns<16>, grid, blk, 0, s, dlogits, (const bf16_t*)wr, (bf16_t*)dx, T, d, dx_acc, tokens, col_groups);
     } else if (E <= 64) {
       // a handful of experts: per-token dot products against contiguous weight rows
       const int col_groups = tiles(d, 1024);

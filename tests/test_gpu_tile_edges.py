@@ -111,3 +111,21 @@ def test_route_of_many_tokens_equals_the_route_of_a_few(T):
         idx2, w2, _ = route(logits[t0:t0 + 100].contiguous())
         assert torch.equal(idx[t0:t0 + 100], idx2) and torch.equal(w[t0:t0 + 100], w2)
     assert torch.equal(counts.long(), torch.bincount(idx.flatten().long(), minlength=E)[e_lo:e_lo + e_cnt])
+
+
+# the router term of dx of 8 or 16 experts: a block per token, then 8, 16 and 32 tokens per block; a token's sum is the same
+@pytest.mark.parametrize("T,d,E", [(1025, 1024, 8), (1027, 520, 16), (8209, 1032, 8), (8197, 1024, 16), (65545, 1032, 8)])
+def test_router_input_gradient_does_not_depend_on_the_batch(T, d, E):
+    print(f"case router-dx-{T}-{d}-{E}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T + d + E)
+    wr = torch.randn((d, E), generator=g, device="cuda", dtype=torch.bfloat16)
+    dl, dx = torch.randn((T, E), generator=g, device="cuda"), torch.randn((T, d), generator=g, device="cuda", dtype=torch.bfloat16)
+
+    def backward(t0, t1):
+        n, out = t1 - t0, dx[t0:t1].clone()
+        ws = torch.empty(B.moe_workspace_bytes(B.WS_ROUTER, B.MOE_BF16, n, 1, d, 0, E, 0), dtype=torch.uint8, device="cuda")
+        B.moe_router_bwd(dx[t0:t1].contiguous(), wr, dl[t0:t1].contiguous(), None, False, out, True, ws)
+        return out
+    whole = backward(0, T)
+    for t0, t1 in ((0, 40), (T // 2, T // 2 + 40), (T - 40, T)):
+        assert torch.equal(whole[t0:t1], backward(t0, t1))
