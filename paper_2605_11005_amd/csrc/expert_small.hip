@@ -368,8 +368,11 @@ int launch_router_fwd_small(const void* x, const void* wr, int T, int d, int E, 
   p.B0 = (const bf16_t*)wr; p.ldb = E;
   p.ldc = E; p.rows = T; p.e_cnt = 1; p.N = E; p.K = d; p.xstep = KP;
   const int cols = (E + COLS - 1) / COLS, cus = device_cu_count(), pieces = d / KP;
-  // as many rows per block as still leave a block for every CU: the weights are read once per block
-  const int tg = (long long)(T + 63) / 64 * cols >= cus ? 4 : ((long long)(T + 31) / 32 * cols >= cus ? 2 : 1);
+  // As few rows per block as make at most one block per CU: the weights are read once per block, and a second round of
+  // blocks nearly doubles the time.  16 / 32 / 64 rows per block, us:
+  //   E = 128:  T = 3000, d = 2048 10.2 / 12.4 / 14.7    5000, 2048 19.1 / 13.3 / 17.4    9001, 2048 28.4 / 24.7 / 17.8
+  //             T = 5000, d = 7168 51.6 / 34.2 / 27.0    9001, 7168 75.5 / 64.7 / 46.7
+  const int tg = (long long)(T + 15) / 16 * cols <= cus ? 1 : ((long long)(T + 31) / 32 * cols <= cus ? 2 : 4);
   const int row_blocks = (T + 16 * tg - 1) / (16 * tg);
   // A CU takes about 65 GB/s of weights, so a handful of blocks is cut along the contraction (at least two pieces per
   // wavefront); the second launch that adds the ranges up pays from three ranges on.
