@@ -608,15 +608,17 @@ int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int d
   const size_t n_w = (size_t)d * E;
   const int red_blocks = device_cu_count() * 4;
   int rc;
-  // Weight gradient of up to 128 experts (two passes over x): the streaming kernel, if the workspace's partial sums leave
-  // room for its operand beside at least one sum per plane.  Its sums need no more bytes than the cut product's.
+  // Weight gradient of up to 128 experts: the streaming kernel, if the workspace's partial sums leave room for its operand
+  // beside at least one sum per plane.  Its sums need no more bytes than the cut product's.  More than 64 rows of planes take
+  // two passes over x, which the big tiles overtake where x is large: E = 128, streaming / tiles, us: T = 32768, d = 2048
+  // 62 / 71; 16384, 4096 60 / 63; 16384, 7168 91 / 84; 32768, 4096 109 / 101; 65536, 4096 198 / 164.
   const bool mfma = mfma_shape(dtype, T, d, E);
   const int planes = mfma ? 1 : 3;
   const size_t sum_bytes = n_w * 4;
   const size_t room = mfma ? align256((size_t)router_dw_splits(T, d, E) * sum_bytes) : align256((size_t)valu_splits(T, d, E) * sum_bytes);
   const size_t piece_bytes = align256((size_t)((T + 31) / 32) * 32 * planes * E * 2);
   const bool dw_small = dwr && dtype == MOE_BF16 && T >= 32 && d % 64 == 0 && planes * E <= 128 &&
-                        room >= piece_bytes + planes * sum_bytes;
+                        !(mfma && E > 64 && (long long)T * d > (1ll << 26)) && room >= piece_bytes + planes * sum_bytes;
   const auto dw_operands = [&](bf16_t* dlb, bf16_t* pieces) -> int {
     ProfScope prof(dwr ? MOE_K_ROUTER_DW : MOE_K_ROUTER_DX, s);
     if (!pieces)
