@@ -289,37 +289,82 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
   if (TR::RAGGED_K) {
     // Every expert has the same number of output tiles, but a tile's cost is the expert's row
     // count.  An expert whose k loop is longer than a workgroup's fair share of the whole launch
-    // (in k-tiles) bounds the kernel from below; it is cut into pieces of up to 1.4 times that share
+    // (in k-tiles) bounds the kernel from below; it may be cut into pieces of a target length
     // (at least 16 k-tiles) when the time saved exceeds the time to write and re-read the fp32
     // partial tiles (p_stride floats per piece, priced at ~4 TB/s against ~0.85 us per k-tile),
-    // heaviest experts first while the budget of partial tiles lasts.  Longer pieces end later,
-    // shorter ones mean more partial tiles: whole training steps with pieces of 0.5 / 1 / 1.4 / 2
-    // shares took 902 / 871 / 878 / 894 us (d = 2048, f = 768, 16 experts, 20000 rows), 2442 / 2435 /
-    // 2403 / 2403 us (4096, 1536, 16, 16000), 654 / 633 / 592 / 605 us (512, 1024, 8, 33000),
-    // 480 / 506 / 488 / 477 us (2048, 1408, 8, 6000) and 983 / 953 / 955 / 1023 us (2560, 640, 16, 17000).
+    // heaviest experts first while the budget of partial tiles lasts.
+    // No target length is right everywhere: longer pieces end later, shorter ones mean more partial
+    // tiles.  So each wavefront prices one plan -- targets of 0.7, 1 and 1.4 fair shares, and no cut --
+    // and the cheapest is taken.  A plan's end is the larger of the total work per workgroup and, over
+    // the lengths of tiles, of the rounds that the tiles of at least this length need, times the length;
+    // in quarter microseconds, 3 per k-tile, 10 per tile and 60 per partial tile (fp32 stores); the
+    // reduction adds 12 and its bytes at 1.5 TB/s.  (Fitted to the backward's time under each plan.)  Over 220
+    // shares (10 shapes of d, f, experts; 3000 to 48000 rows; even, Zipf, one hot expert, half of them
+    // heavier, all rows on one) the whole backward takes 0.96 of its time with pieces of half a share, at
+    // most 1.07 of it; always 1.4 shares took 0.98 and up to 1.18.
     wg_mt = (p.M + BM - 1) / BM;
     wg_tiles_per_e = wg_mt * n_tiles_n;
-    if (tid == 0) {
-      long long units = 0;
-      for (int e = 0; e < e_cnt; ++e) units += (offs[e + 1] - offs[e] + BK - 1) / BK;
-      const int share = (int)(units * wg_tiles_per_e / gridDim.x);
-      const int target = share * 7 / 5 > 16 ? share * 7 / 5 : 16;
-      const int piece_cost = (int)(p.p_stride / 400000) + 1;
-      int used = 0;
-      for (int pos = 0; pos < e_cnt; ++pos) {
-        const int e = order[pos];
-        const int nke = (offs[e + 1] - offs[e] + BK - 1) / BK;
-        int pieces = 1;
-        if (nke > target) {
-          pieces = (nke + target - 1) / target;
+    constexpr int HEAVY = WAVE;                       // experts that may be cut: one per lane
+    int32_t* trial = reinterpret_cast<int32_t*>(smem);      // [plan][position]: pieces (the tile ring is still free)
+    float* price = reinterpret_cast<float*>(trial + 4 * HEAVY);
+    const int grid = gridDim.x;
+    const auto k_tiles = [&](int pos) { return (offs[order[pos] + 1] - offs[order[pos]] + BK - 1) / BK; };
+    const float inv_grid = 1.f / (float)grid;
+    float all = 0.f;                                  // k-tiles of one output tile of every expert
+    for (int pos = lane; pos < e_cnt; pos += WAVE) all += (float)k_tiles(pos);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) all += __shfl_xor(all, o, WAVE);
+    const float share = all * (float)wg_tiles_per_e * inv_grid;
+    const auto target = [&](int plan) { return max(16, (int)((plan == 0 ? 0.7f : (plan == 1 ? 1.f : 1.4f)) * share)); };
+    const bool may_cut = e_cnt > 0 && p.split_budget >= 2 && __builtin_amdgcn_readfirstlane(k_tiles(0)) > target(0);
+    if (may_cut) {
+      const int heavy = min(e_cnt, HEAVY);
+      volatile int32_t* mine = trial + wave * HEAVY;
+      mine[lane] = 1;
+      __builtin_amdgcn_wave_barrier();
+      if (lane == 0 && wave < 3) {
+        const int goal = target(wave);
+        const int piece_cost = (int)(p.p_stride / 400000) + 1;
+        int used = 0;
+        for (int pos = 0; pos < heavy; ++pos) {
+          const int nke = k_tiles(pos);
+          if (nke <= goal) break;                     // heaviest first: nor will the others be cut
+          int pieces = (nke + goal - 1) / goal;
           if (pieces > 255) pieces = 255;
           if (pieces > p.split_budget - used) pieces = p.split_budget - used;
-          if (pieces < 2 || nke - (nke + pieces - 1) / pieces <= pieces * piece_cost) pieces = 1;
+          if (pieces < 2 || nke - (nke + pieces - 1) / pieces <= pieces * piece_cost) continue;
+          used += pieces;
+          mine[pos] = pieces;
         }
-        if (pieces > 1) used += pieces;
-        split[e] = pieces;
       }
+      __builtin_amdgcn_wave_barrier();
+      const int pieces = mine[lane];
+      const float tiles = lane < heavy ? (float)(pieces * wg_tiles_per_e) : 0.f;
+      const float len = lane < heavy ? (float)(3 * ((k_tiles(lane) + pieces - 1) / pieces) + (pieces > 1 ? 60 : 10)) : 0.f;
+      float work = tiles * len, parts = pieces > 1 ? (float)pieces : 0.f;
+      for (int pos = HEAVY + lane; pos < e_cnt; pos += WAVE) work += (float)wg_tiles_per_e * (float)(3 * k_tiles(pos) + 10);
+      float as_long = 0.f;                            // tiles of at least this lane's length
+      for (int j = 0; j < heavy; ++j) {
+        const float other = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(len), j));
+        as_long += other >= len ? __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(tiles), j)) : 0.f;
+      }
+      float end = ceilf(as_long * inv_grid) * len;
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) {
+        work += __shfl_xor(work, o, WAVE);
+        parts += __shfl_xor(parts, o, WAVE);
+        end = fmaxf(end, __shfl_xor(end, o, WAVE));
+      }
+      if (lane == 0) price[wave] = fmaxf(end, work * inv_grid) + (parts > 0.f ? parts * (float)p.p_stride * (4.f / 375000.f) + 12.f : 0.f);
     }
+    __syncthreads();
+    int best = 0;
+    if (may_cut) {
+#pragma unroll
+      for (int c = 1; c < 4; ++c)
+        if (price[c] < price[best]) best = c;
+    }
+    for (int pos = tid; pos < e_cnt; pos += NT) split[order[pos]] = may_cut && pos < HEAVY ? trial[best * HEAVY + pos] : 1;
     __syncthreads();
     // list the experts again, now by the length of one tile's k loop (a cut expert's pieces are
     // shorter than the tiles of the next heaviest ones), longest first

@@ -129,3 +129,31 @@ def test_router_input_gradient_does_not_depend_on_the_batch(T, d, E):
     whole = backward(0, T)
     for t0, t1 in ((0, 40), (T // 2, T // 2 + 40), (T - 40, T)):
         assert torch.equal(whole[t0:t1], backward(t0, t1))
+
+
+# weight gradients whose heavy experts are cut along the rows, by one of several plans or not at all: one expert, a hot one among
+# empty ones, more experts than a wavefront has lanes (only the heaviest 64 may be cut), as heavy as each other
+@pytest.mark.parametrize("d,f,rows", [(128, 192, [9000]), (256, 192, [300, 0, 12000, 10]), (512, 64, [7] * 66 + [4000, 3000, 9000]),
+                                      (64, 320, [2500, 2500, 2500]), (320, 256, [100] * 70)])
+def test_weight_gradients_of_heavy_experts(d, f, rows):
+    print(f"case heavy-{d}-{f}-{rows[:4]}", flush=True)
+    e_cnt, R = len(rows), sum(rows)
+    g = torch.Generator(device="cuda").manual_seed(d + f + R)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda", dtype=torch.bfloat16)  # noqa: E731
+    xp, h1, h3, a, d_o = randn(R, d), randn(R, f), randn(R, f), randn(R, f), randn(R, d)
+    w1, w3, w2 = randn(e_cnt, d, f) * d ** -0.5, randn(e_cnt, d, f) * d ** -0.5, randn(e_cnt, f, d) * f ** -0.5
+    offsets = torch.tensor([0] + rows, device="cuda").cumsum(0).to(torch.int32)
+    dxp = torch.empty_like(xp)
+    dw1, dw3, dw2 = (torch.full_like(w, float("nan")) for w in (w1, w3, w2))
+    ws = torch.empty(B.moe_workspace_bytes(B.WS_EXPERT_BWD, B.MOE_BF16, R, 1, d, f, e_cnt, R), dtype=torch.uint8, device="cuda")
+    B.moe_expert_bwd(xp, h1, h3, d_o, offsets, w1, w3, w2, dxp, dw1, dw3, dw2, False, ws, a=a)
+    for e in range(e_cnt):
+        r = slice(sum(rows[:e]), sum(rows[:e + 1]))
+        if rows[e] == 0:
+            assert not dw1[e].any() and not dw3[e].any() and not dw2[e].any()
+            continue
+        x, p, q, s, do = (t[r].double() for t in (xp, h1, h3, a, d_o))
+        sig = p.sigmoid()
+        da = do @ w2[e].double().t()
+        for got, ref in ((dw2[e], s.t() @ do), (dw1[e], x.t() @ (da * q * sig * (1 + p * (1 - sig)))), (dw3[e], x.t() @ (da * p * sig))):
+            assert rel_err(host(got), host(ref)) < TOL["bf16"]
