@@ -46,6 +46,7 @@ struct SArgs {
   long xstep;                             // elements from a row's piece to its next piece
   int n_experts;                          // RW: rows are (plane, expert), expert fastest
   int range;                              // RL, RW: pieces of the contraction per range (grid z); range z's sums go to F + z * rows * N
+                                          // narrow_router: rows per block
 };
 
 // Loads go through a buffer descriptor: a wave-uniform base and a 32-bit byte offset per lane.  With 64-bit addresses per
@@ -305,6 +306,122 @@ __device__ __forceinline__ void router_tile(const SArgs& p, float* red, int row0
   }
 }
 
+// RL with fewer than 64 experts (E % 8 == 0).  Before there was a matrix-core kernel for them, a block of 256 threads took a
+// token and added its products up in 256 chains and a tree, and the error of that is the measure here: a chain of matrix
+// instructions, whose sums are not rounded to nearest, is up to 2.2 times further off (relative error of the logits at
+// d = 512 / 2048 / 7168: 6.2 / 7.3 / 8.3e-8 with the block per token, 7.1 / 10.3 / 18e-8 with chains of d / 256 instructions
+// and their eight results added in turn).  So every instruction starts from zero, its result goes to one of eight fp32
+// sums per output by an ordinary addition, and these and the wavefronts' results are added in pairs: 6.1 / 7.2 / 8.1e-8.
+// Wavefront w multiplies the w-th eighth of the contraction whatever T is: a token's logits do not depend on the batch.
+// Loads: the 128 columns of router_tile would be up to 16 times the same ones.  A wavefront's piece is 8 KB of whole rows,
+// 512 / G k of 8 G columns (G = 2, 4 or 8, from E / 8 on); a lane's 8 x 8 block is transposed in registers and goes to the
+// lanes that want it through the wavefront's own LDS.
+constexpr int SUMS = 8;
+template <int TG, int G, int NG>          // NG: groups of 16 columns
+__global__ __launch_bounds__(NW_ROUTER * WAVE) void narrow_router(SArgs p) {
+  constexpr int NW = NW_ROUTER, STEPS = 16 / G;                 // steps of 32 k in a piece
+  constexpr int SB = G == 2 ? 8 : 4;                            // steps whose rows are loaded at a time; two batches in flight
+  constexpr int SLOTS = SB > STEPS ? SB / STEPS : 1;            // pieces that start in a batch
+  constexpr int PLACES = 512;
+  __shared__ u32x4 lds[NW * PLACES];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i = lane & 15, g = lane >> 4, E = p.N;
+  const int row0 = blockIdx.x * p.range, row_end = min(p.rows, row0 + p.range);      // up to 16 * TG rows
+  const int units = p.K / 64, per = (units + NW - 1) / NW;
+  const int first = 64 * min(wave * per, units), steps = 2 * (min((wave + 1) * per, units) - first / 64);
+  u32x4* mine = lds + wave * PLACES;
+  // place of k chunk kg (8 k) of column c in a piece: the 16 lanes of a store (columns 8 apart, chunks in turn) and of a fragment
+  // (columns in turn) are on different banks
+  const auto place = [](int c, int kg) {
+    const int x = G == 2 ? kg : (G == 4 ? (c >> 4 & 1) | kg << 1 : (c >> 4 & 3) | kg << 2);
+    return kg * 8 * G + (c & ~7) + ((c ^ x) & 7);
+  };
+  const int ci = lane % G, kg = lane / G;                       // weights: this lane's eight columns and eight k
+  const int wcol = min(8 * ci, E - 8);                          // columns past the end repeat the last ones
+  int xoff[TG];
+#pragma unroll
+  for (int t = 0; t < TG; ++t) xoff[t] = 2 * (min(16 * t + i, row_end - row0 - 1) * (int)p.lda + 8 * g);
+  Piece w[SLOTS];
+  auto load_w = [&](auto slot, int step) {      // the piece that starts at a step; chunks past the end repeat the last one
+    const bool in = step < steps;
+    const int last = in ? 4 * min(steps - step, STEPS) - 1 : 0;
+    w[decltype(slot)::value].template load<0, 8>(p.B0 + (in ? (size_t)(first + step * KP) * E : 0), in, 2 * E, 2 * (8 * min(kg, last) * E + wcol));
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  u32x4 x[2][SB][TG];
+  auto load_x = [&](auto set, int step) {
+    constexpr int S = decltype(set)::value;
+#pragma unroll
+    for (int q = 0; q < SB; ++q) {
+      const bool in = step + q < steps;
+      const __amdgpu_buffer_rsrc_t d = descriptor(p.A + (size_t)row0 * p.lda + (in ? first + (step + q) * KP : 0), in);
+#pragma unroll
+      for (int t = 0; t < TG; ++t) x[S][q][t] = __builtin_amdgcn_raw_buffer_load_b128(d, xoff[t], 0, 0);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+  f32x4 sum[NG][TG][SUMS];
+#pragma unroll
+  for (int n = 0; n < NG; ++n)
+#pragma unroll
+    for (int t = 0; t < TG; ++t)
+#pragma unroll
+      for (int k = 0; k < SUMS; ++k) sum[n][t][k] = zero;
+  auto batch = [&](auto set, int step) {
+    constexpr int S = decltype(set)::value;
+    static_for<SB>([&](auto index) {
+      constexpr int q = decltype(index)::value;
+      if (step + q >= steps) return;
+      if (q % STEPS == 0 && (step + q) % STEPS == 0) {
+        constexpr int slot = q / STEPS;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) mine[place(8 * ci + j, kg)] = __builtin_bit_cast(u32x4, w[slot].operand(j));
+        __builtin_amdgcn_wave_barrier();  // LDS serves a wavefront's accesses in order
+        load_w(Int<slot>{}, step + q + SLOTS * STEPS);
+      }
+#pragma unroll
+      for (int n = 0; n < NG; ++n) {
+        const bf16x8 f = __builtin_bit_cast(bf16x8, mine[place(16 * n + i, 4 * ((step + q) % STEPS) + g)]);
+#pragma unroll
+        for (int t = 0; t < TG; ++t)
+          sum[n][t][(S * SB + q) % SUMS] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, __builtin_bit_cast(bf16x8, x[S][q][t]), zero, 0, 0, 0);
+      }
+      __builtin_amdgcn_wave_barrier();
+    });
+  };
+  static_for<SLOTS>([&](auto slot) { load_w(slot, decltype(slot)::value * STEPS); });
+  load_x(Int<0>{}, 0);
+  for (int step = 0; step < steps; step += 2 * SB) {
+    load_x(Int<1>{}, step + SB);
+    batch(Int<0>{}, step);
+    load_x(Int<0>{}, step + 2 * SB);
+    batch(Int<1>{}, step + SB);
+  }
+  // element r of a sum is row 16t + i, column 16n + 4g + r; a wavefront's results at [row][4 columns] of its LDS
+#pragma unroll
+  for (int n = 0; n < NG; ++n)
+#pragma unroll
+    for (int t = 0; t < TG; ++t) {
+#pragma unroll
+      for (int half = SUMS / 2; half > 0; half /= 2)
+#pragma unroll
+        for (int k = 0; k < half; ++k) sum[n][t][k] += sum[n][t][k + half];
+      mine[(16 * t + i) * 4 * NG + 4 * n + g] = __builtin_bit_cast(u32x4, sum[n][t][0]);
+    }
+  __syncthreads();
+  const int row = row0 + tid / (4 * NG), col = 4 * (tid % (4 * NG));
+  if (tid >= 64 * TG * NG || row >= row_end || col >= E) return;
+  f32x4 v[NW];
+#pragma unroll
+  for (int wv = 0; wv < NW; ++wv) v[wv] = __builtin_bit_cast(f32x4, lds[wv * PLACES + tid]);
+#pragma unroll
+  for (int half = NW / 2; half > 0; half /= 2)
+#pragma unroll
+    for (int wv = 0; wv < half; ++wv) v[wv] += v[wv + half];
+  *reinterpret_cast<f32x4*>(p.F + (size_t)row * E + col) = v[0];
+}
+
 template <int MODE>
 __global__ __launch_bounds__(NW_EXPERT * WAVE) void small_rows(SArgs p) {
   __shared__ u32x4 lds[2 * (WEIGHT_PLACES + ROW_PLACES)];
@@ -357,6 +474,31 @@ int launch_expert_fwd_small(const void* xp, int cap, int d, int f, int e_cnt, co
   w.C0 = (bf16_t*)o; w.ldc = d; w.xstep = KP;
   w.off = offsets; w.e_cnt = e_cnt; w.N = d; w.K = f;
   return launch_small<DOWN>(w, cap, MOE_K_DOWN, s);
+}
+
+// logits of 8 to 56 experts, E % 8 == 0
+int launch_router_fwd_narrow(const void* x, const void* wr, int T, int d, int E, float* logits, hipStream_t s) {
+  SArgs p = {};
+  p.A = (const bf16_t*)x; p.lda = d;
+  p.B0 = (const bf16_t*)wr;
+  p.F = logits; p.rows = T; p.N = E; p.K = d;
+  // As few rows per block as make at most one block per CU, up to 32 (16 for more than 16 experts: the sums take the registers).
+  // Block per token / the 128 columns of router_tile / this, us, d = 4096:
+  //   E = 8:   T = 1 5.7 / 12.1 / 5.8      T = 300 7.9 / 14.9 / 6.6     T = 4096 45 / 15.6 / 9.5     T = 16384 179 / 28.5 / 32.6
+  //   E = 24:  T = 1 13.8 / 12.1 / 6.3     T = 300 20.0 / 14.8 / 7.1    T = 4096 178 / 15.3 / 9.8    T = 16384 695 / 28.2 / 33.1
+  //   E = 56:  T = 1 30.0 / 12.0 / 12.5    T = 300 47.2 / 14.7 / 13.9   T = 4096 438 / 15.5 / 18.5   T = 16384 1723 / 28.4 / 64.9
+  const int cus = device_cu_count(), most = E <= 16 ? 32 : 16;
+  p.range = 1;
+  while (p.range < most && (T + p.range - 1) / p.range > cus) p.range *= 2;
+  const dim3 grid((T + p.range - 1) / p.range), block(NW_ROUTER * WAVE);
+  ProfScope prof(MOE_K_ROUTER_FWD, s);
+  if (p.range > 16) hipLaunchKernelGGL((narrow_router<2, 2, 1>), grid, block, 0, s, p);
+  else if (E <= 16) hipLaunchKernelGGL((narrow_router<1, 2, 1>), grid, block, 0, s, p);
+  else if (E <= 32) hipLaunchKernelGGL((narrow_router<1, 4, 2>), grid, block, 0, s, p);
+  else if (E <= 48) hipLaunchKernelGGL((narrow_router<1, 8, 3>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((narrow_router<1, 8, 4>), grid, block, 0, s, p);
+  HIP_CHECK_LAUNCH();
+  return MOE_OK;
 }
 
 // partials: room for max_ranges * T * E floats.  Returns the number of ranges through `ranges`: 1 = the logits are

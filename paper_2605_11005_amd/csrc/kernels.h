@@ -40,6 +40,7 @@ int launch_expert_bwd_bf16(const void* xp, const void* h1, const void* h3, const
 // forward with few rows per expert (expert_small.hip): h1, h3 both or neither
 int launch_expert_fwd_small(const void* xp, int cap, int d, int f, int e_cnt, const int32_t* offsets, const void* w1,
                             const void* w3, const void* w2, void* h1, void* h3, void* a, void* o, hipStream_t s);
+int launch_router_fwd_narrow(const void* x, const void* wr, int T, int d, int E, float* logits, hipStream_t s);
 int launch_router_fwd_small(const void* x, const void* wr, int T, int d, int E, float* logits, float* partials, int max_ranges,
                             int* ranges, hipStream_t s);
 int launch_router_dw_small(const void* x, const void* dl_pieces, int planes, int T, int d, int E, float* partials, int max_sums,

@@ -2,9 +2,10 @@
 // gradient of the gate weights in one pass over dy), gradient through the gate weights to the
 // logits, and the router's backward GEMMs.
 //
-// bf16 runs on the matrix cores: the logits of E % 8 == 0 experts and the weight gradient of up to 128 (42 where the
-// dlogits stay fp32) through the streaming kernel of expert_small.hip, larger ones and the input gradient
-// of E % 64 == 0 through the grouped-GEMM kernel of expert_bf16.hip.  Every other shape (fp32, odd expert counts) takes
+// bf16 with d % 64 == 0 runs on the matrix cores: the logits of E % 8 == 0 experts and the weight gradient of up to 128 (42
+// where the dlogits stay fp32) through the kernels of expert_small.hip while launch_router_fwd's and launch_router_bwd's
+// rules on sizes and workspace allow, larger ones and the input gradient of E % 64 == 0 through the grouped-GEMM kernel of
+// expert_bf16.hip.  Every other shape (fp32, odd expert counts) takes
 // the plain LDS-tiled FMA kernels below, which accept any size.  The contraction over the tokens (dWr) is
 // always split into fixed chunks whose fp32 sums are added in ascending order, so the result
 // does not depend on scheduling.
@@ -520,6 +521,7 @@ size_t router_ws_bytes(int dtype, int T, int d, int E) {
 int launch_router_fwd(const void* x, const void* wr, int dtype, int T, int d, int E, float* logits, void* ws,
                       hipStream_t s) {
   if (T == 0) return MOE_OK;
+  if (dtype == MOE_BF16 && E % 8 == 0 && d % 64 == 0 && E < 64) return launch_router_fwd_narrow(x, wr, T, d, E, logits, s);
   if (dtype == MOE_BF16 && E % 8 == 0 && d % 64 == 0) {
     float* partial = (float*)((char*)ws + 256);
     const int room = mfma_shape(dtype, T, d, E) ? router_fwd_splits(T, d, E) : 1;      // what the workspace holds

@@ -157,3 +157,27 @@ def test_weight_gradients_of_heavy_experts(d, f, rows):
         da = do @ w2[e].double().t()
         for got, ref in ((dw2[e], s.t() @ do), (dw1[e], x.t() @ (da * q * sig * (1 + p * (1 - sig)))), (dw3[e], x.t() @ (da * p * sig))):
             assert rel_err(host(got), host(ref)) < TOL["bf16"]
+
+
+# logits of 8 to 56 experts: eight fp32 sums per output and wavefront, added in pairs.  A block of 256 threads that adds the same
+# products in 256 chains and a tree is off by 6.2e-8 / 7.3e-8 / 8.3e-8 of the logits' norm, chains of matrix instructions by
+# 7.1e-8 / 1.03e-7 / 1.8e-7; the bounds are halfway for the longer contractions, 5 % above the first for the shortest
+@pytest.mark.parametrize("E", [8, 16, 24, 32, 40, 56])
+@pytest.mark.parametrize("d,bound", [(512, 6.5e-8), (2048, 8.8e-8), (7168, 1.3e-7)])
+def test_logits_of_few_experts(E, d, bound):
+    print(f"case few-experts-{E}-{d}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(E + d)
+    x = torch.randn((5000, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    wr = torch.randn((d, E), generator=g, device="cuda", dtype=torch.bfloat16).mul_(d ** -0.5)
+
+    def logits(rows):
+        out = torch.full((rows.shape[0], E), float("nan"), device="cuda")
+        ws = torch.empty(B.moe_workspace_bytes(B.WS_ROUTER, B.MOE_BF16, rows.shape[0], 1, d, 0, E, 0), dtype=torch.uint8, device="cuda")
+        B.moe_router_fwd(rows.contiguous(), wr, out, ws)
+        return out
+    whole, ref = logits(x), x.double() @ wr.double()
+    assert float((whole.double() - ref).norm() / ref.norm()) < bound
+    # a token's logits do not depend on the batch: blocks of 1, 2, 8, 16 and 32 rows
+    for t0, t1 in ((0, 1), (17, 320), (1000, 2999)):
+        assert torch.equal(logits(x[t0:t1]), whole[t0:t1])
+    assert torch.equal(logits(torch.cat([x[100:], x])), torch.cat([whole[100:], whole]))
