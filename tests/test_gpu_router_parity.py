@@ -22,20 +22,20 @@ CASES = [
     W.TINY,                                                                         # fp32, E = 8: plain path
     W.TINY.scaled(name="tiny-fp32-softmax", gate_mode=W.GATE_SOFTMAX, T=300, E=12, e_lo=3, e_cnt=5, k=3, d=72, f=100),
     W.TINY.scaled(name="tiny-fp32-sigmoid", gate_mode=W.GATE_SIGMOID_RENORM, T=130, E=70, e_lo=0, e_cnt=70, k=6, d=40, f=36),
-    W.MIXTRAL.scaled(name="mixtral-small-router", T=2048, d=256, f=384),           # bf16, E = 8: plain path on bf16
+    W.MIXTRAL.scaled(name="mixtral-small-router", T=2048, d=256, f=384),           # bf16, E = 8: kernel for few experts
     W.QWEN.scaled(name="qwen-small-router", T=2048, d=256, f=192),                 # bf16, E = 128: matrix cores
     W.DSV3.scaled(name="dsv3-small-router", T=4096, d=512, f=256),                 # E = 256, sigmoid gate
     W.DSV3.scaled(name="ragged-router", T=1500, d=320, f=448, E=96, e_lo=8, e_cnt=8, k=6),      # tails in every dimension
     W.QWEN.scaled(name="softmax-router", gate_mode=W.GATE_SOFTMAX, T=777, d=128, f=64, E=160, e_lo=32, e_cnt=64, k=4),
-    # few logit tiles and a long contraction: the router GEMM cuts d into five ranges of 5, 5, 5, 5 and 3 pairs of
-    # k-tiles and adds their fp32 tiles up; the token count leaves a ragged last row tile
+    # a contraction of 23 pairs of k-tiles (two pieces short of whole rounds in the streaming kernel) and a ragged last row block;
+    # the same contraction on the 256x256 tiles, cut into uneven ranges, is in test_gpu_tile_edges.py
     W.QWEN.scaled(name="cut-contraction-router", T=1000, d=1472, f=64, E=128, e_lo=16, e_cnt=16, k=4),
 ]
 
 
 def _random_router_cases(n, seed):
     """Seeded draws for the matrix-core router path (E and d multiples of 64): token counts with ragged
-    last tiles, contractions from one pair of k-tiles to 24 (cut into up to five ranges), any slice."""
+    last row blocks, contractions from one pair of k-tiles to 24, any slice."""
     rng = np.random.default_rng(seed)
     out = []
     for i in range(n):

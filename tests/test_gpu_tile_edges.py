@@ -38,9 +38,12 @@ def test_bf16_forward_with_few_rows(T, d, f):
     check_layer(wl, inp, fw, bw, buf)
 
 
-# router logits: E = 8 n with column blocks of 128, row blocks of 16 to 64, contraction whole or cut into ranges.
+# router logits: E = 8 n with column blocks of 128, row blocks of 16 to 64, contraction whole or cut into ranges: 8 equal ones
+# (17, 4096, 128), 6 of 17 and 15 pieces (17, 3200, 128) and (40, 3200, 64); the 256x256 tiles from one block of 64 tokens by 128
+# experts per CU on, their contraction cut into ranges of 5, 5, 5, 5 and 3 pairs of k-tiles (4100, 1472, 512) or whole (16500, 64, 64).
 # fp32 sums of bf16 products: n products of N(0, 1/n) terms in any order are off by less than 1e-5 of the largest
-@pytest.mark.parametrize("T,d,E", [(1, 64, 8), (15, 448, 24), (17, 4096, 128), (300, 2880, 136), (4100, 128, 192), (16500, 64, 64)])
+@pytest.mark.parametrize("T,d,E", [(1, 64, 8), (15, 448, 24), (17, 4096, 128), (300, 2880, 136), (4100, 128, 192), (16500, 64, 64),
+                                   (17, 3200, 128), (40, 3200, 64), (4100, 1472, 512)])
 def test_router_logits_at_block_edges(T, d, E):
     print(f"case router-{T}-{d}-{E}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(T + d + E)
@@ -71,13 +74,34 @@ def test_plan_in_one_block_and_in_three_launches(T, k, e_cnt):
     assert int(ws[:4].view(torch.int32).item()) == 0
 
 
-# router backward: the streaming weight gradient (32 tokens or more, planes * E <= 128; pieces of 32 tokens, the last one
-# overlapping the one before it), the input gradient of up to 16 experts, and the shapes just outside either.
+def _streams(T, d, E):
+    """Whether the weight gradient of these sizes takes the streaming kernel: three planes of dlogits unless E % 64 == 0, and
+    the operand and a sum per plane must fit where the sums of the cut product would go (rules of router.hip, expert_bf16.hip)."""
+    up = lambda a, b: -(-a // b)  # noqa: E731
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    planes, sum_bytes = (1 if E % 64 == 0 else 3), 4 * d * E
+    if planes == 1:
+        tiles = up(d, 256) * up(E, 256)
+        cost = lambda s: up(tiles * s, cus) * (up(up(T, s), 32) + 16)  # noqa: E731
+        splits = min(range(1, min(32, up(T, 128)) + 1), key=cost)
+    else:
+        splits = max(1, min(up(4 * cus, up(d, 64) * up(E, 64)), (64 << 20) // sum_bytes, up(T, 64), 64))
+    room, operand = up(splits * sum_bytes, 256) * 256, up(up(T, 32) * 64 * planes * E, 256) * 256
+    large = planes == 1 and E > 64 and T * d > 1 << 26
+    return T >= 32 and d % 64 == 0 and planes * E <= 128 and not large and room >= operand + planes * sum_bytes
+
+
+# router backward: the streaming weight gradient (pieces of 32 tokens, the last one whole, of one token or of 31 with the overlap
+# into the piece before it; one row block of planes, a second one, 128 rows), the kernels it leaves the rest to -- too few tokens
+# for its operand to fit beside the sums, more than 128 rows of planes -- and the input gradient.
 # bf16 dlogits (E % 64 == 0): one rounding, 2e-2 as everywhere; fp32 dlogits: bf16 stores only, 2**-8 of the largest
-@pytest.mark.parametrize("T,d,E", [(32, 64, 8), (33, 192, 8), (1000, 2048, 16), (31, 64, 8), (777, 320, 40), (500, 128, 48),
-                                   (2049, 448, 64), (4000, 128, 128), (300, 64, 192)])
-def test_router_backward_at_block_edges(T, d, E):
+@pytest.mark.parametrize("T,d,E,streams", [
+    (32, 64, 8, False), (33, 192, 8, False), (1000, 2048, 16, True), (31, 64, 8, False), (777, 320, 40, True), (500, 128, 48, False),
+    (2049, 448, 64, True), (4000, 128, 128, True), (300, 64, 192, False),
+    (288, 512, 8, True), (289, 512, 8, True), (319, 512, 8, True), (320, 512, 1, True), (1023, 128, 24, True), (256, 512, 64, True), (32, 64, 128, False)])
+def test_router_backward_at_block_edges(T, d, E, streams):
     print(f"case router-bwd-{T}-{d}-{E}", flush=True)
+    assert _streams(T, d, E) == streams
     g = torch.Generator(device="cuda").manual_seed(T + d + E)
     x = torch.randn((T, d), generator=g, device="cuda", dtype=torch.bfloat16)
     wr = torch.randn((d, E), generator=g, device="cuda", dtype=torch.bfloat16).mul_(d ** -0.5)
@@ -91,6 +115,8 @@ def test_router_backward_at_block_edges(T, d, E):
     tol = TOL["bf16"] if E % 64 == 0 else 2.0 ** -8
     assert rel_err(host(dwr), dwr_ref) < tol
     assert rel_err(host(dx), dx0 + dx_ref) < tol
+    B.moe_router_bwd(x, wr, dl, dwr, True, None, False, ws)      # added to the gradient above, which was rounded once
+    assert rel_err(host(dwr), 2.0 * dwr_ref) < tol
 
 
 # a token's selection and the counts, with one, two and four blocks per CU (the lines lie at 64 and 256 tokens per CU)
@@ -181,3 +207,18 @@ def test_logits_of_few_experts(E, d, bound):
     for t0, t1 in ((0, 1), (17, 320), (1000, 2999)):
         assert torch.equal(logits(x[t0:t1]), whole[t0:t1])
     assert torch.equal(logits(torch.cat([x[100:], x])), torch.cat([whole[100:], whole]))
+
+
+# a plan that does not fit its buffers, with the kernels for few rows: the rows that fit are those of the whole plan
+def test_few_rows_with_more_rows_than_the_capacity():
+    wl = W.QWEN.scaled(name="few-rows-overflow", T=40, d=128, f=192, E=8, e_cnt=8, k=4)
+    print(f"case {wl.name}", flush=True)
+    inp = make_inputs(wl)
+    fw, _ = oracle_layer(wl, inp)
+    cap, R = 101, int(fw["offsets"][-1])
+    assert R > cap
+    dev, buf = gpu_layer(wl, inp, cap=cap)
+    assert buf.status() == 1
+    assert (host(buf.offsets) == np.minimum(fw["offsets"], cap)).all()
+    for name, got in (("h1", buf.h1), ("h3", buf.h3), ("o", buf.o)):
+        assert got.shape[0] == cap and rel_err(host(got), fw[name][:cap]) < TOL["bf16"], name
