@@ -205,6 +205,8 @@ size_t moe_workspace_bytes(int which, int dtype, int T, int k, int d, int f, int
  *
  * moe_router_fwd -- logits [T,E] float = x [T,d] Wr [d,E], fp32 accumulation.
  *   x and wr have type `dtype`; bf16 requires d % 8 == 0.  ws: moe_workspace_bytes(MOE_WS_ROUTER).
+ *   A token's logits are the same bit for bit in every batch, except for bf16 with E % 64 == 0 and
+ *   d % 64 == 0, where the order of the sums follows T.
  */
 int moe_router_fwd(const void* x, const void* wr, int dtype, int T, int d, int E, float* logits,
                    void* ws, size_t ws_bytes, moe_stream_t stream);
@@ -241,8 +243,9 @@ int moe_gate_bwd(const float* logits, const int32_t* topk_idx, const float* dgat
  *   1 add to the existing contents (dx_accumulate = 1 adds the router term to the gradient that
  *   the expert path left in dx).  Either output may be NULL to skip it.
  *   bf16: dlogits is rounded to bf16 for the matrix cores when E % 64 == 0 and d % 64 == 0
- *   (fp32 accumulation over T in fixed-size chunks, chunk sums added in fp32); other shapes
- *   take a plain fp32 path.  ws: moe_workspace_bytes(MOE_WS_ROUTER).
+ *   (fp32 accumulation over T in fixed-size chunks, chunk sums added in fp32).  Other shapes keep
+ *   all 24 bits of dlogits: as fp32, or for the weight gradient of up to 42 experts as three bf16
+ *   terms on the matrix cores.  ws: moe_workspace_bytes(MOE_WS_ROUTER).
  */
 int moe_router_bwd(const void* x, const void* wr, const float* dlogits, int dtype, int T, int d, int E,
                    void* dwr, int dwr_accumulate, void* dx, int dx_accumulate, void* ws, size_t ws_bytes,

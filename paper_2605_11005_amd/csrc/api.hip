@@ -20,7 +20,8 @@ int shape_check_expert(int dtype, int cap, int d, int f, int e_cnt) {
   // 32-bit row*ld products inside a tile and 31-bit element counts per activation tensor
   if ((long long)cap * (d > f ? d : f) >= (1ll << 40)) return MOE_EUNSUPPORTED;
   if ((long long)(d > f ? d : f) * 256 >= (1ll << 31)) return MOE_EUNSUPPORTED;
-  // fp32: limits of the row tiles (64 rows each, at most one ragged tile per expert) and of 64-wide tiles of d or f
+  // fp32: at most 65535 row tiles (64 rows each, one ragged tile per expert) and 65535 64-wide tiles of d or f.  The kernels'
+  // 1-D grid would hold more; the accepted range stays what it was.
   if (dtype == MOE_F32 && ((long long)(cap + 63) / 64 + e_cnt > 65535 || (d > f ? d : f) / 64 + 1 > 65535)) return MOE_EUNSUPPORTED;
   return MOE_OK;
 }
@@ -160,7 +161,7 @@ size_t moe_workspace_bytes(int which, int dtype, int T, int k, int d, int f, int
   if (T < 0 || k < 0 || f < 0 || e_cnt < 0 || cap < 0) return 256;
   switch (which) {
     case MOE_WS_DISPATCH: return align256(plan_ws_bytes(T, k, e_cnt));
-    case MOE_WS_EXPERT_FWD:   // a [cap,f] (+ h1, h3 when the caller does not keep them, fp32 path)
+    case MOE_WS_EXPERT_FWD:   // a [cap,f]; the fp32 path asks for three of them as it always has and uses the first
       return align256((dtype == MOE_F32 ? 3 : 1) * (size_t)cap * f * esize(dtype)) + 256;
     case MOE_WS_EXPERT_BWD:   // a, dH1, dH3 [cap,f]; bf16 adds scheduler words and the weight-gradient partial tiles
       return align256(3 * (size_t)cap * f * esize(dtype)) + (dtype == MOE_BF16 && d > 0 ? expert_bwd_extra_ws_bytes(d, f) : 256);

@@ -1302,7 +1302,8 @@ int launch_expert_bwd_bf16(const void* xp, const void* h1, const void* h3, const
 }
 
 // ---- trainable router on the matrix cores (bf16, E % 64 == 0, d % 64 == 0) ----------------
-// ws layout: [0,256) ticket counters; then dl as bf16 [T,E]; then the fp32 chunk sums [S,d,E].
+// ws layout of the backward: [0,256) ticket counters; then dl as bf16 [T,E]; then the fp32 chunk sums [S,d,E], or in the
+// same bytes the streaming weight gradient's operand (pieces of dl) and its sums.  The forward's range tiles start at 256.
 // Into how many chunks of tokens the router's weight gradient is cut: the split whose schedule is
 // shortest, counted in k-tiles per workgroup: rounds of the chip's CUs times (k-tiles per chunk +
 // what a tile costs besides its k loop, about 16 k-tiles for its first loads and its fp32 stores).

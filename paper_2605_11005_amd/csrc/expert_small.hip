@@ -49,8 +49,8 @@ struct SArgs {
                                           // narrow_router: rows per block
 };
 
-// Loads go through a buffer descriptor: a wave-uniform base and a 32-bit byte offset per lane.  With 64-bit addresses per
-// lane a CU's address path limits it to about 27 bytes per cycle, half of what this form reaches.  A descriptor of length
+// Loads go through a buffer descriptor: a wave-uniform base and a 32-bit byte offset per lane (64-bit addresses per lane limit
+// a CU's address path, see dma16 in expert_bf16.hip).  A descriptor of length
 // zero makes a load return zeros without touching memory: pieces past the end of a wavefront's share are issued that way,
 // which keeps the number of loads, and so the wait counts, the same for every piece.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t descriptor(const bf16_t* base, bool in) {
@@ -516,7 +516,7 @@ int launch_router_fwd_small(const void* x, const void* wr, int T, int d, int E, 
   //             T = 5000, d = 7168 51.6 / 34.2 / 27.0    9001, 7168 75.5 / 64.7 / 46.7
   const int tg = (long long)(T + 15) / 16 * cols <= cus ? 1 : ((long long)(T + 31) / 32 * cols <= cus ? 2 : 4);
   const int row_blocks = (T + 16 * tg - 1) / (16 * tg);
-  // A CU takes about 65 GB/s of weights, so a handful of blocks is cut along the contraction (at least two pieces per
+  // A handful of blocks cannot draw the weights fast enough, so it is cut along the contraction (at least two pieces per
   // wavefront); the second launch that adds the ranges up pays from three ranges on.
   int n = cus / (cols * row_blocks);
   if (n > max_ranges) n = max_ranges;
@@ -535,7 +535,7 @@ int launch_router_fwd_small(const void* x, const void* wr, int T, int d, int E, 
   return MOE_OK;
 }
 
-// dlogits as router_dw_operand lays them out: [pieces][planes * E][32].  Partial sums go to partials[ranges * planes][d][E]
+// dlogits as router_dl_operands lays them out: [pieces][planes * E][32].  Partial sums go to partials[ranges * planes][d][E]
 // (range by range, plane by plane); at most max_sums of them.  T >= 32.
 int launch_router_dw_small(const void* x, const void* dl_pieces, int planes, int T, int d, int E, float* partials, int max_sums,
                            int* sums, hipStream_t s) {

@@ -526,9 +526,9 @@ int launch_router_fwd(const void* x, const void* wr, int dtype, int T, int d, in
     float* partial = (float*)((char*)ws + 256);
     const int room = mfma_shape(dtype, T, d, E) ? router_fwd_splits(T, d, E) : 1;      // what the workspace holds
     int splits = 1;
-    // The streaming kernel reads the weights once per 64 tokens: it is the faster one up to a block of 64 tokens by 128
-    // experts per CU (T = 16384, d = 4096, E = 128: 41 us against 56), beyond that the big tiles are (T = 32768, d = 7168,
-    // E = 256: 180 us against 296).
+    // The streaming kernel reads the weights once per 64 tokens.  Up to a block of 64 tokens by 128 experts per CU it is the
+    // faster one (whole calls, streaming / big tiles, us: T = 16384, d = 4096, E = 128 32 / 52; 8192, 4096, 256 31 / 56; 16384,
+    // 2048, 64 18 / 34); beyond that it depends (32768, 4096, 128 75 / 89; 12000, 4096, 256 57 / 62; 32768, 7168, 256 271 / 161).
     const bool stream = !mfma_shape(dtype, T, d, E) || (long long)tiles(T, 64) * tiles(E, 128) <= device_cu_count();
     int rc;
     if (stream) {
