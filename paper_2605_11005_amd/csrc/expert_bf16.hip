@@ -31,7 +31,7 @@
 // are fetched while the current one multiplies, and there is one workgroup barrier per k-tile.
 // Workgroups are persistent and walk a device-built tile list (row counts never visit the
 // host); the list is ordered so that the tiles resident on one XCD share operand panels.
-#include "common.h"
+#include "few_rows.h"
 #include "kernels.h"
 
 namespace {
@@ -44,7 +44,6 @@ __device__ __forceinline__ void store16(void* ptr, uint4 v) {
   __builtin_nontemporal_store(__builtin_bit_cast(u32x4_t, v), reinterpret_cast<u32x4_t*>(ptr));
 }
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
@@ -1051,6 +1050,56 @@ __global__ __launch_bounds__(NT, 1) void gg_kernel(GArgs p) {
   gg_body<MODE>(p);
 }
 
+// Whether the kernel for few rows is the faster one at these row counts (whole wavefronts; the same answer in all of them): its
+// time and the tiles', each from the rounds, the work per CU and the bytes of both GEMMs, in us, fitted to 12 shapes with 1 to 128
+// rows per expert.  The estimate is good to a quarter: over 315 cases (9 shapes, bounds of 17 to 128 rows, filled evenly, by 1/r,
+// by one expert, to an eighth) the kernel for few rows took 0.44 to 0.86 of the tiles' time where the ratio is below 0.75, and
+// 0.6 to 1.9 above.
+__device__ __forceinline__ bool few_rows_pay(const int32_t* __restrict__ off, int e_cnt, int d, int f) {
+  constexpr float C1 = 0.563f, C2 = 0.752f, C4 = 1.173f;       // a round of 128 k with up to 16, 32 and 64 rows
+  float v[5] = {0.f, 0.f, 0.f, 0.f, 0.f};            // rounds' cost of a column block, tiles of 64 rows, of 256, active experts; longest
+  for (int e = lane_id(); e < e_cnt; e += WAVE) {
+    const int rows = off[e + 1] - off[e], rest = rows & 63;
+    const float last = rest > 32 ? C4 : (rest > 16 ? C2 : (rest > 0 ? C1 : 0.f));
+    v[0] += (float)(rows >> 6) * C4 + last;
+    v[1] += (float)((rows + 63) >> 6);
+    v[2] += (float)((rows + 255) >> 8);
+    v[3] += rows > 0 ? 1.f : 0.f;
+    v[4] = fmaxf(v[4], rows > 63 ? C4 : last);
+  }
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) v[k] += __shfl_xor(v[k], o, WAVE);
+    v[4] = fmaxf(v[4], __shfl_xor(v[4], o, WAVE));
+  }
+  const float inv_grid = 1.f / (float)gridDim.x;
+  float few = 0.f, tiles = 2.f * (13.f - 3.85f);     // launch, first loads and last stores
+#pragma unroll
+  for (int g = 0; g < 2; ++g) {
+    const int K = g == 0 ? d : f;
+    const float few_cols = (float)(g == 0 ? (f + 63) / 64 : (d + 127) / 128), cols = (float)(g == 0 ? (f + 127) / 128 : (d + 255) / 256);
+    const float rounds = (float)K / 128.f, bytes = (g == 0 ? 4e-6f : 2e-6f) * (float)d * (float)f;      // of one expert, MB
+    few += fmaxf(fmaxf(v[4] * rounds, v[0] * few_cols * rounds * inv_grid), 0.194f * v[1] * bytes);
+    const float n = v[2] * cols;
+    tiles += fmaxf(fmaxf(0.419f * 4.f * rounds * ceilf(n * inv_grid), 0.866f * 4.f * rounds * n * inv_grid), 0.19f * v[3] * bytes);
+  }
+  return __builtin_amdgcn_readfirstlane(few < 0.75f * tiles);
+}
+
+// Forward GEMM of a call whose capacity leaves open which kernel pays: the row counts decide, in every block alike.
+template <int MODE>
+__global__ __launch_bounds__(NT, 1) void gg_or_few(GArgs p, int d, int f) {
+  if (few_rows_pay(p.off, p.e_cnt, d, f)) {
+    SArgs q = {};
+    q.A = p.A0; q.lda = p.lda; q.B0 = p.B0; q.B1 = p.B1; q.ldb = p.ldb; q.b_es = p.b_es;
+    q.C0 = p.C0; q.C1 = p.C1; q.C2 = p.C2; q.ldc = p.ldc; q.off = p.off; q.e_cnt = p.e_cnt; q.N = p.N; q.K = p.K;
+    for (int b = blockIdx.x; few_rows_tile<MODE == UP>(q, reinterpret_cast<u32x4*>(smem), b); b += gridDim.x) {}
+    return;
+  }
+  gg_body<MODE>(p);
+}
+
 // Two grouped GEMMs that do not depend on each other in one launch: a workgroup that finds no tile
 // of the first left goes on to the second at once, so the second fills the first one's tail (the
 // last round of whole tiles, in which most CUs would idle) and one launch boundary goes away.
@@ -1149,6 +1198,24 @@ int launch_pair(const GArgs& a, const GArgs& b, int prof_id, hipStream_t s) {
 }
 
 template <int MODE>
+int launch_gg_or_few(const GArgs& a, int d, int f, hipStream_t s) {
+  static_assert(FEW_ROWS_PLACES * 16 <= SMEM_BYTES && NW_EXPERT * WAVE == NT, "one block serves both");
+  static bool attr_set[64] = {};
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return MOE_EHIP;
+  if (!attr_set[dev]) {
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&gg_or_few<MODE>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            SMEM_BYTES) != hipSuccess)
+      return MOE_EHIP;
+    attr_set[dev] = true;
+  }
+  ProfScope prof(MOE_K_UP + MODE, s);
+  hipLaunchKernelGGL(gg_or_few<MODE>, dim3(device_cu_count()), dim3(NT), SMEM_BYTES, s, a, d, f);
+  HIP_CHECK_LAUNCH();
+  return MOE_OK;
+}
+
+template <int MODE>
 int launch_gg(const GArgs& a, hipStream_t s) {
   // the LDS opt-in is a per-device attribute of the kernel
   static bool attr_set[64] = {};
@@ -1169,13 +1236,10 @@ int launch_gg(const GArgs& a, hipStream_t s) {
 
 }  // namespace
 
-// Whether the forward takes the kernels for few rows (expert_small.hip) instead of the 256x256 tiles; the results are the
-// same bit for bit.  Those kernels read an expert's weights once per 64 rows, the tiles once per 256 with 256 rows' worth of
-// work each.  The true row counts are on the device, so the line is drawn by the host's bound on the rows per expert, and it
-// has to hold when the bound is filled, evenly or not.  While all weights fit the Infinity Cache (256 MB) the tiles leave the
-// chip idle up to 128 rows; larger weights stream from HBM at nearly its rate either way, and reading them again for further
-// rows costs more than the tiles' padding.  Forward of both GEMMs, few rows / tiles, in us, with the bound filled evenly, by
-// 1/r (Zipf), by one expert alone, and to a tenth:
+// Which kernel the forward takes: the one for few rows (few_rows.h; results are the same bit for bit) or the 256x256 tiles.  The
+// former reads an expert's weights once per 64 rows, the tiles once per 256 with 256 rows' worth of work each.  The true row
+// counts are on the device, the host knows a bound.  Forward of both GEMMs, few rows / tiles, in us, with the bound filled
+// evenly, by 1/r (Zipf), by one expert alone, and to a tenth:
 //   weights  d, f, experts       bound   even         Zipf         one          a tenth
 //   138 MB   2048, 1408, 8       128     62 / 87      77 / 87      63 / 87      37 / 68
 //   151 MB   2048, 768, 16       128     68 / 78      79 / 82      67 / 85      38 / 65
@@ -1186,10 +1250,13 @@ int launch_gg(const GArgs& a, hipStream_t s) {
 //   2.8 GB   7168, 2048, 32      8       502 / 526    544 / 529    94 / 176     337 / 400
 //                                16      514 / 527    656 / 532    125 / 191    493 / 527
 //   2.8 GB   4096, 14336, 8      8       509 / 603    528 / 601    207 / 298    439 / 558
-inline bool few_rows(int cap, int d, int f, int e_cnt) {
+// While all weights fit the Infinity Cache (256 MB) few rows win up to a bound of 128 however it is filled; up to a bound of 16,
+// with more than 1 GB of 8, they win or lose little.  Up to 1 GB and 128 rows it depends on the counts: gg_or_few looks at them.
+enum { MANY_ROWS, FEW_ROWS, COUNTS_DECIDE };
+inline int rows_route(int cap, int d, int f, int e_cnt) {
   const long long mb = 6ll * d * f * e_cnt >> 20;
   const long long bound = mb <= 256 ? 128 : (mb <= 1024 ? 16 : 8);
-  return cap <= bound * e_cnt;
+  return cap <= bound * e_cnt ? FEW_ROWS : (mb <= 1024 && cap <= 128ll * e_cnt ? COUNTS_DECIDE : MANY_ROWS);
 }
 
 int launch_expert_fwd_bf16(const void* xp, int cap, int d, int f, int e_cnt, const int32_t* offsets,
@@ -1197,7 +1264,8 @@ int launch_expert_fwd_bf16(const void* xp, int cap, int d, int f, int e_cnt, con
                            void* a_ws, hipStream_t s) {
   if (cap == 0 || e_cnt == 0) return MOE_OK;
   bf16_t* act = a_out ? (bf16_t*)a_out : (bf16_t*)a_ws;
-  if (few_rows(cap, d, f, e_cnt)) return launch_expert_fwd_small(xp, cap, d, f, e_cnt, offsets, w1, w3, w2, h1, h3, act, o, s);
+  const int route = rows_route(cap, d, f, e_cnt);
+  if (route == FEW_ROWS) return launch_expert_fwd_small(xp, cap, d, f, e_cnt, offsets, w1, w3, w2, h1, h3, act, o, s);
   int32_t* sched = sched_area(a_ws, (size_t)cap * f * 2);
   hipLaunchKernelGGL(zero_words, dim3(1), dim3(64), 0, s, sched, 16);
   HIP_CHECK_LAUNCH();
@@ -1206,14 +1274,15 @@ int launch_expert_fwd_bf16(const void* xp, int cap, int d, int f, int e_cnt, con
   u.B0 = (const bf16_t*)w1; u.B1 = (const bf16_t*)w3; u.ldb = f; u.b_es = (long)d * f;
   u.C0 = (bf16_t*)h1; u.C1 = (bf16_t*)h3; u.C2 = act; u.ldc = f;
   u.off = offsets; u.sched = sched; u.e_cnt = e_cnt; u.N = f; u.K = d; u.save_h = (h1 && h3) ? 1 : 0;
-  int rc = launch_gg<UP>(u, s);
+  const bool decide = route == COUNTS_DECIDE;
+  int rc = decide ? launch_gg_or_few<UP>(u, d, f, s) : launch_gg<UP>(u, s);
   if (rc) return rc;
   GArgs w = {};
   w.A0 = w.A1 = act; w.lda = f;
   w.B0 = w.B1 = (const bf16_t*)w2; w.ldb = d; w.b_es = (long)f * d;
   w.C0 = (bf16_t*)o; w.ldc = d;
   w.off = offsets; w.sched = sched + 8; w.e_cnt = e_cnt; w.N = d; w.K = f;
-  return launch_gg<DOWN>(w, s);
+  return decide ? launch_gg_or_few<DOWN>(w, d, f, s) : launch_gg<DOWN>(w, s);
 }
 
 int launch_expert_bwd_bf16(const void* xp, const void* h1, const void* h3, const void* a_in, const void* d_o, int cap,
