@@ -16,7 +16,7 @@
 //   * UP, DOWN: four wavefronts that share the loads and multiply 32 columns each, every output one chain of sums over
 //     ascending k (expert_tile);
 //   * RL, RW: eight wavefronts that share the contraction, wavefront w the 32-deep pieces w, w + 8, .., two to four of them in
-//     flight; the eight partial results are added in LDS in ascending order (router_tile;
+//     flight; the eight partial results are added in LDS in ascending order (router_tile);
 //   * RL with 8 to 56 experts: eight wavefronts with an eighth of the contraction each, eight sums per output (narrow_router).
 #include "few_rows.h"
 #include "kernels.h"
