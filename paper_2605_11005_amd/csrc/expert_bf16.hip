@@ -30,7 +30,8 @@
 // Per k-tile each wavefront runs two k-steps of 16 MFMAs; the fragments of the next k-step
 // are fetched while the current one multiplies, and there is one workgroup barrier per k-tile.
 // Workgroups are persistent and walk a device-built tile list (row counts never visit the
-// host); the list is ordered so that the tiles resident on one XCD share operand panels.
+// host); the list is ordered so that the tiles resident on one XCD share operand panels.  In the
+// ragged-M shapes a second list of 128x128 tiles (quarter tiles) follows where that ends sooner.
 #include "few_rows.h"
 #include "kernels.h"
 
@@ -49,6 +50,7 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int BM = 256, BN = 256, BK = 32;
+constexpr int QT = 128, QK = 64;        // quarter tiles
 constexpr int NT = 256;                 // threads
 constexpr int NSTAGE = 4;
 constexpr int OPER_BYTES = 256 * BK * 2;           // 16384: one operand tile
@@ -59,8 +61,8 @@ constexpr int TILE_LDS = NSTAGE * STAGE_BYTES;     // 131072
 constexpr int SPITCH = 68, DPITCH = 132;
 constexpr int STAGING_WAVE_BYTES = 16 * SPITCH * 4;   // 4352 >= 8 * DPITCH * 4 = 4224
 static_assert(8 * DPITCH * 4 <= STAGING_WAVE_BYTES, "dual slab must fit");
-// scheduler tables after the ring: tile_start[L+1], offs[L+1], split[L] (int32), order[L] (uint16), ticket
-constexpr int SCHED_BYTES = 2 * (MOE_MAX_LOCAL + 1) * 4 + MOE_MAX_LOCAL * 4 + MOE_MAX_LOCAL * 2 + 16;
+// scheduler tables after the ring: tile_start[L+1], offs[L+1], split[L+1] (int32), order[L] (uint16), ticket
+constexpr int SCHED_BYTES = 3 * (MOE_MAX_LOCAL + 1) * 4 + MOE_MAX_LOCAL * 2 + 16;
 constexpr int STAGING_OFF = (TILE_LDS + SCHED_BYTES + 15) & ~15;
 constexpr int SMEM_BYTES = STAGING_OFF + 4 * STAGING_WAVE_BYTES;
 static_assert(SMEM_BYTES <= 160 * 1024, "one workgroup per CU: 160 KB of LDS");
@@ -90,7 +92,7 @@ struct GArgs {
   long p_stride;
   int split_budget;
   int32_t* plan;
-  int32_t* sched;                         // 8 zeroed ticket counters (one per XCD)
+  int32_t* sched;                         // 8 zeroed ticket counters (one per XCD); ragged-M shapes of the experts: 8 more for the quarter tiles
   int e_cnt;
   int M;                                  // WG/WGD: rows of the output (d or f)
   int N;                                  // output columns (per half for dual tiles)
@@ -101,6 +103,7 @@ struct GArgs {
   int ksplit, k_total;
   int accumulate;
   int save_h;
+  int pair_first;                         // another GEMM follows in this launch and fills the last round
 };
 
 template <int MODE> struct Traits {
@@ -246,6 +249,436 @@ __device__ __forceinline__ bf16x8 lds_frag_tr(const char* p) {
 
 extern __shared__ __align__(16) char smem[];
 
+// Dynamic, XCD-aware tile scheduler.  A list of `total` tiles is cut into chunks of 32 consecutive ones, chunk c belongs to XCD
+// c mod 8 (workgroup b runs on XCD b mod 8), whose workgroups draw tiles from it in order through one atomic counter per XCD.
+// take_ticket takes the ticket waiting in next_q[0], drawn from `queue`, and returns its tile, or -1 when the list is finished.
+// A workgroup whose queue has run dry draws from the next XCD's queue that still has tiles.
+// spread: what is left after whole rounds of eight chunks is cut into eight equal ones.  A list shorter than the chip would
+// otherwise sit on a few XCDs, each of which reads memory at an eighth of the chip's rate (d = f = 4096, 4 experts of 250 rows: the
+// down projection's 64 tiles on two XCDs take 97 us, on eight 74).  Not where the tiles differ in length (ragged K): there a
+// last round of short tiles in every queue keeps workgroups from the long ones that another queue still holds, and for the same
+// reason not in the dA that shares a launch with dW2 (116 us for 126 at 5538 rows, d = 2048, f = 1408, 8 experts).
+template <bool SPREAD>
+__device__ __forceinline__ int take_ticket(int32_t* counters, int n_queues, int& queue, int total, int32_t* next_q, int wave, int lane,
+                                           bool spread = SPREAD) {
+  const int rounds = total / (32 * n_queues), rest = total - rounds * 32 * n_queues;
+  const int share = SPREAD && spread ? (rest + n_queues - 1) / n_queues : 32;
+  while (true) {
+    // (the slot is next written after a whole k loop of barriers)
+    const int q = __builtin_amdgcn_readfirstlane(next_q[0]), i = q - 32 * rounds;
+    const int L = !SPREAD || i < 0 ? 32 * (n_queues * (q >> 5) + queue) + (q & 31)
+                                   : (i < share && queue * share + i < rest ? rounds * 32 * n_queues + queue * share + i : total);
+    if (L < total) return L;
+    // Tickets only grow, so this queue is finished, and so is every queue whose counter has passed
+    // its last ticket.  All counters are looked at in one round trip (an atomic add of zero, one lane
+    // per queue): when none is open the workgroup is done; otherwise it draws from the first open
+    // queue after its own (work stealing at the tail of the schedule) and, should others have emptied
+    // that queue in between, looks again.  Every failed draw means that others took tiles meanwhile,
+    // so the loop ends when the list does.
+    __syncthreads();                         // everyone has read the ticket before it is replaced
+    if (wave == 0) {
+      int open = 0;
+      if (lane < n_queues) open = atomicAdd(counters + lane, 0) < 32 * rounds + max(0, min(share, rest - lane * share));
+      const unsigned all = (1u << n_queues) - 1u;
+      const unsigned m = (unsigned)__ballot(open) & all;
+      if (lane == 0) {
+        if (m == 0) {
+          next_q[0] = -1;
+        } else {
+          const unsigned rot = ((m >> (queue + 1)) | (m << (n_queues - queue - 1))) & all;
+          const int pick = (queue + 1 + __builtin_ctz(rot)) % n_queues;
+          next_q[1] = pick;
+          next_q[0] = atomicAdd(counters + pick, 1);
+        }
+      }
+    }
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(next_q[0]) < 0) return -1;
+    queue = __builtin_amdgcn_readfirstlane(next_q[1]);
+  }
+}
+
+// inclusive sums over a wavefront, on the DPP network: within rows of 16, then across them
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_add(int v) { return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false); }
+__device__ __forceinline__ int wave_scan(int v) {
+  v = dpp_add<0x111, 0xF>(v);      // row_shr:1, 2, 4, 8
+  v = dpp_add<0x112, 0xF>(v);
+  v = dpp_add<0x114, 0xF>(v);
+  v = dpp_add<0x118, 0xF>(v);
+  v = dpp_add<0x142, 0xA>(v);      // row_bcast:15 into rows 1 and 3
+  return dpp_add<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
+}
+__device__ __forceinline__ int wave_sum(int v) { return __builtin_amdgcn_readlane(wave_scan(v), WAVE - 1); }
+
+// Time in us until n_big 256x256 tiles and then n_quarter quarter tiles are done.  active_big, active_quarter: experts whose
+// weights either kind reads (one with both is read twice); rows: of all experts, most: of the heaviest.  A quarter tile moves half
+// of a 256x256 tile's bytes to the CU for a quarter of its work, and both are bound by that path (about 70 GB/s per CU where the
+// panels are shared): 19 us for 47 at a contraction of 2048.  The constants are fitted to the four GEMMs alone over 76 cases
+// (eight shapes, 500 to 40000 rows: even, 1/r, half of them on one expert), each of the four plans forced.
+template <int MODE>
+__device__ __forceinline__ float plan_price(const GArgs& p, int n_big, int n_quarter, int active_big, int active_quarter, int n_quarters_n,
+                                            int rows, int most, bool tails) {
+  const float k = (float)(MODE == DX ? 2 * p.K : p.K);
+  const float alone = (float)(active_quarter * n_quarters_n) / fmaxf((float)n_quarter, 1.f);      // 1 / row tiles that share a weight panel
+  const float big = MODE == DA ? 0.024f * k + 12.f : 0.0215f * k + 3.f;
+  const float quarter = MODE == DA ? (0.008f + 0.0025f * alone) * k + 6.f : (0.0073f + 0.0025f * alone) * k + 4.5f;
+  // the weights at the rate that either kind streams them, MB per us (UP's quarters read 128 bytes of a row, DA's and DX's
+  // 256x256 tiles 64)
+  constexpr float RATE_BIG = MODE == UP || MODE == DOWN ? 5.6f : 5.1f, RATE_QUARTER = MODE == UP ? 4.8f : 5.8f;
+  const float weights = k * (float)p.N * (MODE == UP ? 4e-6f : 2e-6f) * ((float)active_big / RATE_BIG + (float)active_quarter / RATE_QUARTER);
+  const int grid = gridDim.x, full = n_big / grid, rest = n_big - full * grid;
+  const float per_cu = 1.f / (float)grid;
+  // row tiles of which half is empty share no weight panel when they are quarters: their price is the least certain
+  const float doubt = tails && n_big > 0 ? 1.05f : 1.f;
+  if (p.pair_first) {      // the weight gradient that follows in this launch fills the last round: all of one kind
+    const float tile = 0.027f, start = 6.f;
+    const float n_second = (float)(((p.N + BM - 1) / BM) * ((p.K + (MODE == DX ? 127 : 255)) / (MODE == DX ? 128 : 256)));
+    const float second = n_second * (tile * (float)rows + start * (float)p.e_cnt) * per_cu, longest = tile * (float)most + start;
+    if (n_big == 0) return fmaxf(quarter * ceilf((float)n_quarter * per_cu), weights) + fmaxf(second, longest);
+    if (n_quarter > 0) return 1e30f;
+    return fmaxf(fmaxf((float)(full + (rest ? 1 : 0)) * big, longest), fmaxf((float)n_big * big * per_cu, weights) + second);
+  }
+  float t = (float)(full + (rest ? 1 : 0)) * big;
+  if (n_quarter) t = fmaxf(t, (float)full * big + (n_big ? 3.f : 0.f) + quarter * ceilf(((float)n_quarter + (float)rest * (big / quarter)) * per_cu));
+  return doubt * fmaxf(t, weights);
+}
+
+// Position of tile L in an ascending table of first tiles [0, n]: usually the last one's or the one after it (tickets of a
+// queue ascend), otherwise a binary search.
+__device__ __forceinline__ int find_position(const int32_t* start, int n, int L, int hint) {
+  int a = hint;
+  const int t0 = start[a], t1 = start[a + 1], t2 = start[min(a + 2, n)];
+  if (L >= t1 && L < t2) a = a + 1;
+  else if (L < t0 || L >= t1) {
+    a = 0;
+    int c = n;
+    while (c - a > 1) {
+      int mid = (a + c) >> 1;
+      if (start[mid] <= L) a = mid; else c = mid;
+    }
+  }
+  return __builtin_amdgcn_readfirstlane(a);
+}
+
+// ---- what an epilogue does with eight finished columns of a row
+__device__ __forceinline__ uint4 pack8(const float* x) {
+  return make_uint4(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7]));
+}
+__device__ __forceinline__ void add8(float* x, uint4 old) {
+  const uint32_t u[4] = {old.x, old.y, old.z, old.w};
+#pragma unroll
+  for (int i = 0; i < 4; ++i) { x[2 * i] += bf16lo(u[i]); x[2 * i + 1] += bf16hi(u[i]); }
+}
+// UP: h1, h3 and a = silu(h1) h3
+__device__ __forceinline__ void finish_up(const GArgs& p, size_t idx, const float* x1, const float* x3) {
+  float a[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a[i] = silu_f(x1[i]) * x3[i];
+  if (p.save_h) {
+    store16(p.C0 + idx, pack8(x1));
+    store16(p.C1 + idx, pack8(x3));
+  }
+  store16(p.C2 + idx, pack8(a));
+}
+// DA: a, dH1, dH3 from x = dA and the stored h1, h3
+__device__ __forceinline__ void finish_da(const GArgs& p, size_t idx, const float* x, uint4 q1, uint4 q3) {
+  const uint32_t u1[4] = {q1.x, q1.y, q1.z, q1.w}, u3[4] = {q3.x, q3.y, q3.z, q3.w};
+  float av[8], d1[8], d3[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const float z = (i & 1) ? bf16hi(u1[i >> 1]) : bf16lo(u1[i >> 1]);
+    const float gv = (i & 1) ? bf16hi(u3[i >> 1]) : bf16lo(u3[i >> 1]);
+    float ds;
+    const float sl = silu_grad_f(z, &ds);
+    av[i] = sl * gv;
+    d1[i] = x[i] * gv * ds;
+    d3[i] = x[i] * sl;
+  }
+  if (p.C0) store16(p.C0 + idx, pack8(av));      // not stored when the forward's copy is at hand
+  store16(p.C1 + idx, pack8(d1));
+  store16(p.C2 + idx, pack8(d3));
+}
+
+
+// ---- quarter tiles: 128x128 (a dual tile: 64 columns of either output) --------------------------------------------------
+// What is left of a GEMM when the 256x256 tiles no longer fill a round of the chip, and the row tiles of which half is empty, is
+// multiplied in quarters.  The four wavefronts hold 64x64 each; a k-tile is 64 deep, so that every load fetches whole cache
+// lines of either operand, and four of them (128 KB) make the ring.  Every output is the same chain of sums as in a 256x256
+// tile, bit for bit.
+//   K-contiguous operand   [128 rows][8 chunks of 8 k]       chunk' = chunk ^ ((row>>1)&7)
+//   transposed operand     2 x [64 k][8 chunks of 8 n]       chunk' = chunk ^ (4*((k>>1)&1))
+constexpr int QOPER_BYTES = QT * QK * 2;
+static_assert(NSTAGE * 2 * QOPER_BYTES == TILE_LDS, "the ring holds four k-tiles of quarter tiles");
+
+struct QuarterKc {         // load j of a wavefront: rows 8*(4w+j) + lane/8, whole 128-byte lines
+  const bf16_t* base;
+  uint32_t voff[4];
+  __device__ __forceinline__ void setup(const bf16_t* base_, long ld, int rows_valid, int wave, int lane) {
+    base = base_;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int rl = 8 * (4 * wave + j) + (lane >> 3);
+      const int c = (lane & 7) ^ ((rl >> 1) & 7);
+      voff[j] = (uint32_t)(min(rl, rows_valid - 1) * ld * 2 + c * 16);
+    }
+  }
+  __device__ __forceinline__ void issue1(int j, uint32_t oper_lds, int wave, long kofs) const {
+    dma16(base + kofs, voff[j], oper_lds + (4 * wave + j) * 1024);
+  }
+};
+struct QuarterTr {         // sub-tile wave/2, load j: k rows 8*(4*(w%2)+j) + lane/8, 64 columns each
+  const bf16_t* src;
+  long ld;
+  uint32_t coff;
+  __device__ __forceinline__ void setup(const bf16_t* b0, const bf16_t* b1, bool dual, long ld_, int n0, int n_lim, int wave, int lane) {
+    ld = ld_;
+    const int sub = wave >> 1, c = (lane & 7) ^ (4 * ((lane >> 4) & 1));
+    src = (dual && sub) ? b1 : b0;
+    coff = (uint32_t)(2 * min(n0 + (dual ? 0 : sub * 64) + c * 8, n_lim - 8));
+  }
+  template <bool CLAMP>    // source rows above k_last_rel are clamped (the caller zeroes the matching A fragments)
+  __device__ __forceinline__ void issue1(int j, uint32_t oper_lds, int wave, int lane, long k0, int k_last_rel) const {
+    int kr = 8 * (4 * (wave & 1) + j) + (lane >> 3);
+    if (CLAMP && kr > k_last_rel) kr = k_last_rel;
+    dma16(src + k0 * ld, (uint32_t)(kr * ld * 2) + coff, oper_lds + (4 * wave + j) * 1024);
+  }
+};
+// transposed sub-tile: byte offset of the first transposing read of 32 columns at nl (0 or 32), k-step 0; add s*2048 + t*512
+__device__ __forceinline__ int quarter_tr_off(int sub, int nl, int lane) {
+  const int i = lane & 15, g = lane >> 4;
+  const int k = 8 * (g >> 1) + (i >> 2);
+  const int n = nl + 16 * (g & 1) + 4 * (i & 3);
+  return sub * 8192 + k * 128 + (((n >> 3) ^ (4 * ((k >> 1) & 1))) << 4) + ((n & 4) << 1);
+}
+__device__ __forceinline__ bf16x8 quarter_frag_tr(const char* p) {
+  s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p));
+  s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p + 512));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+// The list of quarter tiles: positions in order[], each with the rows that its 256-row tiles leave.
+struct Quarters {
+  const int32_t* offs;
+  const uint16_t* order;
+  const int32_t* tile_start;               // 256x256 tiles before a position
+  const int32_t* start;                    // quarter tiles before a position
+  int n_tiles_n;                           // column tiles of 256x256
+  int total;
+  int32_t* next_q;
+};
+
+template <int MODE>
+__device__ __forceinline__ void quarter_tiles(const GArgs& p, const Quarters& list) {
+  using TR = Traits<MODE>;
+  static_assert(!TR::RAGGED_K, "");
+  constexpr int QN = TR::DUAL ? QT / 2 : QT;             // output columns
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave >> 1, wn = wave & 1;
+  const int n_cols = (p.N + QN - 1) / QN;
+  const uint32_t smem_base = lds_addr(smem);
+  int32_t* const counters = p.sched + 8;
+  const int n_queues = (gridDim.x % 8) == 0 ? 8 : 1;
+  int queue = blockIdx.x % n_queues;
+  int hint = 0;
+
+  int a_off[2], b_off[2];
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const int row = wm * 64 + i * 32 + (lane & 31), col = wn * 64 + i * 32 + (lane & 31);
+    a_off[i] = row * 128 + (((lane >> 5) ^ ((row >> 1) & 7)) << 4);
+    b_off[i] = QOPER_BYTES + (!TR::B_TRANS ? col * 128 + (((lane >> 5) ^ ((col >> 1) & 7)) << 4)
+                                           : TR::DUAL ? quarter_tr_off(i, wn * 32, lane) : quarter_tr_off(wn, i * 32, lane));
+  }
+
+  int row0 = 0, row_end = 0, n0 = 0, nk0 = 0, nk = 0;
+  QuarterKc ia, ib_kc;
+  QuarterTr ib_tr;
+  // q = 0..3: operand A of k-tile kt, 4..7: operand B.  kt is clamped to the last one as in the 256x256 tiles.
+  auto issue_one = [&](int kt, int q) {
+    if (kt > nk - 1) kt = nk - 1;
+    const uint32_t st = smem_base + (kt & (NSTAGE - 1)) * (2 * QOPER_BYTES);
+    const bool seg1 = MODE == DX && kt >= nk0;
+    const long k0 = (long)(seg1 ? kt - nk0 : kt) * QK;
+    if (q < 4) ia.issue1(q, st, wave, k0 + (seg1 ? p.A1 - p.A0 : 0));
+    else if (TR::B_TRANS) ib_tr.template issue1<false>(q - 4, st + QOPER_BYTES, wave, lane, k0, 0);
+    else ib_kc.issue1(q - 4, st + QOPER_BYTES, wave, k0 + (seg1 ? p.B1 - p.B0 : 0));
+  };
+  auto next_tile = [&]() -> bool {
+    const int L = take_ticket<true>(counters, n_queues, queue, list.total, list.next_q, wave, lane);
+    if (L < 0) return false;
+    const int pos = find_position(list.start, p.e_cnt, L, hint);
+    hint = pos;
+    const int li = __builtin_amdgcn_readfirstlane(L - list.start[pos]);
+    const int e = __builtin_amdgcn_readfirstlane((int)list.order[pos]);
+    const int lo = __builtin_amdgcn_readfirstlane(list.offs[e]) +
+                   BM * (__builtin_amdgcn_readfirstlane(list.tile_start[pos + 1] - list.tile_start[pos]) / list.n_tiles_n);
+    const int hi = __builtin_amdgcn_readfirstlane(list.offs[e + 1]);
+    const int m_tiles = (hi - lo + QT - 1) / QT;
+    const int band = li / (8 * n_cols), in_band = li - band * 8 * n_cols, band_rows = min(8, m_tiles - band * 8);
+    const int nt = in_band / band_rows;
+    row0 = lo + (band * 8 + in_band - nt * band_rows) * QT;
+    row_end = hi;
+    n0 = nt * QN;
+    nk0 = p.K / QK;
+    nk = MODE == DX ? 2 * nk0 : nk0;
+    ia.setup(p.A0 + (size_t)row0 * p.lda, p.lda, hi - row0, wave, lane);
+    if (TR::B_TRANS) ib_tr.setup(p.B0 + (size_t)e * p.b_es, p.B1 + (size_t)e * p.b_es, TR::DUAL, p.ldb, n0, p.N, wave, lane);
+    else ib_kc.setup(p.B0 + (size_t)e * p.b_es + (size_t)n0 * p.ldb, p.ldb, p.N - n0, wave, lane);
+#pragma unroll
+    for (int t = 0; t < 3; ++t)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) issue_one(t, q);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) issue_one(3, q);
+    return true;
+  };
+
+  if (tid == 0) list.next_q[0] = atomicAdd(counters + queue, 1);
+  __syncthreads();
+  bool have = next_tile();
+  while (have) {
+    int my_ticket = 0;
+    const int kt_draw = nk > 4 ? nk - 4 : 0;
+    // DA: this tile's h1 and h3 (clamped addresses) are here before its k loop ends; 4 slabs of 16 rows, 2 passes of 8
+    uint4 pre1[4][2], pre3[4][2];
+    const int c8 = lane & 7;
+    if (MODE == DA) {
+#pragma unroll
+      for (int sl = 0; sl < 4; ++sl)
+#pragma unroll
+        for (int pass = 0; pass < 2; ++pass) {
+          const int grow = min(row0 + wm * 64 + 16 * sl + pass * 8 + (lane >> 3), row_end - 1);
+          const int gcol = min(n0 + wn * 64 + c8 * 8, p.N - 8);
+          const size_t idx = (size_t)grow * p.ldc + gcol;
+          pre1[sl][pass] = *reinterpret_cast<const uint4*>(p.H1 + idx);
+          pre3[sl][pass] = *reinterpret_cast<const uint4*>(p.H3 + idx);
+        }
+    }
+    f32x16 acc[2][2];
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+      for (int j = 0; j < 2; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    // Set h holds the fragments of half h of a k-tile (two k-steps of 16).  While a half multiplies, the other half's fragments
+    // are read; at the barrier between the halves of k-tile kt all of its fragments are in registers, so its stage is free, and
+    // k-tile kt+1 has landed.  The first half issues operand B of k-tile kt+3, the second operand A of kt+4, as in the 256x256
+    // tiles: 16 loads may remain at the barrier.
+    bf16x8 fa[2][2][2], fb[2][2][2];
+    auto frag_op = [&](int h, int kt, int o) {           // o: k-step o/4; A0, B0, B1, A1
+      const char* st = smem + (kt & (NSTAGE - 1)) * (2 * QOPER_BYTES);
+      const int s = 2 * h + (o >> 2), i = (o & 3) == 1 ? 0 : (o & 3) == 2 ? 1 : (o & 3) / 3;
+      if ((o & 3) == 0 || (o & 3) == 3) fa[h][o >> 2][i] = lds_frag_kc(st + (a_off[i] ^ (s * 32)));
+      else fb[h][o >> 2][i] = TR::B_TRANS ? quarter_frag_tr(st + b_off[i] + s * 2048) : lds_frag_kc(st + (b_off[i] ^ (s * 32)));
+    };
+    auto mfma_one = [&](int h, int m) {                  // blocks (0,0), (0,1), (1,1), (1,0) of k-step m/4
+      const int i = (m >> 1) & 1, j = i ^ (m & 1);
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[h][m >> 2][i], fb[h][m >> 2][j], acc[i][j], 0, 0, 0);
+    };
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    // MV: 32-row blocks of this wavefront that hold valid rows
+    auto k_loop = [&](auto mv_tag) {
+      constexpr int MV = decltype(mv_tag)::value;
+      auto live = [](int o) { return MV == 2 || (MV == 1 && (o & 3) != 3); };
+      auto half = [&](int kt, auto h_tag) {
+        constexpr int H = decltype(h_tag)::value;
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int m = 0; m < 8; m += 2) {
+          if ((m & 3) < 2 * MV) mfma_one(H, m);
+          if (m < 4) {
+#pragma unroll
+            for (int o = 2 * m; o < 2 * m + 2; ++o)
+              if (live(o)) frag_op(1 - H, H ? kt + 1 : kt, o);
+          }
+          if ((m & 3) < 2 * MV) mfma_one(H, m + 1);
+          if (m < 4) {
+#pragma unroll
+            for (int o = 2 * m + 2; o < 2 * m + 4; ++o)
+              if (live(o)) frag_op(1 - H, H ? kt + 1 : kt, o);
+          }
+          issue_one(H ? kt + 4 : kt + 3, H ? m >> 1 : 4 + (m >> 1));
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      };
+#pragma unroll
+      for (int o = 0; o < 8; ++o)
+        if (live(o)) frag_op(0, 0, o);
+      for (int kt = 0; kt < nk; ++kt) {
+        if (kt == kt_draw && tid == 0) my_ticket = atomicAdd(counters + queue, 1);
+        half(kt, IntC<0>{});
+        asm volatile("s_waitcnt vmcnt(16) lgkmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        half(kt, IntC<1>{});
+      }
+    };
+    const int rows_left = row_end - (row0 + wm * 64);
+    if (rows_left > 32) k_loop(IntC<2>{});
+    else if (rows_left > 0) k_loop(IntC<1>{});
+    else k_loop(IntC<0>{});
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    if (MODE == DA) {      // these have arrived: the compiler is to wait for them here, not behind the next tile's first loads
+#pragma unroll
+      for (int sl = 0; sl < 4; ++sl)
+#pragma unroll
+        for (int pass = 0; pass < 2; ++pass) {
+          u32x4_t u1 = __builtin_bit_cast(u32x4_t, pre1[sl][pass]), u3 = __builtin_bit_cast(u32x4_t, pre3[sl][pass]);
+          asm volatile("" : "+v"(u1), "+v"(u3));
+          pre1[sl][pass] = __builtin_bit_cast(uint4, u1);
+          pre3[sl][pass] = __builtin_bit_cast(uint4, u3);
+        }
+    }
+    if (tid == 0) list.next_q[0] = my_ticket;
+    __syncthreads();
+    const int ep_row0 = row0 + wm * 64, ep_row_end = row_end, ep_n0 = n0;
+    have = next_tile();
+
+    // epilogue: slabs of 16 rows x 64 columns (a dual tile: 32 of either output) through the wavefront's own staging area
+    float* stage = reinterpret_cast<float*>(smem + STAGING_OFF) + wave * (STAGING_WAVE_BYTES / 4);
+    const int acc_col = lane & 31, acc_rg = lane >> 5;
+#pragma unroll
+    for (int sl = 0; sl < 4; ++sl) {
+      const int mi = sl >> 1, h = sl & 1;
+#pragma unroll
+      for (int gg = 0; gg < 2; ++gg)
+#pragma unroll
+        for (int nn = 0; nn < 2; ++nn)
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+            stage[(8 * gg + 4 * acc_rg + i) * SPITCH + nn * 32 + acc_col] = acc[mi][nn][4 * (2 * h + gg) + i];
+      __builtin_amdgcn_wave_barrier();
+      float xs[2][8];
+#pragma unroll
+      for (int pass = 0; pass < 2; ++pass) {             // a dual tile's passes are its two outputs
+        const float* sp = TR::DUAL ? stage + (lane >> 2) * SPITCH + pass * 32 + (lane & 3) * 8
+                                   : stage + (pass * 8 + (lane >> 3)) * SPITCH + c8 * 8;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) xs[pass][i] = sp[i];
+      }
+      __builtin_amdgcn_wave_barrier();
+      if (TR::DUAL) {
+        const int grow = ep_row0 + 16 * sl + (lane >> 2), gcol = ep_n0 + wn * 32 + (lane & 3) * 8;
+        if (grow < ep_row_end && gcol < p.N) finish_up(p, (size_t)grow * p.ldc + gcol, xs[0], xs[1]);
+      } else {
+#pragma unroll
+        for (int pass = 0; pass < 2; ++pass) {
+          const int grow = ep_row0 + 16 * sl + pass * 8 + (lane >> 3), gcol = ep_n0 + wn * 64 + c8 * 8;
+          if (grow < ep_row_end && gcol < p.N) {
+            const size_t idx = (size_t)grow * p.ldc + gcol;
+            if (MODE == DA) finish_da(p, idx, xs[pass], pre1[sl][pass], pre3[sl][pass]);
+            else store16(p.C0 + idx, pack8(xs[pass]));
+          }
+        }
+      }
+    }
+  }
+}
+
 // One grouped GEMM from its set-up to its last tile, run by a persistent workgroup.
 template <int MODE>
 __device__ __forceinline__ void gg_body(const GArgs& p) {
@@ -253,7 +686,9 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
   int32_t* tile_start = reinterpret_cast<int32_t*>(smem + TILE_LDS);
   int32_t* offs = tile_start + (MOE_MAX_LOCAL + 1);      // LDS copy of the row offsets
   int32_t* split = offs + (MOE_MAX_LOCAL + 1);           // ragged-K modes: (first piece << 8) | pieces, by expert
-  uint16_t* order = reinterpret_cast<uint16_t*>(split + MOE_MAX_LOCAL);   // experts by descending row count
+  int32_t* q_start = split;                              // ragged-M modes: quarter tiles before a position
+  constexpr bool SPLIT = MODE <= DX;                     // the rest of a GEMM may be multiplied in quarter tiles
+  uint16_t* order = reinterpret_cast<uint16_t*>(split + MOE_MAX_LOCAL + 1);   // experts by descending row count
   int32_t* next_q = reinterpret_cast<int32_t*>(order + MOE_MAX_LOCAL);    // hand-over slot of the tile scheduler
 
   const int tid = threadIdx.x;
@@ -268,7 +703,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
   // (RL: the ranges of a cut contraction are listed like further column tiles)
   const int n_tiles_cols = (p.N + TR::BN_EFF - 1) / TR::BN_EFF;
   const int n_tiles_n = MODE == RL && p.ksplit > 1 ? n_tiles_cols * p.ksplit : n_tiles_cols;
-  int total;
+  int big;                                 // 256x256 tiles
   int wg_tiles_per_e = 0, wg_mt = 0;
   for (int e = tid; e <= e_cnt; e += NT) {
     const long long cut = (long long)e * p.chunk;
@@ -390,27 +825,76 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
       tile_start[e_cnt] = run;
     }
     __syncthreads();
-    total = tile_start[e_cnt];
+    big = tile_start[e_cnt];
     if (p.plan && blockIdx.x == 0)
       for (int e = tid; e < e_cnt; e += NT) p.plan[e] = split[e];
   } else {
-    for (int pos = tid; pos < e_cnt; pos += NT) {
-      const int e = order[pos];
-      const int rows = offs[e + 1] - offs[e];
-      tile_start[pos] = ((rows + BM - 1) / BM) * n_tiles_n;
-    }
-    __syncthreads();
-    if (tid == 0) {
-      int run = 0;
-      for (int pos = 0; pos < e_cnt; ++pos) {
-        int v = tile_start[pos];
-        tile_start[pos] = run;
-        run += v;
+    // Which rows go to 256x256 tiles and which to quarters.  Wavefront c prices plan c: row tiles of which at most half is
+    // filled as quarters or not (c & 1), and, with c & 2, 256x256 tiles only as many as fill whole rounds of the chip.
+    // Against 256x256 tiles only: d = 4096, f = 1536, 16 experts, 4000 rows by 1/r 174 -> 150 us (UP) and 84 -> 78 (DOWN); d =
+    // 2048, f = 1408, 8 experts of 100 rows 48 -> 28 and 39 -> 24; d = f = 2880, 16 experts of 562 rows 179 -> 162 (DOWN).
+    float* price = reinterpret_cast<float*>(smem);            // (the tile ring is still free)
+    int32_t* limits = reinterpret_cast<int32_t*>(price + 4);
+    const int n_quarters_n = (p.N + TR::BN_EFF / 2 - 1) / (TR::BN_EFF / 2);
+    const auto tiles_m = [&](int rows, int plan) { return (rows + (plan & 1 ? BM / 2 - 1 : BM - 1)) / BM; };
+    // the part of a plan's 256x256 tiles that lies below its limit, and the quarters of the rest, of the 64 positions at base
+    const auto place = [&](int base, int plan, int limit, int& before, int& quarters) {
+      const int pos = base + lane;
+      const int rows = pos < e_cnt ? offs[order[pos] + 1] - offs[order[pos]] : 0;
+      int m = tiles_m(rows, plan);
+      const int first = before + wave_scan(m * n_tiles_n) - m * n_tiles_n;
+      m = min(m, max(0, limit - first) / n_tiles_n);
+      quarters = SPLIT ? (max(0, rows - BM * m) + QT - 1) / QT * n_quarters_n : 0;
+      return m * n_tiles_n;
+    };
+    int limit = 0x7FFFFFFF;
+    if (SPLIT) {
+      int all = 0;
+      for (int pos = lane; pos < e_cnt; pos += WAVE) all += tiles_m(offs[order[pos] + 1] - offs[order[pos]], wave) * n_tiles_n;
+      all = wave_sum(all);
+      if (wave & 2) limit = all / (int)gridDim.x * (int)gridDim.x;
+      int n_big = 0, n_quarter = 0, active_big = 0, active_quarter = 0;
+      for (int base = 0; base < e_cnt; base += WAVE) {
+        int q;
+        const int t = place(base, wave, limit, n_big, q);
+        n_big += wave_sum(t);
+        n_quarter += wave_sum(q);
+        active_big += __popcll(__ballot(t > 0));
+        active_quarter += __popcll(__ballot(q > 0));
       }
-      tile_start[e_cnt] = run;
+      if (lane == 0) {
+        price[wave] = plan_price<MODE>(p, n_big, n_quarter, active_big, active_quarter, n_quarters_n, offs[e_cnt] - offs[0],
+                                       e_cnt > 0 ? offs[order[0] + 1] - offs[order[0]] : 0, wave & 1);
+        limits[wave] = limit;
+      }
     }
     __syncthreads();
-    total = tile_start[e_cnt];
+    int plan = 0;
+    if (SPLIT) {
+#pragma unroll
+      for (int c = 1; c < 4; ++c)
+        if (price[c] < (plan == 0 ? 0.97f : 1.f) * price[plan]) plan = c;
+      limit = limits[plan];
+    }
+    if (wave == 0) {
+      int n_big = 0, n_quarter = 0;
+      for (int base = 0; base < e_cnt; base += WAVE) {
+        int q;
+        const int t = place(base, plan, limit, n_big, q), t_end = wave_scan(t), q_end = SPLIT ? wave_scan(q) : 0;
+        if (base + lane < e_cnt) {
+          tile_start[base + lane] = n_big + t_end - t;
+          if (SPLIT) q_start[base + lane] = n_quarter + q_end - q;
+        }
+        n_big += __builtin_amdgcn_readlane(t_end, WAVE - 1);
+        if (SPLIT) n_quarter += __builtin_amdgcn_readlane(q_end, WAVE - 1);
+      }
+      if (lane == 0) {
+        tile_start[e_cnt] = n_big;
+        if (SPLIT) q_start[e_cnt] = n_quarter;
+      }
+    }
+    __syncthreads();
+    big = tile_start[e_cnt];
   }
 
   // LDS ring.  Ragged-K shapes: four stages of [A tile | B tile].  Ragged-M shapes (PAIR): operand A
@@ -480,78 +964,23 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
     for (int q = 0; q < 8; ++q) issue_one(kt, q);
   };
 
-  // ---- dynamic, XCD-aware tile scheduler.  The list is cut into chunks of 32 consecutive
-  // tiles (an 8 x 4 block of one expert: 8 A panels and 4 B panels); chunk c belongs to XCD
-  // c mod 8 (workgroup b runs on XCD b mod 8), whose workgroups draw tiles from it in order
-  // through one atomic counter per XCD.  Ticket q of XCD x is tile 32*(8*(q/32) + x) + q%32.
-  // The ticket for the next tile is drawn near the end of the current k loop.  A workgroup whose
-  // queue has run dry draws from the next XCD's queue that still has tiles.
+  // A chunk of 32 tiles (take_ticket) is an 8 x 4 block of one expert: 8 A panels and 4 B panels.
+  // The ticket for the next tile is drawn near the end of the current k loop.
   //
   // next_tile: takes the ticket waiting in *next_q, decodes it into the tile state above and
   // starts the loads of that tile's first k-tiles.  The tile ring must be free when it is
   // called (it is called after the barrier that ends a k loop, before that tile's epilogue,
   // so the first operands of the next tile travel while the finished one is being stored).
   auto next_tile = [&]() -> bool {
-    int L;
-    while (true) {
-      const int q = __builtin_amdgcn_readfirstlane(next_q[0]);
-      L = 32 * (n_queues * (q >> 5) + queue) + (q & 31);
-      if (L < total) break;                  // (the slot is next written after a whole k loop of barriers)
-      // Tickets only grow, so this queue is finished, and so is every queue whose counter has passed
-      // its last ticket.  All counters are looked at in one round trip (an atomic add of zero, one lane
-      // per queue): when none is open the workgroup is done; otherwise it draws from the first open
-      // queue after its own (work stealing at the tail of the schedule) and, should others have emptied
-      // that queue in between, looks again.  Every failed draw means that others took tiles meanwhile,
-      // so the loop ends when the list does.
-      __syncthreads();                       // everyone has read the ticket before it is replaced
-      if (wave == 0) {
-        int open = 0;
-        if (lane < n_queues) {
-          const int per_round = 32 * n_queues;
-          const int full = total / per_round;
-          int extra = total - full * per_round - 32 * lane;
-          extra = extra < 0 ? 0 : (extra > 32 ? 32 : extra);
-          open = atomicAdd(p.sched + lane, 0) < 32 * full + extra;
-        }
-        const unsigned all = (1u << n_queues) - 1u;
-        const unsigned m = (unsigned)__ballot(open) & all;
-        if (lane == 0) {
-          if (m == 0) {
-            next_q[0] = -1;
-          } else {
-            const unsigned rot = ((m >> (queue + 1)) | (m << (n_queues - queue - 1))) & all;
-            const int pick = (queue + 1 + __builtin_ctz(rot)) % n_queues;
-            next_q[1] = pick;
-            next_q[0] = atomicAdd(p.sched + pick, 1);
-          }
-        }
-      }
-      __syncthreads();
-      if (__builtin_amdgcn_readfirstlane(next_q[0]) < 0) return false;
-      queue = __builtin_amdgcn_readfirstlane(next_q[1]);
-    }
+    const int L = take_ticket<!TR::RAGGED_K>(p.sched, n_queues, queue, big, next_q, wave, lane, MODE != DA || !p.pair_first);
+    if (L < 0) return false;
     // Within an expert, tiles are ordered in bands of 8 m-tiles, n-tile next, m-tile inside the
     // band fastest: 32 consecutive tiles (one chunk) then form an 8 x 4 block that shares 8 A
     // panels and 4 B panels through one XCD's L2.
     int mt, nt;
     {
       int li, mte;
-      // largest position with tile_start[pos] <= L: tickets of a queue ascend, so it is usually
-      // the position of the previous tile or the one after it; otherwise a binary search
-      int a = pos_hint;
-      {
-        const int t0 = tile_start[a], t1 = tile_start[a + 1], t2 = tile_start[min(a + 2, e_cnt)];
-        if (L >= t1 && L < t2) a = a + 1;
-        else if (L < t0 || L >= t1) {
-          a = 0;
-          int c = e_cnt;
-          while (c - a > 1) {
-            int mid = (a + c) >> 1;
-            if (tile_start[mid] <= L) a = mid; else c = mid;
-          }
-        }
-      }
-      a = __builtin_amdgcn_readfirstlane(a);
+      const int a = find_position(tile_start, e_cnt, L, pos_hint);
       pos_hint = a;
       li = __builtin_amdgcn_readfirstlane(L - tile_start[a]);
       e = __builtin_amdgcn_readfirstlane((int)order[a]);
@@ -572,7 +1001,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
           piece = (sp >> 8) + c_idx;
         }
       } else {
-        mte = (hi - lo + BM - 1) / BM;
+        mte = __builtin_amdgcn_readfirstlane(tile_start[pos_hint + 1] - tile_start[pos_hint]) / n_tiles_n;      // (quarters take the rest)
       }
       const int band = li / (8 * n_tiles_n);
       const int in_band = li - band * 8 * n_tiles_n;
@@ -622,9 +1051,12 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
     return true;
   };
 
-  if (tid == 0) *next_q = atomicAdd(p.sched + queue, 1);
-  __syncthreads();
-  bool have = next_tile();
+  bool have = big > 0;
+  if (have) {
+    if (tid == 0) *next_q = atomicAdd(p.sched + queue, 1);
+    __syncthreads();
+    have = next_tile();
+  }
 
   while (have) {
     // The ticket of the tile after this one is drawn eight k-tiles before the end of the k loop
@@ -863,21 +1295,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
         if (grow < ep_row_end && gcol < p.N) {
           if (MODE == UP) {
             const size_t idx = (size_t)grow * p.ldc + gcol;
-            uint4 o1, o3, oa;
-            uint32_t* w1 = reinterpret_cast<uint32_t*>(&o1);
-            uint32_t* w3 = reinterpret_cast<uint32_t*>(&o3);
-            uint32_t* wa = reinterpret_cast<uint32_t*>(&oa);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              w1[i] = pack_bf16x2(x1[2 * i], x1[2 * i + 1]);
-              w3[i] = pack_bf16x2(x3[2 * i], x3[2 * i + 1]);
-              wa[i] = pack_bf16x2(silu_f(x1[2 * i]) * x3[2 * i], silu_f(x1[2 * i + 1]) * x3[2 * i + 1]);
-            }
-            if (p.save_h) {
-              store16(p.C0 + idx, o1);
-              store16(p.C1 + idx, o3);
-            }
-            store16(p.C2 + idx, oa);
+            finish_up(p, idx, x1, x3);
           } else if (PARTIAL) {   // WGD, one piece of a cut expert: fp32 partial tiles
             float* c0 = p.P0 + (size_t)ep_piece * p.p_stride + (size_t)grow * p.ldc + gcol;
             float* c1 = c0 + (size_t)p.M * p.N;
@@ -890,25 +1308,11 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
             bf16_t* c0 = p.C0 + idx;
             bf16_t* c1 = p.C1 + idx;
             if (rmw) {
-              const uint4 q0 = old0[sl % (C_AHEAD + 1)], q1 = old1[sl % (C_AHEAD + 1)];
-              const uint32_t* u0 = reinterpret_cast<const uint32_t*>(&q0);
-              const uint32_t* u1 = reinterpret_cast<const uint32_t*>(&q1);
-#pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                x1[2 * i] += bf16lo(u0[i]); x1[2 * i + 1] += bf16hi(u0[i]);
-                x3[2 * i] += bf16lo(u1[i]); x3[2 * i + 1] += bf16hi(u1[i]);
-              }
+              add8(x1, old0[sl % (C_AHEAD + 1)]);
+              add8(x3, old1[sl % (C_AHEAD + 1)]);
             }
-            uint4 o1, o3;
-            uint32_t* w1 = reinterpret_cast<uint32_t*>(&o1);
-            uint32_t* w3 = reinterpret_cast<uint32_t*>(&o3);
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-              w1[i] = pack_bf16x2(x1[2 * i], x1[2 * i + 1]);
-              w3[i] = pack_bf16x2(x3[2 * i], x3[2 * i + 1]);
-            }
-            store16(c0, o1);
-            store16(c1, o3);
+            store16(c0, pack8(x1));
+            store16(c1, pack8(x3));
           }
         }
       }
@@ -984,33 +1388,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
           if (grow < ep_row_end && gcol < p.N) {
             if (MODE == DA) {
               const size_t idx = (size_t)grow * p.ldc + gcol;
-              const uint4 q1 = pre1[sl % (DA_AHEAD + 1)][pass], q3 = pre3[sl % (DA_AHEAD + 1)][pass];
-              const uint32_t* u1 = reinterpret_cast<const uint32_t*>(&q1);
-              const uint32_t* u3 = reinterpret_cast<const uint32_t*>(&q3);
-              float av[8], d1[8], d3[8];
-#pragma unroll
-              for (int i = 0; i < 8; ++i) {
-                float z = (i & 1) ? bf16hi(u1[i >> 1]) : bf16lo(u1[i >> 1]);
-                float gv = (i & 1) ? bf16hi(u3[i >> 1]) : bf16lo(u3[i >> 1]);
-                float ds;
-                float sl_ = silu_grad_f(z, &ds);
-                av[i] = sl_ * gv;
-                d1[i] = x[i] * gv * ds;
-                d3[i] = x[i] * sl_;
-              }
-              uint4 oa, o1, o3;
-              uint32_t* wa = reinterpret_cast<uint32_t*>(&oa);
-              uint32_t* w1 = reinterpret_cast<uint32_t*>(&o1);
-              uint32_t* w3 = reinterpret_cast<uint32_t*>(&o3);
-#pragma unroll
-              for (int i = 0; i < 4; ++i) {
-                wa[i] = pack_bf16x2(av[2 * i], av[2 * i + 1]);
-                w1[i] = pack_bf16x2(d1[2 * i], d1[2 * i + 1]);
-                w3[i] = pack_bf16x2(d3[2 * i], d3[2 * i + 1]);
-              }
-              if (p.C0) store16(p.C0 + idx, oa);      // not stored when the forward's copy is at hand
-              store16(p.C1 + idx, o1);
-              store16(p.C2 + idx, o3);
+              finish_da(p, idx, x, pre1[sl % (DA_AHEAD + 1)][pass], pre3[sl % (DA_AHEAD + 1)][pass]);
             } else if (MODE == WG && PARTIAL) {   // one piece of a cut expert: fp32 partial tile
               float* c0 = p.P0 + (size_t)ep_piece * p.p_stride + (size_t)grow * p.ldc + gcol;
               *reinterpret_cast<float4*>(c0) = make_float4(x[0], x[1], x[2], x[3]);
@@ -1022,17 +1400,8 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
             } else {
               const size_t idx = (MODE == WG ? (size_t)ep_e * p.c_es : (size_t)0) + (size_t)grow * p.ldc + gcol;
               bf16_t* c0 = p.C0 + idx;
-              if (rmw) {
-                const uint4 q0 = pre1[sl % (DA_AHEAD + 1)][pass];
-                const uint32_t* u0 = reinterpret_cast<const uint32_t*>(&q0);
-#pragma unroll
-                for (int i = 0; i < 4; ++i) { x[2 * i] += bf16lo(u0[i]); x[2 * i + 1] += bf16hi(u0[i]); }
-              }
-              uint4 o;
-              uint32_t* w = reinterpret_cast<uint32_t*>(&o);
-#pragma unroll
-              for (int i = 0; i < 4; ++i) w[i] = pack_bf16x2(x[2 * i], x[2 * i + 1]);
-              store16(c0, o);
+              if (rmw) add8(x, pre1[sl % (DA_AHEAD + 1)][pass]);
+              store16(c0, pack8(x));
             }
           }
         }
@@ -1042,6 +1411,13 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
     if ((MODE == WG || MODE == WGD) && ep_piece >= 0) epilogue(IntC<1>{}, IntC<0>{});
     else if ((MODE == WG || MODE == WGD || MODE == RX) && p.accumulate) epilogue(IntC<0>{}, IntC<1>{});
     else epilogue(IntC<0>{}, IntC<0>{});
+  }
+  if constexpr (SPLIT) {
+    const Quarters list = {offs, order, tile_start, q_start, n_tiles_n, __builtin_amdgcn_readfirstlane(q_start[e_cnt]), next_q};
+    if (list.total > 0) {
+      __syncthreads();       // everyone has read the ticket that ended the 256x256 tiles
+      quarter_tiles<MODE>(p, list);
+    }
   }
 }
 
@@ -1192,7 +1568,9 @@ int launch_pair(const GArgs& a, const GArgs& b, int prof_id, hipStream_t s) {
     attr_set[dev] = true;
   }
   ProfScope prof(prof_id, s);
-  hipLaunchKernelGGL((gg_pair<M1, M2>), dim3(device_cu_count()), dim3(NT), SMEM_BYTES, s, a, b);
+  GArgs first = a;
+  first.pair_first = 1;
+  hipLaunchKernelGGL((gg_pair<M1, M2>), dim3(device_cu_count()), dim3(NT), SMEM_BYTES, s, first, b);
   HIP_CHECK_LAUNCH();
   return MOE_OK;
 }
@@ -1267,7 +1645,7 @@ int launch_expert_fwd_bf16(const void* xp, int cap, int d, int f, int e_cnt, con
   const int route = rows_route(cap, d, f, e_cnt);
   if (route == FEW_ROWS) return launch_expert_fwd_small(xp, cap, d, f, e_cnt, offsets, w1, w3, w2, h1, h3, act, o, s);
   int32_t* sched = sched_area(a_ws, (size_t)cap * f * 2);
-  hipLaunchKernelGGL(zero_words, dim3(1), dim3(64), 0, s, sched, 16);
+  hipLaunchKernelGGL(zero_words, dim3(1), dim3(64), 0, s, sched, 32);
   HIP_CHECK_LAUNCH();
   GArgs u = {};
   u.A0 = u.A1 = (const bf16_t*)xp; u.lda = d;
@@ -1281,7 +1659,7 @@ int launch_expert_fwd_bf16(const void* xp, int cap, int d, int f, int e_cnt, con
   w.A0 = w.A1 = act; w.lda = f;
   w.B0 = w.B1 = (const bf16_t*)w2; w.ldb = d; w.b_es = (long)f * d;
   w.C0 = (bf16_t*)o; w.ldc = d;
-  w.off = offsets; w.sched = sched + 8; w.e_cnt = e_cnt; w.N = d; w.K = f;
+  w.off = offsets; w.sched = sched + 16; w.e_cnt = e_cnt; w.N = d; w.K = f;
   return decide ? launch_gg_or_few<DOWN>(w, d, f, s) : launch_gg<DOWN>(w, s);
 }
 
@@ -1298,7 +1676,7 @@ int launch_expert_bwd_bf16(const void* xp, const void* h1, const void* h3, const
   float* partials = reinterpret_cast<float*>(reinterpret_cast<char*>(sched) + 256 + WGRAD_PLAN_BYTES);
   const size_t split_bytes = wgrad_split_bytes(d, f);
   const long mn = (long)d * f;
-  hipLaunchKernelGGL(zero_words, dim3(1), dim3(64), 0, s, sched, 32);
+  hipLaunchKernelGGL(zero_words, dim3(1), dim3(64), 0, s, sched, 64);
   HIP_CHECK_LAUNCH();
   GArgs g = {};   // dA = d_o W2^T, epilogue -> a, dH1, dH3
   g.A0 = g.A1 = (const bf16_t*)d_o; g.lda = d;
@@ -1310,18 +1688,18 @@ int launch_expert_bwd_bf16(const void* xp, const void* h1, const void* h3, const
   x.A0 = dh1; x.A1 = dh3; x.lda = f;
   x.B0 = (const bf16_t*)w1; x.B1 = (const bf16_t*)w3; x.ldb = f; x.b_es = (long)d * f;
   x.C0 = (bf16_t*)dxp; x.ldc = d;
-  x.off = offsets; x.sched = sched + 8; x.e_cnt = e_cnt; x.N = d; x.K = f;
+  x.off = offsets; x.sched = sched + 16; x.e_cnt = e_cnt; x.N = d; x.K = f;
   GArgs w = {};   // dW2 = a^T d_o
   w.A0 = w.A1 = a_in ? (const bf16_t*)a_in : a; w.lda = f;
   w.B0 = w.B1 = (const bf16_t*)d_o; w.ldb = d;
   w.C0 = (bf16_t*)dw2; w.ldc = d; w.c_es = (long)f * d;
-  w.off = offsets; w.sched = sched + 16; w.e_cnt = e_cnt; w.M = f; w.N = d; w.accumulate = accumulate;
+  w.off = offsets; w.sched = sched + 32; w.e_cnt = e_cnt; w.M = f; w.N = d; w.accumulate = accumulate;
   w.P0 = partials; w.p_stride = mn; w.split_budget = (int)(split_bytes / (mn * 4)); w.plan = plans;
   GArgs v = {};   // dW1|dW3 = xp^T [dH1|dH3]
   v.A0 = v.A1 = (const bf16_t*)xp; v.lda = d;
   v.B0 = dh1; v.B1 = dh3; v.ldb = f;
   v.C0 = (bf16_t*)dw1; v.C1 = (bf16_t*)dw3; v.ldc = f; v.c_es = (long)d * f;
-  v.off = offsets; v.sched = sched + 24; v.e_cnt = e_cnt; v.M = d; v.N = f; v.accumulate = accumulate;
+  v.off = offsets; v.sched = sched + 48; v.e_cnt = e_cnt; v.M = d; v.N = f; v.accumulate = accumulate;
   v.P0 = partials; v.p_stride = 2 * mn; v.split_budget = (int)(split_bytes / (2 * mn * 4)); v.plan = plans + MOE_MAX_LOCAL;
   // Order and pairing.  dW2 needs a and d_o, dX and dW1|dW3 need what dA's epilogue writes (dH1, dH3).  With the
   // forward's a at hand dA and dW2 are independent, dX and dW1|dW3 always are, and independent GEMMs may share a

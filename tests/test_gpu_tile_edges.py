@@ -222,3 +222,35 @@ def test_few_rows_with_more_rows_than_the_capacity():
     assert (host(buf.offsets) == np.minimum(fw["offsets"], cap)).all()
     for name, got in (("h1", buf.h1), ("h3", buf.h3), ("o", buf.o)):
         assert got.shape[0] == cap and rel_err(host(got), fw[name][:cap]) < TOL["bf16"], name
+
+
+# 128x128 tiles: all of a short GEMM; the rest of one whose 256x256 tiles fill rounds of the chip, cut inside an expert; one k-tile,
+# an odd number of them, widths that are no multiples of either tile, 1 to 129 rows in the last row tile, empty experts
+@pytest.mark.parametrize("d,f,rows", [(64, 192, [129, 0, 128, 1, 65]), (192, 64, [300, 257, 33]), (320, 448, [140] * 9),
+                                      (512, 1472, [3000, 1700, 900, 130, 129, 128, 127, 1]), (1088, 512, [5000, 0, 1400, 290, 2])])
+def test_bf16_gemms_that_end_in_quarter_tiles(d, f, rows):
+    print(f"case quarters-{d}-{f}-{rows[:4]}", flush=True)
+    e_cnt, R = len(rows), sum(rows)
+    g = torch.Generator(device="cuda").manual_seed(d + f + R)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda", dtype=torch.bfloat16)  # noqa: E731
+    cap = max(R, 129 * e_cnt)                      # above every bound of the kernel for few rows
+    xp, d_o, w1, w3, w2 = randn(cap, d), randn(cap, d), randn(e_cnt, d, f) * d ** -0.5, randn(e_cnt, d, f) * d ** -0.5, randn(e_cnt, f, d) * f ** -0.5
+    h1, h3, a, o, dxp = (torch.full((cap, n), float("nan"), device="cuda", dtype=torch.bfloat16) for n in (f, f, f, d, d))
+    dw1, dw3, dw2 = (torch.full_like(w, float("nan")) for w in (w1, w3, w2))
+    offsets = torch.tensor([0] + rows, device="cuda").cumsum(0).to(torch.int32)
+    for keep_a in (a, None):                       # without the kept activation dA is a launch of its own
+        wsf, wsb = (torch.empty(B.moe_workspace_bytes(which, B.MOE_BF16, R, 1, d, f, e_cnt, cap), dtype=torch.uint8, device="cuda")
+                    for which in (B.WS_EXPERT_FWD, B.WS_EXPERT_BWD))
+        B.moe_expert_fwd(xp, offsets, w1, w3, w2, h1, h3, o, wsf, a=keep_a)
+        B.moe_expert_bwd(xp, h1, h3, d_o, offsets, w1, w3, w2, dxp, dw1, dw3, dw2, False, wsb, a=keep_a)
+        off = np.array([0] + rows).cumsum()
+        args = [host(t) for t in (w1, w3, w2)]
+        rh1, rh3, _, ro = O.expert_fwd(host(xp[:R]), off, *args)
+        rdxp, rdw1, rdw3, rdw2 = O.expert_bwd(host(xp[:R]), rh1, rh3, host(d_o[:R]), off, *args)
+        for name, got, ref in (("h1", h1, rh1), ("h3", h3, rh3), ("o", o, ro), ("dxp", dxp, rdxp)):
+            assert torch.isnan(got[R:]).all() and rel_err(host(got[:R]), ref) < TOL["bf16"], name
+        for name, got, ref in (("dw1", dw1, rdw1), ("dw3", dw3, rdw3), ("dw2", dw2, rdw2)):
+            for e in range(e_cnt):
+                assert rel_err(host(got[e]), ref[e]) < TOL["bf16"], (name, e)
+        for t in (h1, h3, o, dxp, dw1, dw3, dw2):
+            t.fill_(float("nan"))
