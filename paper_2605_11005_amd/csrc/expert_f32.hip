@@ -1,4 +1,5 @@
-// fp32 expert FFNs on the fp32 matrix instruction (v_mfma_f32_32x32x2_f32: fp32 products and sums).  The bf16 path is in expert_bf16.hip.
+// fp32 expert FFNs on the matrix cores: every operand as three bf16 terms, whose products are summed in fp32.  The bf16 path is in
+// expert_bf16.hip.
 //
 // One kernel template covers the six GEMM shapes of the layer, with the activation in the epilogue:
 //   UP     h1|h3 = xp [W1|W3]   ragged M, weights n-contiguous, two outputs of one tile -> a = silu(h1) h3
@@ -8,13 +9,18 @@
 //   WG     dW2   = a^T d_o      ragged K (the expert's rows)
 //   WGD    dW1|dW3 = xp^T [dH1|dH3]      ragged K, two outputs of one tile
 //
-// What bounds it: the fp32 matrix rate is 256 FLOP per cycle and CU, twice what plain vector FMAs reach (packed fp32
-// FMAs are not used), and at the sizes of this path (a few hundred rows per expert) the number of tiles per CU and what a
-// tile costs besides its k loop.  Hence a small tile, 64x64 by four wavefronts of 32x32 each, two blocks or more per CU,
-// and two k-tiles of 32 on their way in registers while a third is multiplied (two LDS buffers, one barrier per k-tile).
-// Measured at 3000 rows over 16 experts, d = 520, f = 776 (4.8 GFLOP for the pair of up projections): 77 us, the matrix
-// pipes busy 60 % of the time a CU has work; as two products and an element-wise pass on vector FMAs it took 304 us.
-// Tiles of 32x64 by two wavefronts leave fewer empty rows and took 99 us.
+// The fp32 matrix instruction does 256 FLOP per cycle and CU, the bf16 one sixteen times that, so six bf16 products take 3/8 of
+// the time.  Three terms hold all 24 bits of a number, the products that are left out are below 2^-26 of the whole, and sixteen
+// products are added per rounding instead of two: against 64 bits the outputs are off by half of what the fp32 instruction
+// gave (1.3e-7 for 2.9e-7 for h1 at d = 520, 3.3e-7 for 6.7e-7 for the worst gradient; twelve shapes, none of them further off).
+//
+// What bounds it now, all near 1000 cycles per k-tile of a dual tile: the operands' way to the CU (24 KB), LDS (36 KB written,
+// 114 KB read), splitting the operands (about 150 vector instructions) and the matrix pipe (768).  Only other blocks' waves fill
+// the gaps, hence a small tile, 64x64 by four wavefronts of 32x32 each, one LDS buffer and registers for three (dual) or four
+// blocks per CU, and two k-tiles of 32 on their way in registers while a third is multiplied.  3000 rows over 16 experts, d = 520,
+// f = 776, forward and backward: 106 + 215 us with the fp32 instruction; 87 + 176 with two LDS buffers and two blocks per CU; 79
+// + 160 as it is.  Splitting between the matrix instructions of one wavefront takes more registers and 104 + 181; tiles of
+// 128x64 95 + 199 (better only for a thousand rows and more per expert: 145 for 176 at 3000, d = f = 1024).
 #include "common.h"
 #include "kernels.h"
 
@@ -25,7 +31,7 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 enum { UP, DOWN, DA, DX, WG, WGD };
 
-// A matrix instruction contracts two values of k, one per half of the wavefront.  Which two is free as long as both
+// An fp32 matrix instruction contracts two values of k, one per half of the wavefront.  Which two is free as long as both
 // operands agree: in groups of eight steps the lower half takes k = 0..7 and the upper one k = 8..15 of a group of 16, so
 // that a lane of a k-contiguous operand reads consecutive words (16 bytes serve four steps).
 // Pitches: [64 rows][k] at 36 words -- 16 lanes reading 16 bytes each hit 64 banks; [k][64 columns] at 68 -- rows eight
@@ -39,9 +45,48 @@ __device__ __forceinline__ float4 keep(float4 v, bool in) {
   return make_float4(in ? v.x : 0.f, in ? v.y : 0.f, in ? v.z : 0.f, in ? v.w : 0.f);
 }
 
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+// x = h + m + l in bf16, each the rounded rest of the ones before it (what is left over is below 2^-26 of x)
+struct Split4 {
+  uint2 h, m, l;
+  __device__ __forceinline__ explicit Split4(float4 v) {
+    h = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
+    v.x -= bf16lo(h.x); v.y -= bf16hi(h.x); v.z -= bf16lo(h.y); v.w -= bf16hi(h.y);
+    m = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
+    v.x -= bf16lo(m.x); v.y -= bf16hi(m.x); v.z -= bf16lo(m.y); v.w -= bf16hi(m.y);
+    l = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
+  }
+};
+// The three terms of an operand's k-tile lie one behind the other, 4 KB each.
+constexpr int PLANE_BYTES = 64 * TK * 2;
+__device__ __forceinline__ void store_planes(char* s, int off, float4 v) {
+  const Split4 t(v);
+  *reinterpret_cast<uint2*>(s + off) = t.h;
+  *reinterpret_cast<uint2*>(s + PLANE_BYTES + off) = t.m;
+  *reinterpret_cast<uint2*>(s + 2 * PLANE_BYTES + off) = t.l;
+}
+
 // k-contiguous operand: rows [0, rows) of a matrix with leading dimension ld; k in [0, K), K % 4 == 0
 struct OperKC {
   static constexpr int WORDS = 64 * PITCH_KC;
+  // plane: [64 rows][4 chunks of 8 k], chunk' = chunk ^ ((row>>2)&3): 16 lanes reading 16 bytes each hit 64 banks
+  __device__ __forceinline__ void store_split(const float4* v, char* s, int tid) const {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int idx = tid + NT * i, r = idx >> 3, q = idx & 7;
+      store_planes(s, r * 64 + (((q >> 1) ^ ((r >> 2) & 3)) << 4) + (q & 1) * 8, v[i]);
+    }
+  }
+  __device__ __forceinline__ void mask(float4* v, int k0, int tid) const {       // zeros past the end of the contraction
+#pragma unroll
+    for (int i = 0; i < 2; ++i) v[i] = keep(v[i], k0 + 4 * ((tid + NT * i) & 7) < K);
+  }
+  // pos0: first of the wavefront's 32 rows or columns; k-step t of 16
+  static __device__ __forceinline__ bf16x8 split_frag(const char* plane, int pos0, int lane, int t) {
+    const int r = pos0 + (lane & 31);
+    return *reinterpret_cast<const bf16x8*>(plane + r * 64 + (((2 * t + (lane >> 5)) ^ ((r >> 2) & 3)) << 4));
+  }
   const float* base;
   long ld;
   int rows, K;
@@ -73,6 +118,26 @@ struct OperKC {
 // operand whose rows or columns are contiguous: base points at k = 0, tile column 0; cols columns are valid (cols % 4 == 0)
 struct OperMN {
   static constexpr int WORDS = TK * PITCH_MN;
+  // plane: [32 k][8 chunks of 8 columns], chunk' = chunk ^ (4*((k>>1)&1)), read by the transposing LDS reads
+  __device__ __forceinline__ void store_split(const float4* v, char* s, int tid) const {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int idx = tid + NT * i, k = idx >> 4, c = idx & 15;
+      store_planes(s, k * 128 + (((c >> 1) ^ (4 * ((k >> 1) & 1))) << 4) + (c & 1) * 8, v[i]);
+    }
+  }
+  __device__ __forceinline__ void mask(float4* v, int k0, int tid) const {
+#pragma unroll
+    for (int i = 0; i < 2; ++i) v[i] = keep(v[i], k0 + ((tid + NT * i) >> 4) < K);
+  }
+  static __device__ __forceinline__ bf16x8 split_frag(const char* plane, int pos0, int lane, int t) {
+    const int i = lane & 15, g = lane >> 4;
+    const int k = 8 * (g >> 1) + (i >> 2), n = pos0 + 16 * (g & 1) + 4 * (i & 3);
+    const char* p = plane + t * 2048 + k * 128 + (((n >> 3) ^ (4 * ((k >> 1) & 1))) << 4) + ((n & 4) << 1);
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)p);
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(p + 512));
+    return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+  }
   const float* base;
   long ld;
   int cols, K;
@@ -115,13 +180,16 @@ struct Args {
 // 1-D grid over the tiles: ragged_tile's list for the ragged-M shapes, the same with a fixed number of row tiles per
 // expert for the ragged-K ones.
 template <int MODE>
-__global__ __launch_bounds__(NT) void gemm_f32(Args p) {
+__global__ __launch_bounds__(NT, MODE == UP || MODE == WGD ? 3 : 4) void gemm_f32(Args p) {
   constexpr bool RAGGED_K = MODE == WG || MODE == WGD;
   constexpr bool DUAL = MODE == UP || MODE == WGD;
   constexpr int NB = DUAL ? 2 : 1;
   typedef typename Pick<RAGGED_K, OperMN, OperKC>::type OperA;
   typedef typename Pick<MODE == DA || MODE == DX, OperKC, OperMN>::type OperB;
-  __shared__ __align__(16) float lds[2][OperA::WORDS + NB * OperB::WORDS];
+  // one k-tile: the three bf16 terms of each operand, or the operands themselves
+  constexpr int SPLIT_BYTES = (1 + NB) * 3 * PLANE_BYTES, PLAIN_BYTES = (OperA::WORDS + NB * OperB::WORDS) * 4;
+  constexpr int BUFFER = SPLIT_BYTES > PLAIN_BYTES ? SPLIT_BYTES : PLAIN_BYTES;
+  __shared__ __align__(16) char lds[BUFFER];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -165,74 +233,126 @@ __global__ __launch_bounds__(NT) void gemm_f32(Args p) {
       }
     }
   };
-  // two chains of sums per output (even and odd steps), added at the end: half as many roundings in a row, and
-  // consecutive matrix instructions do not wait for each other
-  f32x16 acc[NB][2];
-#pragma unroll
-  for (int i = 0; i < NB; ++i)
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[i][0][r] = acc[i][1][r] = 0.f;
+  f32x16 acc[NB][2];         // two sums per output, added at the end
 
   const int wm = wave >> 1, wn = wave & 1;
   const int a_pos = wm * 32 + (lane & 31), b_pos = wn * 32 + (lane & 31), up = lane >> 5;
   const int nk1 = (K + TK - 1) / TK, nk = MODE == DX ? 2 * nk1 : nk1;
-  // two k-tiles travel in registers while one is multiplied
-  float4 va[2][2], vb[2][NB][2];
-  const auto first_k = [&](int kt) { return (MODE == DX && kt >= nk1 ? kt - nk1 : kt) * TK; };
-  auto fetch = [&](int kt, auto set) {
-    constexpr int S = decltype(set)::value;
-    if (kt > nk - 1) kt = nk - 1;                // (surplus loads at the end, never multiplied)
-    if (MODE == DX && kt == nk1) setup(1);       // the second half of the k-tiles is the second segment
-    const int k0 = first_k(kt);
-    a.load(va[S], k0, tid);
-#pragma unroll
-    for (int i = 0; i < NB; ++i) b[i].load(vb[S][i], k0, tid);
-  };
-  auto publish = [&](int kt, auto set) {         // k-tiles of set S live in LDS buffer S
-    constexpr int S = decltype(set)::value;
-    a.store(va[S], lds[S], first_k(kt), tid);
-#pragma unroll
-    for (int i = 0; i < NB; ++i) b[i].store(vb[S][i], lds[S] + OperA::WORDS + i * OperB::WORDS, first_k(kt), tid);
-  };
   const bool live = wm * 32 < row_end - row0;    // a wavefront without valid rows only moves data
-  auto multiply = [&](auto set) {
-    constexpr int S = decltype(set)::value;
-    if (!live) return;
-    float fa[2][HALF], fb[2][NB][HALF];
-    auto read = [&](int h) {
-      OperA::frags(fa[h], lds[S], a_pos, up, h);
+  // SPLIT: on the bf16 matrix instruction, the operands as three terms each.  Six products: h h in one sum, h m, m h, h l, l h and
+  // m m in the other; the three left out are below 2^-26 of the whole.  Else: on the fp32 matrix instruction, even and odd steps
+  // in the two sums.
+  auto sums = [&](auto split_tag) {
+    constexpr bool SPLIT = decltype(split_tag)::value != 0;
 #pragma unroll
-      for (int i = 0; i < NB; ++i) OperB::frags(fb[h][i], lds[S] + OperA::WORDS + i * OperB::WORDS, b_pos, up, h);
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][0][r] = acc[i][1][r] = 0.f;
+    // two k-tiles travel in registers while one is multiplied
+    float4 va[2][2], vb[2][NB][2];
+    const auto first_k = [&](int kt) { return (MODE == DX && kt >= nk1 ? kt - nk1 : kt) * TK; };
+    auto fetch = [&](int kt, auto set) {
+      constexpr int S = decltype(set)::value;
+      if (kt > nk - 1) kt = nk - 1;                // (surplus loads at the end, never multiplied)
+      if (MODE == DX && kt == nk1) setup(1);       // the second half of the k-tiles is the second segment
+      const int k0 = first_k(kt);
+      a.load(va[S], k0, tid);
+#pragma unroll
+      for (int i = 0; i < NB; ++i) b[i].load(vb[S][i], k0, tid);
     };
-    read(0);
-    read(1);
+    auto publish = [&](int kt, auto set) {
+      constexpr int S = decltype(set)::value;
+      if constexpr (SPLIT) {
+        if (first_k(kt) + TK > K) {
+          a.mask(va[S], first_k(kt), tid);
 #pragma unroll
-    for (int h = 0; h < 2; ++h)
+          for (int i = 0; i < NB; ++i) b[i].mask(vb[S][i], first_k(kt), tid);
+        }
+        a.store_split(va[S], lds, tid);
 #pragma unroll
-      for (int q = 0; q < HALF; ++q)
+        for (int i = 0; i < NB; ++i) b[i].store_split(vb[S][i], lds + (1 + i) * 3 * PLANE_BYTES, tid);
+      } else {
+        float* buf = reinterpret_cast<float*>(lds);
+        a.store(va[S], buf, first_k(kt), tid);
 #pragma unroll
-        for (int i = 0; i < NB; ++i)
-          acc[i][q & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[h][q], fb[h][i][q], acc[i][q & 1], 0, 0, 0);
+        for (int i = 0; i < NB; ++i) b[i].store(vb[S][i], buf + OperA::WORDS + i * OperB::WORDS, first_k(kt), tid);
+      }
+    };
+    auto multiply = [&]() {
+      if (!live) return;
+      if constexpr (SPLIT) {
+#pragma unroll
+        for (int t = 0; t < TK / 16; ++t) {
+          bf16x8 fa[3], fb[NB][3];
+#pragma unroll
+          for (int q = 0; q < 3; ++q) {
+            fa[q] = OperA::split_frag(lds + q * PLANE_BYTES, wm * 32, lane, t);
+#pragma unroll
+            for (int i = 0; i < NB; ++i) fb[i][q] = OperB::split_frag(lds + ((1 + i) * 3 + q) * PLANE_BYTES, wn * 32, lane, t);
+          }
+          const auto mfma = [&](int i, int c, int x, int y) { acc[i][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[x], fb[i][y], acc[i][c], 0, 0, 0); };
+          // consecutive instructions add to different sums
+#pragma unroll
+          for (int i = 0; i < NB; ++i) { mfma(i, 1, 1, 1); mfma(i, 0, 0, 0); }
+#pragma unroll
+          for (int i = 0; i < NB; ++i) mfma(i, 1, 0, 2);
+#pragma unroll
+          for (int i = 0; i < NB; ++i) mfma(i, 1, 2, 0);
+#pragma unroll
+          for (int i = 0; i < NB; ++i) mfma(i, 1, 0, 1);
+#pragma unroll
+          for (int i = 0; i < NB; ++i) mfma(i, 1, 1, 0);
+        }
+      } else {
+        const float* buf = reinterpret_cast<const float*>(lds);
+        float fa[2][HALF], fb[2][NB][HALF];
+        auto read = [&](int h) {
+          OperA::frags(fa[h], buf, a_pos, up, h);
+#pragma unroll
+          for (int i = 0; i < NB; ++i) OperB::frags(fb[h][i], buf + OperA::WORDS + i * OperB::WORDS, b_pos, up, h);
+        };
+        read(0);
+        read(1);
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+#pragma unroll
+          for (int q = 0; q < HALF; ++q)
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+              acc[i][q & 1] = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[h][q], fb[h][i][q], acc[i][q & 1], 0, 0, 0);
+      }
+    };
+    setup(0);
+    if (nk > 0) {
+      fetch(0, Int<0>{});
+      fetch(1, Int<1>{});
+    }
+    // published, multiplied, and the buffer is free again
+    auto step = [&](int kt, auto set) {
+      publish(kt, set);
+      __syncthreads();
+      fetch(kt + 2, set);
+      multiply();
+      __syncthreads();
+    };
+    for (int kt = 0; kt < nk; kt += 2) {
+      step(kt, Int<0>{});
+      if (kt + 1 < nk) step(kt + 1, Int<1>{});
+    }
   };
-  setup(0);
-  if (nk > 0) {
-    fetch(0, Int<0>{});
-    fetch(1, Int<1>{});
-    publish(0, Int<0>{});
-  }
-  __syncthreads();
-  // LDS buffer 1 is written while buffer 0 is multiplied and the other way round; the barrier ends both
-  for (int kt = 0; kt + 1 < nk; kt += 2) {
-    fetch(kt + 2, Int<0>{});
-    multiply(Int<0>{});
-    publish(kt + 1, Int<1>{});
-    __syncthreads();
-    fetch(kt + 3, Int<1>{});
-    multiply(Int<1>{});
-    publish(kt + 2, Int<0>{});
-    __syncthreads();
-  }
-  if (nk & 1) multiply(Int<0>{});
+  sums(Int<1>{});
+  // An infinity, or a number beyond bf16's largest, has no such terms: its first one is infinite, the others NaN, and so are all
+  // sums that it enters.  The last terms of numbers below 1e-31 are lost to bf16's smallest ones.  Tiles with such sums are done
+  // again with the operands as they are.
+  bool lost = false;
+#pragma unroll
+  for (int i = 0; i < NB; ++i)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const float v = fabsf(acc[i][0][r] + acc[i][1][r]);
+      lost |= !(v <= 3.402823466e38f) || (v < 1e-20f && v > 0.f);
+    }
+  if (__syncthreads_or(lost)) sums(Int<0>{});
 
   // accumulator element 4g + i of a lane is row 8g + 4*(lane/32) + i, column lane%32 of its wavefront's block
   const int col = col0 + wn * 32 + (lane & 31);

@@ -27,6 +27,32 @@ def test_fp32_experts_at_tile_edges(T, d, f):
         assert rel_err(host(got), 2.0 * ref) < TOL["f32"]
 
 
+# numbers without three bf16 terms (infinities, what lies beyond bf16's largest number, what is close to its smallest) behave as
+# fp32 products do
+@pytest.mark.parametrize("T,d,f", [(70, 68, 132), (1, 36, 64)])
+def test_fp32_experts_with_infinities(T, d, f):
+    print(f"case fp32-inf-{T}-{d}-{f}", flush=True)
+    g = torch.Generator().manual_seed(T)
+    x = torch.randn((T, d), generator=g)
+    w1, w3, w2 = (torch.randn(s, generator=g) * 1e-2 for s in ((d, f), (d, f), (f, d)))
+    x[0, 3], x[T // 2, 35] = float("inf"), 3.4e38
+    dev = lambda t: t.cuda().contiguous()  # noqa: E731
+    h1, h3, o = (torch.empty((T, n), device="cuda") for n in (f, f, d))
+    ws = torch.empty(B.moe_workspace_bytes(B.WS_EXPERT_FWD, B.MOE_F32, T, 1, d, f, 1, T), dtype=torch.uint8, device="cuda")
+    offsets = torch.tensor([0, T], dtype=torch.int32, device="cuda")
+    B.moe_expert_fwd(dev(x), offsets, dev(w1[None]), dev(w3[None]), dev(w2[None]), h1, h3, o, ws)
+    for got, w in ((h1, w1), (h3, w3)):
+        ref, got = x.double() @ w.double(), got.cpu().double()
+        assert torch.equal(torch.isinf(got), torch.isinf(ref)) and not torch.isnan(got).any()
+        assert torch.equal(got[0], ref[0]) or T == 1           # the row of the infinity: its signs
+        assert ((got - ref)[1:].norm(dim=1) <= 1e-5 * ref[1:].norm(dim=1)).all()
+    x = torch.randn((T, d), generator=g) * 1e-33
+    B.moe_expert_fwd(dev(x), offsets, dev(w1[None]), dev(w3[None]), dev(w2[None]), h1, h3, o, ws)
+    for got, w in ((h1, w1), (h3, w3)):        # sums of up to 68 fp32 products
+        ref = x.double() @ w.double()
+        assert float((got.cpu().double() - ref).norm() / ref.norm()) < 68 ** 0.5 * 2.0 ** -24
+
+
 # kernels for few rows: 16, 32 or 64 rows per block, wavefronts without a piece of the contraction (d = 64), columns past the end
 @pytest.mark.parametrize("T,d,f", [(1, 64, 64), (16, 192, 320), (17, 1088, 64), (33, 64, 192), (64, 320, 128), (65, 128, 448), (127, 256, 64)])
 def test_bf16_forward_with_few_rows(T, d, f):
