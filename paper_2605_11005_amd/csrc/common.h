@@ -36,48 +36,61 @@ __device__ __forceinline__ void static_for(F f) {
   f(Int<N - 1>{});
 }
 
-// The tile of workgroup b in a launch whose list of tiles is known on the device only: experts in ascending order, each
-// cut into row tiles of TM rows, each of them into n_cols column tiles (fastest).  Workgroup b runs on XCD b % 8, and every
-// XCD takes a contiguous eighth of the list, so that an expert's weights pass through one or two of the eight L2s instead
-// of all of them.  The grid is the host's bound on the list rounded up to a multiple of eight: false for a surplus
-// workgroup.  Called by whole wavefronts; 64 experts per step.
-template <int TM>
-__device__ __forceinline__ int row_tiles_scan(const int32_t* __restrict__ off, int e_cnt, int e, int lane, int& n) {
-  n = e < e_cnt ? (off[e + 1] - off[e] + TM - 1) / TM : 0;
-  int incl = n;
-#pragma unroll
-  for (int o = 1; o < WAVE; o <<= 1) {
-    const int v = __shfl_up(incl, o, WAVE);
-    if (lane >= o) incl += v;
-  }
-  return incl;
+// inclusive sums over a wavefront, on the DPP network: within rows of 16, then across them
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_add(int v) { return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false); }
+__device__ __forceinline__ int wave_scan(int v) {
+  v = dpp_add<0x111, 0xF>(v);      // row_shr:1, 2, 4, 8
+  v = dpp_add<0x112, 0xF>(v);
+  v = dpp_add<0x114, 0xF>(v);
+  v = dpp_add<0x118, 0xF>(v);
+  v = dpp_add<0x142, 0xA>(v);      // row_bcast:15 into rows 1 and 3
+  return dpp_add<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
 }
+__device__ __forceinline__ int wave_sum(int v) { return __builtin_amdgcn_readlane(wave_scan(v), WAVE - 1); }
+
+// The tiles of a launch whose list is known on the device only: experts in ascending order, each cut into row tiles of TM rows,
+// each of them into n_cols column tiles (fastest).  Workgroup b runs on XCD b % 8, and every XCD takes a contiguous eighth of the
+// list, so that an expert's weights pass through one or two of the eight L2s instead of all of them.  The grid is the host's bound
+// on the list rounded up to a multiple of eight.  Called by whole wavefronts; 64 experts per step.
 template <int TM>
-__device__ __forceinline__ bool ragged_tile(const int32_t* __restrict__ off, int e_cnt, int n_cols, int b, int lane, int& e,
-                                            int& row_tile, int& col_tile) {
-  int n, incl = row_tiles_scan<TM>(off, e_cnt, lane, lane, n);
-  int total = __builtin_amdgcn_readfirstlane(__shfl(incl, WAVE - 1, WAVE));
-  for (int base = WAVE; base < e_cnt; base += WAVE) {
-    int m;
-    total += __builtin_amdgcn_readfirstlane(__shfl(row_tiles_scan<TM>(off, e_cnt, base + lane, lane, m), WAVE - 1, WAVE));
+struct RaggedTiles {
+  const int32_t* off;
+  int e_cnt, lane;
+  int n, incl;         // row tiles of expert `lane`, and of all up to it
+  int total;           // row tiles of all experts
+  __device__ __forceinline__ int scan(int e, int& rows) const {
+    rows = e < e_cnt ? (off[e + 1] - off[e] + TM - 1) / TM : 0;
+    return wave_scan(rows);
   }
-  const int share = (total * n_cols + 7) / 8;
-  const int tile = (b % 8) * share + b / 8;
-  if (b / 8 >= share || tile >= total * n_cols) return false;
-  int t = tile / n_cols;
-  col_tile = tile - t * n_cols;
-  for (int base = 0;; base += WAVE) {          // ends: t < total
-    if (base > 0) incl = row_tiles_scan<TM>(off, e_cnt, base + lane, lane, n);
-    const unsigned long long past = __ballot(incl > t);
-    if (past) {
-      const int who = __builtin_ctzll(past);
-      row_tile = __builtin_amdgcn_readfirstlane(t - __shfl(incl - n, who, WAVE));
-      e = base + who;
-      return true;
+  __device__ __forceinline__ RaggedTiles(const int32_t* __restrict__ off_, int e_cnt_, int lane_) : off(off_), e_cnt(e_cnt_), lane(lane_) {
+    incl = scan(lane, n);
+    total = __builtin_amdgcn_readlane(incl, WAVE - 1);
+    for (int base = WAVE; base < e_cnt; base += WAVE) {
+      int m;
+      total += __builtin_amdgcn_readlane(scan(base + lane, m), WAVE - 1);
     }
-    t = __builtin_amdgcn_readfirstlane(t - __shfl(incl, WAVE - 1, WAVE));
   }
-}
+  // the tile of workgroup b; false for a surplus one
+  __device__ __forceinline__ bool tile(int n_cols, int b, int& e, int& row_tile, int& col_tile) const {
+    const int share = (total * n_cols + 7) / 8;
+    const int at = (b % 8) * share + b / 8;
+    if (b / 8 >= share || at >= total * n_cols) return false;
+    int t = at / n_cols, rows = n, up_to = incl;
+    col_tile = at - t * n_cols;
+    for (int base = 0;; base += WAVE) {          // ends: t < total
+      if (base > 0) up_to = scan(base + lane, rows);
+      const unsigned long long past = __ballot(up_to > t);
+      if (past) {
+        const int who = __builtin_ctzll(past);
+        row_tile = t - __builtin_amdgcn_readlane(up_to - rows, who);
+        e = base + who;
+        return true;
+      }
+      t -= __builtin_amdgcn_readlane(up_to, WAVE - 1);
+    }
+  }
+};
 
 // logistic function with the hardware exp2 and reciprocal (about 1 ulp each; used by the bf16
 // epilogues, whose results are rounded to 8 bits of mantissa)

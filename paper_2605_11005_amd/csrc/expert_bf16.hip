@@ -298,19 +298,6 @@ __device__ __forceinline__ int take_ticket(int32_t* counters, int n_queues, int&
   }
 }
 
-// inclusive sums over a wavefront, on the DPP network: within rows of 16, then across them
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int dpp_add(int v) { return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false); }
-__device__ __forceinline__ int wave_scan(int v) {
-  v = dpp_add<0x111, 0xF>(v);      // row_shr:1, 2, 4, 8
-  v = dpp_add<0x112, 0xF>(v);
-  v = dpp_add<0x114, 0xF>(v);
-  v = dpp_add<0x118, 0xF>(v);
-  v = dpp_add<0x142, 0xA>(v);      // row_bcast:15 into rows 1 and 3
-  return dpp_add<0x143, 0xC>(v);   // row_bcast:31 into rows 2 and 3
-}
-__device__ __forceinline__ int wave_sum(int v) { return __builtin_amdgcn_readlane(wave_scan(v), WAVE - 1); }
-
 // Time in us until n_big 256x256 tiles and then n_quarter quarter tiles are done.  active_big, active_quarter: experts whose
 // weights either kind reads (one with both is read twice); rows: of all experts, most: of the heaviest.  A quarter tile moves half
 // of a 256x256 tile's bytes to the CU for a quarter of its work, and both are bound by that path (about 70 GB/s per CU where the
@@ -1470,7 +1457,8 @@ __global__ __launch_bounds__(NT, 1) void gg_or_few(GArgs p, int d, int f) {
     SArgs q = {};
     q.A = p.A0; q.lda = p.lda; q.B0 = p.B0; q.B1 = p.B1; q.ldb = p.ldb; q.b_es = p.b_es;
     q.C0 = p.C0; q.C1 = p.C1; q.C2 = p.C2; q.ldc = p.ldc; q.off = p.off; q.e_cnt = p.e_cnt; q.N = p.N; q.K = p.K;
-    for (int b = blockIdx.x; few_rows_tile<MODE == UP>(q, reinterpret_cast<u32x4*>(smem), b); b += gridDim.x) {}
+    const RaggedTiles<ROWS> list(q.off, q.e_cnt, threadIdx.x & 63);
+    for (int b = blockIdx.x; few_rows_tile<MODE == UP, NW_TILES>(q, list, reinterpret_cast<u32x4*>(smem), b); b += gridDim.x) {}
     return;
   }
   gg_body<MODE>(p);
@@ -1577,7 +1565,7 @@ int launch_pair(const GArgs& a, const GArgs& b, int prof_id, hipStream_t s) {
 
 template <int MODE>
 int launch_gg_or_few(const GArgs& a, int d, int f, hipStream_t s) {
-  static_assert(FEW_ROWS_PLACES * 16 <= SMEM_BYTES && NW_EXPERT * WAVE == NT, "one block serves both");
+  static_assert(FEW_ROWS_PLACES<NW_TILES> * 16 <= SMEM_BYTES && NW_TILES * WAVE == NT, "one block serves both");
   static bool attr_set[64] = {};
   int dev = 0;
   if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return MOE_EHIP;

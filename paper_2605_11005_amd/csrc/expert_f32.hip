@@ -177,7 +177,7 @@ struct Args {
   int e_cnt, beta;
 };
 
-// 1-D grid over the tiles: ragged_tile's list for the ragged-M shapes, the same with a fixed number of row tiles per
+// 1-D grid over the tiles: RaggedTiles' list for the ragged-M shapes, the same with a fixed number of row tiles per
 // expert for the ragged-K ones.
 template <int MODE>
 __global__ __launch_bounds__(NT, MODE == UP || MODE == WGD ? 3 : 4) void gemm_f32(Args p) {
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(NT, MODE == UP || MODE == WGD ? 3 : 4) void gemm_f3
     row_end = p.M;
     K = p.off[e + 1] - p.off[e];
   } else {
-    if (!ragged_tile<TM>(p.off, p.e_cnt, n_tiles, blockIdx.x, lane, e, mt, nt)) return;
+    if (!RaggedTiles<TM>(p.off, p.e_cnt, lane).tile(n_tiles, blockIdx.x, e, mt, nt)) return;
     row0 = p.off[e] + mt * TM;
     row_end = p.off[e + 1];
     K = p.K;

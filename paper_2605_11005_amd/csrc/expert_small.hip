@@ -237,10 +237,20 @@ __global__ __launch_bounds__(NW_ROUTER * WAVE) void narrow_router(SArgs p) {
   *reinterpret_cast<f32x4*>(p.F + (size_t)row * E + col) = v[0];
 }
 
+// A CU alone reads 50 to 85 GB/s however many loads are on their way, so tiles for at most a quarter of the CUs (p.range) are
+// halved: two wavefronts with 64 columns (UP: 32 of either matrix) each, the other two leave.  Beyond that the halves cost: they
+// read 64 bytes of a row (UP) and more blocks read the same rows.  Whole / halved tiles, us: UP, d = 4096, f = 1536, 2 experts
+// with rows (48 tiles) 28 / 23, 10 experts 49 / 67; d = f = 2880, 1 expert 18 / 16, 12 experts 59 / 73; d = 7168, f = 2048, 2
+// experts (64 tiles) 40 / 36; DOWN, d = 4096, f = 14336, 2 experts (64 tiles) 89 / 67; d = 7168, f = 2048, 2 experts (112) 15 / 20.
+constexpr int NW_HALF = NW_TILES / 2;
+template <int MODE> constexpr int TILE_COLS = (MODE == UP ? 16 : 32) * NW_TILES;
 template <int MODE>
-__global__ __launch_bounds__(NW_EXPERT * WAVE) void small_rows(SArgs p) {
-  __shared__ u32x4 lds[FEW_ROWS_PLACES];
-  few_rows_tile<MODE == UP>(p, lds, blockIdx.x);
+__global__ __launch_bounds__(NW_TILES * WAVE) void small_rows(SArgs p) {
+  __shared__ u32x4 lds[FEW_ROWS_PLACES<NW_TILES>];
+  const int n_cols = (p.N + TILE_COLS<MODE> - 1) / TILE_COLS<MODE>;
+  const RaggedTiles<ROWS> list(p.off, p.e_cnt, threadIdx.x & 63);
+  if (list.total * n_cols > p.range) few_rows_tile<MODE == UP, NW_TILES>(p, list, lds, blockIdx.x);
+  else if (threadIdx.x < NW_HALF * WAVE) few_rows_tile<MODE == UP, NW_HALF>(p, list, lds, blockIdx.x);
 }
 
 // grid = (row blocks of 16 * TG, column blocks, ranges of the contraction)
@@ -254,12 +264,14 @@ __global__ __launch_bounds__(NW_ROUTER * WAVE) void small_rows_router(SArgs p) {
 }
 
 template <int MODE>
-int launch_small(const SArgs& p, int cap, int prof_id, hipStream_t s) {
-  const long long cols = MODE == UP ? p.N / 64 : (p.N + COLS - 1) / COLS;
-  const long long blocks = (((long long)cap / ROWS + (cap < p.e_cnt ? cap : p.e_cnt)) * cols + 7) / 8 * 8;
+int launch_small(SArgs p, int cap, int prof_id, hipStream_t s) {
+  p.range = device_cu_count() / 4;
+  const long long bound = ((long long)cap / ROWS + (cap < p.e_cnt ? cap : p.e_cnt)) * ((p.N + TILE_COLS<MODE> - 1) / TILE_COLS<MODE>);
+  const long long halves = 2 * (bound < p.range ? bound : p.range);
+  const long long blocks = ((bound > halves ? bound : halves) + 7) / 8 * 8;
   if (blocks >= (1ll << 31)) return MOE_EUNSUPPORTED;
   ProfScope prof(prof_id, s);
-  hipLaunchKernelGGL(small_rows<MODE>, dim3((unsigned)blocks), dim3(NW_EXPERT * WAVE), 0, s, p);
+  hipLaunchKernelGGL(small_rows<MODE>, dim3((unsigned)blocks), dim3(NW_TILES * WAVE), 0, s, p);
   HIP_CHECK_LAUNCH();
   return MOE_OK;
 }

@@ -13,7 +13,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int COLS = 128;                 // columns of a block (UP: 64 of W1 and the same 64 of W3)
 constexpr int ROWS = 64;                  // rows of an expert block at most
 constexpr int KP = 32;                    // depth of a piece
-constexpr int NW_EXPERT = 4;               // wavefronts per block
+constexpr int NW_TILES = 4;                // wavefronts of a block that also runs the 256x256 tiles
 
 struct SArgs {
   const bf16_t* A; long lda;
@@ -26,7 +26,7 @@ struct SArgs {
   long xstep;                             // elements from a row's piece to its next piece
   int n_experts;                          // RW: rows are (plane, expert), expert fastest
   int range;                              // RL, RW: pieces of the contraction per range (grid z); range z's sums go to F + z * rows * N
-                                          // narrow_router: rows per block
+                                          // narrow_router: rows per block; UP, DOWN: most tiles that are halved
 };
 
 // Loads go through a buffer descriptor: a wave-uniform base and a 32-bit byte offset per lane (64-bit addresses per lane limit
@@ -64,9 +64,10 @@ struct Piece {
 // a store (columns 8 apart, in UP over two chunks) on different banks.
 __device__ __forceinline__ int place(int c, int g) { return 16 * (4 * (c >> 4) + g) + ((c & 15) ^ (c >> 4) ^ ((g & 1) << 2)); }
 
-// UP, DOWN: up to 16 * TG rows of one expert against COLS columns.  The wavefronts share the loads, in rounds of 128 k: in
-// DOWN wavefront w fetches 32 k of the 128 columns, in UP 64 k of the 64 columns of matrix w % 2.  It hands the operands over
-// through LDS, with 32 k of the rows.  Each wavefront then multiplies its own 32 columns (UP: 16 of either matrix) through the
+// UP, DOWN: up to 16 * TG rows of one expert against 32 * NW columns (UP: 16 * NW of either matrix).  The NW wavefronts share the
+// loads, in rounds of 128 k: with four of them wavefront w fetches in DOWN 32 k of the 128 columns, in UP 64 k of the 64 columns of
+// matrix w % 2; with two it is 64 k and 128 k of half as many columns.  It hands the operands over through LDS, with its share of
+// the rows' k.  Each wavefront then multiplies its own 32 columns (UP: 16 of either matrix) through the
 // round's steps in ascending order, so that an output is one chain of sums over ascending k.  It is the chain of the 256x256
 // tiles: a 16x16x32 instruction gives the bits of two 32x32x16 ones, in either order of the operands.  The forward's results
 // therefore do not depend on which of the two kernels a call takes, which the caller's capacity decides.
@@ -76,44 +77,57 @@ __device__ __forceinline__ int place(int c, int g) { return 16 * (4 * (c >> 4) +
 // beside the LDS reads of the multiplication, 38 as it is now: one block per CU (96 KB of LDS see to it) with two rounds on
 // their way.  More are no faster: 32 experts of 1 row, d = 7168, f = 2048, take 489 / 493 / 497 us with two / three / four
 // rounds, 513 us with three and two blocks per CU.
-constexpr int STEP_PLACES = KP * COLS / 8, WEIGHT_PLACES = NW_EXPERT * STEP_PLACES, ROW_PLACES = NW_EXPERT * ROWS / 16 * WAVE;
-template <bool DUAL, int TG>
+constexpr int STEPS = 4;                   // of 32 k, per round
+template <int NW> constexpr int STEP_PLACES = KP * 32 * NW / 8;
+template <int NW> constexpr int WEIGHT_PLACES = STEPS * STEP_PLACES<NW>;
+constexpr int ROW_PLACES = STEPS * ROWS / 16 * WAVE;
+template <bool DUAL, int TG, int NW>
 __device__ __forceinline__ void expert_tile(const SArgs& p, u32x4* lds, int e, int row0, int row_end, int n0, int tid) {
-  constexpr int NW = NW_EXPERT, DEPTH = 2;
+  constexpr int DEPTH = 2, XS = STEPS / NW;           // XS: steps of the rows per wavefront
+  constexpr int CHUNKS = (DUAL ? 2 : 4) * NW;         // of 8 columns, in a row of a wavefront's piece
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = lane & 15, g = lane >> 4;
   // weights: lane (ci, kg) loads columns 8 ci .. 8 ci + 7 of rows 8 kg .. 8 kg + 7
-  const int ci = DUAL ? lane & 7 : i, kg = DUAL ? lane >> 3 : g;
+  const int ci = lane % CHUNKS, kg = lane / CHUNKS;
+  const int wk0 = DUAL ? (NW == 4 ? wave & 2 : 0) : XS * wave;        // first step of this wavefront's piece in a round
   const bf16_t* b = (DUAL && (wave & 1) ? p.B1 : p.B0) + (size_t)e * p.b_es + n0;
   const bf16_t* xrow = p.A + (size_t)row0 * p.lda;
   // columns and rows past the end repeat the last ones
-  const int woff = 2 * (8 * kg * (int)p.ldb + min(8 * ci, p.N - n0 - 8));
+  const int wcol = 2 * min(8 * ci, p.N - n0 - 8);
   int xoff[TG];
 #pragma unroll
   for (int t = 0; t < TG; ++t) xoff[t] = 2 * (min(16 * t + i, row_end - row0 - 1) * (int)p.lda + 8 * g);
-  const int steps = p.K / KP, rounds = (steps + NW - 1) / NW;       // of 32 k; of 128 k
+  const int steps = p.K / KP, rounds = (steps + STEPS - 1) / STEPS;       // of 32 k; of 128 k
   Piece w[DEPTH];
-  u32x4 x[DEPTH][TG];
+  u32x4 x[DEPTH][XS][TG];
   auto load = [&](auto slot, int round, auto half) {
     constexpr int S = decltype(slot)::value, H = decltype(half)::value;
-    const int wk = NW * round + (DUAL ? wave & 2 : wave), xk = NW * round + wave;      // first step; steps is even: two or none
+    const int wk = STEPS * round + wk0;           // (steps is even: of a round there are four, two or none)
+    // rows past the contraction repeat its last ones (their steps are not multiplied)
+    const int woff = min(8 * kg, max(8, KP * (steps - wk)) - 8) * 2 * (int)p.ldb + wcol;
     w[S].template load<4 * H, 4 * H + 4>(b + (wk < steps ? (long)wk * KP : 0) * p.ldb, wk < steps, 2 * (int)p.ldb, woff);
     if (H) {
-      const __amdgpu_buffer_rsrc_t dx = descriptor(xrow + (xk < steps ? xk * KP : 0), xk < steps);
 #pragma unroll
-      for (int t = 0; t < TG; ++t) x[S][t] = __builtin_amdgcn_raw_buffer_load_b128(dx, xoff[t], 0, 0);
+      for (int q = 0; q < XS; ++q) {
+        const int xk = STEPS * round + XS * wave + q;
+        const __amdgpu_buffer_rsrc_t dx = descriptor(xrow + (xk < steps ? xk * KP : 0), xk < steps);
+#pragma unroll
+        for (int t = 0; t < TG; ++t) x[S][q][t] = __builtin_amdgcn_raw_buffer_load_b128(dx, xoff[t], 0, 0);
+      }
     }
     __builtin_amdgcn_sched_barrier(0);    // loads stay in order: waiting for one round must not wait for the next
   };
-  u32x4* const xlds = lds + 2 * WEIGHT_PLACES;
+  u32x4* const xlds = lds + 2 * WEIGHT_PLACES<NW>;
   auto publish = [&](auto slot, int round) {
     constexpr int S = decltype(slot)::value;
-    u32x4* buf = lds + (round & 1) * WEIGHT_PLACES + (DUAL ? (wave & 2) + (kg >> 2) : wave) * STEP_PLACES;
+    u32x4* buf = lds + (round & 1) * WEIGHT_PLACES<NW> + (wk0 + (kg >> 2)) * STEP_PLACES<NW>;
 #pragma unroll
-    for (int j = 0; j < 8; ++j)           // (in UP the second matrix's columns are kept 64 further on)
-      buf[place((DUAL ? 64 * (wave & 1) : 0) + 8 * ci + j, kg & 3)] = __builtin_bit_cast(u32x4, w[S].operand(j));
+    for (int j = 0; j < 8; ++j)           // (in UP the second matrix's columns are kept behind the first one's)
+      buf[place((DUAL ? 16 * NW * (wave & 1) : 0) + 8 * ci + j, kg & 3)] = __builtin_bit_cast(u32x4, w[S].operand(j));
 #pragma unroll
-    for (int t = 0; t < TG; ++t) xlds[(round & 1) * ROW_PLACES + (wave * TG + t) * WAVE + lane] = x[S][t];
+    for (int q = 0; q < XS; ++q)
+#pragma unroll
+      for (int t = 0; t < TG; ++t) xlds[(round & 1) * ROW_PLACES + ((XS * wave + q) * TG + t) * WAVE + lane] = x[S][q][t];
     __builtin_amdgcn_sched_barrier(0);
   };
   f32x4 acc[2][TG];
@@ -121,14 +135,14 @@ __device__ __forceinline__ void expert_tile(const SArgs& p, u32x4* lds, int e, i
   for (int c = 0; c < 2; ++c)
 #pragma unroll
     for (int t = 0; t < TG; ++t) acc[c][t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  const int col0 = DUAL ? 16 * wave : 32 * wave, col1 = DUAL ? 64 + col0 : col0 + 16;
+  const int col0 = DUAL ? 16 * wave : 32 * wave, col1 = DUAL ? 16 * NW + col0 : col0 + 16;
   bf16x8 f[2][2], r[2][TG];
   auto read = [&](int round, int q0) {    // operands of steps q0, q0 + 1 of a round
-    const u32x4* buf = lds + (round & 1) * WEIGHT_PLACES;
+    const u32x4* buf = lds + (round & 1) * WEIGHT_PLACES<NW>;
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
-      f[q][0] = __builtin_bit_cast(bf16x8, buf[(q0 + q) * STEP_PLACES + place(col0 + i, g)]);
-      f[q][1] = __builtin_bit_cast(bf16x8, buf[(q0 + q) * STEP_PLACES + place(col1 + i, g)]);
+      f[q][0] = __builtin_bit_cast(bf16x8, buf[(q0 + q) * STEP_PLACES<NW> + place(col0 + i, g)]);
+      f[q][1] = __builtin_bit_cast(bf16x8, buf[(q0 + q) * STEP_PLACES<NW> + place(col1 + i, g)]);
 #pragma unroll
       for (int t = 0; t < TG; ++t) r[q][t] = __builtin_bit_cast(bf16x8, xlds[(round & 1) * ROW_PLACES + ((q0 + q) * TG + t) * WAVE + lane]);
     }
@@ -150,7 +164,7 @@ __device__ __forceinline__ void expert_tile(const SArgs& p, u32x4* lds, int e, i
     if (refill) load(next, round + 1 + DEPTH, Int<0>{});
     multiply();
     // the last round has four steps or two, and multiplying the others' zeros could turn a -0 into +0
-    const bool full = steps - NW * round >= NW;
+    const bool full = steps - STEPS * round >= STEPS;
     if (full) read(round, 2);
     if (refill) load(next, round + 1 + DEPTH, Int<1>{});
     if (full) multiply();
@@ -194,18 +208,18 @@ __device__ __forceinline__ void expert_tile(const SArgs& p, u32x4* lds, int e, i
 }
 
 
-// Tile b of a launch over all experts (ragged_tile's list); false: the list is shorter.
-constexpr int FEW_ROWS_PLACES = 2 * (WEIGHT_PLACES + ROW_PLACES);      // LDS, 16 bytes each
-template <bool DUAL>
-__device__ __forceinline__ bool few_rows_tile(const SArgs& p, u32x4* lds, int b) {
-  constexpr int WIDTH = DUAL ? COLS / 2 : COLS;
+// Tile b of a launch over all experts; false: the list is shorter.
+template <int NW> constexpr int FEW_ROWS_PLACES = 2 * (WEIGHT_PLACES<NW> + ROW_PLACES);      // LDS, 16 bytes each
+template <bool DUAL, int NW>
+__device__ __forceinline__ bool few_rows_tile(const SArgs& p, const RaggedTiles<ROWS>& list, u32x4* lds, int b) {
+  constexpr int WIDTH = (DUAL ? 16 : 32) * NW;
   const int tid = threadIdx.x;
   int e, mt, nt;
-  if (!ragged_tile<ROWS>(p.off, p.e_cnt, (p.N + WIDTH - 1) / WIDTH, b, tid & 63, e, mt, nt)) return false;
+  if (!list.tile((p.N + WIDTH - 1) / WIDTH, b, e, mt, nt)) return false;
   const int row0 = p.off[e] + mt * ROWS, row_end = min(p.off[e + 1], row0 + ROWS), rows = row_end - row0;
-  if (rows <= 16) expert_tile<DUAL, 1>(p, lds, e, row0, row_end, nt * WIDTH, tid);
-  else if (rows <= 32) expert_tile<DUAL, 2>(p, lds, e, row0, row_end, nt * WIDTH, tid);
-  else expert_tile<DUAL, 4>(p, lds, e, row0, row_end, nt * WIDTH, tid);
+  if (rows <= 16) expert_tile<DUAL, 1, NW>(p, lds, e, row0, row_end, nt * WIDTH, tid);
+  else if (rows <= 32) expert_tile<DUAL, 2, NW>(p, lds, e, row0, row_end, nt * WIDTH, tid);
+  else expert_tile<DUAL, 4, NW>(p, lds, e, row0, row_end, nt * WIDTH, tid);
   return true;
 }
 

@@ -12,6 +12,8 @@ pytestmark = pytest.mark.gpu
 # of whole rounds; columns past the end of a block of 128; empty experts; more experts than lanes
 @pytest.mark.parametrize("d,f,rows", [(64, 64, [1]), (192, 320, [16, 17]), (1088, 64, [33, 0, 31]), (256, 192, [64, 65, 127]),
                                       (2048, 1408, [0, 3, 40, 0, 17, 1, 100, 70]), (448, 704, [5, 0] * 40), (4096, 1536, [4, 2, 1, 1, 0, 0]),
+                                      # at most 64 tiles, which are halved, and one more; a last round with 2 of its 4 steps
+                                      (2112, 2048, [1, 33]), (2112, 2048, [1, 33, 64]),
                                       # more than 256 MB of weights: with the middle capacity the counts decide, for few rows and for tiles
                                       (2048, 2304, [9, 0, 0, 17, 1, 0, 2, 0, 0, 0]), (2048, 2304, [100, 90, 110, 120, 80, 100, 95, 60, 128, 99])])
 def test_forward_bits_do_not_depend_on_the_capacity(d, f, rows):
