@@ -342,7 +342,8 @@ __global__ __launch_bounds__(NT, MODE == UP || MODE == WGD ? 3 : 4) void gemm_f3
   };
   sums(Int<1>{});
   // An infinity, or a number beyond bf16's largest, has no such terms: its first one is infinite, the others NaN, and so are all
-  // sums that it enters.  The last terms of numbers below 1e-31 are lost to bf16's smallest ones.  Tiles with such sums are done
+  // sums that it enters.  The last terms of numbers below 1e-31 are lost to bf16's smallest ones, by at most 2^-126 each: a sum of K
+  // products of 1e-20 and more keeps its 24 bits beside factors of up to 2^35 / K.  Tiles with smaller sums or lost ones are done
   // again with the operands as they are.
   bool lost = false;
 #pragma unroll
