@@ -17,8 +17,9 @@
 // What bounds it now, all near 1000 cycles per k-tile of a dual tile: the operands' way to the CU (24 KB), LDS (36 KB written,
 // 114 KB read), splitting the operands (about 150 vector instructions) and the matrix pipe (768).  Only other blocks' waves fill
 // the gaps, hence a small tile, 64x64 by four wavefronts of 32x32 each, one LDS buffer and registers for three (dual) or four
-// blocks per CU, and two k-tiles of 32 on their way in registers while a third is multiplied.  3000 rows over 16 experts, d = 520,
-// f = 776, forward and backward: 106 + 215 us with the fp32 instruction; 87 + 176 with two LDS buffers and two blocks per CU; 79
+// blocks per CU (two buffers where two blocks per CU or fewer are all there are: launch()), and two k-tiles of 32 on their way in
+// registers while a third is multiplied.  3000 rows over 16 experts, d = 520, f = 776, forward and backward: 106 + 215 us with the
+// fp32 instruction; 87 + 176 with two LDS buffers and two blocks per CU; 79
 // + 160 as it is.  Splitting between the matrix instructions of one wavefront takes more registers and 104 + 181; tiles of
 // 128x64 95 + 199 (better only for a thousand rows and more per expert: 145 for 176 at 3000, d = f = 1024).
 #include "common.h"
@@ -26,7 +27,7 @@
 
 namespace {
 
-constexpr int TM = 64, TN = 64, TK = 32, NT = 256;
+constexpr int TM = 64, TN = 64, TK = 32, NT = 256, CUS = 256;
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 enum { UP, DOWN, DA, DX, WG, WGD };
@@ -179,8 +180,9 @@ struct Args {
 
 // 1-D grid over the tiles: RaggedTiles' list for the ragged-M shapes, the same with a fixed number of row tiles per
 // expert for the ragged-K ones.
-template <int MODE>
-__global__ __launch_bounds__(NT, MODE == UP || MODE == WGD ? 3 : 4) void gemm_f32(Args p) {
+// BUFS: LDS buffers, two in launches of few blocks (launch()).
+template <int MODE, int BUFS>
+__global__ __launch_bounds__(NT, BUFS == 2 ? 2 : MODE == UP || MODE == WGD ? 3 : 4) void gemm_f32(Args p) {
   constexpr bool RAGGED_K = MODE == WG || MODE == WGD;
   constexpr bool DUAL = MODE == UP || MODE == WGD;
   constexpr int NB = DUAL ? 2 : 1;
@@ -189,7 +191,7 @@ __global__ __launch_bounds__(NT, MODE == UP || MODE == WGD ? 3 : 4) void gemm_f3
   // one k-tile: the three bf16 terms of each operand, or the operands themselves
   constexpr int SPLIT_BYTES = (1 + NB) * 3 * PLANE_BYTES, PLAIN_BYTES = (OperA::WORDS + NB * OperB::WORDS) * 4;
   constexpr int BUFFER = SPLIT_BYTES > PLAIN_BYTES ? SPLIT_BYTES : PLAIN_BYTES;
-  __shared__ __align__(16) char lds[BUFFER];
+  __shared__ __align__(16) char lds[BUFS * BUFFER];
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -262,23 +264,25 @@ __global__ __launch_bounds__(NT, MODE == UP || MODE == WGD ? 3 : 4) void gemm_f3
     };
     auto publish = [&](int kt, auto set) {
       constexpr int S = decltype(set)::value;
+      char* const to = lds + (BUFS == 2 ? S * BUFFER : 0);
       if constexpr (SPLIT) {
         if (first_k(kt) + TK > K) {
           a.mask(va[S], first_k(kt), tid);
 #pragma unroll
           for (int i = 0; i < NB; ++i) b[i].mask(vb[S][i], first_k(kt), tid);
         }
-        a.store_split(va[S], lds, tid);
+        a.store_split(va[S], to, tid);
 #pragma unroll
-        for (int i = 0; i < NB; ++i) b[i].store_split(vb[S][i], lds + (1 + i) * 3 * PLANE_BYTES, tid);
+        for (int i = 0; i < NB; ++i) b[i].store_split(vb[S][i], to + (1 + i) * 3 * PLANE_BYTES, tid);
       } else {
-        float* buf = reinterpret_cast<float*>(lds);
+        float* buf = reinterpret_cast<float*>(to);
         a.store(va[S], buf, first_k(kt), tid);
 #pragma unroll
         for (int i = 0; i < NB; ++i) b[i].store(vb[S][i], buf + OperA::WORDS + i * OperB::WORDS, first_k(kt), tid);
       }
     };
-    auto multiply = [&]() {
+    auto multiply = [&](auto set) {
+      const char* const from = lds + (BUFS == 2 ? decltype(set)::value * BUFFER : 0);
       if (!live) return;
       if constexpr (SPLIT) {
 #pragma unroll
@@ -286,9 +290,9 @@ __global__ __launch_bounds__(NT, MODE == UP || MODE == WGD ? 3 : 4) void gemm_f3
           bf16x8 fa[3], fb[NB][3];
 #pragma unroll
           for (int q = 0; q < 3; ++q) {
-            fa[q] = OperA::split_frag(lds + q * PLANE_BYTES, wm * 32, lane, t);
+            fa[q] = OperA::split_frag(from + q * PLANE_BYTES, wm * 32, lane, t);
 #pragma unroll
-            for (int i = 0; i < NB; ++i) fb[i][q] = OperB::split_frag(lds + ((1 + i) * 3 + q) * PLANE_BYTES, wn * 32, lane, t);
+            for (int i = 0; i < NB; ++i) fb[i][q] = OperB::split_frag(from + ((1 + i) * 3 + q) * PLANE_BYTES, wn * 32, lane, t);
           }
           const auto mfma = [&](int i, int c, int x, int y) { acc[i][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[x], fb[i][y], acc[i][c], 0, 0, 0); };
           // consecutive instructions add to different sums
@@ -304,7 +308,7 @@ __global__ __launch_bounds__(NT, MODE == UP || MODE == WGD ? 3 : 4) void gemm_f3
           for (int i = 0; i < NB; ++i) mfma(i, 1, 1, 0);
         }
       } else {
-        const float* buf = reinterpret_cast<const float*>(lds);
+        const float* buf = reinterpret_cast<const float*>(from);
         float fa[2][HALF], fb[2][NB][HALF];
         auto read = [&](int h) {
           OperA::frags(fa[h], buf, a_pos, up, h);
@@ -327,17 +331,34 @@ __global__ __launch_bounds__(NT, MODE == UP || MODE == WGD ? 3 : 4) void gemm_f3
       fetch(0, Int<0>{});
       fetch(1, Int<1>{});
     }
-    // published, multiplied, and the buffer is free again
-    auto step = [&](int kt, auto set) {
-      publish(kt, set);
+    if constexpr (BUFS == 2) {
+      // one buffer is written while the other is multiplied; the barrier ends both
+      if (nk > 0) publish(0, Int<0>{});
       __syncthreads();
-      fetch(kt + 2, set);
-      multiply();
-      __syncthreads();
-    };
-    for (int kt = 0; kt < nk; kt += 2) {
-      step(kt, Int<0>{});
-      if (kt + 1 < nk) step(kt + 1, Int<1>{});
+      for (int kt = 0; kt + 1 < nk; kt += 2) {
+        fetch(kt + 2, Int<0>{});
+        multiply(Int<0>{});
+        publish(kt + 1, Int<1>{});
+        __syncthreads();
+        fetch(kt + 3, Int<1>{});
+        multiply(Int<1>{});
+        publish(kt + 2, Int<0>{});
+        __syncthreads();
+      }
+      if (nk & 1) multiply(Int<0>{});
+    } else {
+      // published, multiplied, and the buffer is free again
+      auto step = [&](int kt, auto set) {
+        publish(kt, set);
+        __syncthreads();
+        fetch(kt + 2, set);
+        multiply(set);
+        __syncthreads();
+      };
+      for (int kt = 0; kt < nk; kt += 2) {
+        step(kt, Int<0>{});
+        if (kt + 1 < nk) step(kt + 1, Int<1>{});
+      }
     }
   };
   sums(Int<1>{});
@@ -397,7 +418,12 @@ template <int MODE>
 int launch(const Args& p, long long m_tiles, hipStream_t s) {
   const long long blocks = (m_tiles * ((p.N + TN - 1) / TN) + 7) / 8 * 8;
   if (blocks >= (1ll << 31)) return MOE_EUNSUPPORTED;
-  hipLaunchKernelGGL(gemm_f32<MODE>, dim3((unsigned)blocks), dim3(NT), 0, s, p);
+  // Two LDS buffers while at most two blocks share a CU: nothing else fills the gaps there.  The sums and their order are the same.
+  // Training step, us, one buffer / two up to 256 blocks / two up to 512 (T, d, f, experts, k): 100, 256, 512, 8, 2 107 / 99 / 97;
+  // 256, 1024, 512, 8, 1 170 / 152 / 151; 300, 400, 600, 16, 2 146 / 137 / 131; 600, 1000, 1000, 8, 2 300 / 300 / 293.  At 1500, 520,
+  // 776, 16, 2 (800 blocks and more) two buffers for all take 87 + 176 for 79 + 160 in the six GEMMs.
+  const auto kernel = blocks <= 2 * CUS ? gemm_f32<MODE, 2> : gemm_f32<MODE, 1>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(NT), 0, s, p);
   HIP_CHECK_LAUNCH();
   return MOE_OK;
 }

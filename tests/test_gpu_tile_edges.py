@@ -53,6 +53,36 @@ def test_fp32_experts_with_infinities(T, d, f):
         assert float((got.cpu().double() - ref).norm() / ref.norm()) < 68 ** 0.5 * 2.0 ** -24
 
 
+# launches of up to 512 blocks have two LDS buffers, larger ones one: the capacity decides for the forward, dA and dX, the widths for the
+# weight gradients (576 blocks with 16 experts); one k-tile, odd and even numbers of them, empty experts
+@pytest.mark.parametrize("d,f,rows", [(32, 64, [1]), (200, 520, [40, 0, 1, 33, 64, 65, 7, 0, 96, 3, 2, 1, 100, 0, 31, 32]), (100, 36, [70, 0, 33])])
+def test_fp32_experts_with_one_and_two_buffers(d, f, rows):
+    print(f"case fp32-buffers-{d}-{f}", flush=True)
+    e_cnt, R = len(rows), sum(rows)
+    g = torch.Generator().manual_seed(d + f)
+    randn = lambda *shape: torch.randn(shape, generator=g)  # noqa: E731
+    xp, d_o, w1, w3, w2 = randn(R, d), randn(R, d), randn(e_cnt, d, f) * d ** -0.5, randn(e_cnt, d, f) * d ** -0.5, randn(e_cnt, f, d) * f ** -0.5
+    off = np.array([0] + rows).cumsum()
+    args = [t.numpy().astype(np.float64) for t in (w1, w3, w2)]
+    rh1, rh3, _, ro = O.expert_fwd(xp.numpy().astype(np.float64), off, *args)
+    rdxp, rdw1, rdw3, rdw2 = O.expert_bwd(xp.numpy().astype(np.float64), rh1, rh3, d_o.numpy().astype(np.float64), off, *args)
+    offsets, weights, results = torch.tensor(off, dtype=torch.int32, device="cuda"), [w.cuda() for w in (w1, w3, w2)], []
+    for cap in (R, 40000):
+        x, dy = (torch.zeros((cap, d), device="cuda") for _ in range(2))
+        x[:R], dy[:R] = xp.cuda(), d_o.cuda()
+        h1, h3, o, dxp = (torch.zeros((cap, n), device="cuda") for n in (f, f, d, d))
+        dws = [torch.zeros_like(w) for w in weights]
+        wsf, wsb = (torch.empty(B.moe_workspace_bytes(which, B.MOE_F32, R, 1, d, f, e_cnt, cap), dtype=torch.uint8, device="cuda")
+                    for which in (B.WS_EXPERT_FWD, B.WS_EXPERT_BWD))
+        B.moe_expert_fwd(x, offsets, *weights, h1, h3, o, wsf)
+        B.moe_expert_bwd(x, h1, h3, dy, offsets, *weights, dxp, *dws, False, wsb)
+        got = [t[:R] for t in (h1, h3, o, dxp)] + dws
+        for t, ref in zip(got, (rh1, rh3, ro, rdxp, rdw1, rdw3, rdw2)):
+            assert rel_err(host(t), ref) < TOL["f32"]
+        results.append(got)
+    assert all(torch.equal(a, b) for a, b in zip(*results))
+
+
 # kernels for few rows: 16, 32 or 64 rows per block, wavefronts without a piece of the contraction (d = 64), columns past the end
 @pytest.mark.parametrize("T,d,f", [(1, 64, 64), (16, 192, 320), (17, 1088, 64), (33, 64, 192), (64, 320, 128), (65, 128, 448), (127, 256, 64)])
 def test_bf16_forward_with_few_rows(T, d, f):
