@@ -48,10 +48,16 @@ __device__ __forceinline__ float4 keep(float4 v, bool in) {
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-// x = h + m + l in bf16, each the rounded rest of the ones before it (what is left over is below 2^-26 of x)
+// SCALE x = h + m + l in bf16, each the rounded rest of the ones before it.  The scale brings the last bit of fp32's smallest
+// number, 2^-149, among bf16's normal numbers, so that the three hold every x up to 2^96 exactly; products, and with them sums,
+// are SCALE^2 times what they stand for.  Beyond 2^96 the first term is infinite and the second NaN, and so are the sums that it enters.
+// (Without the scale numbers below 2^-109 lost bits and those below 2^-134 everything; it takes 0 to 2 % of a training step: 293 ->
+// 300 us at T = 600, d = f = 1000, 8 experts, k = 2.)
+constexpr float SCALE = 0x1p32f, UNSCALE = 0x1p-64f;
 struct Split4 {
   uint2 h, m, l;
   __device__ __forceinline__ explicit Split4(float4 v) {
+    v.x *= SCALE; v.y *= SCALE; v.z *= SCALE; v.w *= SCALE;
     h = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
     v.x -= bf16lo(h.x); v.y -= bf16hi(h.x); v.z -= bf16lo(h.y); v.w -= bf16hi(h.y);
     m = make_uint2(pack_bf16x2(v.x, v.y), pack_bf16x2(v.z, v.w));
@@ -362,19 +368,18 @@ __global__ __launch_bounds__(NT, BUFS == 2 ? 2 : MODE == UP || MODE == WGD ? 3 :
     }
   };
   sums(Int<1>{});
-  // An infinity, or a number beyond bf16's largest, has no such terms: its first one is infinite, the others NaN, and so are all
-  // sums that it enters.  The last terms of numbers below 1e-31 are lost to bf16's smallest ones, by at most 2^-126 each: a sum of K
-  // products of 1e-20 and more keeps its 24 bits beside factors of up to 2^35 / K.  Tiles with smaller sums or lost ones are done
-  // again with the operands as they are.
+  // Tiles with an infinity, a NaN, a number beyond 2^96 or a sum beyond 2^64 have sums that are no numbers and are done again with
+  // the operands as they are.
+  float scale = UNSCALE;
   bool lost = false;
 #pragma unroll
   for (int i = 0; i < NB; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float v = fabsf(acc[i][0][r] + acc[i][1][r]);
-      lost |= !(v <= 3.402823466e38f) || (v < 1e-20f && v > 0.f);
-    }
-  if (__syncthreads_or(lost)) sums(Int<0>{});
+    for (int r = 0; r < 16; ++r) lost |= !(fabsf(acc[i][0][r] + acc[i][1][r]) <= 3.402823466e38f);
+  if (__syncthreads_or(lost)) {
+    sums(Int<0>{});
+    scale = 1.f;
+  }
 
   // accumulator element 4g + i of a lane is row 8g + 4*(lane/32) + i, column lane%32 of its wavefront's block
   const int col = col0 + wn * 32 + (lane & 31);
@@ -395,8 +400,8 @@ __global__ __launch_bounds__(NT, BUFS == 2 ? 2 : MODE == UP || MODE == WGD ? 3 :
     for (int i = 0; i < 4; ++i) {
       if (r0 + i >= row_end) continue;
       const size_t idx = (size_t)e * p.c_es + (size_t)(r0 + i) * p.ldc + col;
-      const float x = acc[0][0][4 * g + i] + acc[0][1][4 * g + i];
-      const float x3 = acc[NB - 1][0][4 * g + i] + acc[NB - 1][1][4 * g + i];      // second output of a dual tile
+      const float x = (acc[0][0][4 * g + i] + acc[0][1][4 * g + i]) * scale;
+      const float x3 = (acc[NB - 1][0][4 * g + i] + acc[NB - 1][1][4 * g + i]) * scale;      // second output of a dual tile
       if (MODE == UP) {
         if (p.C[0]) { p.C[0][idx] = x; p.C[1][idx] = x3; }
         p.C[2][idx] = (x / (1.0f + expf(-x))) * x3;

@@ -27,8 +27,7 @@ def test_fp32_experts_at_tile_edges(T, d, f):
         assert rel_err(host(got), 2.0 * ref) < TOL["f32"]
 
 
-# numbers without three bf16 terms (infinities, what lies beyond bf16's largest number, what is close to its smallest) behave as
-# fp32 products do
+# numbers without three bf16 terms (infinities, what lies beyond 2^96) behave as fp32 products do, and so do sums of 1e-35
 @pytest.mark.parametrize("T,d,f", [(70, 68, 132), (1, 36, 64)])
 def test_fp32_experts_with_infinities(T, d, f):
     print(f"case fp32-inf-{T}-{d}-{f}", flush=True)
@@ -51,6 +50,51 @@ def test_fp32_experts_with_infinities(T, d, f):
     for got, w in ((h1, w1), (h3, w3)):        # sums of up to 68 fp32 products
         ref = x.double() @ w.double()
         assert float((got.cpu().double() - ref).norm() / ref.norm()) < 68 ** 0.5 * 2.0 ** -24
+
+
+def fp32_pass(rows, x, w1, w3, w2, d_o, h1=None, h3=None, a=None, cap=None):
+    """Forward, then backward from the given h1, h3 and a where they are not the forward's, of experts with these rows."""
+    R, (e_cnt, d, f) = sum(rows), w1.shape
+    cap = cap or R
+    up = lambda t: None if t is None else torch.cat([t, torch.zeros((cap - R, t.shape[1]))]).cuda()  # noqa: E731
+    offsets = torch.tensor([0] + rows).cumsum(0).to(torch.int32).cuda()
+    weights = [w.cuda() for w in (w1, w3, w2)]
+    fh1, fh3, fa, o, dxp = (torch.zeros((cap, n), device="cuda") for n in (f, f, f, d, d))
+    grads = [torch.zeros_like(w) for w in weights]
+    wsf, wsb = (torch.empty(B.moe_workspace_bytes(which, B.MOE_F32, R, 1, d, f, e_cnt, cap), dtype=torch.uint8, device="cuda")
+                for which in (B.WS_EXPERT_FWD, B.WS_EXPERT_BWD))
+    B.moe_expert_fwd(up(x), offsets, *weights, fh1, fh3, o, wsf, a=fa)
+    pick = lambda given, own: own if given is None else up(given)  # noqa: E731
+    B.moe_expert_bwd(up(x), pick(h1, fh1), pick(h3, fh3), up(d_o), offsets, *weights, dxp, *grads, False, wsb, a=pick(a, fa))
+    names = ("h1", "h3", "o", "dxp", "dw1", "dw3", "dw2")
+    return dict(zip(names, [t[:R].cpu() for t in (fh1, fh3, o, dxp)] + [t.cpu() for t in grads]))
+
+
+# numbers whose bf16 terms would lie below bf16's smallest ones, beside factors that make their sums ordinary; either operand of every
+# GEMM, with one and two LDS buffers (the capacity decides)
+@pytest.mark.parametrize("tiny,large", [(1e-33, 1e18), (1e-37, 1e22), (1e-41, 1e25), (2.0 ** -147, 1e28)])
+@pytest.mark.parametrize("cap", [70, 40000])
+def test_fp32_experts_hold_small_operands(tiny, large, cap):
+    print(f"case fp32-small-{tiny}-{cap}", flush=True)
+    T, d, f = 70, 68, 132
+    g = torch.Generator().manual_seed(5)
+    randn = lambda scale, *shape: torch.randn(shape, generator=g) * scale  # noqa: E731
+    r = lambda t: t.double()  # noqa: E731
+    for sx, sw in ((tiny, large), (large, tiny)):
+        x, w1, w3, w2, d_o = randn(sx, T, d), randn(sw, 1, d, f), randn(sw, 1, d, f), randn(sw, 1, f, d), randn(sx, T, d)
+        h1, h3, a = randn(1.0, T, f), randn(1.0, T, f), randn(sw, T, f)
+        got = fp32_pass([T], x, w1, w3, w2, d_o, h1, h3, a, cap)
+        sig = torch.sigmoid(r(h1))
+        dA = r(d_o) @ r(w2[0]).T
+        dh1, dh3 = dA * r(h3) * sig * (1 + r(h1) * (1 - sig)), dA * r(h1) * sig
+        ref = {"h1": r(x) @ r(w1[0]), "h3": r(x) @ r(w3[0]), "dw2": r(a).T @ r(d_o)}
+        # sums of up to 132 products, as fp32 makes them; dxp, dw1, dw3: of products with a rounded dh1, dh3 (a few roundings and expf)
+        for name, want in ref.items():
+            assert float((r(got[name]).reshape(want.shape) - want).norm() / want.norm()) < 132 ** 0.5 * 2.0 ** -24, (name, sx)
+        ref = {"dxp": dh1 @ r(w1[0]).T + dh3 @ r(w3[0]).T, "dw1": r(x).T @ dh1, "dw3": r(x).T @ dh3}
+        for name, want in ref.items():
+            if float(want.norm()) / want.numel() ** 0.5 > 1e-30:          # (otherwise the results themselves are subnormal)
+                assert float((r(got[name]).reshape(want.shape) - want).norm() / want.norm()) < TOL["f32"], (name, sx)
 
 
 # launches of up to 512 blocks have two LDS buffers, larger ones one: the capacity decides for the forward, dA and dX, the widths for the
