@@ -367,54 +367,60 @@ __global__ __launch_bounds__(NT, BUFS == 2 ? 2 : MODE == UP || MODE == WGD ? 3 :
       }
     }
   };
-  sums(Int<1>{});
-  // Tiles with an infinity, a NaN, a number beyond 2^96 or a sum beyond 2^64 have sums that are no numbers and are done again with
-  // the operands as they are.
-  float scale = UNSCALE;
-  bool lost = false;
+  // The outputs of the accumulator elements in todo (bit r: element r).  Element 4g + i of a lane is row 8g + 4*(lane/32) + i,
+  // column lane%32 of its wavefront's block.
+  auto finish = [&](uint32_t todo, float scale) {
+    const int col = col0 + wn * 32 + (lane & 31);
+    if (col >= p.N) return;
 #pragma unroll
-  for (int i = 0; i < NB; ++i)
+    for (int g = 0; g < 4; ++g) {
+      float h1[4], h3[4];
+      const int r0 = row0 + wm * 32 + 8 * g + 4 * (lane >> 5);
+      if (MODE == DA) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) lost |= !(fabsf(acc[i][0][r] + acc[i][1][r]) <= 3.402823466e38f);
-  if (__syncthreads_or(lost)) {
-    sums(Int<0>{});
-    scale = 1.f;
-  }
-
-  // accumulator element 4g + i of a lane is row 8g + 4*(lane/32) + i, column lane%32 of its wavefront's block
-  const int col = col0 + wn * 32 + (lane & 31);
-  if (col >= p.N) return;
-#pragma unroll
-  for (int g = 0; g < 4; ++g) {
-    float h1[4], h3[4];
-    const int r0 = row0 + wm * 32 + 8 * g + 4 * (lane >> 5);
-    if (MODE == DA) {
+        for (int i = 0; i < 4; ++i) {
+          const size_t idx = (size_t)(r0 + i < row_end ? r0 + i : row_end - 1) * p.ldc + col;
+          h1[i] = p.H[0][idx];
+          h3[i] = p.H[1][idx];
+        }
+      }
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const size_t idx = (size_t)(r0 + i < row_end ? r0 + i : row_end - 1) * p.ldc + col;
-        h1[i] = p.H[0][idx];
-        h3[i] = p.H[1][idx];
+        if (r0 + i >= row_end || !(todo >> (4 * g + i) & 1)) continue;
+        const size_t idx = (size_t)e * p.c_es + (size_t)(r0 + i) * p.ldc + col;
+        const float x = (acc[0][0][4 * g + i] + acc[0][1][4 * g + i]) * scale;
+        const float x3 = (acc[NB - 1][0][4 * g + i] + acc[NB - 1][1][4 * g + i]) * scale;      // second output of a dual tile
+        if (MODE == UP) {
+          if (p.C[0]) { p.C[0][idx] = x; p.C[1][idx] = x3; }
+          p.C[2][idx] = (x / (1.0f + expf(-x))) * x3;
+        } else if (MODE == DA) {
+          const float z = h1[i], sg = 1.0f / (1.0f + expf(-z)), sl = z * sg;
+          if (p.C[0]) p.C[0][idx] = sl * h3[i];      // not stored when the forward's copy is at hand
+          p.C[1][idx] = x * h3[i] * (sg * (1.0f + z * (1.0f - sg)));
+          p.C[2][idx] = x * sl;
+        } else {
+          p.C[0][idx] = p.beta ? p.C[0][idx] + x : x;
+          if (DUAL) p.C[1][idx] = p.beta ? p.C[1][idx] + x3 : x3;
+        }
       }
     }
+  };
+  sums(Int<1>{});
+  // Outputs with an infinity, a NaN, a number beyond 2^96 or a sum beyond 2^64 in them have sums that are no numbers.  Those, and no
+  // others of their tile, come from the operands as they are: what a row or column holds does not show in its neighbours' bits.
+  uint32_t lost = 0;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      if (r0 + i >= row_end) continue;
-      const size_t idx = (size_t)e * p.c_es + (size_t)(r0 + i) * p.ldc + col;
-      const float x = (acc[0][0][4 * g + i] + acc[0][1][4 * g + i]) * scale;
-      const float x3 = (acc[NB - 1][0][4 * g + i] + acc[NB - 1][1][4 * g + i]) * scale;      // second output of a dual tile
-      if (MODE == UP) {
-        if (p.C[0]) { p.C[0][idx] = x; p.C[1][idx] = x3; }
-        p.C[2][idx] = (x / (1.0f + expf(-x))) * x3;
-      } else if (MODE == DA) {
-        const float z = h1[i], sg = 1.0f / (1.0f + expf(-z)), sl = z * sg;
-        if (p.C[0]) p.C[0][idx] = sl * h3[i];      // not stored when the forward's copy is at hand
-        p.C[1][idx] = x * h3[i] * (sg * (1.0f + z * (1.0f - sg)));
-        p.C[2][idx] = x * sl;
-      } else {
-        p.C[0][idx] = p.beta ? p.C[0][idx] + x : x;
-        if (DUAL) p.C[1][idx] = p.beta ? p.C[1][idx] + x3 : x3;
-      }
-    }
+  for (int r = 0; r < 16; ++r) {
+    bool whole = true;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) whole &= fabsf(acc[i][0][r] + acc[i][1][r]) <= 3.402823466e38f;
+    lost |= whole ? 0u : 1u << r;
+  }
+  const bool again = __syncthreads_or(lost != 0);
+  finish(~lost, UNSCALE);
+  if (again) {
+    sums(Int<0>{});
+    finish(lost, 1.f);
   }
 }
 

@@ -97,6 +97,32 @@ def test_fp32_experts_hold_small_operands(tiny, large, cap):
                 assert float((r(got[name]).reshape(want.shape) - want).norm() / want.norm()) < TOL["f32"], (name, sx)
 
 
+# what one row (for the weight gradients: one column) holds does not show in the bits of its neighbours in a tile
+@pytest.mark.parametrize("what", [float("inf"), float("nan"), 3e38, 1e25, 1e-25, 1e-40])
+@pytest.mark.parametrize("cap", [70, 40000])
+def test_fp32_outputs_do_not_depend_on_their_neighbours(what, cap):
+    print(f"case fp32-neighbours-{what}-{cap}", flush=True)
+    T, d, f = 70, 68, 132
+    g = torch.Generator().manual_seed(6)
+    randn = lambda *shape: torch.randn(shape, generator=g)  # noqa: E731
+    weights = (randn(1, d, f) * 0.1, randn(1, d, f) * 0.1, randn(1, f, d) * 0.1)
+    acts = dict(x=randn(T, d), d_o=randn(T, d), h1=randn(T, f), h3=randn(T, f), a=randn(T, f))
+    call = lambda c: fp32_pass([T], c["x"], *weights, c["d_o"], c["h1"], c["h3"], c["a"], cap)  # noqa: E731
+    want = call(acts)
+    rows, cols = torch.arange(T) != 5, torch.arange(f) != 7
+    other = dict(acts, x=acts["x"].clone(), d_o=acts["d_o"].clone())
+    other["x"][5], other["d_o"][5] = what, what
+    got = call(other)
+    for name in ("h1", "h3", "o", "dxp"):
+        assert torch.equal(got[name][rows], want[name][rows]), name
+    other = dict(acts, x=acts["x"].clone(), a=acts["a"].clone())
+    other["x"][:, 7], other["a"][:, 7] = what, what
+    got = call(other)
+    for name in ("dw1", "dw3"):
+        assert torch.equal(got[name][:, cols[:d]], want[name][:, cols[:d]]), name
+    assert torch.equal(got["dw2"][:, cols], want["dw2"][:, cols])
+
+
 # launches of up to 512 blocks have two LDS buffers, larger ones one: the capacity decides for the forward, dA and dX, the widths for the
 # weight gradients (576 blocks with 16 experts); one k-tile, odd and even numbers of them, empty experts
 @pytest.mark.parametrize("d,f,rows", [(32, 64, [1]), (200, 520, [40, 0, 1, 33, 64, 65, 7, 0, 96, 3, 2, 1, 100, 0, 31, 32]), (100, 36, [70, 0, 33])])
