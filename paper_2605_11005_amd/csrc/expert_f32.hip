@@ -10,9 +10,11 @@
 //   WGD    dW1|dW3 = xp^T [dH1|dH3]      ragged K, two outputs of one tile
 //
 // The fp32 matrix instruction does 256 FLOP per cycle and CU, the bf16 one sixteen times that, so six bf16 products take 3/8 of
-// the time.  Three terms hold all 24 bits of a number, the products that are left out are below 2^-26 of the whole, and sixteen
-// products are added per rounding instead of two: against 64 bits the outputs are off by half of what the fp32 instruction
-// gave (1.3e-7 for 2.9e-7 for h1 at d = 520, 3.3e-7 for 6.7e-7 for the worst gradient; twelve shapes, none of them further off).
+// the time.  Three terms hold all 24 bits of a number.  The three products of terms that are left out are up to 2^-24.0 of a product of
+// operands (x = y = 1.0039), 2^-27.4 in the root mean square; two more of them would make that 2^-33 and training steps 5 to 10 %
+// longer.  Sixteen products are added per rounding instead of two: against 64 bits the outputs are off by half of what the fp32
+// instruction gave (1.3e-7 for 2.9e-7 for h1 at d = 520, 3.3e-7 for 6.7e-7 for the worst gradient; twelve shapes, none of them further
+// off).
 //
 // What bounds it now, all near 1000 cycles per k-tile of a dual tile: the operands' way to the CU (24 KB), LDS (36 KB written,
 // 114 KB read), splitting the operands (about 150 vector instructions) and the matrix pipe (768).  Only other blocks' waves fill
@@ -48,6 +50,11 @@ __device__ __forceinline__ float4 keep(float4 v, bool in) {
 
 typedef short s16x4 __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+// Weight gradients of up to this many rows are summed by the fp32 instruction.  Largest error of 400000 outputs in units of 2^-24 sum
+// |products| (rms), fp32 instruction / terms, Gaussian operands: one row 1.00 / 1.54 (0.425 / 0.435; a product is rounded
+// correctly, the terms leave out up to 2^-24 of it), two 1.89 / 2.70 (0.516 / 0.369), three 2.45 / 2.37 (0.490 / 0.328), eight 2.92
+// / 1.92 (0.412 / 0.240), 64 3.07 / 1.83 (0.345 / 0.160).
+constexpr int EXACT_ROWS = 2;
 // SCALE x = h + m + l in bf16, each the rounded rest of the ones before it.  The scale brings the last bit of fp32's smallest
 // number, 2^-149, among bf16's normal numbers, so that the three hold every x up to 2^96 exactly; products, and with them sums,
 // are SCALE^2 times what they stand for.  Beyond 2^96 the first term is infinite and the second NaN, and so are the sums that it enters.
@@ -248,7 +255,7 @@ __global__ __launch_bounds__(NT, BUFS == 2 ? 2 : MODE == UP || MODE == WGD ? 3 :
   const int nk1 = (K + TK - 1) / TK, nk = MODE == DX ? 2 * nk1 : nk1;
   const bool live = wm * 32 < row_end - row0;    // a wavefront without valid rows only moves data
   // SPLIT: on the bf16 matrix instruction, the operands as three terms each.  Six products: h h in one sum, h m, m h, h l, l h and
-  // m m in the other; the three left out are below 2^-26 of the whole.  Else: on the fp32 matrix instruction, even and odd steps
+  // m m in the other; the three left out are below 2^-24 of the whole.  Else: on the fp32 matrix instruction, even and odd steps
   // in the two sums.
   auto sums = [&](auto split_tag) {
     constexpr bool SPLIT = decltype(split_tag)::value != 0;
@@ -405,16 +412,21 @@ __global__ __launch_bounds__(NT, BUFS == 2 ? 2 : MODE == UP || MODE == WGD ? 3 :
       }
     }
   };
-  sums(Int<1>{});
   // Outputs with an infinity, a NaN, a number beyond 2^96 or a sum beyond 2^64 in them have sums that are no numbers.  Those, and no
   // others of their tile, come from the operands as they are: what a row or column holds does not show in its neighbours' bits.
-  uint32_t lost = 0;
+  // (With one in every tile the six GEMMs of 3000 rows, d = 520, f = 776, take 178 + 360 us for 90 + 175.)
+  // So do all weight gradients of an expert with one or two rows, which the terms would not round as well (EXACT_ROWS).
+  const bool exact = RAGGED_K && K <= EXACT_ROWS;
+  uint32_t lost = exact ? 0xFFFFu : 0u;
+  if (!exact) {
+    sums(Int<1>{});
 #pragma unroll
-  for (int r = 0; r < 16; ++r) {
-    bool whole = true;
+    for (int r = 0; r < 16; ++r) {
+      bool whole = true;
 #pragma unroll
-    for (int i = 0; i < NB; ++i) whole &= fabsf(acc[i][0][r] + acc[i][1][r]) <= 3.402823466e38f;
-    lost |= whole ? 0u : 1u << r;
+      for (int i = 0; i < NB; ++i) whole &= fabsf(acc[i][0][r] + acc[i][1][r]) <= 3.402823466e38f;
+      lost |= whole ? 0u : 1u << r;
+    }
   }
   const bool again = __syncthreads_or(lost != 0);
   finish(~lost, UNSCALE);

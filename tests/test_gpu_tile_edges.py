@@ -123,6 +123,27 @@ def test_fp32_outputs_do_not_depend_on_their_neighbours(what, cap):
     assert torch.equal(got["dw2"][:, cols], want["dw2"][:, cols])
 
 
+# weight gradients of experts with one row are rounded products; of two rows, sums with a rounding per product and one of the sum
+@pytest.mark.parametrize("d,f", [(4, 4), (68, 132), (260, 200)])
+def test_fp32_weight_gradients_of_one_and_two_rows(d, f):
+    print(f"case fp32-one-row-{d}-{f}", flush=True)
+    rows, g = [1, 0, 2, 1, 3], torch.Generator().manual_seed(7)
+    randn = lambda *shape: torch.randn(shape, generator=g)  # noqa: E731
+    R, e_cnt = sum(rows), len(rows)
+    x, d_o, a = randn(R, d), randn(R, d), randn(R, f)
+    x[:, 0] = 1.0                              # row 0 of dw1 and dw3 then shows what the columns of x are multiplied by
+    got = fp32_pass(rows, x, randn(e_cnt, d, f), randn(e_cnt, d, f), randn(e_cnt, f, d), d_o, randn(R, f), randn(R, f), a)
+    off = [0] + list(np.cumsum(rows))
+    for e in (0, 3):
+        r = off[e]
+        assert torch.equal(got["dw2"][e], a[r][:, None] * d_o[r][None, :])
+        for name in ("dw1", "dw3"):
+            assert torch.equal(got[name][e], x[r][:, None] * got[name][e][0][None, :]), name
+    assert not any(got[name][1].any() for name in ("dw1", "dw3", "dw2"))
+    a2, d2 = a[off[2]:off[3]].double(), d_o[off[2]:off[3]].double()
+    assert ((got["dw2"][2].double() - a2.T @ d2).abs() <= 2.001 * 2.0 ** -24 * (a2.abs().T @ d2.abs())).all()
+
+
 # launches of up to 512 blocks have two LDS buffers, larger ones one: the capacity decides for the forward, dA and dX, the widths for the
 # weight gradients (576 blocks with 16 experts); one k-tile, odd and even numbers of them, empty experts
 @pytest.mark.parametrize("d,f,rows", [(32, 64, [1]), (200, 520, [40, 0, 1, 33, 64, 65, 7, 0, 96, 3, 2, 1, 100, 0, 31, 32]), (100, 36, [70, 0, 33])])
