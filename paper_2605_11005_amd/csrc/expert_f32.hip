@@ -29,7 +29,7 @@
 
 namespace {
 
-constexpr int TM = 64, TN = 64, TK = 32, NT = 256, CUS = 256;
+constexpr int TM = 64, TN = 64, TK = 32, NT = 256;
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 enum { UP, DOWN, DA, DX, WG, WGD };
@@ -445,7 +445,7 @@ int launch(const Args& p, long long m_tiles, hipStream_t s) {
   // Training step, us, one buffer / two up to 256 blocks / two up to 512 (T, d, f, experts, k): 100, 256, 512, 8, 2 107 / 99 / 97;
   // 256, 1024, 512, 8, 1 170 / 152 / 151; 300, 400, 600, 16, 2 146 / 137 / 131; 600, 1000, 1000, 8, 2 300 / 300 / 293.  At 1500, 520,
   // 776, 16, 2 (800 blocks and more) two buffers for all take 87 + 176 for 79 + 160 in the six GEMMs.
-  const auto kernel = blocks <= 2 * CUS ? gemm_f32<MODE, 2> : gemm_f32<MODE, 1>;
+  const auto kernel = blocks <= 2 * device_cu_count() ? gemm_f32<MODE, 2> : gemm_f32<MODE, 1>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(NT), 0, s, p);
   HIP_CHECK_LAUNCH();
   return MOE_OK;
