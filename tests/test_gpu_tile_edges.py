@@ -401,3 +401,59 @@ def test_bf16_gemms_that_end_in_quarter_tiles(d, f, rows):
                 assert rel_err(host(got[e]), ref[e]) < TOL["bf16"], (name, e)
         for t in (h1, h3, o, dxp, dw1, dw3, dw2):
             t.fill_(float("nan"))
+
+
+def bf16_pass(rows, weights, xp, d_o, cap):
+    """Forward and backward of experts with these rows; outputs, and which tiles each ragged GEMM drew tickets for: (256x256, 128x128).
+    The capacity keeps dX in a launch of its own, and so does the activation that is not kept with dA."""
+    R, (e_cnt, d, f) = sum(rows), weights[0].shape
+    empty = lambda n: torch.empty((cap, n), device="cuda", dtype=torch.bfloat16)  # noqa: E731
+    x, dy, h1, h3, o, dxp = empty(d), empty(d), empty(f), empty(f), empty(d), empty(d)
+    x[:R], dy[:R] = xp, d_o
+    grads = [torch.empty_like(w) for w in weights]
+    offsets = torch.tensor([0] + rows).cumsum(0).to(torch.int32).cuda()
+    wsf, wsb = (torch.empty(B.moe_workspace_bytes(which, B.MOE_BF16, R, 1, d, f, e_cnt, cap), dtype=torch.uint8, device="cuda")
+                for which in (B.WS_EXPERT_FWD, B.WS_EXPERT_BWD))
+    B.moe_expert_fwd(x, offsets, *weights, h1, h3, o, wsf)
+    B.moe_expert_bwd(x, h1, h3, dy, offsets, *weights, dxp, *grads, False, wsb)
+    kinds = {}
+    for ws, scratch, names in ((wsf, cap * f * 2, ("up", "down")), (wsb, 3 * cap * f * 2, ("da", "dx"))):
+        first = (scratch + 255) // 256 * 256             # the ticket counters lie behind the scratch matrices, 16 words per GEMM
+        for i, name in enumerate(names):
+            words = ws[first + 64 * i:first + 64 * (i + 1)].view(torch.int32)
+            kinds[name] = (bool(words[:8].any()), bool(words[8:].any()))
+    return dict(h1=h1[:R], h3=h3[:R], o=o[:R], dxp=dxp[:R]), kinds
+
+
+# 256x256 tiles that fill whole rounds of 256 CUs and then 128x128 ones, the list cut inside an expert; alone an expert's rows go to
+# other tiles, with the same bits
+@pytest.mark.parametrize("d,f,rows,both", [(2048, 1024, [5000, 3500, 1400, 290, 2], ("up", "dx")),
+                                           (2048, 2048, [5000, 0, 3700, 290, 2], ("down", "da", "dx"))])
+def test_bf16_gemms_with_both_kinds_of_tiles(d, f, rows, both):
+    print(f"case both-kinds-{d}-{f}", flush=True)
+    e_cnt, R, cap = len(rows), sum(rows), 110000
+    g = torch.Generator(device="cuda").manual_seed(d + f)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda", dtype=torch.bfloat16)  # noqa: E731
+    xp, d_o = randn(R, d), randn(R, d)
+    w1, w3, w2 = weights = [randn(e_cnt, d, f) * d ** -0.5, randn(e_cnt, d, f) * d ** -0.5, randn(e_cnt, f, d) * f ** -0.5]
+    got, kinds = bf16_pass(rows, weights, xp, d_o, cap)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        for name in both:
+            assert kinds[name] == (True, True), (name, kinds)
+    off, other = [0] + list(np.cumsum(rows)), set()
+    for e in range(e_cnt):
+        if rows[e] == 0:
+            continue
+        part = slice(off[e], off[e + 1])
+        x, dy, a1, a3, a2 = (t.float() for t in (xp[part], d_o[part], w1[e], w3[e], w2[e]))
+        h1, h3 = x @ a1, x @ a3
+        sig = torch.sigmoid(h1)
+        dA = dy @ a2.T
+        want = dict(h1=h1, h3=h3, o=(h1 * sig * h3) @ a2,
+                    dxp=(dA * h3 * sig * (1 + h1 * (1 - sig))) @ a1.T + (dA * h1 * sig) @ a3.T)
+        alone, kinds_alone = bf16_pass([rows[e]], [w[e:e + 1].contiguous() for w in weights], xp[part], d_o[part], cap)
+        other |= {name for name in both if kinds_alone[name] != (True, True)}
+        for name, ref in want.items():
+            assert rel_err(host(got[name][part]), ref.cpu().numpy()) < TOL["bf16"], (name, e)
+            assert torch.equal(got[name][part], alone[name]), (name, e)
+    assert other == set(both)
