@@ -257,7 +257,10 @@ extern __shared__ __align__(16) char smem[];
 // otherwise sit on a few XCDs, each of which reads memory at an eighth of the chip's rate (d = f = 4096, 4 experts of 250 rows: the
 // down projection's 64 tiles on two XCDs take 97 us, on eight 74).  Not where the tiles differ in length (ragged K): there a
 // last round of short tiles in every queue keeps workgroups from the long ones that another queue still holds, and for the same
-// reason not in the dA that shares a launch with dW2 (116 us for 126 at 5538 rows, d = 2048, f = 1408, 8 experts).
+// reason not in the dA that shares a launch with dW2 (116 us for 126 at 5538 rows, d = 2048, f = 1408, 8 experts).  The dX that shares
+// one with dW1|dW3 gains 1 % on average over 150 cases (5 shapes, 1 to 3 rounds; -6 to +3 %), but rows by 1/r that leave 8 or 16
+// tiles beyond a round take 232 us for 215 (8000 rows, d = 2048, f = 1408, 8 experts) or 480 for 457 (16400 rows, d = 1024, f =
+// 3584); spreading more than 16 or 64 tiles only, or lists of less than one or four rounds only, was no better on the whole.
 template <bool SPREAD>
 __device__ __forceinline__ int take_ticket(int32_t* counters, int n_queues, int& queue, int total, int32_t* next_q, int wave, int lane,
                                            bool spread = SPREAD) {
@@ -302,7 +305,12 @@ __device__ __forceinline__ int take_ticket(int32_t* counters, int n_queues, int&
 // weights either kind reads (one with both is read twice); rows: of all experts, most: of the heaviest.  A quarter tile moves half
 // of a 256x256 tile's bytes to the CU for a quarter of its work, and both are bound by that path (about 70 GB/s per CU where the
 // panels are shared): 19 us for 47 at a contraction of 2048.  The constants are fitted to the four GEMMs alone over 76 cases
-// (eight shapes, 500 to 40000 rows: even, 1/r, half of them on one expert), each of the four plans forced.
+// (eight shapes, 500 to 40000 rows: even, 1/r, half of them on one expert), each of the four plans forced.  Over 297 others (nine
+// shapes, 40 to 2500 rows per expert, the same three ways) the plan taken is the best one or within 2 % of it in 86 to 88 % of the
+// cases of each GEMM, 0.7 to 0.9 % above it on average and at worst 13 (UP), 14 (DOWN), 17 (DA) and 11 % (DX).  Against 256x256
+// tiles only it saves 3, 10, 13 and 16 % on average; 21 of the 1188 cases lose more than 3 %, at worst 8, 7, 17 and 11 % (DA, d = 4096,
+// f = 14336, 4 experts of 290 rows: 202 us, as plan 1 237).  Other constants or margins that do better on one half of the cases do
+// worse on the other.  The set-up takes 1.4 us longer for it (4100 cycles for 900: most of it fetching the instructions).
 template <int MODE>
 __device__ __forceinline__ float plan_price(const GArgs& p, int n_big, int n_quarter, int active_big, int active_quarter, int n_quarters_n,
                                             int rows, int most, bool tails) {
@@ -316,9 +324,13 @@ __device__ __forceinline__ float plan_price(const GArgs& p, int n_big, int n_qua
   const float weights = k * (float)p.N * (MODE == UP ? 4e-6f : 2e-6f) * ((float)active_big / RATE_BIG + (float)active_quarter / RATE_QUARTER);
   const int grid = gridDim.x, full = n_big / grid, rest = n_big - full * grid;
   const float per_cu = 1.f / (float)grid;
-  // row tiles of which half is empty share no weight panel when they are quarters: their price is the least certain
+  // row tiles of which half is empty share no weight panel when they are quarters: their price is the least certain (without this
+  // the plan taken for UP is 1.3 % above the best on average instead of 0.9, and 22 cases of 297 lose more than 3 % instead of 10)
   const float doubt = tails && n_big > 0 ? 1.05f : 1.f;
-  if (p.pair_first) {      // the weight gradient that follows in this launch fills the last round: all of one kind
+  // The weight gradient that follows in this launch fills the last round: all tiles of one kind.  tile and start are the weight
+  // gradients' time per row and tile, in us.  Over 90 pairs of each kind (5 shapes, 240 to 3000 rows per expert, even and 1/r) dA|dW2
+  // takes 0.93 to 1.07 times, 1.013 on average, and dX|dW1|dW3 0.86 to 1.08 times, 0.99 on average, what 256x256 tiles alone took.
+  if (p.pair_first) {
     const float tile = 0.027f, start = 6.f;
     const float n_second = (float)(((p.N + BM - 1) / BM) * ((p.K + (MODE == DX ? 127 : 255)) / (MODE == DX ? 128 : 256)));
     const float second = n_second * (tile * (float)rows + start * (float)p.e_cnt) * per_cu, longest = tile * (float)most + start;
@@ -858,6 +870,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
     __syncthreads();
     int plan = 0;
     if (SPLIT) {
+      // (0.97: without it 16 of 297 UPs lose more than 3 % against 256x256 tiles instead of 10, at worst 12 % instead of 8)
 #pragma unroll
       for (int c = 1; c < 4; ++c)
         if (price[c] < (plan == 0 ? 0.97f : 1.f) * price[plan]) plan = c;
@@ -1417,7 +1430,9 @@ __global__ __launch_bounds__(NT, 1) void gg_kernel(GArgs p) {
 // time and the tiles', each from the rounds, the work per CU and the bytes of both GEMMs, in us, fitted to 12 shapes with 1 to 128
 // rows per expert.  The estimate is good to a quarter: over 315 cases (9 shapes, bounds of 17 to 128 rows, filled evenly, by 1/r,
 // by one expert, to an eighth) the kernel for few rows took 0.44 to 0.86 of the tiles' time where the ratio is below 0.75, and
-// 0.6 to 1.9 above.
+// 0.6 to 1.9 above.  The tiles' price is that of 256x256 ones.  With quarter tiles among them the choice is 6 % above the better
+// kernel on average over 64 cases (4 shapes, bounds of 32 to 128, the four ways of filling below), at worst 21 % (16 experts of
+// d = f = 2880 with three rows each: 146 us for few rows, 174 for the tiles it takes).
 __device__ __forceinline__ bool few_rows_pay(const int32_t* __restrict__ off, int e_cnt, int d, int f) {
   constexpr float C1 = 0.563f, C2 = 0.752f, C4 = 1.173f;       // a round of 128 k with up to 16, 32 and 64 rows
   float v[5] = {0.f, 0.f, 0.f, 0.f, 0.f};            // rounds' cost of a column block, tiles of 64 rows, of 256, active experts; longest
@@ -1607,17 +1622,22 @@ int launch_gg(const GArgs& a, hipStream_t s) {
 // counts are on the device, the host knows a bound.  Forward of both GEMMs, few rows / tiles, in us, with the bound filled
 // evenly, by 1/r (Zipf), by one expert alone, and to a tenth:
 //   weights  d, f, experts       bound   even         Zipf         one          a tenth
-//   138 MB   2048, 1408, 8       128     62 / 87      77 / 87      63 / 87      37 / 68
-//   151 MB   2048, 768, 16       128     68 / 78      79 / 82      67 / 85      38 / 65
-//   604 MB   4096, 1536, 16      16      129 / 143    158 / 146    62 / 116     122 / 143
-//                                128     249 / 155    295 / 177    204 / 155    147 / 145
-//   796 MB   2880, 2880, 16      16      154 / 189    188 / 185    60 / 122     145 / 185
-//                                64      198 / 193    268 / 195    152 / 146    153 / 183
-//   2.8 GB   7168, 2048, 32      8       502 / 526    544 / 529    94 / 176     337 / 400
-//                                16      514 / 527    656 / 532    125 / 191    493 / 527
-//   2.8 GB   4096, 14336, 8      8       509 / 603    528 / 601    207 / 298    439 / 558
-// While all weights fit the Infinity Cache (256 MB) few rows win up to a bound of 128 however it is filled; up to a bound of 16,
-// with more than 1 GB of 8, they win or lose little.  Up to 1 GB and 128 rows it depends on the counts: gg_or_few looks at them.
+//   138 MB   2048, 1408, 8       64      40 / 47      43 / 51      41 / 45      28 / 42
+//                                96      54 / 49      61 / 54      60 / 46      28 / 43
+//                                128     61 / 51      75 / 55      61 / 48      28 / 43
+//   151 MB   2048, 768, 16       64      38 / 51      66 / 59      36 / 42      30 / 49
+//                                128     66 / 50      77 / 75      65 / 46      31 / 50
+//   604 MB   4096, 1536, 16      16      128 / 144    158 / 145    62 / 60      122 / 145
+//                                128     247 / 153    296 / 176    208 / 109    129 / 143
+//   796 MB   2880, 2880, 16      16      152 / 177    187 / 177    59 / 59      145 / 172
+//                                64      197 / 185    269 / 189    148 / 84     148 / 174
+//   2.8 GB   7168, 2048, 32      8       501 / 531    536 / 531    93 / 81      399 / 423
+//                                16      514 / 532    652 / 537    123 / 83     492 / 527
+//   2.8 GB   4096, 14336, 8      8       509 / 515    531 / 514    174 / 191    379 / 387
+// While all weights fit the Infinity Cache (256 MB) few rows win up to a bound of 64, bar one case.  Between 64 and 128 they win where
+// the bound is far above the counts and lose by up to 45 % where it is full: the line at 128 was drawn against tiles of 256x256 only,
+// which took 87 us in the first row of 128.  Up to a bound of 16, with more than 1 GB of 8, they win or lose little.  Up to 1 GB
+// and 128 rows it depends on the counts: gg_or_few looks at them.
 enum { MANY_ROWS, FEW_ROWS, COUNTS_DECIDE };
 inline int rows_route(int cap, int d, int f, int e_cnt) {
   const long long mb = 6ll * d * f * e_cnt >> 20;

@@ -17,13 +17,14 @@
 // off).
 //
 // What bounds it now, all near 1000 cycles per k-tile of a dual tile: the operands' way to the CU (24 KB), LDS (36 KB written,
-// 114 KB read), splitting the operands (about 150 vector instructions) and the matrix pipe (768).  Only other blocks' waves fill
+// 114 KB read), splitting the operands (about 175 vector instructions) and the matrix pipe (768).  Only other blocks' waves fill
 // the gaps, hence a small tile, 64x64 by four wavefronts of 32x32 each, one LDS buffer and registers for three (dual) or four
 // blocks per CU (two buffers where two blocks per CU or fewer are all there are: launch()), and two k-tiles of 32 on their way in
-// registers while a third is multiplied.  3000 rows over 16 experts, d = 520, f = 776, forward and backward: 106 + 215 us with the
-// fp32 instruction; 87 + 176 with two LDS buffers and two blocks per CU; 79
-// + 160 as it is.  Splitting between the matrix instructions of one wavefront takes more registers and 104 + 181; tiles of
-// 128x64 95 + 199 (better only for a thousand rows and more per expert: 145 for 176 at 3000, d = f = 1024).
+// registers while a third is multiplied.  3000 rows over 16 experts, d = 520, f = 776, forward + backward on one card: 107 + 215 us
+// with the fp32 instruction, 90 + 175 as it is.  Tried, on another card and before the operands were scaled, against 79 + 160:
+// two LDS buffers and two blocks per CU 87 + 176; splitting between the matrix instructions of one wavefront, which takes more
+// registers, 104 + 181; tiles of 128x64 95 + 199 (better only for a thousand rows and more per expert: 145 for 176 at 3000, d = f =
+// 1024).
 #include "common.h"
 #include "kernels.h"
 
@@ -442,9 +443,9 @@ int launch(const Args& p, long long m_tiles, hipStream_t s) {
   const long long blocks = (m_tiles * ((p.N + TN - 1) / TN) + 7) / 8 * 8;
   if (blocks >= (1ll << 31)) return MOE_EUNSUPPORTED;
   // Two LDS buffers while at most two blocks share a CU: nothing else fills the gaps there.  The sums and their order are the same.
-  // Training step, us, one buffer / two up to 256 blocks / two up to 512 (T, d, f, experts, k): 100, 256, 512, 8, 2 107 / 99 / 97;
-  // 256, 1024, 512, 8, 1 170 / 152 / 151; 300, 400, 600, 16, 2 146 / 137 / 131; 600, 1000, 1000, 8, 2 300 / 300 / 293.  At 1500, 520,
-  // 776, 16, 2 (800 blocks and more) two buffers for all take 87 + 176 for 79 + 160 in the six GEMMs.
+  // Training step before the operands were scaled, us, one buffer / two up to 256 blocks / two up to 512 (T, d, f, experts, k): 100,
+  // 256, 512, 8, 2 107 / 99 / 97; 256, 1024, 512, 8, 1 170 / 152 / 151; 300, 400, 600, 16, 2 146 / 137 / 131; 600, 1000, 1000, 8, 2 300 /
+  // 300 / 293.  At 1500, 520, 776, 16, 2 (800 blocks and more) two buffers for all take 87 + 176 for 79 + 160 in the six GEMMs.
   const auto kernel = blocks <= 2 * device_cu_count() ? gemm_f32<MODE, 2> : gemm_f32<MODE, 1>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(NT), 0, s, p);
   HIP_CHECK_LAUNCH();

@@ -238,10 +238,15 @@ __global__ __launch_bounds__(NW_ROUTER * WAVE) void narrow_router(SArgs p) {
 }
 
 // A CU alone reads 50 to 85 GB/s however many loads are on their way, so tiles for at most a quarter of the CUs (p.range) are
-// halved: two wavefronts with 64 columns (UP: 32 of either matrix) each, the other two leave.  Beyond that the halves cost: they
-// read 64 bytes of a row (UP) and more blocks read the same rows.  Whole / halved tiles, us: UP, d = 4096, f = 1536, 2 experts
-// with rows (48 tiles) 28 / 23, 10 experts 49 / 67; d = f = 2880, 1 expert 18 / 16, 12 experts 59 / 73; d = 7168, f = 2048, 2
-// experts (64 tiles) 40 / 36; DOWN, d = 4096, f = 14336, 2 experts (64 tiles) 89 / 67; d = 7168, f = 2048, 2 experts (112) 15 / 20.
+// halved: two wavefronts with 64 columns (UP: 32 of either matrix) each, the other two leave.  Once there are more halves than CUs
+// they cost: they read 64 bytes of a row (UP) and more blocks read the same rows.  Experts of one row each, whole / halved tiles,
+// us, weights in the Infinity Cache (and fetched from memory):
+//   UP    d = 4096, f = 1536    48 tiles  28 / 22 (47 / 43)   96  29 / 24 (50 / 47)    144  (62 / 77)           192  (78 / 86)
+//   UP    d = 7168, f = 2048    64 tiles  41 / 35 (70 / 67)   128  64 / 62 (99 / 99)   160  (113 / 131)         192  (125 / 131)
+//   DOWN  d = 4096, f = 1536    64 tiles  12 / 10 (17 / 14)   128  13 / 14 (24 / 23)   160  (28 / 30)           256  (35 / 35)
+//   DOWN  d = 7168, f = 2048    56 tiles  14 / 12 (21 / 17)   112  15 / 15 (28 / 26)   168  18 / 23 (36 / 40)   224  24 / 28 (32 / 36)
+//   DOWN  d = 4096, f = 14336   64 tiles  89 / 66 (90 / 66)   128  100 / 83 (101 / 83) 160  (110 / 133)         256  (162 / 173)
+// Halves win while every one of them has a CU to itself, so the line could lie at half the CUs; at a quarter they win throughout.
 constexpr int NW_HALF = NW_TILES / 2;
 template <int MODE> constexpr int TILE_COLS = (MODE == UP ? 16 : 32) * NW_TILES;
 template <int MODE>
