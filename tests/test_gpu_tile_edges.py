@@ -371,8 +371,8 @@ def test_few_rows_with_more_rows_than_the_capacity():
         assert got.shape[0] == cap and rel_err(host(got), fw[name][:cap]) < TOL["bf16"], name
 
 
-# 128x128 tiles: all of a short GEMM; the rest of one whose 256x256 tiles fill rounds of the chip, cut inside an expert; one k-tile,
-# an odd number of them, widths that are no multiples of either tile, 1 to 129 rows in the last row tile, empty experts
+# GEMMs all of 128x128 tiles and all of 256x256 ones (both kinds in one launch: the last test); one k-tile, an odd number of them,
+# widths that are no multiples of either tile, 1 to 129 rows in the last row tile, empty experts
 @pytest.mark.parametrize("d,f,rows", [(64, 192, [129, 0, 128, 1, 65]), (192, 64, [300, 257, 33]), (320, 448, [140] * 9),
                                       (512, 1472, [3000, 1700, 900, 130, 129, 128, 127, 1]), (1088, 512, [5000, 0, 1400, 290, 2])])
 def test_bf16_gemms_that_end_in_quarter_tiles(d, f, rows):
@@ -425,13 +425,15 @@ def bf16_pass(rows, weights, xp, d_o, cap):
     return dict(h1=h1[:R], h3=h3[:R], o=o[:R], dxp=dxp[:R]), kinds
 
 
-# 256x256 tiles that fill whole rounds of 256 CUs and then 128x128 ones, the list cut inside an expert; alone an expert's rows go to
-# other tiles, with the same bits
+# 256x256 tiles and then 128x128 ones: of what whole rounds of 256 CUs leave, the list cut inside an expert; of the row tiles of which
+# half is empty (third case, up); of both (fourth case, dA).  Alone an expert's rows go to other tiles, with the same bits.
 @pytest.mark.parametrize("d,f,rows,both", [(2048, 1024, [5000, 3500, 1400, 290, 2], ("up", "dx")),
-                                           (2048, 2048, [5000, 0, 3700, 290, 2], ("down", "da", "dx"))])
+                                           (2048, 2048, [5000, 0, 3700, 290, 2], ("down", "da", "dx")),
+                                           (2112, 1024, [20, 2916, 2204, 2716], ("up", "down", "dx")),
+                                           (1664, 2176, [2048, 511, 356, 1024, 1556, 1024, 1436], ("up", "da"))])
 def test_bf16_gemms_with_both_kinds_of_tiles(d, f, rows, both):
     print(f"case both-kinds-{d}-{f}", flush=True)
-    e_cnt, R, cap = len(rows), sum(rows), 110000
+    e_cnt, R, cap = len(rows), sum(rows), 130000
     g = torch.Generator(device="cuda").manual_seed(d + f)
     randn = lambda *shape: torch.randn(shape, generator=g, device="cuda", dtype=torch.bfloat16)  # noqa: E731
     xp, d_o = randn(R, d), randn(R, d)
