@@ -144,8 +144,8 @@ int moe_dispatch_static(const void* x, int dtype, int T, int d, int k, const int
  * A row's results depend on that row and its expert's weights alone, bit for bit: not on cap (which picks the kernel),
  * nor on the rows beside it.
  * fp32: operands enter with all 24 bits and sums are fp32; a product of two operands may be off by 2^-24 of it before it is
- * added (in the root mean square 2^-27.4).  Infinities, NaN and numbers or sums beyond 2^64 behave as in fp32, but a 64x64 tile
- * that holds one takes twice its time.
+ * added (in the root mean square 2^-27.4).  Infinities, NaN, numbers beyond 2^96 and sums beyond 2^64 behave as in fp32, but a
+ * 64x64 tile that holds one takes twice its time.
  */
 int moe_expert_fwd(const void* xp, int dtype, int cap, int d, int f, int e_cnt,
                    const int32_t* offsets, const void* w1, const void* w3, const void* w2,
