@@ -192,20 +192,28 @@ struct Args {
   int e_cnt, beta;
 };
 
-// 1-D grid over the tiles: RaggedTiles' list for the ragged-M shapes, the same with a fixed number of row tiles per
-// expert for the ragged-K ones.
-// BUFS: LDS buffers, two in launches of few blocks (launch()).
-template <int MODE, int BUFS>
-__global__ __launch_bounds__(NT, BUFS == 2 ? 2 : MODE == UP || MODE == WGD ? 3 : 4) void gemm_f32(Args p) {
-  constexpr bool RAGGED_K = MODE == WG || MODE == WGD;
-  constexpr bool DUAL = MODE == UP || MODE == WGD;
-  constexpr int NB = DUAL ? 2 : 1;
+// LDS of one k-tile: the three bf16 terms of each operand, or the operands themselves
+template <int MODE> struct Traits {
+  static constexpr bool RAGGED_K = MODE == WG || MODE == WGD;
+  static constexpr bool DUAL = MODE == UP || MODE == WGD;
+  static constexpr int NB = DUAL ? 2 : 1;
   typedef typename Pick<RAGGED_K, OperMN, OperKC>::type OperA;
   typedef typename Pick<MODE == DA || MODE == DX, OperKC, OperMN>::type OperB;
-  // one k-tile: the three bf16 terms of each operand, or the operands themselves
-  constexpr int SPLIT_BYTES = (1 + NB) * 3 * PLANE_BYTES, PLAIN_BYTES = (OperA::WORDS + NB * OperB::WORDS) * 4;
-  constexpr int BUFFER = SPLIT_BYTES > PLAIN_BYTES ? SPLIT_BYTES : PLAIN_BYTES;
-  __shared__ __align__(16) char lds[BUFS * BUFFER];
+  static constexpr int SPLIT_BYTES = (1 + NB) * 3 * PLANE_BYTES, PLAIN_BYTES = (OperA::WORDS + NB * OperB::WORDS) * 4;
+  static constexpr int BUFFER = SPLIT_BYTES > PLAIN_BYTES ? SPLIT_BYTES : PLAIN_BYTES;
+  static constexpr int BLOCKS = DUAL ? 3 : 4;      // per CU, with one LDS buffer
+};
+
+// Block `block` of one GEMM, a 1-D list of tiles: RaggedTiles' for the ragged-M shapes, the same with a fixed number of row tiles
+// per expert for the ragged-K ones.
+// BUFS: LDS buffers, two in launches of few blocks (use_two()).
+template <int MODE, int BUFS>
+__device__ __forceinline__ void gemm_tile(const Args& p, int block, char* lds) {
+  using TR = Traits<MODE>;
+  constexpr bool RAGGED_K = TR::RAGGED_K, DUAL = TR::DUAL;
+  constexpr int NB = TR::NB, BUFFER = TR::BUFFER;
+  typedef typename TR::OperA OperA;
+  typedef typename TR::OperB OperB;
 
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -213,8 +221,8 @@ __global__ __launch_bounds__(NT, BUFS == 2 ? 2 : MODE == UP || MODE == WGD ? 3 :
   int e, mt, nt, row0, row_end, K;                       // output rows [row0, row_end)
   if (RAGGED_K) {
     const int total = p.e_cnt * m_tiles * n_tiles, share = (total + 7) / 8;
-    const int tile = (blockIdx.x % 8) * share + blockIdx.x / 8;
-    if ((int)(blockIdx.x / 8) >= share || tile >= total) return;
+    const int tile = (block % 8) * share + block / 8;
+    if (block / 8 >= share || tile >= total) return;
     e = tile / (m_tiles * n_tiles);
     mt = (tile - e * m_tiles * n_tiles) / n_tiles;
     nt = tile % n_tiles;
@@ -222,7 +230,7 @@ __global__ __launch_bounds__(NT, BUFS == 2 ? 2 : MODE == UP || MODE == WGD ? 3 :
     row_end = p.M;
     K = p.off[e + 1] - p.off[e];
   } else {
-    if (!RaggedTiles<TM>(p.off, p.e_cnt, lane).tile(n_tiles, blockIdx.x, e, mt, nt)) return;
+    if (!RaggedTiles<TM>(p.off, p.e_cnt, lane).tile(n_tiles, block, e, mt, nt)) return;
     row0 = p.off[e] + mt * TM;
     row_end = p.off[e + 1];
     K = p.K;
@@ -437,17 +445,49 @@ __global__ __launch_bounds__(NT, BUFS == 2 ? 2 : MODE == UP || MODE == WGD ? 3 :
   }
 }
 
+template <int MODE, int BUFS>
+__global__ __launch_bounds__(NT, BUFS == 2 ? 2 : Traits<MODE>::BLOCKS) void gemm_f32(Args p) {
+  __shared__ __align__(16) char lds[BUFS * Traits<MODE>::BUFFER];
+  gemm_tile<MODE, BUFS>(p, blockIdx.x, lds);
+}
+
+// Two GEMMs that do not depend on each other in one launch, the first one's tiles, which take longer, in blocks [0, first).
+template <int M1, int M2, int BUFS>
+__global__ __launch_bounds__(NT, BUFS == 2 ? 2 : (Traits<M1>::BLOCKS < Traits<M2>::BLOCKS ? Traits<M1>::BLOCKS : Traits<M2>::BLOCKS))
+void gemm_f32_pair(Args p1, Args p2, int first) {
+  __shared__ __align__(16) char lds[BUFS * (Traits<M1>::BUFFER > Traits<M2>::BUFFER ? Traits<M1>::BUFFER : Traits<M2>::BUFFER)];
+  if ((int)blockIdx.x < first) gemm_tile<M1, BUFS>(p1, blockIdx.x, lds);
+  else gemm_tile<M2, BUFS>(p2, blockIdx.x - first, lds);
+}
+
+// Two LDS buffers while at most two blocks share a CU: nothing else fills the gaps there.  The sums and their order are the same.
+// Training step before the operands were scaled, us, one buffer / two up to 256 blocks / two up to 512 (T, d, f, experts, k): 100,
+// 256, 512, 8, 2 107 / 99 / 97; 256, 1024, 512, 8, 1 170 / 152 / 151; 300, 400, 600, 16, 2 146 / 137 / 131; 600, 1000, 1000, 8, 2 300 /
+// 300 / 293.  At 1500, 520, 776, 16, 2 (800 blocks and more) two buffers for all take 87 + 176 for 79 + 160 in the six GEMMs.
+inline bool use_two(long long blocks) { return blocks <= 2 * device_cu_count(); }
+
 // m_tiles: bound on the row tiles of all experts
+inline long long tile_blocks(const Args& p, long long m_tiles) { return (m_tiles * ((p.N + TN - 1) / TN) + 7) / 8 * 8; }
+
 template <int MODE>
 int launch(const Args& p, long long m_tiles, hipStream_t s) {
-  const long long blocks = (m_tiles * ((p.N + TN - 1) / TN) + 7) / 8 * 8;
+  const long long blocks = tile_blocks(p, m_tiles);
   if (blocks >= (1ll << 31)) return MOE_EUNSUPPORTED;
-  // Two LDS buffers while at most two blocks share a CU: nothing else fills the gaps there.  The sums and their order are the same.
-  // Training step before the operands were scaled, us, one buffer / two up to 256 blocks / two up to 512 (T, d, f, experts, k): 100,
-  // 256, 512, 8, 2 107 / 99 / 97; 256, 1024, 512, 8, 1 170 / 152 / 151; 300, 400, 600, 16, 2 146 / 137 / 131; 600, 1000, 1000, 8, 2 300 /
-  // 300 / 293.  At 1500, 520, 776, 16, 2 (800 blocks and more) two buffers for all take 87 + 176 for 79 + 160 in the six GEMMs.
-  const auto kernel = blocks <= 2 * device_cu_count() ? gemm_f32<MODE, 2> : gemm_f32<MODE, 1>;
+  const auto kernel = use_two(blocks) ? gemm_f32<MODE, 2> : gemm_f32<MODE, 1>;
   hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(NT), 0, s, p);
+  HIP_CHECK_LAUNCH();
+  return MOE_OK;
+}
+
+template <int M1, int M2>
+int launch_pair(const Args& p1, long long m_tiles1, const Args& p2, long long m_tiles2, hipStream_t s) {
+  const long long first = tile_blocks(p1, m_tiles1), blocks = first + tile_blocks(p2, m_tiles2);
+  if (blocks >= (1ll << 31)) {
+    const int rc = launch<M1>(p1, m_tiles1, s);
+    return rc ? rc : launch<M2>(p2, m_tiles2, s);
+  }
+  const auto kernel = use_two(blocks) ? gemm_f32_pair<M1, M2, 2> : gemm_f32_pair<M1, M2, 1>;
+  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(NT), 0, s, p1, p2, (int)first);
   HIP_CHECK_LAUNCH();
   return MOE_OK;
 }
@@ -479,25 +519,36 @@ int launch_expert_bwd_f32(const float* xp, const float* h1, const float* h3, con
   float* dh1 = ws + (size_t)cap * f;
   float* dh3 = ws + 2 * (size_t)cap * f;
   int rc;
-  if (cap > 0) {
-    const long long mtb = ((long long)cap + TM - 1) / TM + e_cnt;
-    Args g = {};
-    g.A[0] = d_o; g.lda = d; g.B[0] = w2; g.ldb = d; g.b_es = (long)f * d;
-    g.C[0] = a_in ? nullptr : a; g.C[1] = dh1; g.C[2] = dh3; g.H[0] = h1; g.H[1] = h3; g.ldc = f;
-    g.N = f; g.K = d; g.off = offsets; g.e_cnt = e_cnt;
-    if ((rc = launch<DA>(g, mtb, s))) return rc;
-    Args x = {};
-    x.A[0] = dh1; x.A[1] = dh3; x.lda = f; x.B[0] = w1; x.B[1] = w3; x.ldb = f; x.b_es = (long)d * f;
-    x.C[0] = dxp; x.ldc = d; x.N = d; x.K = f; x.off = offsets; x.e_cnt = e_cnt;
-    if ((rc = launch<DX>(x, mtb, s))) return rc;
-  }
-  // dW2 takes the activation the forward kept, if the caller passed it, else the one recomputed above
+  const long long mtb = ((long long)cap + TM - 1) / TM + e_cnt;
+  Args g = {};
+  g.A[0] = d_o; g.lda = d; g.B[0] = w2; g.ldb = d; g.b_es = (long)f * d;
+  g.C[0] = a_in ? nullptr : a; g.C[1] = dh1; g.C[2] = dh3; g.H[0] = h1; g.H[1] = h3; g.ldc = f;
+  g.N = f; g.K = d; g.off = offsets; g.e_cnt = e_cnt;
+  Args x = {};
+  x.A[0] = dh1; x.A[1] = dh3; x.lda = f; x.B[0] = w1; x.B[1] = w3; x.ldb = f; x.b_es = (long)d * f;
+  x.C[0] = dxp; x.ldc = d; x.N = d; x.K = f; x.off = offsets; x.e_cnt = e_cnt;
+  // dW2 takes the activation the forward kept, if the caller passed it, else the one that dA recomputes
   Args w = {};
   w.A[0] = a_in ? a_in : a; w.lda = f; w.B[0] = d_o; w.ldb = d;
   w.C[0] = dw2; w.ldc = d; w.c_es = (long)f * d; w.M = f; w.N = d; w.off = offsets; w.e_cnt = e_cnt; w.beta = accumulate;
-  if ((rc = launch<WG>(w, (long long)e_cnt * ((f + TM - 1) / TM), s))) return rc;
   Args v = {};
   v.A[0] = xp; v.lda = d; v.B[0] = dh1; v.B[1] = dh3; v.ldb = f;
   v.C[0] = dw1; v.C[1] = dw3; v.ldc = f; v.c_es = (long)d * f; v.M = d; v.N = f; v.off = offsets; v.e_cnt = e_cnt; v.beta = accumulate;
-  return launch<WGD>(v, (long long)e_cnt * ((d + TM - 1) / TM), s);
+  // With the forward's activation dA and dW2 do not depend on each other, dX and dW1|dW3 never do: they share launches, the second
+  // one's blocks filling the CUs that the first one's leave.  dX has one round of blocks or less even where the gradients have
+  // several (T = 1500, d = 520, f = 776, 16 experts, k = 2: 568 and 1872 blocks for 768 places), and a small GEMM is little more
+  // than its launch, its first loads and its last stores.  Training steps, us, four launches / two (T, d, f, experts, k): 1500, 520,
+  // 776, 16, 2 292 / 265; 309, 736, 792, 32, 2 399 / 361; 261, 120, 992, 12, 4 176 / 157; 126, 336, 808, 8, 4 153 / 131.
+  const long long wt = (long long)e_cnt * ((f + TM - 1) / TM), vt = (long long)e_cnt * ((d + TM - 1) / TM);
+  if (cap == 0) {
+    if ((rc = launch<WG>(w, wt, s))) return rc;
+    return launch<WGD>(v, vt, s);
+  }
+  if (a_in) {
+    if ((rc = launch_pair<DA, WG>(g, mtb, w, wt, s))) return rc;
+  } else {
+    if ((rc = launch<DA>(g, mtb, s))) return rc;
+    if ((rc = launch<WG>(w, wt, s))) return rc;
+  }
+  return launch_pair<DX, WGD>(x, mtb, v, vt, s);
 }

@@ -174,6 +174,34 @@ def test_fp32_experts_with_one_and_two_buffers(d, f, rows):
     assert all(torch.equal(a, b) for a, b in zip(*results))
 
 
+# dA and dW2 share a launch where the forward's activation is kept, dX and dW1|dW3 always do: blocks beyond the tiles of the first GEMM,
+# one and two LDS buffers (the capacity decides), experts without rows, and the same bits as dA and dW2 in launches of their own
+@pytest.mark.parametrize("d,f,rows", [(4, 4, [1]), (68, 132, [65, 0, 3, 64]), (200, 520, [40, 0, 129, 7] * 4)])
+def test_fp32_gradients_that_share_launches(d, f, rows):
+    print(f"case fp32-shared-{d}-{f}", flush=True)
+    e_cnt, R = len(rows), sum(rows)
+    g = torch.Generator().manual_seed(d * f)
+    randn = lambda *shape: torch.randn(shape, generator=g)  # noqa: E731
+    x, d_o, weights = randn(R, d), randn(R, d), [randn(e_cnt, d, f) * d ** -0.5, randn(e_cnt, d, f) * d ** -0.5, randn(e_cnt, f, d) * f ** -0.5]
+    off, up = np.array([0] + rows).cumsum(), lambda t, cap: torch.cat([t, torch.zeros((cap - R, t.shape[1]))]).cuda()  # noqa: E731
+    args = [t.numpy().astype(np.float64) for t in (x, *weights, d_o)]
+    rh1, rh3, _, _ = O.expert_fwd(args[0], off, *args[1:4])
+    refs = O.expert_bwd(args[0], rh1, rh3, args[4], off, *args[1:4])
+    results = []
+    for cap in (R, 40000):
+        kept = fp32_pass(rows, x, *weights, d_o, cap=cap)
+        results.append([kept[n] for n in ("dxp", "dw1", "dw3", "dw2")])
+        dw, dxp = [torch.zeros_like(w).cuda() for w in weights], torch.zeros((cap, d), device="cuda")
+        ws = torch.empty(B.moe_workspace_bytes(B.WS_EXPERT_BWD, B.MOE_F32, R, 1, d, f, e_cnt, cap), dtype=torch.uint8, device="cuda")
+        B.moe_expert_bwd(up(x, cap), up(kept["h1"], cap), up(kept["h3"], cap), up(d_o, cap), torch.tensor(off, dtype=torch.int32, device="cuda"),
+                         *[w.cuda() for w in weights], dxp, *dw, False, ws)
+        for got, own, ref in zip(results[-1], (dxp[:R], *dw), refs):
+            assert rel_err(host(got), ref) < TOL["f32"] and rel_err(host(own), ref) < TOL["f32"]
+        assert all(torch.equal(got, own.cpu()) for got, own in zip(results[-1], (dxp[:R], *dw[:2])))
+    assert all(torch.equal(a, b) for a, b in zip(*results))
+
+
+
 # kernels for few rows: 16, 32 or 64 rows per block, wavefronts without a piece of the contraction (d = 64), columns past the end
 @pytest.mark.parametrize("T,d,f", [(1, 64, 64), (16, 192, 320), (17, 1088, 64), (33, 64, 192), (64, 320, 128), (65, 128, 448), (127, 256, 64)])
 def test_bf16_forward_with_few_rows(T, d, f):
