@@ -253,6 +253,8 @@ extern __shared__ __align__(16) char smem[];
 // c mod 8 (workgroup b runs on XCD b mod 8), whose workgroups draw tiles from it in order through one atomic counter per XCD.
 // take_ticket takes the ticket waiting in next_q[0], drawn from `queue`, and returns its tile, or -1 when the list is finished.
 // A workgroup whose queue has run dry draws from the next XCD's queue that still has tiles.
+// first: the tickets of every queue below it are not drawn: the workgroups of a launch's first GEMM begin with one each (256
+// atomics at a time take 1.7 us on average, the last of them 3).
 // spread: what is left after whole rounds of eight chunks is cut into eight equal ones.  A list shorter than the chip would
 // otherwise sit on a few XCDs, each of which reads memory at an eighth of the chip's rate (d = f = 4096, 4 experts of 250 rows: the
 // down projection's 64 tiles on two XCDs take 97 us, on eight 74).  Not where the tiles differ in length (ragged K): there a
@@ -263,7 +265,7 @@ extern __shared__ __align__(16) char smem[];
 // 3584); spreading more than 16 or 64 tiles only, or lists of less than one or four rounds only, was no better on the whole.
 template <bool SPREAD>
 __device__ __forceinline__ int take_ticket(int32_t* counters, int n_queues, int& queue, int total, int32_t* next_q, int wave, int lane,
-                                           bool spread = SPREAD) {
+                                           int first, bool spread = SPREAD) {
   const int rounds = total / (32 * n_queues), rest = total - rounds * 32 * n_queues;
   const int share = SPREAD && spread ? (rest + n_queues - 1) / n_queues : 32;
   while (true) {
@@ -281,7 +283,7 @@ __device__ __forceinline__ int take_ticket(int32_t* counters, int n_queues, int&
     __syncthreads();                         // everyone has read the ticket before it is replaced
     if (wave == 0) {
       int open = 0;
-      if (lane < n_queues) open = atomicAdd(counters + lane, 0) < 32 * rounds + max(0, min(share, rest - lane * share));
+      if (lane < n_queues) open = first + atomicAdd(counters + lane, 0) < 32 * rounds + max(0, min(share, rest - lane * share));
       const unsigned all = (1u << n_queues) - 1u;
       const unsigned m = (unsigned)__ballot(open) & all;
       if (lane == 0) {
@@ -291,7 +293,7 @@ __device__ __forceinline__ int take_ticket(int32_t* counters, int n_queues, int&
           const unsigned rot = ((m >> (queue + 1)) | (m << (n_queues - queue - 1))) & all;
           const int pick = (queue + 1 + __builtin_ctz(rot)) % n_queues;
           next_q[1] = pick;
-          next_q[0] = atomicAdd(counters + pick, 1);
+          next_q[0] = first + atomicAdd(counters + pick, 1);
         }
       }
     }
@@ -358,6 +360,19 @@ __device__ __forceinline__ int find_position(const int32_t* start, int n, int L,
     }
   }
   return __builtin_amdgcn_readfirstlane(a);
+}
+
+// Position of lane `lane` when the lanes are listed by descending v, ties by lane (whole wavefronts; lanes n .. 63 all hold the same
+// v, which is lower than the others').
+__device__ __forceinline__ int descending_rank(int v, int n, int lane) {
+  int rank = 0;
+  for (int first = 0; first < n; first += 8)
+#pragma unroll
+    for (int o = 0; o < 8; ++o) {
+      const int v2 = __builtin_amdgcn_readlane(v, first + o);
+      rank += (v2 > v || (v2 == v && first + o < lane)) ? 1 : 0;
+    }
+  return rank;
 }
 
 // ---- what an epilogue does with eight finished columns of a row
@@ -505,7 +520,7 @@ __device__ __forceinline__ void quarter_tiles(const GArgs& p, const Quarters& li
     else ib_kc.issue1(q - 4, st + QOPER_BYTES, wave, k0 + (seg1 ? p.B1 - p.B0 : 0));
   };
   auto next_tile = [&]() -> bool {
-    const int L = take_ticket<true>(counters, n_queues, queue, list.total, list.next_q, wave, lane);
+    const int L = take_ticket<true>(counters, n_queues, queue, list.total, list.next_q, wave, lane, 0);
     if (L < 0) return false;
     const int pos = find_position(list.start, p.e_cnt, L, hint);
     hint = pos;
@@ -678,8 +693,9 @@ __device__ __forceinline__ void quarter_tiles(const GArgs& p, const Quarters& li
   }
 }
 
-// One grouped GEMM from its set-up to its last tile, run by a persistent workgroup.
-template <int MODE>
+// One grouped GEMM from its set-up to its last tile, run by a persistent workgroup.  FIRST: the launch's first one, which all
+// workgroups begin together.
+template <int MODE, bool FIRST>
 __device__ __forceinline__ void gg_body(const GArgs& p) {
   using TR = Traits<MODE>;
   int32_t* tile_start = reinterpret_cast<int32_t*>(smem + TILE_LDS);
@@ -709,16 +725,29 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
     offs[e] = p.off ? p.off[e] : (int)(cut < p.rows ? cut : p.rows);
   }
   __syncthreads();
-  for (int e = tid; e < e_cnt; e += NT) {
-    const int rows = offs[e + 1] - offs[e];
-    int rank = 0;
-    for (int o = 0; o < e_cnt; ++o) {
-      const int r2 = offs[o + 1] - offs[o];
-      rank += (r2 > rows || (r2 == rows && o < e)) ? 1 : 0;
+  // (up to 64 experts: every wavefront by itself, one expert per lane)
+  const bool in_lanes = e_cnt <= WAVE;
+  int sorted = 0;                          // rows at position `lane`
+  if (in_lanes) {
+    const int rows = lane < e_cnt ? offs[lane + 1] - offs[lane] : -1;
+    const int rank = descending_rank(rows, e_cnt, lane);
+    sorted = __builtin_amdgcn_ds_permute(4 * rank, rows);
+    if (wave == 0 && lane < e_cnt) order[rank] = (uint16_t)lane;
+  } else {
+    for (int e = tid; e < e_cnt; e += NT) {
+      const int rows = offs[e + 1] - offs[e];
+      int rank = 0;
+      for (int o = 0; o < e_cnt; ++o) {
+        const int r2 = offs[o + 1] - offs[o];
+        rank += (r2 > rows || (r2 == rows && o < e)) ? 1 : 0;
+      }
+      order[rank] = (uint16_t)e;
     }
-    order[rank] = (uint16_t)e;
   }
   __syncthreads();
+  const auto rows_at = [&](int pos) {      // pos: the lane's of the 64 positions at hand
+    return pos >= e_cnt ? 0 : (in_lanes ? sorted : offs[order[pos] + 1] - offs[order[pos]]);
+  };
   if (TR::RAGGED_K) {
     // Every expert has the same number of output tiles, but a tile's cost is the expert's row
     // count.  An expert whose k loop is longer than a workgroup's fair share of the whole launch
@@ -744,7 +773,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
     const auto k_tiles = [&](int pos) { return (offs[order[pos] + 1] - offs[order[pos]] + BK - 1) / BK; };
     const float inv_grid = 1.f / (float)grid;
     float all = 0.f;                                  // k-tiles of one output tile of every expert
-    for (int pos = lane; pos < e_cnt; pos += WAVE) all += (float)k_tiles(pos);
+    for (int pos = lane; pos < e_cnt; pos += WAVE) all += (float)((rows_at(pos) + BK - 1) / BK);
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) all += __shfl_xor(all, o, WAVE);
     const float share = all * (float)wg_tiles_per_e * inv_grid;
@@ -753,11 +782,15 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
     if (may_cut) {
       const int heavy = min(e_cnt, HEAVY);
       volatile int32_t* mine = trial + wave * HEAVY;
-      mine[lane] = 1;
+      const int goal = target(wave), piece_cost = (int)(p.p_stride / 400000) + 1;
+      // every expert by itself while the budget holds them all, else one after the other
+      const int own = lane < heavy ? (rows_at(lane) + BK - 1) / BK : 0, want = min(255, (own + goal - 1) / goal);
+      const bool worth = wave < 3 && own > goal && own - (own + want - 1) / want > want * piece_cost;
+      mine[lane] = worth ? want : 1;
+      const bool over = wave_sum(wave < 3 && own > goal ? want : 0) > p.split_budget;
+      if (over) mine[lane] = 1;
       __builtin_amdgcn_wave_barrier();
-      if (lane == 0 && wave < 3) {
-        const int goal = target(wave);
-        const int piece_cost = (int)(p.p_stride / 400000) + 1;
+      if (lane == 0 && over) {
         int used = 0;
         for (int pos = 0; pos < heavy; ++pos) {
           const int nke = k_tiles(pos);
@@ -801,27 +834,37 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
     __syncthreads();
     // list the experts again, now by the length of one tile's k loop (a cut expert's pieces are
     // shorter than the tiles of the next heaviest ones), longest first
-    for (int e = tid; e < e_cnt; e += NT) {
-      const int len = ((offs[e + 1] - offs[e] + BK - 1) / BK + split[e] - 1) / split[e];
-      int rank = 0;
-      for (int o = 0; o < e_cnt; ++o) {
-        const int l2 = ((offs[o + 1] - offs[o] + BK - 1) / BK + split[o] - 1) / split[o];
-        rank += (l2 > len || (l2 == len && o < e)) ? 1 : 0;
+    const auto length = [&](int e) { return ((offs[e + 1] - offs[e] + BK - 1) / BK + split[e] - 1) / split[e]; };
+    if (in_lanes) {
+      if (wave == 0) {
+        const int rank = descending_rank(lane < e_cnt ? length(lane) : -1, e_cnt, lane);
+        if (lane < e_cnt) order[rank] = (uint16_t)lane;
       }
-      order[rank] = (uint16_t)e;
+    } else {
+      for (int e = tid; e < e_cnt; e += NT) {
+        const int len = length(e);
+        int rank = 0;
+        for (int o = 0; o < e_cnt; ++o) {
+          const int l2 = length(o);
+          rank += (l2 > len || (l2 == len && o < e)) ? 1 : 0;
+        }
+        order[rank] = (uint16_t)e;
+      }
+      __syncthreads();
     }
-    __syncthreads();
-    if (tid == 0) {
-      int run = 0, used = 0;
-      for (int pos = 0; pos < e_cnt; ++pos) {
-        const int e = order[pos];
-        const int pieces = split[e];
-        split[e] = pieces > 1 ? ((used << 8) | pieces) : 1;
-        if (pieces > 1) used += pieces;
-        tile_start[pos] = run;
-        run += pieces * wg_tiles_per_e;
+    if (wave == 0) {
+      int tiles = 0, used = 0;
+      for (int base = 0; base < e_cnt; base += WAVE) {
+        const int pos = base + lane, e = pos < e_cnt ? order[pos] : 0, pieces = pos < e_cnt ? split[e] : 0;
+        const int t = wave_scan(pieces), cut = pieces > 1 ? pieces : 0, c = wave_scan(cut);
+        if (pos < e_cnt) {
+          tile_start[pos] = (tiles + t - pieces) * wg_tiles_per_e;
+          if (cut) split[e] = ((used + c - cut) << 8) | pieces;
+        }
+        tiles += __builtin_amdgcn_readlane(t, WAVE - 1);
+        used += __builtin_amdgcn_readlane(c, WAVE - 1);
       }
-      tile_start[e_cnt] = run;
+      if (lane == 0) tile_start[e_cnt] = tiles * wg_tiles_per_e;
     }
     __syncthreads();
     big = tile_start[e_cnt];
@@ -839,7 +882,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
     // the part of a plan's 256x256 tiles that lies below its limit, and the quarters of the rest, of the 64 positions at base
     const auto place = [&](int base, int plan, int limit, int& before, int& quarters) {
       const int pos = base + lane;
-      const int rows = pos < e_cnt ? offs[order[pos] + 1] - offs[order[pos]] : 0;
+      const int rows = rows_at(pos);
       int m = tiles_m(rows, plan);
       const int first = before + wave_scan(m * n_tiles_n) - m * n_tiles_n;
       m = min(m, max(0, limit - first) / n_tiles_n);
@@ -849,7 +892,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
     int limit = 0x7FFFFFFF;
     if (SPLIT) {
       int all = 0;
-      for (int pos = lane; pos < e_cnt; pos += WAVE) all += tiles_m(offs[order[pos] + 1] - offs[order[pos]], wave) * n_tiles_n;
+      for (int pos = lane; pos < e_cnt; pos += WAVE) all += tiles_m(rows_at(pos), wave) * n_tiles_n;
       all = wave_sum(all);
       if (wave & 2) limit = all / (int)gridDim.x * (int)gridDim.x;
       int n_big = 0, n_quarter = 0, active_big = 0, active_quarter = 0;
@@ -915,6 +958,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
   const int G = gridDim.x;
   const int n_queues = (G % 8) == 0 ? 8 : 1;
   int queue = blockIdx.x % n_queues;       // the queue this workgroup currently draws from
+  const int first_ticket = FIRST ? G / n_queues : 0;
   int pos_hint = 0;                        // list position of the last decoded tile
   const uint32_t smem_base = lds_addr(smem);
 
@@ -972,7 +1016,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
   // called (it is called after the barrier that ends a k loop, before that tile's epilogue,
   // so the first operands of the next tile travel while the finished one is being stored).
   auto next_tile = [&]() -> bool {
-    const int L = take_ticket<!TR::RAGGED_K>(p.sched, n_queues, queue, big, next_q, wave, lane, MODE != DA || !p.pair_first);
+    const int L = take_ticket<!TR::RAGGED_K>(p.sched, n_queues, queue, big, next_q, wave, lane, first_ticket, MODE != DA || !p.pair_first);
     if (L < 0) return false;
     // Within an expert, tiles are ordered in bands of 8 m-tiles, n-tile next, m-tile inside the
     // band fastest: 32 consecutive tiles (one chunk) then form an 8 x 4 block that shares 8 A
@@ -1053,7 +1097,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
 
   bool have = big > 0;
   if (have) {
-    if (tid == 0) *next_q = atomicAdd(p.sched + queue, 1);
+    if (tid == 0) *next_q = FIRST ? (int)blockIdx.x / n_queues : atomicAdd(p.sched + queue, 1);
     __syncthreads();
     have = next_tile();
   }
@@ -1066,7 +1110,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
     // It is handed over through LDS after the k loop.
     int my_ticket = 0;
     const int kt_draw = nk > 8 ? nk - 8 : 0;
-    if (nk == 0 && tid == 0) my_ticket = atomicAdd(p.sched + queue, 1);
+    if (nk == 0 && tid == 0) my_ticket = first_ticket + atomicAdd(p.sched + queue, 1);
 
     f32x16 acc[4][4];
 #pragma unroll
@@ -1143,7 +1187,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
       // fragment read o is needed iff it feeds a live MFMA: A0, B0..B3, A1, A2, A3
       auto live = [](int o) { return MV == 4 || (MV == 2 && o <= 5); };
       for (int kt = 0; kt < nk; ++kt) {
-        if (kt == kt_draw && tid == 0) my_ticket = atomicAdd(p.sched + queue, 1);
+        if (kt == kt_draw && tid == 0) my_ticket = first_ticket + atomicAdd(p.sched + queue, 1);
         if (TR::RAGGED_K && kt == nk - 1) mask_tail(0, kt, 0);
         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -1216,7 +1260,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
         }
       };
       for (int kt = 0; kt < nk; kt += 2) {
-        if (kt == kt_draw && tid == 0) my_ticket = atomicAdd(p.sched + queue, 1);
+        if (kt == kt_draw && tid == 0) my_ticket = first_ticket + atomicAdd(p.sched + queue, 1);
         iteration(kt, IntC<0>{});
         iteration(kt + 1, IntC<1>{});
       }
@@ -1423,7 +1467,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
 
 template <int MODE>
 __global__ __launch_bounds__(NT, 1) void gg_kernel(GArgs p) {
-  gg_body<MODE>(p);
+  gg_body<MODE, true>(p);
 }
 
 // Whether the kernel for few rows is the faster one at these row counts (whole wavefronts; the same answer in all of them): its
@@ -1476,7 +1520,7 @@ __global__ __launch_bounds__(NT, 1) void gg_or_few(GArgs p, int d, int f) {
     for (int b = blockIdx.x; few_rows_tile<MODE == UP, NW_TILES>(q, list, reinterpret_cast<u32x4*>(smem), b); b += gridDim.x) {}
     return;
   }
-  gg_body<MODE>(p);
+  gg_body<MODE, true>(p);
 }
 
 // Two grouped GEMMs that do not depend on each other in one launch: a workgroup that finds no tile
@@ -1484,9 +1528,9 @@ __global__ __launch_bounds__(NT, 1) void gg_or_few(GArgs p, int d, int f) {
 // last round of whole tiles, in which most CUs would idle) and one launch boundary goes away.
 template <int M1, int M2>
 __global__ __launch_bounds__(NT, 1) void gg_pair(GArgs p1, GArgs p2) {
-  gg_body<M1>(p1);
+  gg_body<M1, true>(p1);
   __syncthreads();          // the first GEMM's scheduler tables in LDS are rewritten by the second's set-up
-  gg_body<M2>(p2);
+  gg_body<M2, false>(p2);
 }
 
 __global__ void zero_words(int32_t* p, int n) {

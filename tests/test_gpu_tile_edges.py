@@ -360,6 +360,12 @@ def test_weight_gradients_of_heavy_experts(d, f, rows):
             assert rel_err(host(got), host(ref)) < TOL["bf16"]
 
 
+# as many experts as a wavefront has lanes, and more: lists of tiles and pieces are then made 64 experts at a time
+@pytest.mark.parametrize("d,f,rows", [(192, 64, [5, 0, 3000, 1] + [2] * 60), (128, 64, [1, 0] * 34 + [2500, 3, 700])])
+def test_weight_gradients_of_more_experts_than_lanes(d, f, rows):
+    test_weight_gradients_of_heavy_experts(d, f, rows)
+
+
 # logits of 8 to 56 experts: eight fp32 sums per output and wavefront, added in pairs.  A block of 256 threads that adds the same
 # products in 256 chains and a tree is off by 6.2e-8 / 7.3e-8 / 8.3e-8 of the logits' norm, chains of matrix instructions by
 # 7.1e-8 / 1.03e-7 / 1.8e-7; the bounds are halfway for the longer contractions, 5 % above the first for the shortest
