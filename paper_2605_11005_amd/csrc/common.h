@@ -105,6 +105,28 @@ __device__ __forceinline__ float silu_grad_f(float z, float* ds) {
   return z * s;
 }
 
+// 16 bytes per lane from global memory straight into LDS: lane l lands at lds_wave_base + 16*l
+// (lds_wave_base is wave-uniform and travels in M0).  The global address is a wave-uniform
+// 64-bit base in SGPRs plus a 32-bit per-lane byte offset: with 64-bit per-lane addresses the
+// address path, not the data path, limits a CU to ~27 B/clk; this form sustains ~42 B/clk.
+// Written as inline assembly so that the compiler's wait-count pass does not serialise later
+// LDS reads against these loads; the kernel waits for them itself (s_waitcnt vmcnt) before
+// the barrier that publishes a tile.
+__device__ __forceinline__ void lds_load16(const bf16_t* sbase, uint32_t voff_bytes, uint32_t lds_wave_base) {
+  // make the uniformity of the base explicit so that it is allocated to an SGPR pair
+  const uint64_t u = (uint64_t)sbase;
+  const uint64_t ub = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32)) << 32) |
+                      (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
+  sbase = (const bf16_t*)ub;
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+               :
+               : "s"(lds_wave_base), "v"(voff_bytes), "s"(sbase)
+               : "memory", "m0");
+}
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
+}
+
 #define HIP_CHECK_LAUNCH()                                  \
   do {                                                      \
     if (hipGetLastError() != hipSuccess) return MOE_EHIP;   \

@@ -114,28 +114,6 @@ template <int MODE> struct Traits {
   static constexpr int BN_EFF = DUAL ? BN / 2 : BN;   // output columns covered per tile
 };
 
-// 16 bytes per lane from global memory straight into LDS: lane l lands at lds_wave_base + 16*l
-// (lds_wave_base is wave-uniform and travels in M0).  The global address is a wave-uniform
-// 64-bit base in SGPRs plus a 32-bit per-lane byte offset: with 64-bit per-lane addresses the
-// address path, not the data path, limits a CU to ~27 B/clk; this form sustains ~42 B/clk.
-// Written as inline assembly so that the compiler's wait-count pass does not serialise later
-// LDS reads against these loads; the kernel waits for them itself (s_waitcnt vmcnt) before
-// the barrier that publishes a tile.
-__device__ __forceinline__ void dma16(const bf16_t* sbase, uint32_t voff_bytes, uint32_t lds_wave_base) {
-  // make the uniformity of the base explicit so that it is allocated to an SGPR pair
-  const uint64_t u = (uint64_t)sbase;
-  const uint64_t ub = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32)) << 32) |
-                      (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
-  sbase = (const bf16_t*)ub;
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :
-               : "s"(lds_wave_base), "v"(voff_bytes), "s"(sbase)
-               : "memory", "m0");
-}
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
-}
-
 // ---- K-contiguous operand B (source rows are tile rows; a k-tile is 64 contiguous bytes) -
 // Wavefront w issues 4 loads per k-tile; load j covers LDS chunks [(4w+j)*64, +64):
 // row = 16*(4w+j) + lane/4, LDS slot = lane%4, logical chunk = slot ^ ((row>>2)&3).
@@ -155,7 +133,7 @@ struct KcIssue {
     }
   }
   __device__ __forceinline__ void issue1(int j, uint32_t oper_lds, int wave, long kofs) const {
-    dma16(base + kofs, voff[j], oper_lds + (4 * wave + j) * 1024);
+    lds_load16(base + kofs, voff[j], oper_lds + (4 * wave + j) * 1024);
   }
 };
 
@@ -180,7 +158,7 @@ struct KcPairIssue {
     }
   }
   __device__ __forceinline__ void issue1(int q, uint32_t dstage_lds, int wave, long kofs) const {
-    dma16(base + kofs, voff[q], dstage_lds + (8 * wave + q) * 1024);
+    lds_load16(base + kofs, voff[q], dstage_lds + (8 * wave + q) * 1024);
   }
 };
 
@@ -211,7 +189,7 @@ struct TrIssue {
     const int id = 4 * wave + j;
     int kr = 4 * (id & 7) + (lane >> 4);
     if (CLAMP && kr > k_last_rel) kr = k_last_rel;
-    dma16(src + k0 * ld, (uint32_t)(kr * ld * 2) + coff, oper_lds + id * 1024);
+    lds_load16(src + k0 * ld, (uint32_t)(kr * ld * 2) + coff, oper_lds + id * 1024);
   }
 };
 
@@ -438,7 +416,7 @@ struct QuarterKc {         // load j of a wavefront: rows 8*(4w+j) + lane/8, who
     }
   }
   __device__ __forceinline__ void issue1(int j, uint32_t oper_lds, int wave, long kofs) const {
-    dma16(base + kofs, voff[j], oper_lds + (4 * wave + j) * 1024);
+    lds_load16(base + kofs, voff[j], oper_lds + (4 * wave + j) * 1024);
   }
 };
 struct QuarterTr {         // sub-tile wave/2, load j: k rows 8*(4*(w%2)+j) + lane/8, 64 columns each
@@ -455,7 +433,7 @@ struct QuarterTr {         // sub-tile wave/2, load j: k rows 8*(4*(w%2)+j) + la
   __device__ __forceinline__ void issue1(int j, uint32_t oper_lds, int wave, int lane, long k0, int k_last_rel) const {
     int kr = 8 * (4 * (wave & 1) + j) + (lane >> 3);
     if (CLAMP && kr > k_last_rel) kr = k_last_rel;
-    dma16(src + k0 * ld, (uint32_t)(kr * ld * 2) + coff, oper_lds + (4 * wave + j) * 1024);
+    lds_load16(src + k0 * ld, (uint32_t)(kr * ld * 2) + coff, oper_lds + (4 * wave + j) * 1024);
   }
 };
 // transposed sub-tile: byte offset of the first transposing read of 32 columns at nl (0 or 32), k-step 0; add s*2048 + t*512

@@ -30,7 +30,7 @@ struct SArgs {
 };
 
 // Loads go through a buffer descriptor: a wave-uniform base and a 32-bit byte offset per lane (64-bit addresses per lane limit
-// a CU's address path, see dma16 in expert_bf16.hip).  A descriptor of length
+// a CU's address path, see lds_load16 in common.h).  A descriptor of length
 // zero makes a load return zeros without touching memory: pieces past the end of a wavefront's share are issued that way,
 // which keeps the number of loads, and so the wait counts, the same for every piece.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t descriptor(const bf16_t* base, bool in) {

@@ -665,6 +665,7 @@ int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int d
                          dwr_acc);
       HIP_CHECK_LAUNCH();
     }
+    if (dx && router_dx_streams(E, d)) return launch_router_dx_stream(dlb, wr, T, d, E, dx, dx_acc, s);
     if (dx) return launch_router_dx_bf16(dlb, wr, T, d, E, dx, dx_acc, sched + 8, s);
     return MOE_OK;
   }
@@ -690,6 +691,7 @@ int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int d
       hipLaunchKernelGGL((reduce_chunks<float>), dim3(red_blocks), dim3(256), 0, s, partial, splits, n_w, (float*)dwr, dwr_acc);
     HIP_CHECK_LAUNCH();
   }
+  if (dx && T > 0 && dtype == MOE_BF16 && router_dx_streams(E, d)) return launch_router_dx_stream(dlogits, wr, T, d, E, dx, dx_acc, s);
   if (dx && T > 0) {
     ProfScope prof(MOE_K_ROUTER_DX, s);
     if (dtype == MOE_BF16 && (E == 8 || E == 16) && (long long)T * d * E >= (1ll << 23)) {

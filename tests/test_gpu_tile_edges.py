@@ -294,6 +294,31 @@ def test_router_backward_at_block_edges(T, d, E, streams):
     assert rel_err(host(dwr), 2.0 * dwr_ref) < tol
 
 
+# router_dx.hip: rounded dlogits (E = 64, 128, 192, 256) and three terms of them (32, 96, 160); one token, tiles of 32 and 64 tokens with one
+# more or less, several tiles and ranges per block; wavefronts past the last column.  Against the products of what the kernel is given
+# (bf16 dlogits where E % 64 == 0), 2**-8 for the one rounding of a result, bit for bit without the products
+@pytest.mark.parametrize("T,d,E", [(1, 64, 32), (33, 192, 96), (65, 320, 32), (127, 256, 160), (31, 64, 64), (64, 576, 128), (129, 448, 192),
+                                   (20011, 64, 96), (9001, 512, 64), (33, 320, 256)])
+def test_router_input_gradient_stream(T, d, E):
+    print(f"case router-dx-{T}-{d}-{E}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T + d + E)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda")  # noqa: E731
+    x, wr, dl, dx0 = randn(T, d).bfloat16(), randn(d, E).bfloat16(), randn(T, E) * 0.1, randn(T, d).bfloat16()
+    ws = torch.empty(B.moe_workspace_bytes(B.WS_ROUTER, B.MOE_BF16, T, 1, d, 0, E, 0), dtype=torch.uint8, device="cuda")
+    ref = (dl.bfloat16() if E % 64 == 0 else dl).double() @ wr.double().t()
+    for accumulate in (False, True):
+        room = torch.full((T + 1, d), 3.0, device="cuda", dtype=torch.bfloat16)
+        room[:T] = dx0
+        B.moe_router_bwd(x, wr, dl, None, False, room[:T], accumulate, ws)
+        want = ref + (dx0.double() if accumulate else 0.0)
+        assert ((room[:T].double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5 * ref.abs().max()).all() and (room[T] == 3.0).all()
+    dl[T // 2] = 0.0
+    dl[T - 1, E - 1] = float("inf")
+    B.moe_router_bwd(x, wr, dl, None, False, room[:T], False, ws)
+    assert (room[T - 1] == wr[:, E - 1].float() * float("inf")).all() and (T < 3 or (room[T // 2] == 0.0).all())
+    assert torch.isfinite(room[:T - 1]).all()
+
+
 # a token's selection and the counts, with one, two and four blocks per CU (the lines lie at 64 and 256 tokens per CU)
 @pytest.mark.parametrize("T", [16385, 65537])
 def test_route_of_many_tokens_equals_the_route_of_a_few(T):
