@@ -621,7 +621,8 @@ int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int d
   const size_t n_w = (size_t)d * E;
   const int red_blocks = device_cu_count() * 4;
   int rc;
-  // Weight gradient of up to 128 experts: the streaming kernel, if the workspace's partial sums leave room for its operand
+  // Weight gradient: router_dw.hip where router_dw_streams says so; else, up to 128 experts, the streaming kernel of few rows, both
+  // if the workspace's partial sums leave room for the operand
   // beside at least one sum per plane.  Its sums need no more bytes than the cut product's.  More than 64 rows of planes take
   // two passes over x, which the big tiles overtake where x is large: E = 128, streaming / tiles, us: T = 32768, d = 2048
   // 62 / 71; 16384, 4096 60 / 63; 16384, 7168 91 / 84; 32768, 4096 109 / 101; 65536, 4096 198 / 164.
@@ -630,8 +631,9 @@ int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int d
   const size_t sum_bytes = n_w * 4;
   const size_t room = mfma ? align256((size_t)router_dw_splits(T, d, E) * sum_bytes) : align256((size_t)valu_splits(T, d, E) * sum_bytes);
   const size_t piece_bytes = align256((size_t)((T + 31) / 32) * 32 * planes * E * 2);
-  const bool dw_small = dwr && dtype == MOE_BF16 && T >= 32 && d % 64 == 0 && planes * E <= 128 &&
-                        !(mfma && E > 64 && (long long)T * d > (1ll << 26)) && room >= piece_bytes + planes * sum_bytes;
+  const bool dw_wide = dwr && dtype == MOE_BF16 && router_dw_streams(T, d, E) && room >= piece_bytes + sum_bytes;      // router_dw.hip
+  const bool dw_small = dw_wide || (dwr && dtype == MOE_BF16 && T >= 32 && d % 64 == 0 && planes * E <= 128 &&
+                        !(mfma && E > 64 && (long long)T * d > (1ll << 26)) && room >= piece_bytes + planes * sum_bytes);
   const auto dw_operands = [&](bf16_t* dlb, bf16_t* pieces) -> int {
     ProfScope prof(dwr ? MOE_K_ROUTER_DW : MOE_K_ROUTER_DX, s);
     if (!pieces)
@@ -645,7 +647,9 @@ int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int d
   const auto dw_stream = [&](bf16_t* pieces) -> int {
     float* sums = (float*)((char*)pieces + piece_bytes);
     int n = 0;
-    const int rc2 = launch_router_dw_small(x, pieces, planes, T, d, E, sums, (int)((room - piece_bytes) / sum_bytes), &n, s);
+    const int most = (int)((room - piece_bytes) / sum_bytes);
+    const int rc2 = dw_wide ? launch_router_dw_stream(x, pieces, T, d, E, sums, most, &n, s)
+                            : launch_router_dw_small(x, pieces, planes, T, d, E, sums, most, &n, s);
     if (rc2) return rc2;
     ProfScope prof(MOE_K_ROUTER_DW, s);
     hipLaunchKernelGGL((reduce_chunks<bf16_t>), dim3(red_blocks), dim3(256), 0, s, sums, n, n_w, (bf16_t*)dwr, dwr_acc);

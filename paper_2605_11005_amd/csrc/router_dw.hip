@@ -1,0 +1,172 @@
+// Weight gradient of the trainable router, dWr = x^T dlogits, in bf16 for 32 to 256 experts: a stream over x.
+//
+// Bound by reading x once (T d 2 bytes).  A block owns 128 columns of x, all experts and a range of tokens; its four wavefronts
+// hold 64 columns by half of the experts each as 32x32 blocks of sums.  Pieces of 32 tokens pass through a ring in LDS, four to
+// eight of them, so that 30 to 56 KB of x per CU are on their way: x in its own layout, read by the transposing LDS reads, the
+// dlogits as router_dl_operands lays them out, tokens contiguous.  The fp32 sums of a range go to memory and reduce_chunks adds
+// them up; one block per CU keeps those few.
+#include "common.h"
+#include "kernels.h"
+
+namespace {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef short s16x4 __attribute__((ext_vector_type(4)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+constexpr int NT = 256, COLS = 128, PIECE = 32;
+
+// NE: experts / 32; PLANES: terms per dlogit (1: rounded to bf16, 3: their sum keeps all 24 bits)
+template <int NE, int PLANES> struct Shape {
+  static constexpr int E = 32 * NE;
+  static constexpr int X_BYTES = COLS * PIECE * 2, STAGE = X_BYTES + PLANES * E * PIECE * 2;
+  static constexpr int STAGES = 155 * 1024 / STAGE < 8 ? 155 * 1024 / STAGE : 8;
+  static constexpr int DL_LOADS = PLANES * E / 16, PER_WAVE = (DL_LOADS + 3) / 4, LOADS = 2 + PER_WAVE;      // of 1 KB, per stage
+  static constexpr int BLOCKS = (NE + 1) / 2;       // of 32 experts, per wavefront
+  static_assert((STAGES - 2) * LOADS < 64 && STAGES >= 3, "the wait counter holds 63");
+};
+
+// 32 columns from n on of the [32 tokens][64 columns] tile at p, k-step s of 16 tokens; chunk' = chunk ^ (4*((token>>1)&1))
+__device__ __forceinline__ bf16x8 x_fragment(const char* p, int n, int s, int lane) {
+  const int i = lane & 15, g = lane >> 4;
+  const int t = 8 * (g >> 1) + (i >> 2), c = n + 16 * (g & 1) + 4 * (i & 3);
+  const char* q = p + s * 2048 + t * 128 + (((c >> 3) ^ (4 * ((t >> 1) & 1))) << 4) + ((c & 4) << 1);
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)q);
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s16x4*)(q + 512));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+template <int NE, int PLANES>
+__global__ __launch_bounds__(NT, 1) void router_dw_stream(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dl, float* __restrict__ sums,
+                                                         int T, int d, int n_cols, int per_range) {
+  using S = Shape<NE, PLANES>;
+  extern __shared__ __align__(16) char lds[];
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wc = wave >> 1, we = wave & 1;
+  const int range = blockIdx.x / n_cols, c0 = (blockIdx.x - range * n_cols) * COLS;
+  const int first = range * per_range, n = min(per_range, (T + PIECE - 1) / PIECE - first);       // pieces
+  const uint32_t base = lds_addr(lds);
+
+  // stage s: piece first + s, in place s % STAGES; past the end the last piece again, so that the number of loads stays the same
+  auto issue = [&](int s) {
+    const int piece = first + min(s, n - 1), t0 = min(piece * PIECE, T - PIECE);      // (the last piece ends at the last token)
+    const uint32_t at = base + s % S::STAGES * S::STAGE;
+#pragma unroll
+    for (int j = 0; j < 2; ++j) {         // 8 tokens of 64 columns
+      const int id = 2 * wave + j, t = 8 * (id & 3) + (lane >> 3), chunk = (lane & 7) ^ (4 * ((lane >> 4) & 1));
+      const int c = min(c0 + 64 * (id >> 2) + 8 * chunk, d - 8);
+      lds_load16(x + (size_t)t0 * d, (uint32_t)((t * d + c) * 2), at + id * 1024);
+    }
+#pragma unroll
+    for (int j = 0; j < S::PER_WAVE; ++j) {      // 16 experts of a plane: chunk' = chunk ^ ((expert>>2)&3)
+      const int id = min(wave * S::PER_WAVE + j, S::DL_LOADS - 1);
+      lds_load16(dl + (size_t)piece * PLANES * S::E * PIECE, (uint32_t)(id * 1024 + (lane >> 2) * 64 + (((lane & 3) ^ ((lane >> 4) & 3)) << 4)),
+                 at + S::X_BYTES + id * 1024);
+    }
+  };
+  f32x16 acc[2][S::BLOCKS];
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+#pragma unroll
+    for (int b = 0; b < S::BLOCKS; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[m][b][r] = 0.f;
+  int expert[S::BLOCKS];                  // of this lane; past the last one it again (never stored)
+#pragma unroll
+  for (int b = 0; b < S::BLOCKS; ++b) expert[b] = min((we * S::BLOCKS + b) * 32 + (lane & 31), S::E - 1);
+
+#pragma unroll
+  for (int s = 0; s < S::STAGES - 1; ++s) issue(s);
+  for (int s = 0; s < n; ++s) {
+    // stage s has landed once those after it are all that is on its way; and everyone is done with the one whose place is filled next
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"((S::STAGES - 2) * S::LOADS) : "memory");
+    __builtin_amdgcn_s_barrier();
+    issue(s + S::STAGES - 1);
+    const char* const stage = lds + s % S::STAGES * S::STAGE;
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      const bf16x8 f0 = x_fragment(stage + wc * 4096, 0, k, lane), f1 = x_fragment(stage + wc * 4096, 32, k, lane);
+#pragma unroll
+      for (int p = 0; p < PLANES; ++p)
+#pragma unroll
+        for (int b = 0; b < S::BLOCKS; ++b) {
+          const int row = p * S::E + expert[b];
+          const bf16x8 g = *reinterpret_cast<const bf16x8*>(stage + S::X_BYTES + row * 64 + (((2 * k + (lane >> 5)) ^ ((row >> 2) & 3)) << 4));
+          acc[0][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f0, g, acc[0][b], 0, 0, 0);
+          acc[1][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1, g, acc[1][b], 0, 0, 0);
+        }
+    }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  float* const out = sums + (size_t)range * d * S::E;
+#pragma unroll
+  for (int m = 0; m < 2; ++m) {
+    const int col = c0 + 64 * wc + 32 * m + 4 * (lane >> 5);
+    if (col >= d) continue;               // d % 64 == 0: 32 columns at a time
+#pragma unroll
+    for (int b = 0; b < S::BLOCKS; ++b) {
+      const int e = (we * S::BLOCKS + b) * 32 + (lane & 31);
+      if (e >= S::E) continue;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) out[(size_t)(col + 8 * (r >> 2) + (r & 3)) * S::E + e] = acc[m][b][r];
+    }
+  }
+}
+
+template <int NE, int PLANES>
+int launch(const bf16_t* x, const bf16_t* dl, float* sums, int T, int d, int max_sums, int* n_sums, hipStream_t s) {
+  using S = Shape<NE, PLANES>;
+  constexpr int LDS = S::STAGES * S::STAGE;
+  static bool attr_set[64] = {};         // a per-device attribute of the kernel
+  int dev = 0;
+  if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return MOE_EHIP;
+  if (!attr_set[dev]) {
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(&router_dw_stream<NE, PLANES>), hipFuncAttributeMaxDynamicSharedMemorySize,
+                            LDS) != hipSuccess)
+      return MOE_EHIP;
+    attr_set[dev] = true;
+  }
+  // one block per CU; ranges of at least four pieces
+  const int n_cols = (d + COLS - 1) / COLS, pieces = (T + PIECE - 1) / PIECE;
+  int ranges = device_cu_count() / n_cols;
+  if (ranges > pieces / 4) ranges = pieces / 4;
+  if (ranges > max_sums) ranges = max_sums;
+  if (ranges < 1) ranges = 1;
+  const int per = (pieces + ranges - 1) / ranges;
+  ranges = (pieces + per - 1) / per;
+  ProfScope prof(MOE_K_ROUTER_DW, s);
+  hipLaunchKernelGGL((router_dw_stream<NE, PLANES>), dim3((unsigned)(ranges * n_cols)), dim3(NT), LDS, s, x, dl, sums, T, d, n_cols, per);
+  HIP_CHECK_LAUNCH();
+  *n_sums = ranges;
+  return MOE_OK;
+}
+
+}  // namespace
+
+// dl: pieces of router_dl_operands, one plane where E % 64 == 0, three of 32, 96 or 160 experts; T >= 32.
+// Weight gradient alone (operands, product, reduction), us, the streaming kernel of few rows (E <= 128 and E = 32), big tiles (E = 192,
+// 256) or plain fp32 products (E = 96, 160) / this one:
+//   T = 16384, d = 4096, E = 128  60 / 45     T = 9001, d = 2880, E = 128  37 / 33      T = 4096, d = 2048, E = 64  22 / 19 (kernels alone)
+//   T = 8192, d = 2048, E = 32    30 / 22     T = 30000, d = 7168, E = 32  225 / 126    T = 8192, d = 2048, E = 96  112 / 35
+//   T = 2000, d = 7168, E = 256   50 / 42     T = 9000, d = 7168, E = 256  73 / 68      T = 16384, d = 7168, E = 256  103 / 114
+//   T = 1000, d = 2880, E = 128   20 / 22     T = 3000, d = 1024, E = 128  21 / 24      T = 100, d = 4096, E = 32  14 / 17
+// Small x are the few rows' (their sums are fewer); 192 and more experts of a large x the big tiles', which read the dlogits half as
+// often per column.  Two pieces per barrier were no faster (E = 256 slower).
+bool router_dw_streams(int T, int d, int E) {
+  if (T < PIECE || d % 64) return false;
+  if (E == 96 || E == 160) return true;
+  const long long x = (long long)T * d;
+  return x >= (1ll << 22) && (E == 32 || E == 64 || E == 128 || ((E == 192 || E == 256) && x <= (1ll << 26)));
+}
+int launch_router_dw_stream(const void* x, const void* dl, int T, int d, int E, float* sums, int max_sums, int* n_sums, hipStream_t s) {
+  const bf16_t *a = (const bf16_t*)x, *b = (const bf16_t*)dl;
+  switch (E / 32) {
+    case 1: return launch<1, 3>(a, b, sums, T, d, max_sums, n_sums, s);
+    case 2: return launch<2, 1>(a, b, sums, T, d, max_sums, n_sums, s);
+    case 3: return launch<3, 3>(a, b, sums, T, d, max_sums, n_sums, s);
+    case 4: return launch<4, 1>(a, b, sums, T, d, max_sums, n_sums, s);
+    case 5: return launch<5, 3>(a, b, sums, T, d, max_sums, n_sums, s);
+    case 6: return launch<6, 1>(a, b, sums, T, d, max_sums, n_sums, s);
+    default: return launch<8, 1>(a, b, sums, T, d, max_sums, n_sums, s);
+  }
+}

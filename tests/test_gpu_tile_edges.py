@@ -319,6 +319,25 @@ def test_router_input_gradient_stream(T, d, E):
     assert torch.isfinite(room[:T - 1]).all()
 
 
+# router_dw.hip, one plane (E = 64, 128, 192, 256) and three (32, 96, 160): fewer pieces than the ring holds, a last piece that overlaps
+# the one before it, several ranges, a last block of 64 columns.  Against float64; the results are rounded to bf16 (2**-8), bf16
+# dlogits first (then: against what the kernel is given), sums of up to T products in fp32 (1e-5 of the largest)
+@pytest.mark.parametrize("T,d,E", [(32, 64, 96), (33, 192, 160), (300, 320, 96), (65600, 64, 32), (21900, 192, 64), (6600, 640, 128),
+                                   (4100, 1024, 192), (4097, 1088, 256)])
+def test_router_weight_gradient_stream(T, d, E):
+    print(f"case router-dw-{T}-{d}-{E}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T + d + E)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda")  # noqa: E731
+    x, wr, dl, dw0 = randn(T, d).bfloat16(), randn(d, E).bfloat16(), randn(T, E) * 0.1, randn(d, E).bfloat16()
+    ws = torch.empty(B.moe_workspace_bytes(B.WS_ROUTER, B.MOE_BF16, T, 1, d, 0, E, 0), dtype=torch.uint8, device="cuda")
+    ref = x.double().t() @ (dl.bfloat16() if E % 64 == 0 else dl).double()
+    for accumulate in (False, True):
+        dwr = dw0.clone()
+        B.moe_router_bwd(x, wr, dl, dwr, accumulate, None, False, ws)
+        want = ref + (dw0.double() if accumulate else 0.0)
+        assert ((dwr.double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5 * ref.abs().max()).all()
+
+
 # a token's selection and the counts, with one, two and four blocks per CU (the lines lie at 64 and 256 tokens per CU)
 @pytest.mark.parametrize("T", [16385, 65537])
 def test_route_of_many_tokens_equals_the_route_of_a_few(T):
