@@ -258,6 +258,8 @@ int moe_dispatch(const void* x, int dtype, int T, int d, int k, const int32_t* t
   if (!reuse_plan) {
     if (T > 0 && !topk_idx) return MOE_EINVAL;
     if (!ws || misaligned(ws, 256) || ws_bytes < plan_ws_bytes(T, k, e_cnt)) return MOE_EWORKSPACE;
+    if (plan_and_dispatch_fits(T, k, d, dtype))
+      return launch_plan_and_dispatch(x, dtype, T, d, k, topk_idx, row_scale, e_lo, e_cnt, offsets, perm, inv, cap, (int32_t*)ws, xp, s);
     int rc = launch_plan(topk_idx, T, k, e_lo, e_cnt, offsets, perm, inv, cap, ws, nullptr, s);
     if (rc) return rc;
   }
@@ -282,6 +284,9 @@ int moe_dispatch_static(const void* x, int dtype, int T, int d, int k, const int
   int rc = plan_static_scratch(&ws);
   if (rc) return rc;
   hipStream_t s = (hipStream_t)stream;
+  if (plan_and_dispatch_fits(T, k, d, dtype))
+    return launch_plan_and_dispatch(x, dtype, T, d, k, topk_idx, row_scale, e_lo, e_cnt, offsets, perm, inv, cap,
+                                    status ? status : (int32_t*)ws, xp, s);
   if ((rc = launch_plan(topk_idx, T, k, e_lo, e_cnt, offsets, perm, inv, cap, ws, status, s))) return rc;
   return launch_dispatch_rows(x, dtype, T, d, k, inv, row_scale, xp, s);
 }

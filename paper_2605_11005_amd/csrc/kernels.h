@@ -18,6 +18,10 @@ int plan_static_scratch(void** ptr);
 
 int launch_dispatch_rows(const void* x, int dtype, int T, int d, int k, const int32_t* inv,
                          const float* row_scale, void* xp, hipStream_t s);
+// plan and move in one launch, for few slots
+bool plan_and_dispatch_fits(int T, int k, int d, int dtype);
+int launch_plan_and_dispatch(const void* x, int dtype, int T, int d, int k, const int32_t* topk_idx, const float* row_scale, int e_lo,
+                             int e_cnt, int32_t* offsets, int32_t* perm, int32_t* inv, int cap, int32_t* status, void* xp, hipStream_t s);
 int launch_combine_rows(const void* o, int dtype, int T, int d, int k, const int32_t* inv,
                         const float* topk_w, void* y, hipStream_t s);
 

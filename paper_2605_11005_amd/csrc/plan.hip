@@ -12,7 +12,8 @@
 //                      the key) and a popcount of the lower lanes, and a per-wave LDS counter
 //                      carries it forward.
 // Small batches (up to SMALL_SLOTS slots) take plan_small instead: the same three steps in one
-// block, whose wavefronts are the chunks.
+// block, whose wavefronts are the chunks.  The smallest are planned by the dispatch itself
+// (plan_and_dispatch in rowmove.hip).
 #include "common.h"
 #include "kernels.h"
 

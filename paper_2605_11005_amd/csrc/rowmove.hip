@@ -65,6 +65,88 @@ __global__ __launch_bounds__(DISPATCH_BLOCK) void dispatch_rows(const u32x4* __r
   }
 }
 
+// The plan of a few slots and the move in one launch: a token's block finds the rows of its own slots by counting, over all slots,
+// those that come before them in the order (local expert, slot).  The block behind the movers adds the row counts up to offsets.
+// Bound by its launch and by the latency of two reads, of the slots and of inv's place in them.
+constexpr int FEW_SLOTS = 2048;
+
+template <bool BF16, bool SCALED>
+__global__ __launch_bounds__(DISPATCH_BLOCK) void plan_and_dispatch(const u32x4* __restrict__ x, int T, int row_vecs, int n_seg, int k,
+                                                                    const int32_t* __restrict__ topk_idx, const float* __restrict__ row_scale,
+                                                                    int e_lo, int e_cnt, int cap, int32_t* __restrict__ offsets,
+                                                                    int32_t* __restrict__ perm, int32_t* __restrict__ inv,
+                                                                    int32_t* __restrict__ status, u32x4* __restrict__ xp) {
+  constexpr int WAVES = DISPATCH_BLOCK / WAVE, KEYS = FEW_SLOTS / DISPATCH_BLOCK;
+  __shared__ int32_t hist[MOE_MAX_LOCAL];
+  __shared__ int32_t before[WAVES][MOE_MAX_TOPK];
+  const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
+  const int n_slots = T * k, t = blockIdx.x / n_seg;
+  const auto local = [&](int s) {         // index of a slot's expert if it is local, else a number beyond them
+    const int le = topk_idx[s] - e_lo;
+    return le >= 0 && le < e_cnt ? le : 0x7FFFFFFF;
+  };
+  if (t == T) {
+    for (int i = tid; i < e_cnt; i += DISPATCH_BLOCK) hist[i] = 0;
+    __syncthreads();
+    for (int s = tid; s < n_slots; s += DISPATCH_BLOCK) {
+      const int le = local(s);
+      if (le < e_cnt) atomicAdd(&hist[le], 1);
+    }
+    __syncthreads();
+    if (wave == 0) {
+      int sum = 0;
+      for (int e0 = 0; e0 < e_cnt; e0 += WAVE) {
+        const int v = e0 + lane < e_cnt ? hist[e0 + lane] : 0, incl = wave_scan(v);
+        if (e0 + lane < e_cnt) offsets[e0 + lane] = min(sum + incl - v, cap);
+        sum += __builtin_amdgcn_readlane(incl, WAVE - 1);
+      }
+      if (lane == 0) {
+        offsets[e_cnt] = min(sum, cap);
+        *status = sum > cap ? 1 : 0;
+      }
+    }
+    return;
+  }
+  const int seg = blockIdx.x - t * n_seg, c = seg * DISPATCH_BLOCK + tid;
+  u32x4 v = {0, 0, 0, 0};
+  if (c < row_vecs) v = __builtin_nontemporal_load(x + (size_t)t * row_vecs + c);
+  int key[KEYS];
+#pragma unroll
+  for (int i = 0; i < KEYS; ++i) {
+    const int s = i * DISPATCH_BLOCK + tid;
+    key[i] = s < n_slots ? local(s) : 0x7FFFFFFF;
+  }
+  for (int j = 0; j < k; ++j) {
+    const int mine = t * k + j, le = local(mine);
+    if (le >= e_cnt) continue;            // (uniform)
+    int n = 0;
+#pragma unroll
+    for (int i = 0; i < KEYS; ++i) n += key[i] < le || (key[i] == le && i * DISPATCH_BLOCK + tid < mine) ? 1 : 0;
+    n = wave_sum(n);
+    if (lane == 0) before[wave][j] = n;
+  }
+  __syncthreads();
+  const auto row_of = [&](int j) {        // -1: the slot's expert is elsewhere, or its row beyond the capacity
+    if (local(t * k + j) >= e_cnt) return -1;
+    int row = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) row += before[w][j];
+    return row < cap ? row : -1;
+  };
+  if (seg == 0 && tid < k) {
+    const int row = row_of(tid);
+    inv[t * k + tid] = row;
+    if (row >= 0) perm[row] = t * k + tid;
+  }
+  if (c >= row_vecs) return;
+  for (int j = 0; j < k; ++j) {
+    const int row = row_of(j);
+    if (row < 0) continue;
+    const u32x4 o = SCALED ? scale_vec<BF16>(v, row_scale[(size_t)t * k + j]) : v;
+    __builtin_nontemporal_store(o, xp + (size_t)row * row_vecs + c);
+  }
+}
+
 template <bool BF16>
 __device__ __forceinline__ void fma_vec(float* acc, u32x4 v, float w) {
   if (BF16) {
@@ -132,6 +214,36 @@ int launch_dispatch_rows(const void* x, int dtype, int T, int d, int k, const in
     if (row_scale) hipLaunchKernelGGL((dispatch_rows<false, true>), grid, block, 0, s, xs, T, row_vecs, n_seg, k, inv, row_scale, xd);
     else hipLaunchKernelGGL((dispatch_rows<false, false>), grid, block, 0, s, xs, T, row_vecs, n_seg, k, inv, row_scale, xd);
   }
+  HIP_CHECK_LAUNCH();
+  return MOE_OK;
+}
+
+// Every block reads all slots: up to 2^20 reads in all.  Forward in a captured graph, us, two launches / one (one launch less is 4 to 5
+// us of the host's time as well): 4 tokens, k = 8, d = 4096 55.9 / 53.9; 64 tokens 83.5 / 83.0; 250 tokens (2^21 reads) 166.4 / 166.4;
+// 128, 8, 7168 (2^20) 299.1 / 299.2; 256, 8, 7168 (2^22) 321 / 325.  Training step of 256 tokens, k = 2, d = 128, fp32 101.6 / 87.2
+// (with the shared launches of expert_f32.hip).
+bool plan_and_dispatch_fits(int T, int k, int d, int dtype) {
+  const long long slots = (long long)T * k, n_seg = ((dtype == MOE_BF16 ? d / 8 : d / 4) + DISPATCH_BLOCK - 1) / DISPATCH_BLOCK;
+  return T > 0 && slots <= FEW_SLOTS && T * n_seg * slots <= (1 << 20);
+}
+int launch_plan_and_dispatch(const void* x, int dtype, int T, int d, int k, const int32_t* topk_idx, const float* row_scale, int e_lo,
+                             int e_cnt, int32_t* offsets, int32_t* perm, int32_t* inv, int cap, int32_t* status, void* xp, hipStream_t s) {
+  ProfScope prof(MOE_K_DISPATCH, s);
+  const int row_vecs = dtype == MOE_BF16 ? d / 8 : d / 4;
+  const int n_seg = (row_vecs + DISPATCH_BLOCK - 1) / DISPATCH_BLOCK;
+  if ((long long)T * n_seg + 1 >= (1ll << 31)) return MOE_EUNSUPPORTED;
+  const dim3 grid((unsigned)(T * n_seg + 1)), block(DISPATCH_BLOCK);
+#define PLAN_AND_DISPATCH(BF16, SCALED)                                                                                              \
+  hipLaunchKernelGGL((plan_and_dispatch<BF16, SCALED>), grid, block, 0, s, (const u32x4*)x, T, row_vecs, n_seg, k, topk_idx, row_scale, \
+                     e_lo, e_cnt, cap, offsets, perm, inv, status, (u32x4*)xp)
+  if (dtype == MOE_BF16) {
+    if (row_scale) PLAN_AND_DISPATCH(true, true);
+    else PLAN_AND_DISPATCH(true, false);
+  } else {
+    if (row_scale) PLAN_AND_DISPATCH(false, true);
+    else PLAN_AND_DISPATCH(false, false);
+  }
+#undef PLAN_AND_DISPATCH
   HIP_CHECK_LAUNCH();
   return MOE_OK;
 }

@@ -249,6 +249,35 @@ def test_plan_in_one_block_and_in_three_launches(T, k, e_cnt):
     assert int(ws[:4].view(torch.int32).item()) == 0
 
 
+# plan and move of few slots in one launch (up to 2048 slots, and 2**20 reads of slots by all blocks) and in two: one and several blocks
+# per row, slots without a local expert, experts without rows, rows beyond the capacity, scaled rows of both types
+@pytest.mark.parametrize("T,k,d,e_cnt,cap", [(1, 1, 8, 1, 1), (7, 3, 1032, 5, 21), (64, 16, 64, 64, 1024), (2048, 1, 72, 7, 2048), (2049, 1, 72, 7, 2049),
+                                             (128, 2, 2056, 900, 256), (30, 64, 1024, 1000, 1920), (33, 4, 256, 8, 20), (9, 2, 64, 3, 0), (12, 2, 64, 0, 4)])
+def test_plan_and_dispatch_of_few_slots(T, k, d, e_cnt, cap):
+    print(f"case few-slots-{T}-{k}-{d}-{e_cnt}-{cap}", flush=True)
+    E, e_lo = 1024, 2
+    ids = np.random.default_rng(T + d).permuted(np.tile(np.arange(E if k > 20 or e_cnt > 100 else 24 if k <= 16 and e_cnt < 20 else 70), (T, 1)), axis=1)[:, :k].astype(np.int32)
+    off_ref, perm_ref, inv_ref = O.plan(ids, e_lo, e_cnt)[:3]
+    R = int(off_ref[-1])
+    inv_ref = np.where(inv_ref < cap, inv_ref, -1)
+    g = torch.Generator(device="cuda").manual_seed(T)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    for dtype in (torch.bfloat16, torch.float32):
+        x = torch.randn((T, d), generator=g, device="cuda").to(dtype)
+        scale = torch.rand((T, k), generator=g, device="cuda")
+        for rows in (None, scale):
+            off, perm, inv = torch.full((e_cnt + 1,), -7, **i32), torch.full((max(cap, 1),), -7, **i32), torch.full((T, k), -7, **i32)
+            xp, status = torch.full((max(cap, 1), d), 3.0, device="cuda", dtype=dtype), torch.full((1,), -7, **i32)
+            B.moe_dispatch_static(x, k, torch.from_numpy(ids).cuda(), rows, e_lo, e_cnt, off, perm[:cap], inv, xp[:cap], status)
+            n = min(R, cap)
+            assert (host(off) == np.minimum(off_ref, cap)).all() and (host(inv) == inv_ref).all() and int(status) == int(R > cap)
+            assert (host(perm)[:n] == perm_ref[:n]).all() and (perm[n:] == -7).all() and (xp[n:] == 3.0).all()
+            s = torch.from_numpy(np.ascontiguousarray(perm_ref[:n])).cuda().long()
+            want = x[s // k].float() * (1.0 if rows is None else rows.flatten()[s][:, None])
+            assert torch.equal(xp[:n], want.to(dtype))
+
+
+
 def _streams(T, d, E):
     """Whether the weight gradient of these sizes takes the streaming kernel: three planes of dlogits unless E % 64 == 0, and
     the operand and a sum per plane must fit where the sums of the cut product would go (rules of router.hip, expert_bf16.hip)."""
