@@ -11,9 +11,8 @@
 //                      of 64 slots the rank among equal keys comes from ballots (one per bit of
 //                      the key) and a popcount of the lower lanes, and a per-wave LDS counter
 //                      carries it forward.
-// Small batches (up to SMALL_SLOTS slots) take plan_small instead: the same three steps in one
-// block, whose wavefronts are the chunks.  The smallest are planned by the dispatch itself
-// (plan_and_dispatch in rowmove.hip).
+// Up to some ten thousand slots plan_direct does the three steps in one launch.  The smallest batches are planned by the dispatch
+// itself (plan_and_dispatch in rowmove.hip).
 #include "common.h"
 #include "kernels.h"
 
@@ -148,66 +147,68 @@ __global__ __launch_bounds__(64) void plan_scatter(const int32_t* __restrict__ t
   for (int g = 0; g < CHUNK / WAVE; ++g) scatter_group(base + g * WAVE + lane, le[g], bits, lane, n_slots, cap, run, perm, inv);
 }
 
-// One block of SMALL_WAVES wavefronts; wavefront w owns the slots [w * per, (w + 1) * per), per a multiple of 64.
-// LDS: hist[SMALL_WAVES][e_cnt] (becomes each wavefront's next row per expert), total[e_cnt + 1].
-constexpr int SMALL_WAVES = 16, SMALL_SLOTS = 8 * SMALL_WAVES * WAVE;
-constexpr int SMALL_MAX_LOCAL = 900;       // the tables fit the 64 KB of LDS that need no opt-in
+// All three steps in one launch, for a few ten thousand slots (direct_slots()): block b owns the DIRECT_CHUNK slots from b * DIRECT_CHUNK on, one group
+// of 64 per wavefront, and counts the experts of all slots by itself.
+// LDS: hist[DIRECT_WAVES][e_cnt] (of the own groups; becomes each wavefront's next row per expert), before[e_cnt] (in the blocks before
+// this one), total[e_cnt + 1].
+constexpr int DIRECT_WAVES = 16, DIRECT_CHUNK = DIRECT_WAVES * WAVE;
+constexpr int DIRECT_MAX_LOCAL = 900;      // the tables fit the 64 KB of LDS that need no opt-in
 
-__global__ __launch_bounds__(SMALL_WAVES* WAVE) void plan_small(const int32_t* __restrict__ topk_idx, int n_slots, int e_lo,
-                                                               int e_cnt, int bits, int cap, int32_t* __restrict__ offsets,
-                                                               int32_t* __restrict__ perm, int32_t* __restrict__ inv,
-                                                               int32_t* __restrict__ status) {
+__global__ __launch_bounds__(DIRECT_CHUNK) void plan_direct(const int32_t* __restrict__ topk_idx, int n_slots, int e_lo, int e_cnt, int bits,
+                                                           int cap, int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
+                                                           int32_t* __restrict__ inv, int32_t* __restrict__ status) {
   extern __shared__ int32_t hist[];
-  int32_t* total = hist + SMALL_WAVES * e_cnt;
+  int32_t* const before = hist + DIRECT_WAVES * e_cnt;
+  int32_t* const total = before + e_cnt;
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
-  const int groups = (n_slots + SMALL_WAVES * WAVE - 1) / (SMALL_WAVES * WAVE);      // of 64 slots, per wavefront: at most 8
-  const int base = wave * groups * WAVE;
-  int32_t* mine = hist + wave * e_cnt;
-  int le[8];
-#pragma unroll
-  for (int g = 0; g < 8; ++g) le[g] = g < groups ? local_expert(topk_idx, base + g * WAVE + lane, n_slots, e_lo, e_cnt) : -1;
-  for (int i = tid; i < SMALL_WAVES * e_cnt; i += SMALL_WAVES * WAVE) hist[i] = 0;
+  const int n_groups = (n_slots + WAVE - 1) / WAVE, first = blockIdx.x * DIRECT_WAVES, own = first + wave;
+  int32_t* const mine = hist + wave * e_cnt;
+  const int le_own = local_expert(topk_idx, own * WAVE + lane, n_slots, e_lo, e_cnt);
+  for (int i = tid; i < (DIRECT_WAVES + 2) * e_cnt; i += DIRECT_CHUNK) hist[i] = 0;
   __syncthreads();
+  // eight groups at a time: one memory round trip for all of them
+  for (int g0 = wave; g0 < n_groups; g0 += 8 * DIRECT_WAVES) {
+    int le[8];
 #pragma unroll
-  for (int g = 0; g < 8; ++g)
-    if (le[g] >= 0) atomicAdd(&mine[le[g]], 1);
+    for (int i = 0; i < 8; ++i) le[i] = local_expert(topk_idx, (g0 + i * DIRECT_WAVES) * WAVE + lane, n_slots, e_lo, e_cnt);
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int g = g0 + i * DIRECT_WAVES;
+      if (le[i] >= 0) {
+        atomicAdd(&total[le[i]], 1);
+        if (g < first) atomicAdd(&before[le[i]], 1);
+        if (g == own) atomicAdd(&mine[le[i]], 1);
+      }
+    }
+  }
   __syncthreads();
-  if (tid < e_cnt) {                                 // e_cnt <= 1024 = threads of the block
-    int run = 0;
+  if (tid < e_cnt) {                                 // e_cnt <= 900 < threads of the block
+    int run = before[tid];
 #pragma unroll
-    for (int w = 0; w < SMALL_WAVES; ++w) {
+    for (int w = 0; w < DIRECT_WAVES; ++w) {
       const int v = hist[w * e_cnt + tid];
       hist[w * e_cnt + tid] = run;
       run += v;
     }
-    total[tid] = run;
   }
-  __syncthreads();
   if (wave == 0) {                                   // exclusive scan over the experts, 64 at a time
     int carry = 0;
     for (int e0 = 0; e0 < e_cnt; e0 += WAVE) {
-      const int v = e0 + lane < e_cnt ? total[e0 + lane] : 0;
-      int incl = v;
-#pragma unroll
-      for (int off = 1; off < WAVE; off <<= 1) {
-        const int t = __shfl_up(incl, off, WAVE);
-        if (lane >= off) incl += t;
-      }
+      const int v = e0 + lane < e_cnt ? total[e0 + lane] : 0, incl = wave_scan(v);
       if (e0 + lane < e_cnt) total[e0 + lane] = carry + incl - v;
-      carry += __shfl(incl, WAVE - 1, WAVE);
+      carry += __builtin_amdgcn_readlane(incl, WAVE - 1);
     }
     if (lane == 0) {
       total[e_cnt] = carry;
-      *status = carry > cap ? 1 : 0;
+      if (blockIdx.x == 0) *status = carry > cap ? 1 : 0;
     }
   }
   __syncthreads();
-  for (int i = tid; i <= e_cnt; i += SMALL_WAVES * WAVE) offsets[i] = total[i] < cap ? total[i] : cap;
+  if (blockIdx.x == 0)
+    for (int i = tid; i <= e_cnt; i += DIRECT_CHUNK) offsets[i] = total[i] < cap ? total[i] : cap;
   for (int i = lane; i < e_cnt; i += WAVE) mine[i] += total[i];      // read and written by this wavefront only
   __builtin_amdgcn_wave_barrier();
-#pragma unroll
-  for (int g = 0; g < 8; ++g)
-    if (g < groups) scatter_group(base + g * WAVE + lane, le[g], bits, lane, n_slots, cap, mine, perm, inv);
+  scatter_group(own * WAVE + lane, le_own, bits, lane, n_slots, cap, mine, perm, inv);
 }
 
 }  // namespace
@@ -236,6 +237,16 @@ int plan_static_scratch(void** ptr) {
   return MOE_OK;
 }
 
+// Every block counts all slots, in one round of LDS additions per 1024 of them, which queue up where few experts share them all; the
+// three launches' scan takes a round per 16 experts.  Plan and move of 16 bytes per row in a captured graph, us, before (one block up
+// to 8192 slots, then three launches) / in one launch:
+//   slots, local experts of E   8188, 16 of 128  11.1 / 8.2    16384, 8 of 64  15.9 / 10.5    36004, 16 of 128  18.4 / 16.3
+//                               8192, 8 of 8     12.5 / 11.0   65536, 8 of 64  19.1 / 23.6    60000, 8 of 8     22.2 / 37.9
+//                               65536, 32 of 256 22.5 / 22.9   32768, 128 of 128 38.2 / 15.6  56000, 256 of 256 61.4 / 21.9
+static int direct_slots(int e_cnt) {
+  return e_cnt > DIRECT_MAX_LOCAL ? -1 : (e_cnt >= 64 ? 65536 : (e_cnt >= 16 ? 32768 : 16384));
+}
+
 size_t plan_ws_bytes(int T, int k, int e_cnt) {
   size_t n_slots = (size_t)T * (size_t)k;
   size_t n_chunks = (n_slots + CHUNK - 1) / CHUNK;
@@ -251,10 +262,10 @@ int launch_plan(const int32_t* topk_idx, int T, int k, int e_lo, int e_cnt, int3
   const long long n_slots = (long long)T * k;
   int bits = 0;                                      // of a local expert's index
   while ((1 << bits) < e_cnt) ++bits;
-  if (n_slots <= SMALL_SLOTS && e_cnt <= SMALL_MAX_LOCAL) {
-    // one launch instead of three (about 5 us each): 13 us -> 5 us at a few dozen slots
-    const size_t shm_small = ((size_t)SMALL_WAVES * e_cnt + e_cnt + 1) * sizeof(int32_t);
-    hipLaunchKernelGGL(plan_small, dim3(1), dim3(SMALL_WAVES * WAVE), shm_small, s, topk_idx, (int)n_slots, e_lo, e_cnt, bits, cap,
+  if (n_slots <= direct_slots(e_cnt)) {
+    const size_t shm = ((size_t)(DIRECT_WAVES + 2) * e_cnt + 1) * sizeof(int32_t);
+    const int blocks = (int)((n_slots + DIRECT_CHUNK - 1) / DIRECT_CHUNK);
+    hipLaunchKernelGGL(plan_direct, dim3(blocks > 0 ? blocks : 1), dim3(DIRECT_CHUNK), shm, s, topk_idx, (int)n_slots, e_lo, e_cnt, bits, cap,
                        offsets, perm, inv, status);
     HIP_CHECK_LAUNCH();
     return MOE_OK;

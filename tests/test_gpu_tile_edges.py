@@ -249,6 +249,12 @@ def test_plan_in_one_block_and_in_three_launches(T, k, e_cnt):
     assert int(ws[:4].view(torch.int32).item()) == 0
 
 
+# one launch plans up to 16384 slots (32768 of 16 local experts or more, 65536 of 64 or more), several blocks of 1024; three beyond
+@pytest.mark.parametrize("T,k,e_cnt", [(1025, 2, 7), (4096, 4, 7), (4097, 4, 7), (8192, 4, 16), (8193, 4, 16), (8192, 8, 64), (8193, 8, 64), (1200, 8, 900)])
+def test_plan_of_several_blocks(T, k, e_cnt):
+    test_plan_in_one_block_and_in_three_launches(T, k, e_cnt)
+
+
 # plan and move of few slots in one launch (up to 2048 slots, and 2**20 reads of slots by all blocks) and in two: one and several blocks
 # per row, slots without a local expert, experts without rows, rows beyond the capacity, scaled rows of both types
 @pytest.mark.parametrize("T,k,d,e_cnt,cap", [(1, 1, 8, 1, 1), (7, 3, 1032, 5, 21), (64, 16, 64, 64, 1024), (2048, 1, 72, 7, 2048), (2049, 1, 72, 7, 2049),
