@@ -61,7 +61,8 @@ int launch_gate_bwd(const float* logits, const int32_t* topk_idx, const float* d
 int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int dtype, int T, int d, int E, void* dwr,
                       int dwr_acc, void* dx, int dx_acc, void* ws, hipStream_t s);
 bool router_dw_streams(int T, int d, int E);      // router_dw.hip takes the weight gradient of this shape
-int launch_router_dw_stream(const void* x, const void* dl, int T, int d, int E, float* sums, int max_sums, int* n_sums, hipStream_t s);
+int launch_router_dw_stream(const void* x, const void* dl, const float* dlogits, int T, int d, int E, float* sums, int max_sums,
+                            int* n_sums, hipStream_t s);
 bool router_dx_streams(int E, int d);      // router_dx.hip takes the input gradient of this shape
 int launch_router_dx_stream(const void* dl, const void* wr, int T, int d, int E, void* dx, int accumulate, hipStream_t s);
 int router_dw_splits(int T, int d, int E);

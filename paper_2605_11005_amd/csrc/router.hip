@@ -648,7 +648,7 @@ int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int d
     float* sums = (float*)((char*)pieces + piece_bytes);
     int n = 0;
     const int most = (int)((room - piece_bytes) / sum_bytes);
-    const int rc2 = dw_wide ? launch_router_dw_stream(x, pieces, T, d, E, sums, most, &n, s)
+    const int rc2 = dw_wide ? launch_router_dw_stream(x, pieces, dlogits, T, d, E, sums, most, &n, s)
                             : launch_router_dw_small(x, pieces, planes, T, d, E, sums, most, &n, s);
     if (rc2) return rc2;
     ProfScope prof(MOE_K_ROUTER_DW, s);

@@ -37,8 +37,9 @@ __device__ __forceinline__ bf16x8 x_fragment(const char* p, int n, int s, int la
 }
 
 template <int NE, int PLANES>
-__global__ __launch_bounds__(NT, 1) void router_dw_stream(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dl, float* __restrict__ sums,
-                                                         int T, int d, int n_cols, int per_range) {
+__global__ __launch_bounds__(NT, 1) void router_dw_stream(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dl,
+                                                         const float* __restrict__ dlogits, float* __restrict__ sums, int T, int d,
+                                                         int n_cols, int per_range) {
   using S = Shape<NE, PLANES>;
   extern __shared__ __align__(16) char lds[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -99,22 +100,50 @@ __global__ __launch_bounds__(NT, 1) void router_dw_stream(const bf16_t* __restri
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   float* const out = sums + (size_t)range * d * S::E;
+  const auto place = [&](int m, int b, int r) {      // of element r of a block of sums; ~0: past the last column or expert
+    const int col = c0 + 64 * wc + 32 * m + 4 * (lane >> 5) + 8 * (r >> 2) + (r & 3), e = (we * S::BLOCKS + b) * 32 + (lane & 31);
+    return col < d && e < S::E ? (size_t)col * S::E + e : ~(size_t)0;
+  };
+  bool odd = false;
 #pragma unroll
-  for (int m = 0; m < 2; ++m) {
-    const int col = c0 + 64 * wc + 32 * m + 4 * (lane >> 5);
-    if (col >= d) continue;               // d % 64 == 0: 32 columns at a time
+  for (int m = 0; m < 2; ++m)
 #pragma unroll
-    for (int b = 0; b < S::BLOCKS; ++b) {
-      const int e = (we * S::BLOCKS + b) * 32 + (lane & 31);
-      if (e >= S::E) continue;
+    for (int b = 0; b < S::BLOCKS; ++b)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) out[(size_t)(col + 8 * (r >> 2) + (r & 3)) * S::E + e] = acc[m][b][r];
+      for (int r = 0; r < 16; ++r) {
+        const size_t at = place(m, b, r);
+        if (at == ~(size_t)0) continue;
+        out[at] = acc[m][b][r];
+        odd |= !(fabsf(acc[m][b][r]) < INFINITY);
+      }
+  if (!odd) return;
+  // Zeros that stand for no product, a dlogit's empty terms and the overlap of the last piece, make NaN of an infinite x, and an
+  // infinite dlogit's terms are no sum.  Sums that are no numbers are formed again, in plain fp32.
+  const int end = min(T, (first + n) * PIECE);
+#pragma unroll 1
+  for (int i = 0; i < 2 * S::BLOCKS * 16; ++i) {
+    const size_t at = place(i / (S::BLOCKS * 16), i / 16 % S::BLOCKS, i % 16);
+    if (at == ~(size_t)0 || fabsf(out[at]) < INFINITY) continue;
+    const size_t col = at / S::E, e = at % S::E;
+    float sum = 0.f;
+    for (int t0 = first * PIECE; t0 < end && sum == sum; t0 += 8) {
+      float a[8], g[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        const size_t t = min(t0 + k, end - 1);
+        a[k] = bf16_to_f32(x[t * d + col]);
+        g[k] = dlogits[t * S::E + e];
+        if (PLANES == 1) g[k] = bf16lo(pack_bf16x2(g[k], 0.f));
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) sum += t0 + k < end ? a[k] * g[k] : 0.f;
     }
+    out[at] = sum;
   }
 }
 
 template <int NE, int PLANES>
-int launch(const bf16_t* x, const bf16_t* dl, float* sums, int T, int d, int max_sums, int* n_sums, hipStream_t s) {
+int launch(const bf16_t* x, const bf16_t* dl, const float* dlogits, float* sums, int T, int d, int max_sums, int* n_sums, hipStream_t s) {
   using S = Shape<NE, PLANES>;
   constexpr int LDS = S::STAGES * S::STAGE;
   static bool attr_set[64] = {};         // a per-device attribute of the kernel
@@ -135,7 +164,8 @@ int launch(const bf16_t* x, const bf16_t* dl, float* sums, int T, int d, int max
   const int per = (pieces + ranges - 1) / ranges;
   ranges = (pieces + per - 1) / per;
   ProfScope prof(MOE_K_ROUTER_DW, s);
-  hipLaunchKernelGGL((router_dw_stream<NE, PLANES>), dim3((unsigned)(ranges * n_cols)), dim3(NT), LDS, s, x, dl, sums, T, d, n_cols, per);
+  hipLaunchKernelGGL((router_dw_stream<NE, PLANES>), dim3((unsigned)(ranges * n_cols)), dim3(NT), LDS, s, x, dl, dlogits, sums, T, d,
+                     n_cols, per);
   HIP_CHECK_LAUNCH();
   *n_sums = ranges;
   return MOE_OK;
@@ -158,15 +188,16 @@ bool router_dw_streams(int T, int d, int E) {
   const long long x = (long long)T * d;
   return x >= (1ll << 22) && (E == 32 || E == 64 || E == 128 || ((E == 192 || E == 256) && x <= (1ll << 26)));
 }
-int launch_router_dw_stream(const void* x, const void* dl, int T, int d, int E, float* sums, int max_sums, int* n_sums, hipStream_t s) {
+int launch_router_dw_stream(const void* x, const void* dl, const float* dlogits, int T, int d, int E, float* sums, int max_sums,
+                            int* n_sums, hipStream_t s) {
   const bf16_t *a = (const bf16_t*)x, *b = (const bf16_t*)dl;
   switch (E / 32) {
-    case 1: return launch<1, 3>(a, b, sums, T, d, max_sums, n_sums, s);
-    case 2: return launch<2, 1>(a, b, sums, T, d, max_sums, n_sums, s);
-    case 3: return launch<3, 3>(a, b, sums, T, d, max_sums, n_sums, s);
-    case 4: return launch<4, 1>(a, b, sums, T, d, max_sums, n_sums, s);
-    case 5: return launch<5, 3>(a, b, sums, T, d, max_sums, n_sums, s);
-    case 6: return launch<6, 1>(a, b, sums, T, d, max_sums, n_sums, s);
-    default: return launch<8, 1>(a, b, sums, T, d, max_sums, n_sums, s);
+    case 1: return launch<1, 3>(a, b, dlogits, sums, T, d, max_sums, n_sums, s);
+    case 2: return launch<2, 1>(a, b, dlogits, sums, T, d, max_sums, n_sums, s);
+    case 3: return launch<3, 3>(a, b, dlogits, sums, T, d, max_sums, n_sums, s);
+    case 4: return launch<4, 1>(a, b, dlogits, sums, T, d, max_sums, n_sums, s);
+    case 5: return launch<5, 3>(a, b, dlogits, sums, T, d, max_sums, n_sums, s);
+    case 6: return launch<6, 1>(a, b, dlogits, sums, T, d, max_sums, n_sums, s);
+    default: return launch<8, 1>(a, b, dlogits, sums, T, d, max_sums, n_sums, s);
   }
 }

@@ -373,6 +373,28 @@ def test_router_weight_gradient_stream(T, d, E):
         assert ((dwr.double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5 * ref.abs().max()).all()
 
 
+# Infinities and numbers that round up to them, where the weight gradient's terms and the overlap of its last piece multiply by zeros that
+# stand for nothing: every output is what one product per token gives, in one plane (E = 64, 192) and three.  Finite outputs as above
+@pytest.mark.parametrize("T,d,E", [(777, 128, 160), (1001, 320, 96), (4100, 1024, 32), (4100, 1088, 64), (4100, 1024, 192)])
+def test_router_weight_gradient_of_infinities(T, d, E):
+    print(f"case router-dw-inf-{T}-{d}-{E}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T + d + E)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda")  # noqa: E731
+    x, wr, dl = randn(T, d).bfloat16(), randn(d, E).bfloat16(), randn(T, E)
+    x[20] *= 2.0 ** -30
+    dl[20, 2] = 3.4e38
+    x[10, 9], x[T - T % 32 - 1, 7] = -float("inf"), float("inf")       # the second one in the last piece's overlap
+    dl[5, 3], dl[T - 1, 30] = float("inf"), -float("inf")
+    seen = dl.bfloat16().double() if E % 64 == 0 else dl.double()
+    want, size = x.double().t() @ seen, x.double().abs().t() @ seen.abs()
+    dwr = torch.zeros_like(wr)
+    ws = torch.empty(B.moe_workspace_bytes(B.WS_ROUTER, B.MOE_BF16, T, 1, d, 0, E, 0), dtype=torch.uint8, device="cuda")
+    B.moe_router_bwd(x, wr, dl, dwr, False, None, False, ws)
+    got, finite = dwr.double(), torch.isfinite(want)
+    assert torch.equal(got.nan_to_num(7.0)[~finite], want.nan_to_num(7.0)[~finite])
+    assert ((got - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5 * size)[finite].all()
+
+
 # a token's selection and the counts, with one, two and four blocks per CU (the lines lie at 64 and 256 tokens per CU)
 @pytest.mark.parametrize("T", [16385, 65537])
 def test_route_of_many_tokens_equals_the_route_of_a_few(T):
