@@ -83,12 +83,12 @@ __global__ __launch_bounds__(NT, 2) void router_dx_stream(const void* __restrict
         const int at4 = tid + NT * n, token = at4 / (S::E / 4), e = 4 * (at4 % (S::E / 4));
         float x[4] = {v[n].x, v[n].y, v[n].z, v[n].w};
 #pragma unroll
-        for (int p = 0; p < 3; ++p) {      // the leading 8 bits each time (an infinity is its own first term)
+        for (int p = 0; p < 3; ++p) {      // the leading 8 bits each time
           uint32_t h[4];
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
             h[r] = __float_as_uint(x[r]) & 0xFFFF0000u;
-            x[r] = fabsf(x[r]) == INFINITY ? 0.f : x[r] - __uint_as_float(h[r]);
+            x[r] -= __uint_as_float(h[r]);
           }
           const int k = p * S::E + e;
           *reinterpret_cast<uint2*>(lds + buf * S::BUFFER + token * S::ROW + S::swizzle(token, k >> 3) * 16 + (k & 4) * 2) =
@@ -132,6 +132,31 @@ __global__ __launch_bounds__(NT, 2) void router_dx_stream(const void* __restrict
         for (int b = 0; b < 4; ++b) acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[b][k % NK], f, acc[b][t], 0, 0, 0);
       }
     if (more) publish(buf ^ 1);
+    if constexpr (SPLIT) {
+      // The terms of an infinite dlogit are no sum of it, and an empty term makes NaN of an infinite weight: sums that are no numbers
+      // are formed again, in plain fp32.
+      float probe = 0.f;
+#pragma unroll
+      for (int n = 0; n < 16 * TG; ++n) probe += acc[n >> 2 & 3][n >> 4][n & 3] * 0.f;
+      if (probe != 0.f) {
+#pragma unroll 1
+        for (int n = 0; n < 16 * TG; ++n) {
+          const int t = n >> 4, b = n >> 2 & 3, token = t0 + 16 * t + i;
+          float sum = 0.f;
+#pragma unroll
+          for (int o = 0; o < 16 * TG; ++o) sum = o == n ? acc[o >> 2 & 3][o >> 4][o & 3] : sum;
+          if (!active || token >= T || fabsf(sum) < INFINITY) continue;
+          const float* row = (const float*)dl + (size_t)token * S::E;
+          const bf16_t* weights = wr + (size_t)(c0 + 8 * (4 * (b >> 1) + g) + 4 * (b & 1) + (n & 3)) * S::E;
+          sum = 0.f;
+          for (int e = 0; e < S::E; ++e) sum += row[e] * bf16_to_f32(weights[e]);
+          int place = n;
+          asm volatile("" : "+s"(place));      // (compared again: the comparisons above would be kept)
+#pragma unroll
+          for (int o = 0; o < 16 * TG; ++o) acc[o >> 2 & 3][o >> 4][o & 3] = o == place ? sum : acc[o >> 2 & 3][o >> 4][o & 3];
+        }
+      }
+    }
 #pragma unroll
     for (int t = 0; t < TG; ++t)
 #pragma unroll

@@ -354,6 +354,29 @@ def test_router_input_gradient_stream(T, d, E):
     assert torch.isfinite(room[:T - 1]).all()
 
 
+# the same with infinities, where the terms that are zero multiply an infinite weight: dlogits of one and two terms, a row that rounds up to
+# infinity, and infinite weights in several columns of a wavefront
+@pytest.mark.parametrize("T,d,E", [(33, 192, 96), (65, 320, 32), (127, 256, 160)])
+def test_router_input_gradient_of_infinities(T, d, E):
+    print(f"case router-dx-inf-{T}-{d}-{E}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T + d + E)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda")  # noqa: E731
+    x, wr, dl, dx0 = randn(T, d).bfloat16(), randn(d, E).bfloat16(), randn(T, E), randn(T, d).bfloat16()
+    dl[::2] = dl[::2].bfloat16().float()
+    wr[3, 1] = wr[5, E - 1] = wr[d - 1, 7] = float("inf")
+    wr[4, 0] = -float("inf")
+    dl[7, 2], dl[8, 2], dl[9, 5], wr[:, 5] = float("inf"), -float("inf"), 3.4e38, 2.0 ** -30
+    want, size = dl.double() @ wr.double().t(), dl.double().abs() @ wr.double().abs().t()
+    ws = torch.empty(B.moe_workspace_bytes(B.WS_ROUTER, B.MOE_BF16, T, 1, d, 0, E, 0), dtype=torch.uint8, device="cuda")
+    finite = torch.isfinite(want)
+    for accumulate in (False, True):
+        dx = dx0.clone()
+        B.moe_router_bwd(x, wr, dl, None, False, dx, accumulate, ws)
+        got, ref = dx.double(), want + (dx0.double() if accumulate else 0.0)
+        assert torch.equal(got.nan_to_num(7.0)[~finite], want.nan_to_num(7.0)[~finite])
+        assert ((got - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5 * size)[finite].all()
+
+
 # router_dw.hip, one plane (E = 64, 128, 192, 256) and three (32, 96, 160): fewer pieces than the ring holds, a last piece that overlaps
 # the one before it, several ranges, a last block of 64 columns.  Against float64; the results are rounded to bf16 (2**-8), bf16
 # dlogits first (then: against what the kernel is given), sums of up to T products in fp32 (1e-5 of the largest)
