@@ -100,31 +100,33 @@ __global__ __launch_bounds__(NT, 1) void router_dw_stream(const bf16_t* __restri
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   float* const out = sums + (size_t)range * d * S::E;
-  const auto place = [&](int m, int b, int r) {      // of element r of a block of sums; ~0: past the last column or expert
-    const int col = c0 + 64 * wc + 32 * m + 4 * (lane >> 5) + 8 * (r >> 2) + (r & 3), e = (we * S::BLOCKS + b) * 32 + (lane & 31);
-    return col < d && e < S::E ? (size_t)col * S::E + e : ~(size_t)0;
-  };
-  bool odd = false;
+  float probe = 0.f;
 #pragma unroll
-  for (int m = 0; m < 2; ++m)
+  for (int m = 0; m < 2; ++m) {
+    const int col = c0 + 64 * wc + 32 * m + 4 * (lane >> 5);
+    if (col >= d) continue;               // d % 64 == 0: 32 columns at a time
 #pragma unroll
-    for (int b = 0; b < S::BLOCKS; ++b)
+    for (int b = 0; b < S::BLOCKS; ++b) {
+      const int e = (we * S::BLOCKS + b) * 32 + (lane & 31);
+      if (e >= S::E) continue;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        const size_t at = place(m, b, r);
-        if (at == ~(size_t)0) continue;
-        out[at] = acc[m][b][r];
-        odd |= !(fabsf(acc[m][b][r]) < INFINITY);
+        out[(size_t)(col + 8 * (r >> 2) + (r & 3)) * S::E + e] = acc[m][b][r];
+        probe += acc[m][b][r] * 0.f;
       }
-  if (!odd) return;
+    }
+  }
+  if (probe == 0.f) return;
   // Zeros that stand for no product, a dlogit's empty terms and the overlap of the last piece, make NaN of an infinite x, and an
   // infinite dlogit's terms are no sum.  Sums that are no numbers are formed again, in plain fp32.
   const int end = min(T, (first + n) * PIECE);
 #pragma unroll 1
   for (int i = 0; i < 2 * S::BLOCKS * 16; ++i) {
-    const size_t at = place(i / (S::BLOCKS * 16), i / 16 % S::BLOCKS, i % 16);
-    if (at == ~(size_t)0 || fabsf(out[at]) < INFINITY) continue;
-    const size_t col = at / S::E, e = at % S::E;
+    const int r = i % 16, col = c0 + 64 * wc + 32 * (i / (S::BLOCKS * 16)) + 4 * (lane >> 5) + 8 * (r >> 2) + (r & 3);
+    const int e = (we * S::BLOCKS + i / 16 % S::BLOCKS) * 32 + (lane & 31);
+    if (col >= d || e >= S::E) continue;
+    const size_t at = (size_t)col * S::E + e;
+    if (fabsf(out[at]) < INFINITY) continue;
     float sum = 0.f;
     for (int t0 = first * PIECE; t0 < end && sum == sum; t0 += 8) {
       float a[8], g[8];
