@@ -60,6 +60,10 @@ int launch_gate_bwd(const float* logits, const int32_t* topk_idx, const float* d
                     int gate_mode, float* dlogits, hipStream_t s);
 int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int dtype, int T, int d, int E, void* dwr,
                       int dwr_acc, void* dx, int dx_acc, void* ws, hipStream_t s);
+// Dlogits as three bf16 terms are multiplied by this on the way into router_dw.hip and router_dx.hip and their sums divided by it: it brings
+// the last bit of fp32's smallest number, 2^-149, among bf16's normal numbers.  (Beyond 2^96 a term is infinite, and so are the sums
+// it enters, which are formed again.)
+constexpr float DL_SCALE = 0x1p32f, DL_UNSCALE = 0x1p-32f;
 bool router_dw_streams(int T, int d, int E);      // router_dw.hip takes the weight gradient of this shape
 int launch_router_dw_stream(const void* x, const void* dl, const float* dlogits, int T, int d, int E, float* sums, int max_sums,
                             int* n_sums, hipStream_t s);

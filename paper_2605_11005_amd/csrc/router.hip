@@ -249,12 +249,12 @@ __global__ void round_to_bf16(const float* __restrict__ in, bf16_t* __restrict__
 //   dlb     [T][E] bf16 (NULL: not wanted): operand of the input-gradient product
 //   pieces  [piece][plane][E][32] bf16: operand of the weight-gradient product, tokens contiguous.
 //           PLANES = 1: rounded once, the path whose dlogits are bf16.  PLANES = 3: three terms whose sum keeps all 24 bits,
-//           for shapes whose dlogits stay fp32.  The last piece ends at the last token, with zeros for the tokens that the
+//           for shapes whose dlogits stay fp32, times `scale`.  The last piece ends at the last token, with zeros for the tokens that the
 //           piece before it has covered (T >= 32).
 // The first block also clears the ticket counters of the product that follows (n_words; a launch of its own otherwise).
 template <int PLANES>
 __global__ __launch_bounds__(256) void router_dl_operands(const float* __restrict__ dl, int T, int E, bf16_t* __restrict__ dlb,
-                                                         bf16_t* __restrict__ pieces, int32_t* __restrict__ words, int n_words) {
+                                                         bf16_t* __restrict__ pieces, float scale, int32_t* __restrict__ words, int n_words) {
   __shared__ float tile[32][65];
   const int tid = threadIdx.x;
   if (blockIdx.x == 0 && tid < n_words) words[tid] = 0;
@@ -275,7 +275,7 @@ __global__ __launch_bounds__(256) void router_dl_operands(const float* __restric
     if (e < E) {
       float v[8];
 #pragma unroll
-      for (int i = 0; i < 8; ++i) v[i] = tile[k + i][tid >> 2];
+      for (int i = 0; i < 8; ++i) v[i] = tile[k + i][tid >> 2] * scale;
 #pragma unroll
       for (int p = 0; p < PLANES; ++p) {
         uint32_t w[4];
@@ -639,9 +639,10 @@ int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int d
     if (!pieces)
       hipLaunchKernelGGL(round_to_bf16, dim3(red_blocks), dim3(256), 0, s, dlogits, dlb, (size_t)T * E, sched, 16);
     else if (planes == 1)
-      hipLaunchKernelGGL(router_dl_operands<1>, dim3((T + 31) / 32), dim3(256), 0, s, dlogits, T, E, dlb, pieces, sched, 16);
+      hipLaunchKernelGGL(router_dl_operands<1>, dim3((T + 31) / 32), dim3(256), 0, s, dlogits, T, E, dlb, pieces, 1.f, sched, 16);
     else
-      hipLaunchKernelGGL(router_dl_operands<3>, dim3((T + 31) / 32), dim3(256), 0, s, dlogits, T, E, dlb, pieces, sched, 0);
+      hipLaunchKernelGGL(router_dl_operands<3>, dim3((T + 31) / 32), dim3(256), 0, s, dlogits, T, E, dlb, pieces, dw_wide ? DL_SCALE : 1.f,
+                         sched, 0);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
   };
   const auto dw_stream = [&](bf16_t* pieces) -> int {

@@ -111,7 +111,7 @@ __global__ __launch_bounds__(NT, 1) void router_dw_stream(const bf16_t* __restri
       if (e >= S::E) continue;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        out[(size_t)(col + 8 * (r >> 2) + (r & 3)) * S::E + e] = acc[m][b][r];
+        out[(size_t)(col + 8 * (r >> 2) + (r & 3)) * S::E + e] = PLANES == 1 ? acc[m][b][r] : acc[m][b][r] * DL_UNSCALE;
         probe += acc[m][b][r] * 0.f;
       }
     }
@@ -175,7 +175,7 @@ int launch(const bf16_t* x, const bf16_t* dl, const float* dlogits, float* sums,
 
 }  // namespace
 
-// dl: pieces of router_dl_operands, one plane where E % 64 == 0, three of 32, 96 or 160 experts; T >= 32.
+// dl: pieces of router_dl_operands, one plane where E % 64 == 0, three of 32, 96 or 160 experts, these times DL_SCALE; T >= 32.
 // Weight gradient alone (operands, product, reduction), us, the streaming kernel of few rows (E <= 128 and E = 32), big tiles (E = 192,
 // 256) or plain fp32 products (E = 96, 160) / this one:
 //   T = 16384, d = 4096, E = 128  60 / 45     T = 9001, d = 2880, E = 128  37 / 33      T = 4096, d = 2048, E = 64  22 / 19 (kernels alone)

@@ -81,7 +81,7 @@ __global__ __launch_bounds__(NT, 2) void router_dx_stream(const void* __restrict
 #pragma unroll
       for (int n = 0; n < VECS; ++n) {
         const int at4 = tid + NT * n, token = at4 / (S::E / 4), e = 4 * (at4 % (S::E / 4));
-        float x[4] = {v[n].x, v[n].y, v[n].z, v[n].w};
+        float x[4] = {v[n].x * DL_SCALE, v[n].y * DL_SCALE, v[n].z * DL_SCALE, v[n].w * DL_SCALE};
 #pragma unroll
         for (int p = 0; p < 3; ++p) {      // the leading 8 bits each time
           uint32_t h[4];
@@ -133,6 +133,10 @@ __global__ __launch_bounds__(NT, 2) void router_dx_stream(const void* __restrict
       }
     if (more) publish(buf ^ 1);
     if constexpr (SPLIT) {
+#pragma unroll
+      for (int b = 0; b < 4; ++b)
+#pragma unroll
+        for (int t = 0; t < TG; ++t) acc[b][t] *= DL_UNSCALE;
       // The terms of an infinite dlogit are no sum of it, and an empty term makes NaN of an infinite weight: sums that are no numbers
       // are formed again, in plain fp32.
       float probe = 0.f;

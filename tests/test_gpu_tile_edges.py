@@ -418,6 +418,24 @@ def test_router_weight_gradient_of_infinities(T, d, E):
     assert ((got - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5 * size)[finite].all()
 
 
+# dlogits down to the smallest numbers keep their bits in three terms: both gradients, with x and weights that bring the results back among
+# bf16's normal numbers.  Bounds as above
+@pytest.mark.parametrize("T,d,E", [(777, 128, 160), (1001, 320, 96), (4100, 1024, 32)])
+@pytest.mark.parametrize("exponent", [-112, -130, -143])
+def test_router_gradients_of_tiny_dlogits(T, d, E, exponent):
+    print(f"case router-tiny-{T}-{d}-{E}-{exponent}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T + d + E)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda")  # noqa: E731
+    x, wr = (randn(T, d) * 2.0 ** 40).bfloat16(), (randn(d, E) * 2.0 ** 40).bfloat16()
+    dl = (randn(T, E).double() * 2.0 ** exponent).float()
+    dwr, dx = torch.empty_like(wr), torch.empty_like(x)
+    ws = torch.empty(B.moe_workspace_bytes(B.WS_ROUTER, B.MOE_BF16, T, 1, d, 0, E, 0), dtype=torch.uint8, device="cuda")
+    B.moe_router_bwd(x, wr, dl, dwr, False, dx, False, ws)
+    for got, a, b in ((dwr, x.t(), dl), (dx, dl, wr.t())):
+        want, size = a.double() @ b.double(), a.double().abs() @ b.double().abs()
+        assert ((got.double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5 * size).all()
+
+
 # a token's selection and the counts, with one, two and four blocks per CU (the lines lie at 64 and 256 tokens per CU)
 @pytest.mark.parametrize("T", [16385, 65537])
 def test_route_of_many_tokens_equals_the_route_of_a_few(T):
