@@ -5,6 +5,17 @@
 // eight of them, so that 30 to 56 KB of x per CU are on their way: x in its own layout, read by the transposing LDS reads, the
 // dlogits as router_dl_operands lays them out, tokens contiguous.  The fp32 sums of a range go to memory and reduce_chunks adds
 // them up; one block per CU keeps those few.
+//
+// A chain of matrix instructions does not round to nearest: its error grows with its length, and faster than that of additions.  So a
+// range is summed in several chains, added up in fp32, as many as leave no shape further off than the kernels that had it before, and
+// the chain of the dlogits' first terms is free of the others (E = 160, whose registers do not hold both, is exact enough without).
+// Error of dWr against 64 bits before it is rounded to bf16, of sqrt(T) times the operands' size (rms, 1e-8; exact sums of zero): the
+// kernels before / one chain per range / now:
+//   T = 16384, d = 4096, E = 128  13.4 / 25.9 / 12.1    T = 16384, d = 512, E = 64   9.2 / 18.4 / 9.1     T = 8192, d = 1024, E = 32    9.9 / 18.4 / 8.5
+//   T = 9001, d = 2880, E = 128   9.7 / 15.9 / 9.0      T = 9001, d = 2880, E = 64   8.5 / 16.0 / 8.5     T = 30000, d = 7168, E = 32   35.9 / 100 / 20.9
+//   T = 3000, d = 4096, E = 128   7.3 / 10.4 / 7.0      T = 16384, d = 4096, E = 192  18.4 / 25.9 / 15.0  T = 8192, d = 2048, E = 96    38.0 / 30.3 / 11.8
+//   T = 9001, d = 2880, E = 256   12.3 / 15.9 / 10.0    T = 2000, d = 4096, E = 256  7.1 / 8.5 / 7.1      T = 8192, d = 2048, E = 160   45.4 / 41.4 / 41.4
+// It costs up to 3 us (E = 256, T = 9001, d = 2880 50.5 -> 53.6); E = 32, 96 and 160 nothing or 1.
 #include "common.h"
 #include "kernels.h"
 
@@ -23,6 +34,8 @@ template <int NE, int PLANES> struct Shape {
   static constexpr int STAGES = 155 * 1024 / STAGE < 8 ? 155 * 1024 / STAGE : 8;
   static constexpr int DL_LOADS = PLANES * E / 16, PER_WAVE = (DL_LOADS + 3) / 4, LOADS = 2 + PER_WAVE;      // of 1 KB, per stage
   static constexpr int BLOCKS = (NE + 1) / 2;       // of 32 experts, per wavefront
+  static constexpr int PARTS = PLANES > 1 && NE < 5 ? 2 : 1;       // chains at a time: of the first plane, of the others
+  static constexpr int CHAINS = NE <= 2 ? 8 : NE == 3 ? 2 : NE == 4 ? 5 : NE == 5 ? 1 : 3;      // one after the other in a range
   static_assert((STAGES - 2) * LOADS < 64 && STAGES >= 3, "the wait counter holds 63");
 };
 
@@ -37,7 +50,7 @@ __device__ __forceinline__ bf16x8 x_fragment(const char* p, int n, int s, int la
 }
 
 template <int NE, int PLANES>
-__global__ __launch_bounds__(NT, 1) void router_dw_stream(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dl,
+__global__ __launch_bounds__(NT, NE <= 3 ? 2 : 1) void router_dw_stream(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dl,
                                                          const float* __restrict__ dlogits, float* __restrict__ sums, int T, int d,
                                                          int n_cols, int per_range) {
   using S = Shape<NE, PLANES>;
@@ -65,39 +78,56 @@ __global__ __launch_bounds__(NT, 1) void router_dw_stream(const bf16_t* __restri
                  at + S::X_BYTES + id * 1024);
     }
   };
-  f32x16 acc[2][S::BLOCKS];
+  f32x16 acc[S::PARTS][2][S::BLOCKS], total[2][S::BLOCKS];
 #pragma unroll
   for (int m = 0; m < 2; ++m)
 #pragma unroll
-    for (int b = 0; b < S::BLOCKS; ++b)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[m][b][r] = 0.f;
+    for (int b = 0; b < S::BLOCKS; ++b) {
+      total[m][b] = f32x16{};
+      acc[S::PARTS - 1][m][b] = f32x16{};
+    }
   int expert[S::BLOCKS];                  // of this lane; past the last one it again (never stored)
 #pragma unroll
   for (int b = 0; b < S::BLOCKS; ++b) expert[b] = min((we * S::BLOCKS + b) * 32 + (lane & 31), S::E - 1);
 
 #pragma unroll
   for (int s = 0; s < S::STAGES - 1; ++s) issue(s);
-  for (int s = 0; s < n; ++s) {
-    // stage s has landed once those after it are all that is on its way; and everyone is done with the one whose place is filled next
-    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"((S::STAGES - 2) * S::LOADS) : "memory");
-    __builtin_amdgcn_s_barrier();
-    issue(s + S::STAGES - 1);
-    const char* const stage = lds + s % S::STAGES * S::STAGE;
+  const int per_chain = max(2, (n + S::CHAINS - 1) / S::CHAINS);
+  for (int chain = 0; chain < n; chain += per_chain) {
 #pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const bf16x8 f0 = x_fragment(stage + wc * 4096, 0, k, lane), f1 = x_fragment(stage + wc * 4096, 32, k, lane);
+    for (int m = 0; m < 2; ++m)
 #pragma unroll
-      for (int p = 0; p < PLANES; ++p)
+      for (int b = 0; b < S::BLOCKS; ++b) acc[0][m][b] = f32x16{};
+    for (int s = chain; s < min(n, chain + per_chain); ++s) {
+      // stage s has landed once those after it are all that is on its way; and everyone is done with the one whose place is filled next
+      asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" : : "n"((S::STAGES - 2) * S::LOADS) : "memory");
+      __builtin_amdgcn_s_barrier();
+      issue(s + S::STAGES - 1);
+      const char* const stage = lds + s % S::STAGES * S::STAGE;
 #pragma unroll
-        for (int b = 0; b < S::BLOCKS; ++b) {
-          const int row = p * S::E + expert[b];
-          const bf16x8 g = *reinterpret_cast<const bf16x8*>(stage + S::X_BYTES + row * 64 + (((2 * k + (lane >> 5)) ^ ((row >> 2) & 3)) << 4));
-          acc[0][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f0, g, acc[0][b], 0, 0, 0);
-          acc[1][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1, g, acc[1][b], 0, 0, 0);
-        }
+      for (int k = 0; k < 2; ++k) {
+        const bf16x8 f0 = x_fragment(stage + wc * 4096, 0, k, lane), f1 = x_fragment(stage + wc * 4096, 32, k, lane);
+#pragma unroll
+        for (int p = 0; p < PLANES; ++p)
+#pragma unroll
+          for (int b = 0; b < S::BLOCKS; ++b) {
+            const int row = p * S::E + expert[b], h = p < S::PARTS ? p : S::PARTS - 1;
+            const bf16x8 g = *reinterpret_cast<const bf16x8*>(stage + S::X_BYTES + row * 64 + (((2 * k + (lane >> 5)) ^ ((row >> 2) & 3)) << 4));
+            acc[h][0][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f0, g, acc[h][0][b], 0, 0, 0);
+            acc[h][1][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f1, g, acc[h][1][b], 0, 0, 0);
+          }
+      }
     }
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int b = 0; b < S::BLOCKS; ++b) total[m][b] += acc[0][m][b];
   }
+  if (S::PARTS > 1)
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+      for (int b = 0; b < S::BLOCKS; ++b) total[m][b] += acc[S::PARTS - 1][m][b];
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   float* const out = sums + (size_t)range * d * S::E;
   float probe = 0.f;
@@ -111,8 +141,8 @@ __global__ __launch_bounds__(NT, 1) void router_dw_stream(const bf16_t* __restri
       if (e >= S::E) continue;
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        out[(size_t)(col + 8 * (r >> 2) + (r & 3)) * S::E + e] = PLANES == 1 ? acc[m][b][r] : acc[m][b][r] * DL_UNSCALE;
-        probe += acc[m][b][r] * 0.f;
+        out[(size_t)(col + 8 * (r >> 2) + (r & 3)) * S::E + e] = PLANES == 1 ? total[m][b][r] : total[m][b][r] * DL_UNSCALE;
+        probe += total[m][b][r] * 0.f;
       }
     }
   }

@@ -396,6 +396,23 @@ def test_router_weight_gradient_stream(T, d, E):
         assert ((dwr.double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5 * ref.abs().max()).all()
 
 
+# the sums of the weight gradient before they are rounded to bf16: every token has a partner whose products are the same with the other
+# sign, so what comes out is the error of the sums.  Of sqrt(T) and the operands' size other kernels with these shapes are off by
+# 0.9, 1.3, 0.9 and 1.8e-7, one chain of matrix instructions per range by 2.4, 2.6, 1.5 and 2.6e-7, several added up by 0.9, 1.2, 0.9 and 1.5e-7
+@pytest.mark.parametrize("T,d,E,bound", [(8192, 2048, 32, 1.3e-7), (16384, 4096, 128, 1.6e-7), (16384, 1024, 64, 1.2e-7), (16384, 4096, 192, 2e-7)])
+def test_router_weight_gradient_sums(T, d, E, bound):
+    print(f"case router-dw-sums-{T}-{d}-{E}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(T + d + E)
+    randn = lambda *shape: torch.randn(shape, generator=g, device="cuda")  # noqa: E731
+    order = torch.randperm(T, generator=g, device="cuda")
+    x, dl, wr = randn(T // 2, d).bfloat16(), randn(T // 2, E), randn(d, E).bfloat16()
+    x, dl = torch.cat([x, -x])[order].contiguous(), torch.cat([dl, dl])[order].contiguous()
+    ws = torch.empty(B.moe_workspace_bytes(B.WS_ROUTER, B.MOE_BF16, T, 1, d, 0, E, 0), dtype=torch.uint8, device="cuda")
+    dwr = torch.empty_like(wr)
+    B.moe_router_bwd(x, wr, dl, dwr, False, None, False, ws)
+    assert float(dwr.double().norm()) < bound * (T * dwr.numel()) ** 0.5
+
+
 # Infinities and numbers that round up to them, where the weight gradient's terms and the overlap of its last piece multiply by zeros that
 # stand for nothing: every output is what one product per token gives, in one plane (E = 64, 192) and three.  Finite outputs as above
 @pytest.mark.parametrize("T,d,E", [(777, 128, 160), (1001, 320, 96), (4100, 1024, 32), (4100, 1088, 64), (4100, 1024, 192)])
