@@ -64,9 +64,9 @@ int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int d
 // the last bit of fp32's smallest number, 2^-149, among bf16's normal numbers.  (Beyond 2^96 a term is infinite, and so are the sums
 // it enters, which are formed again.)
 constexpr float DL_SCALE = 0x1p32f, DL_UNSCALE = 0x1p-32f;
-bool router_dw_streams(int T, int d, int E);      // router_dw.hip takes the weight gradient of this shape
-int launch_router_dw_stream(const void* x, const void* dl, const float* dlogits, int T, int d, int E, float* sums, int max_sums,
-                            int* n_sums, hipStream_t s);
+// > 0: router_dw.hip takes the weight gradient of this shape
+int router_dw_ranges(int T, int d, int E, long long max_sums, int splits);
+int launch_router_dw_stream(const void* x, const void* dl, const float* dlogits, int T, int d, int E, float* sums, int ranges, hipStream_t s);
 bool router_dx_streams(int E, int d);      // router_dx.hip takes the input gradient of this shape
 int launch_router_dx_stream(const void* dl, const void* wr, int T, int d, int E, void* dx, int accumulate, hipStream_t s);
 int router_dw_splits(int T, int d, int E);

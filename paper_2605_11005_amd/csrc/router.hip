@@ -621,19 +621,20 @@ int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int d
   const size_t n_w = (size_t)d * E;
   const int red_blocks = device_cu_count() * 4;
   int rc;
-  // Weight gradient: router_dw.hip where router_dw_streams says so; else, up to 128 experts, the streaming kernel of few rows, both
-  // if the workspace's partial sums leave room for the operand
-  // beside at least one sum per plane.  Its sums need no more bytes than the cut product's.  More than 64 rows of planes take
-  // two passes over x, which the big tiles overtake where x is large: E = 128, streaming / tiles, us: T = 32768, d = 2048
-  // 62 / 71; 16384, 4096 60 / 63; 16384, 7168 91 / 84; 32768, 4096 109 / 101; 65536, 4096 198 / 164.
+  // Weight gradient: router_dw.hip where router_dw_ranges says so; else, up to 128 experts, the streaming kernel of few rows if the
+  // workspace's partial sums leave room for its operand beside at least one sum per plane.  Its sums need no more bytes than the cut
+  // product's.  More than 64 rows of planes take two passes over x, which the big tiles overtake where x is large: E = 128, few rows /
+  // tiles, us: T = 32768, d = 2048 62 / 71; 16384, 4096 60 / 63; 16384, 7168 91 / 84; 32768, 4096 109 / 101; 65536, 4096 198 / 164.
   const bool mfma = mfma_shape(dtype, T, d, E);
   const int planes = mfma ? 1 : 3;
   const size_t sum_bytes = n_w * 4;
-  const size_t room = mfma ? align256((size_t)router_dw_splits(T, d, E) * sum_bytes) : align256((size_t)valu_splits(T, d, E) * sum_bytes);
+  const int splits = T == 0 ? 0 : mfma ? router_dw_splits(T, d, E) : valu_splits(T, d, E);
+  const size_t room = align256((size_t)splits * sum_bytes);
   const size_t piece_bytes = align256((size_t)((T + 31) / 32) * 32 * planes * E * 2);
-  const bool dw_wide = dwr && dtype == MOE_BF16 && router_dw_streams(T, d, E) && room >= piece_bytes + sum_bytes;      // router_dw.hip
-  const bool dw_small = dw_wide || (dwr && dtype == MOE_BF16 && T >= 32 && d % 64 == 0 && planes * E <= 128 &&
-                        !(mfma && E > 64 && (long long)T * d > (1ll << 26)) && room >= piece_bytes + planes * sum_bytes);
+  const int max_sums = room > piece_bytes ? (int)((room - piece_bytes) / sum_bytes) : 0;
+  const int ranges = dwr && dtype == MOE_BF16 ? router_dw_ranges(T, d, E, max_sums, splits) : 0;
+  const bool dw_small = ranges > 0 || (dwr && dtype == MOE_BF16 && T >= 32 && d % 64 == 0 && planes * E <= 128 &&
+                        !(mfma && E > 64 && (long long)T * d > (1ll << 26)) && max_sums >= planes);
   const auto dw_operands = [&](bf16_t* dlb, bf16_t* pieces) -> int {
     ProfScope prof(dwr ? MOE_K_ROUTER_DW : MOE_K_ROUTER_DX, s);
     if (!pieces)
@@ -641,16 +642,15 @@ int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int d
     else if (planes == 1)
       hipLaunchKernelGGL(router_dl_operands<1>, dim3((T + 31) / 32), dim3(256), 0, s, dlogits, T, E, dlb, pieces, 1.f, sched, 16);
     else
-      hipLaunchKernelGGL(router_dl_operands<3>, dim3((T + 31) / 32), dim3(256), 0, s, dlogits, T, E, dlb, pieces, dw_wide ? DL_SCALE : 1.f,
+      hipLaunchKernelGGL(router_dl_operands<3>, dim3((T + 31) / 32), dim3(256), 0, s, dlogits, T, E, dlb, pieces, ranges > 0 ? DL_SCALE : 1.f,
                          sched, 0);
     return hipGetLastError() == hipSuccess ? MOE_OK : MOE_EHIP;
   };
   const auto dw_stream = [&](bf16_t* pieces) -> int {
     float* sums = (float*)((char*)pieces + piece_bytes);
-    int n = 0;
-    const int most = (int)((room - piece_bytes) / sum_bytes);
-    const int rc2 = dw_wide ? launch_router_dw_stream(x, pieces, dlogits, T, d, E, sums, most, &n, s)
-                            : launch_router_dw_small(x, pieces, planes, T, d, E, sums, most, &n, s);
+    int n = ranges;
+    const int rc2 = ranges > 0 ? launch_router_dw_stream(x, pieces, dlogits, T, d, E, sums, ranges, s)
+                               : launch_router_dw_small(x, pieces, planes, T, d, E, sums, max_sums, &n, s);
     if (rc2) return rc2;
     ProfScope prof(MOE_K_ROUTER_DW, s);
     hipLaunchKernelGGL((reduce_chunks<bf16_t>), dim3(red_blocks), dim3(256), 0, s, sums, n, n_w, (bf16_t*)dwr, dwr_acc);
@@ -663,7 +663,6 @@ int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int d
     if (dw_small) {
       if ((rc = dw_stream((bf16_t*)partial))) return rc;
     } else if (dwr) {
-      const int splits = router_dw_splits(T, d, E);
       if ((rc = launch_router_dw_bf16(x, dlb, T, d, E, partial, splits, sched, s))) return rc;
       ProfScope prof(MOE_K_ROUTER_DW, s);
       hipLaunchKernelGGL((reduce_chunks<bf16_t>), dim3(red_blocks), dim3(256), 0, s, partial, splits, n_w, (bf16_t*)dwr,
@@ -679,7 +678,6 @@ int launch_router_bwd(const void* x, const void* wr, const float* dlogits, int d
     if ((rc = dw_operands(nullptr, (bf16_t*)base))) return rc;
     if ((rc = dw_stream((bf16_t*)base))) return rc;
   } else if (dwr) {
-    const int splits = T > 0 ? valu_splits(T, d, E) : 0;
     if (splits > 0) {
       ProfScope prof(MOE_K_ROUTER_DW, s);
       const int chunk = (T + splits - 1) / splits;

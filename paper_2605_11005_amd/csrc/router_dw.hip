@@ -11,7 +11,7 @@
 // the chain of the dlogits' first terms is free of the others (E = 160, whose registers do not hold both, is exact enough without).
 // Error of dWr against 64 bits before it is rounded to bf16, of sqrt(T) times the operands' size (rms, 1e-8; exact sums of zero): the
 // kernels before / one chain per range / now:
-//   T = 16384, d = 4096, E = 128  13.4 / 25.9 / 12.1    T = 16384, d = 512, E = 64   9.2 / 18.4 / 9.1     T = 8192, d = 1024, E = 32    9.9 / 18.4 / 8.5
+//   T = 16384, d = 4096, E = 128  13.4 / 25.9 / 12.1    T = 16384, d = 512, E = 64   9.2 / 18.4 / 9.1     T = 8192, d = 1024, E = 32    9.9 / 18.4 / 8.8
 //   T = 9001, d = 2880, E = 128   9.7 / 15.9 / 9.0      T = 9001, d = 2880, E = 64   8.5 / 16.0 / 8.5     T = 30000, d = 7168, E = 32   35.9 / 100 / 20.9
 //   T = 3000, d = 4096, E = 128   7.3 / 10.4 / 7.0      T = 16384, d = 4096, E = 192  18.4 / 25.9 / 15.0  T = 8192, d = 2048, E = 96    38.0 / 30.3 / 11.8
 //   T = 9001, d = 2880, E = 256   12.3 / 15.9 / 10.0    T = 2000, d = 4096, E = 256  7.1 / 8.5 / 7.1      T = 8192, d = 2048, E = 160   45.4 / 41.4 / 41.4
@@ -49,8 +49,10 @@ __device__ __forceinline__ bf16x8 x_fragment(const char* p, int n, int s, int la
   return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
 }
 
+// (64 and 96 experts: bounds that leave the sums no accumulation registers, which an addition cannot read: E = 96 38.2 -> 37.2 us, T = 8192,
+// d = 2048.  E = 32 is 7 to 11 % faster with them.)
 template <int NE, int PLANES>
-__global__ __launch_bounds__(NT, NE <= 3 ? 2 : 1) void router_dw_stream(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dl,
+__global__ __launch_bounds__(NT, NE == 2 || NE == 3 ? 2 : 1) void router_dw_stream(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dl,
                                                          const float* __restrict__ dlogits, float* __restrict__ sums, int T, int d,
                                                          int n_cols, int per_range) {
   using S = Shape<NE, PLANES>;
@@ -175,7 +177,7 @@ __global__ __launch_bounds__(NT, NE <= 3 ? 2 : 1) void router_dw_stream(const bf
 }
 
 template <int NE, int PLANES>
-int launch(const bf16_t* x, const bf16_t* dl, const float* dlogits, float* sums, int T, int d, int max_sums, int* n_sums, hipStream_t s) {
+int launch(const bf16_t* x, const bf16_t* dl, const float* dlogits, float* sums, int T, int d, int ranges, hipStream_t s) {
   using S = Shape<NE, PLANES>;
   constexpr int LDS = S::STAGES * S::STAGE;
   static bool attr_set[64] = {};         // a per-device attribute of the kernel
@@ -187,49 +189,75 @@ int launch(const bf16_t* x, const bf16_t* dl, const float* dlogits, float* sums,
       return MOE_EHIP;
     attr_set[dev] = true;
   }
-  // one block per CU; ranges of at least four pieces
-  const int n_cols = (d + COLS - 1) / COLS, pieces = (T + PIECE - 1) / PIECE;
-  int ranges = device_cu_count() / n_cols;
-  if (ranges > pieces / 4) ranges = pieces / 4;
-  if (ranges > max_sums) ranges = max_sums;
-  if (ranges < 1) ranges = 1;
-  const int per = (pieces + ranges - 1) / ranges;
-  ranges = (pieces + per - 1) / per;
+  const int n_cols = (d + COLS - 1) / COLS, per = ((T + PIECE - 1) / PIECE + ranges - 1) / ranges;
   ProfScope prof(MOE_K_ROUTER_DW, s);
   hipLaunchKernelGGL((router_dw_stream<NE, PLANES>), dim3((unsigned)(ranges * n_cols)), dim3(NT), LDS, s, x, dl, dlogits, sums, T, d,
                      n_cols, per);
   HIP_CHECK_LAUNCH();
-  *n_sums = ranges;
   return MOE_OK;
 }
 
 }  // namespace
 
-// dl: pieces of router_dl_operands, one plane where E % 64 == 0, three of 32, 96 or 160 experts, these times DL_SCALE; T >= 32.
-// Weight gradient alone (operands, product, reduction), us, the streaming kernel of few rows (E <= 128 and E = 32), big tiles (E = 192,
-// 256) or plain fp32 products (E = 96, 160) / this one:
-//   T = 16384, d = 4096, E = 128  60 / 45     T = 9001, d = 2880, E = 128  37 / 33      T = 4096, d = 2048, E = 64  22 / 19 (kernels alone)
-//   T = 8192, d = 2048, E = 32    30 / 22     T = 30000, d = 7168, E = 32  225 / 126    T = 8192, d = 2048, E = 96  112 / 35
-//   T = 2000, d = 7168, E = 256   50 / 42     T = 9000, d = 7168, E = 256  73 / 68      T = 16384, d = 7168, E = 256  103 / 114
-//   T = 1000, d = 2880, E = 128   20 / 22     T = 3000, d = 1024, E = 128  21 / 24      T = 100, d = 4096, E = 32  14 / 17
-// Small x are the few rows' (their sums are fewer); 192 and more experts of a large x the big tiles', which read the dlogits half as
-// often per column.  Two pieces per barrier were no faster (E = 256 slower).
-bool router_dw_streams(int T, int d, int E) {
-  if (T < PIECE || d % 64) return false;
-  if (E == 96 || E == 160) return true;
+// Into how many ranges of tokens, one sum each, the weight gradient of a shape is cut here with room for max_sums of them; 0: other
+// kernels are faster, or there is no room.  splits: of the product that takes the shape otherwise.  Weight gradient alone (operands,
+// product, reduction), us, the streaming kernel of few rows (E = 32, 64 and, up to T d = 2^26, 128), big tiles (E = 128 beyond, 192, 256) or
+// plain fp32 products (E = 96, 160) / this one:
+//   T = 16384, d = 4096, E = 128  61 / 46     T = 9001, d = 2880, E = 128  37 / 35       T = 4096, d = 2048, E = 64    19.0 / 17.5
+//   T = 8192, d = 2048, E = 32    32 / 25     T = 30000, d = 7168, E = 32  229 / 132     T = 8192, d = 2048, E = 96    113 / 37
+//   T = 2000, d = 4096, E = 256   53 / 40     T = 9000, d = 7168, E = 256  76 / 72       T = 16384, d = 7168, E = 256  103 / 114
+// Small x are the others' (their sums are fewer; E = 128, T = 2048, d = 4096 25.3 / 26.0, 4096, 2048 26.1 / 25.9, 6000, 2048 29.7 / 29.0; E = 96,
+// T = 100, d = 2048 12.4 / 13.2, 1000, 256 16.7 / 15.2; E = 160, T = 1000, d = 256 17.1 / 18.0, 3000, 128 27.7 / 23.2), 192 and more experts of a
+// large x the big tiles', which read the dlogits half as often per column.
+// A block per CU, but at least 12 pieces in a range (8 for E = 32; 4 for E = 96 and 160, whose alternative is slow): every range is one more
+// sum to write and read.  4 / 8 / 12 / 16 pieces: T = 4096, d = 1024, E = 64 20.1 / 17.1 / 16.1 / 16.0; 2048, 2048, E = 256 40.7 / 39.4 / 38.0 /
+// 38.5; 4096, 1024, E = 32 21.2 / 17.1 / 17.4 / 18.0, 1024, 4096, E = 32 13.6 / 13.3 / 15.7 / 15.7; 512, 2048, E = 160 20.5 / 23 / 28.6 / 28.6.
+// Where T is large beside d the operand takes the room of the sums.  Few long ranges are slower than the big tiles' many, than the few
+// rows' two blocks per range (E = 128) or eight wavefronts per block (E = 64), and than many more of plain products:
+//   E = 128: T = 20000, d = 512 (12 ranges, tiles 32) 33.5 / 38     30000, 1024 (17) 46 / 41.5     70000, 1536 (9) 106 / 125
+//   E = 192: T = 16384, d = 512 (16) 52 / 41    24000, 512 (8) 59.5 / 62    50000, 1024 (7) 87 / 115    E = 256: 60000, 1024 (2) 105 / 461
+//   E = 64: T = 60000, d = 1536 (12) 58 / 53    24000, 512 (8) 33.4 / 36.1    60000, 1024 (2) 150 / 209
+//   E = 96: T = 16384, d = 4096 (2, plain products 8) 409 / 176    E = 160: 12000, 4096 (1, 6) 457 / 347
+//   E = 32: T = 20000, d = 512 (5, 64) 100 / 56    21000, 512 (2, 64) 77 / 120
+// Two pieces per barrier were no faster (E = 256 slower).
+int router_dw_ranges(int T, int d, int E, long long max_sums, int splits) {
+  if (T < PIECE || d % 64 || max_sums < 1) return 0;
   const long long x = (long long)T * d;
-  return x >= (1ll << 22) && (E == 32 || E == 64 || E == 128 || ((E == 192 || E == 256) && x <= (1ll << 26)));
+  long long least = 1ll << 22, most = 1ll << 40;      // of T d
+  int pieces_per_range = 12;
+  double longer = 2.25;                               // as many pieces in a range as the alternative's, at most, where there is little room
+  switch (E) {
+    case 32: pieces_per_range = 8; longer = 14; break;
+    case 64: longer = 2.75; break;
+    case 96: least = 7 << 15; pieces_per_range = 4; longer = 9; break;
+    case 128: least = (1 << 23) + 1; break;
+    case 160: least = 5 << 16; pieces_per_range = 4; longer = 6; break;
+    case 192: case 256: most = 1ll << 26; break;
+    default: return 0;
+  }
+  if (x < least || x > most) return 0;
+  const int n_cols = (d + COLS - 1) / COLS, pieces = (T + PIECE - 1) / PIECE;
+  int ranges = device_cu_count() / n_cols;
+  if (ranges > pieces / pieces_per_range) ranges = pieces / pieces_per_range;
+  if (ranges > max_sums) {
+    if (splits > longer * max_sums) return 0;
+    ranges = (int)max_sums;
+  }
+  if (ranges < 1) ranges = 1;
+  const int per = (pieces + ranges - 1) / ranges;
+  return (pieces + per - 1) / per;
 }
-int launch_router_dw_stream(const void* x, const void* dl, const float* dlogits, int T, int d, int E, float* sums, int max_sums,
-                            int* n_sums, hipStream_t s) {
+// dl: pieces of router_dl_operands, one plane where E % 64 == 0, three of 32, 96 or 160 experts, these times DL_SCALE; T >= 32.
+// sums: [ranges][d][E]
+int launch_router_dw_stream(const void* x, const void* dl, const float* dlogits, int T, int d, int E, float* sums, int ranges, hipStream_t s) {
   const bf16_t *a = (const bf16_t*)x, *b = (const bf16_t*)dl;
   switch (E / 32) {
-    case 1: return launch<1, 3>(a, b, dlogits, sums, T, d, max_sums, n_sums, s);
-    case 2: return launch<2, 1>(a, b, dlogits, sums, T, d, max_sums, n_sums, s);
-    case 3: return launch<3, 3>(a, b, dlogits, sums, T, d, max_sums, n_sums, s);
-    case 4: return launch<4, 1>(a, b, dlogits, sums, T, d, max_sums, n_sums, s);
-    case 5: return launch<5, 3>(a, b, dlogits, sums, T, d, max_sums, n_sums, s);
-    case 6: return launch<6, 1>(a, b, dlogits, sums, T, d, max_sums, n_sums, s);
-    default: return launch<8, 1>(a, b, dlogits, sums, T, d, max_sums, n_sums, s);
+    case 1: return launch<1, 3>(a, b, dlogits, sums, T, d, ranges, s);
+    case 2: return launch<2, 1>(a, b, dlogits, sums, T, d, ranges, s);
+    case 3: return launch<3, 3>(a, b, dlogits, sums, T, d, ranges, s);
+    case 4: return launch<4, 1>(a, b, dlogits, sums, T, d, ranges, s);
+    case 5: return launch<5, 3>(a, b, dlogits, sums, T, d, ranges, s);
+    case 6: return launch<6, 1>(a, b, dlogits, sums, T, d, ranges, s);
+    default: return launch<8, 1>(a, b, dlogits, sums, T, d, ranges, s);
   }
 }

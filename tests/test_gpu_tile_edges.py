@@ -377,13 +377,41 @@ def test_router_input_gradient_of_infinities(T, d, E):
         assert ((got - ref).abs() <= 2.0 ** -8 * ref.abs() + 1e-5 * size)[finite].all()
 
 
+def _dw_ranges(T, d, E):
+    """(ranges, offset of their sums in the workspace): into how many ranges of tokens the stream over x (router_dw.hip) cuts the weight
+    gradient of a shape, 0 where it goes to another kernel (rules of router.hip and router_dw.hip)."""
+    up = lambda a, b: -(-a // b)  # noqa: E731
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    planes, sum_bytes, pieces, x = (1 if E % 64 == 0 else 3), 4 * d * E, up(T, 32), T * d
+    tiles = up(d, 256) * up(E, 256)
+    splits = min(range(1, min(32, up(T, 128)) + 1), key=lambda s: up(tiles * s, cus) * (up(up(T, s), 32) + 16))
+    if planes == 3:
+        splits = max(1, min(up(4 * cus, up(d, 64) * up(E, 64)), (64 << 20) // sum_bytes, up(T, 64), 64))
+    operand = up(pieces * 64 * planes * E, 256) * 256
+    room = (up(splits * sum_bytes, 256) * 256 - operand) // sum_bytes
+    least = {32: 1 << 22, 64: 1 << 22, 96: 7 << 15, 128: (1 << 23) + 1, 160: 5 << 16, 192: 1 << 22, 256: 1 << 22}.get(E)
+    if T < 32 or d % 64 or room < 1 or least is None or x < least or (E in (192, 256) and x > 1 << 26):
+        return 0, 0
+    ranges = min(cus // up(d, 128), pieces // {1: 12, 3: 8 if E == 32 else 4}[planes])
+    if ranges > room and splits > {32: 14, 64: 2.75, 96: 9, 160: 6}.get(E, 2.25) * room:
+        return 0, 0
+    ranges = max(1, min(ranges, room))
+    return up(pieces, up(pieces, ranges)), 256 + (up(2 * T * E, 256) * 256 if planes == 1 else 0) + operand
+
+
 # router_dw.hip, one plane (E = 64, 128, 192, 256) and three (32, 96, 160): fewer pieces than the ring holds, a last piece that overlaps
-# the one before it, several ranges, a last block of 64 columns.  Against float64; the results are rounded to bf16 (2**-8), bf16
-# dlogits first (then: against what the kernel is given), sums of up to T products in fp32 (1e-5 of the largest)
-@pytest.mark.parametrize("T,d,E", [(32, 64, 96), (33, 192, 160), (300, 320, 96), (65600, 64, 32), (21900, 192, 64), (6600, 640, 128),
-                                   (4100, 1024, 192), (4097, 1088, 256)])
-def test_router_weight_gradient_stream(T, d, E):
+# the one before it, one and several ranges, as many as there are CUs or as the room holds, a last block of 64 columns; and shapes it leaves
+# to others (ranges = 0), of small x, without room, with few long ranges beside those of big tiles (28000, 512, 256).  Against float64; the results
+# are rounded to bf16 (2**-8), bf16 dlogits first (then: against what the kernel is given), sums of up to T products in fp32 (1e-5 of
+# the largest)
+@pytest.mark.parametrize("T,d,E,ranges", [
+    (65, 3584, 96, 1), (300, 768, 96, 2), (1000, 1088, 96, 8), (100, 3328, 160, 1), (777, 448, 160, 5), (4100, 1024, 32, 15), (700, 7168, 32, 2),
+    (4097, 1088, 64, 10), (600, 7168, 64, 1), (2100, 4096, 128, 5), (9001, 1024, 128, 22), (4100, 1024, 192, 10), (9000, 512, 192, 22),
+    (4097, 1088, 256, 10), (32, 64, 96, 0), (33, 192, 160, 0), (65600, 64, 32, 0), (21900, 192, 64, 0), (6600, 640, 128, 0), (28000, 512, 256, 0)])
+def test_router_weight_gradient_stream(T, d, E, ranges):
     print(f"case router-dw-{T}-{d}-{E}", flush=True)
+    n, at = _dw_ranges(T, d, E)
+    assert n == ranges
     g = torch.Generator(device="cuda").manual_seed(T + d + E)
     randn = lambda *shape: torch.randn(shape, generator=g, device="cuda")  # noqa: E731
     x, wr, dl, dw0 = randn(T, d).bfloat16(), randn(d, E).bfloat16(), randn(T, E) * 0.1, randn(d, E).bfloat16()
@@ -391,9 +419,17 @@ def test_router_weight_gradient_stream(T, d, E):
     ref = x.double().t() @ (dl.bfloat16() if E % 64 == 0 else dl).double()
     for accumulate in (False, True):
         dwr = dw0.clone()
+        ws.fill_(0x7b)
         B.moe_router_bwd(x, wr, dl, dwr, accumulate, None, False, ws)
         want = ref + (dw0.double() if accumulate else 0.0)
         assert ((dwr.double() - want).abs() <= 2.0 ** -8 * want.abs() + 1e-5 * ref.abs().max()).all()
+        words = ws.view(torch.int32)
+        if n:       # as many sums as ranges, and nobody drew a ticket
+            sums = words[at // 4:]
+            assert not (sums[:n * d * E] == 0x7b7b7b7b).any() and (sums[n * d * E:] == 0x7b7b7b7b).all()
+            assert E % 64 or not words[:16].any()
+        elif d * T > 1 << 23:
+            assert words[:16].any()
 
 
 # the sums of the weight gradient before they are rounded to bf16: every token has a partner whose products are the same with the other
@@ -415,7 +451,7 @@ def test_router_weight_gradient_sums(T, d, E, bound):
 
 # Infinities and numbers that round up to them, where the weight gradient's terms and the overlap of its last piece multiply by zeros that
 # stand for nothing: every output is what one product per token gives, in one plane (E = 64, 192) and three.  Finite outputs as above
-@pytest.mark.parametrize("T,d,E", [(777, 128, 160), (1001, 320, 96), (4100, 1024, 32), (4100, 1088, 64), (4100, 1024, 192)])
+@pytest.mark.parametrize("T,d,E", [(777, 448, 160), (1001, 320, 96), (4100, 1024, 32), (4100, 1088, 64), (4100, 1024, 192)])
 def test_router_weight_gradient_of_infinities(T, d, E):
     print(f"case router-dw-inf-{T}-{d}-{E}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(T + d + E)
@@ -437,7 +473,7 @@ def test_router_weight_gradient_of_infinities(T, d, E):
 
 # dlogits down to the smallest numbers keep their bits in three terms: both gradients, with x and weights that bring the results back among
 # bf16's normal numbers.  Bounds as above
-@pytest.mark.parametrize("T,d,E", [(777, 128, 160), (1001, 320, 96), (4100, 1024, 32)])
+@pytest.mark.parametrize("T,d,E", [(777, 448, 160), (1001, 320, 96), (4100, 1024, 32)])
 @pytest.mark.parametrize("exponent", [-112, -130, -143])
 def test_router_gradients_of_tiny_dlogits(T, d, E, exponent):
     print(f"case router-tiny-{T}-{d}-{E}-{exponent}", flush=True)
