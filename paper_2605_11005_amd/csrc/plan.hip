@@ -148,42 +148,49 @@ __global__ __launch_bounds__(64) void plan_scatter(const int32_t* __restrict__ t
 }
 
 // All three steps in one launch, for a few ten thousand slots (direct_slots()): block b owns the DIRECT_CHUNK slots from b * DIRECT_CHUNK on, one group
-// of 64 per wavefront, and counts the experts of all slots by itself.
-// LDS: hist[DIRECT_WAVES][e_cnt] (of the own groups; becomes each wavefront's next row per expert), before[e_cnt] (in the blocks before
-// this one), total[e_cnt + 1].
+// of 64 per wavefront, and counts the experts of all slots by itself.  Additions to one word wait for each other, and one expert may
+// hold most of the slots, so lanes add to `copies` tables in turn (direct_copies()).
+// LDS: hist[DIRECT_WAVES][e_cnt] (of the own groups; becomes each wavefront's next row per expert), before[copies][pitch] (slots of the
+// blocks before this one), total[copies][pitch] (the other slots; the first copy becomes the first row per expert).
 constexpr int DIRECT_WAVES = 16, DIRECT_CHUNK = DIRECT_WAVES * WAVE;
 constexpr int DIRECT_MAX_LOCAL = 900;      // the tables fit the 64 KB of LDS that need no opt-in
 
 __global__ __launch_bounds__(DIRECT_CHUNK) void plan_direct(const int32_t* __restrict__ topk_idx, int n_slots, int e_lo, int e_cnt, int bits,
-                                                           int cap, int32_t* __restrict__ offsets, int32_t* __restrict__ perm,
-                                                           int32_t* __restrict__ inv, int32_t* __restrict__ status) {
+                                                           int copies, int cap, int32_t* __restrict__ offsets,
+                                                           int32_t* __restrict__ perm, int32_t* __restrict__ inv,
+                                                           int32_t* __restrict__ status) {
   extern __shared__ int32_t hist[];
+  const int pitch = e_cnt | 1;                       // odd: an expert's copies are on different banks
   int32_t* const before = hist + DIRECT_WAVES * e_cnt;
-  int32_t* const total = before + e_cnt;
+  int32_t* const total = before + copies * pitch;
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
-  const int n_groups = (n_slots + WAVE - 1) / WAVE, first = blockIdx.x * DIRECT_WAVES, own = first + wave;
+  const int n_groups = (n_slots + WAVE - 1) / WAVE, first = blockIdx.x * DIRECT_WAVES, own = (first + wave) * WAVE + lane;
   int32_t* const mine = hist + wave * e_cnt;
-  const int le_own = local_expert(topk_idx, own * WAVE + lane, n_slots, e_lo, e_cnt);
-  for (int i = tid; i < (DIRECT_WAVES + 2) * e_cnt; i += DIRECT_CHUNK) hist[i] = 0;
+  const int le_own = local_expert(topk_idx, own, n_slots, e_lo, e_cnt);
+  for (int i = tid; i < DIRECT_WAVES * e_cnt + 2 * copies * pitch; i += DIRECT_CHUNK) hist[i] = 0;
+  const unsigned long long same = same_key(le_own, bits);
+  const int rank = __popcll(same & ((1ull << lane) - 1ull));
   __syncthreads();
+  if (le_own >= 0 && rank == 0) mine[le_own] = __popcll(same);
+  const int copy = (lane & (copies - 1)) * pitch;
   // eight groups at a time: one memory round trip for all of them
   for (int g0 = wave; g0 < n_groups; g0 += 8 * DIRECT_WAVES) {
     int le[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) le[i] = local_expert(topk_idx, (g0 + i * DIRECT_WAVES) * WAVE + lane, n_slots, e_lo, e_cnt);
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int g = g0 + i * DIRECT_WAVES;
-      if (le[i] >= 0) {
-        atomicAdd(&total[le[i]], 1);
-        if (g < first) atomicAdd(&before[le[i]], 1);
-        if (g == own) atomicAdd(&mine[le[i]], 1);
-      }
-    }
+    for (int i = 0; i < 8; ++i)
+      if (le[i] >= 0) atomicAdd((g0 + i * DIRECT_WAVES < first ? before : total) + copy + le[i], 1);
   }
   __syncthreads();
   if (tid < e_cnt) {                                 // e_cnt <= 900 < threads of the block
-    int run = before[tid];
+    int run = 0, rest = 0;
+#pragma unroll 8
+    for (int c = 0; c < copies; ++c) {
+      run += before[c * pitch + tid];
+      rest += total[c * pitch + tid];
+    }
+    total[tid] = run + rest;
 #pragma unroll
     for (int w = 0; w < DIRECT_WAVES; ++w) {
       const int v = hist[w * e_cnt + tid];
@@ -191,24 +198,26 @@ __global__ __launch_bounds__(DIRECT_CHUNK) void plan_direct(const int32_t* __res
       run += v;
     }
   }
+  __syncthreads();
   if (wave == 0) {                                   // exclusive scan over the experts, 64 at a time
     int carry = 0;
     for (int e0 = 0; e0 < e_cnt; e0 += WAVE) {
-      const int v = e0 + lane < e_cnt ? total[e0 + lane] : 0, incl = wave_scan(v);
-      if (e0 + lane < e_cnt) total[e0 + lane] = carry + incl - v;
-      carry += __builtin_amdgcn_readlane(incl, WAVE - 1);
+      const int v = e0 + lane < e_cnt ? total[e0 + lane] : 0, start = carry + wave_scan(v) - v;
+      if (e0 + lane < e_cnt) total[e0 + lane] = start;
+      if (blockIdx.x == 0 && e0 + lane < e_cnt) offsets[e0 + lane] = min(start, cap);
+      carry = __builtin_amdgcn_readlane(start + v, WAVE - 1);
     }
-    if (lane == 0) {
-      total[e_cnt] = carry;
-      if (blockIdx.x == 0) *status = carry > cap ? 1 : 0;
+    if (blockIdx.x == 0 && lane == 0) {
+      offsets[e_cnt] = min(carry, cap);
+      *status = carry > cap ? 1 : 0;
     }
   }
   __syncthreads();
-  if (blockIdx.x == 0)
-    for (int i = tid; i <= e_cnt; i += DIRECT_CHUNK) offsets[i] = total[i] < cap ? total[i] : cap;
-  for (int i = lane; i < e_cnt; i += WAVE) mine[i] += total[i];      // read and written by this wavefront only
-  __builtin_amdgcn_wave_barrier();
-  scatter_group(own * WAVE + lane, le_own, bits, lane, n_slots, cap, mine, perm, inv);
+  if (own >= n_slots) return;
+  int row = le_own >= 0 ? mine[le_own] + total[le_own] + rank : -1;
+  if (row >= cap) row = -1;                          // dropped: caller's cap was too small
+  inv[own] = row;
+  if (row >= 0) perm[row] = own;
 }
 
 }  // namespace
@@ -237,15 +246,20 @@ int plan_static_scratch(void** ptr) {
   return MOE_OK;
 }
 
-// Every block counts all slots, in one round of LDS additions per 1024 of them, which queue up where few experts share them all; the
-// three launches' scan takes a round per 16 experts.  Plan and move of 16 bytes per row in a captured graph, us, before (one block up
-// to 8192 slots, then three launches) / in one launch:
-//   slots, local experts of E   8188, 16 of 128  11.1 / 8.2    16384, 8 of 64  15.9 / 10.5    36004, 16 of 128  18.4 / 16.3
-//                               8192, 8 of 8     12.5 / 11.0   65536, 8 of 64  19.1 / 23.6    60000, 8 of 8     22.2 / 37.9
-//                               65536, 32 of 256 22.5 / 22.9   32768, 128 of 128 38.2 / 15.6  56000, 256 of 256 61.4 / 21.9
+// Every block counts all slots, in one round of LDS additions per 1024 of them; the three launches' scan takes a round per 16 experts.
+// Plan and move of 16 bytes per row in a captured graph, us, three launches (one block up to 8192 slots) / one launch whose lanes all add
+// to one table / now:
+//   slots, local experts of E, experts alike         8192, 8 of 8      13.1 / 11.6 / 9.4     16384, 8 of 8  18.6 / 16.8 / 13.0    32768, 16 of 16  20.0 / 20.1 / 16.3
+//                                                    16384, 16 of 128  17.0 / 10.4 / 9.9     65536, 64 of 64  28.8 / 23.5 / 21.9  65536, 256 of 256  62.1 / 24.3 / 23.0
+//   one expert holding all slots                     2049, 8 of 8      8.9 / 9.8 / 6.7       8192, 8 of 8   18.5 / 22.0 / 9.2     16384, 8 of 8    18.4 / 37.6 / 12.7
+//   half of them; a quarter                          32768, 16 of 16   20.0 / 38.4 / 16.4    32768, 32 of 32  21.6 / 23.6 / 14.9
+// (Where the lines lie was measured before there were copies: 60000 slots of 8 experts 22.2 in three launches, 37.9 in one.)
 static int direct_slots(int e_cnt) {
   return e_cnt > DIRECT_MAX_LOCAL ? -1 : (e_cnt >= 64 ? 65536 : (e_cnt >= 16 ? 32768 : 16384));
 }
+// 8 / 16 / 32 copies: 16384 slots of 8 experts alike 13.0 / 13.1 / 13.3, on one of them 12.7 / 12.6 / 12.8; the many tables of many experts
+// take LDS, and their additions rarely meet.
+static int direct_copies(int e_cnt) { return e_cnt <= 128 ? 8 : e_cnt <= 256 ? 4 : 1; }
 
 size_t plan_ws_bytes(int T, int k, int e_cnt) {
   size_t n_slots = (size_t)T * (size_t)k;
@@ -263,10 +277,11 @@ int launch_plan(const int32_t* topk_idx, int T, int k, int e_lo, int e_cnt, int3
   int bits = 0;                                      // of a local expert's index
   while ((1 << bits) < e_cnt) ++bits;
   if (n_slots <= direct_slots(e_cnt)) {
-    const size_t shm = ((size_t)(DIRECT_WAVES + 2) * e_cnt + 1) * sizeof(int32_t);
+    const int copies = direct_copies(e_cnt);
+    const size_t shm = ((size_t)DIRECT_WAVES * e_cnt + 2 * (size_t)copies * (e_cnt | 1)) * sizeof(int32_t);
     const int blocks = (int)((n_slots + DIRECT_CHUNK - 1) / DIRECT_CHUNK);
-    hipLaunchKernelGGL(plan_direct, dim3(blocks > 0 ? blocks : 1), dim3(DIRECT_CHUNK), shm, s, topk_idx, (int)n_slots, e_lo, e_cnt, bits, cap,
-                       offsets, perm, inv, status);
+    hipLaunchKernelGGL(plan_direct, dim3(blocks > 0 ? blocks : 1), dim3(DIRECT_CHUNK), shm, s, topk_idx, (int)n_slots, e_lo, e_cnt, bits, copies,
+                       cap, offsets, perm, inv, status);
     HIP_CHECK_LAUNCH();
     return MOE_OK;
   }

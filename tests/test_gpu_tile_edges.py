@@ -230,7 +230,7 @@ def test_router_logits_at_block_edges(T, d, E):
     assert rel_err(host(logits), host(x) @ host(wr)) < 1e-5
 
 
-# one block plans up to 8192 slots of up to 900 local experts; beyond either the plan is three launches
+# plans of one block of 1024 slots and of several; up to 2048 slots the dispatch makes the plan itself
 @pytest.mark.parametrize("T,k,e_cnt", [(1, 1, 1), (63, 1, 3), (64, 16, 64), (1024, 8, 7), (1025, 8, 7), (300, 4, 900), (300, 4, 901), (40, 2, 0)])
 def test_plan_in_one_block_and_in_three_launches(T, k, e_cnt):
     print(f"case plan-{T}-{k}-{e_cnt}", flush=True)
@@ -249,10 +249,28 @@ def test_plan_in_one_block_and_in_three_launches(T, k, e_cnt):
     assert int(ws[:4].view(torch.int32).item()) == 0
 
 
-# one launch plans up to 16384 slots (32768 of 16 local experts or more, 65536 of 64 or more), several blocks of 1024; three beyond
-@pytest.mark.parametrize("T,k,e_cnt", [(1025, 2, 7), (4096, 4, 7), (4097, 4, 7), (8192, 4, 16), (8193, 4, 16), (8192, 8, 64), (8193, 8, 64), (1200, 8, 900)])
+# one launch plans up to 16384 slots (32768 of 16 local experts or more, 65536 of 64 or more), several blocks of 1024; three beyond, and for
+# more than 900 local experts
+@pytest.mark.parametrize("T,k,e_cnt", [(1025, 2, 7), (4096, 4, 7), (4097, 4, 7), (8192, 4, 16), (8193, 4, 16), (8192, 8, 64), (8193, 8, 64), (1200, 8, 900), (600, 4, 900), (600, 4, 901), (1025, 2, 0)])
 def test_plan_of_several_blocks(T, k, e_cnt):
     test_plan_in_one_block_and_in_three_launches(T, k, e_cnt)
+
+
+# the same where most slots, or all, are one expert's, whose additions go to eight, four or one tables; other experts in between, slots that are
+# not local, blocks whose first slots are
+@pytest.mark.parametrize("T,k,e_cnt", [(2049, 1, 1), (5000, 1, 8), (16384, 1, 8), (3000, 3, 128), (3000, 3, 129), (2000, 8, 256), (2000, 8, 257)])
+def test_plan_of_a_hot_expert(T, k, e_cnt):
+    print(f"case hot-plan-{T}-{k}-{e_cnt}", flush=True)
+    rng, e_lo, cap = np.random.default_rng(T + e_cnt), 3, T * k
+    ids = rng.permuted(np.tile(np.arange(e_cnt + 20), (T, 1)), axis=1)[:, :k].astype(np.int32)
+    hot = e_lo + e_cnt // 2
+    ids[:, 0] = np.where((ids == hot).any(axis=1) | (rng.random(T) < 0.1), ids[:, 0], hot)
+    off_ref, perm_ref, inv_ref = O.plan(ids, e_lo, e_cnt)[:3]
+    i32 = dict(dtype=torch.int32, device="cuda")
+    off, perm, inv = torch.full((e_cnt + 1,), -7, **i32), torch.full((cap,), -7, **i32), torch.full((T, k), -7, **i32)
+    x, xp = torch.zeros((T, 8), dtype=torch.bfloat16, device="cuda"), torch.empty((cap, 8), dtype=torch.bfloat16, device="cuda")
+    B.moe_dispatch_static(x, k, torch.from_numpy(ids).cuda(), None, e_lo, e_cnt, off, perm, inv, xp, torch.full((1,), -7, **i32))
+    assert (host(off) == off_ref).all() and (host(inv) == inv_ref).all() and (host(perm)[:int(off_ref[-1])] == perm_ref).all()
 
 
 # plan and move of few slots in one launch (up to 2048 slots, and 2**20 reads of slots by all blocks) and in two: one and several blocks
