@@ -1,8 +1,9 @@
 // Row movers: dispatch (token order -> expert order) and combine (expert order -> token
 // order, gate-weighted).  Both are token-major (a token's row is split over a few blocks), so every row
 // of x / o is read exactly once and every row of xp / y is written exactly once:
-//   dispatch : read x[t] once (skipped when the token has no local slot), write it to each
-//              of the token's local rows            -> (U + R) * d * b bytes
+//   dispatch : read x[t] once (skipped when the token has no local slot, but for a few slots, whose
+//              plan is made meanwhile), write it to each of the token's local rows
+//                                                   -> (U + R) * d * b bytes
 //   combine  : read the token's local rows, write y[t] once (zeros when none)
 //                                                   -> (R + T) * d * b bytes
 // Accesses are 16 bytes per lane and one vector per thread: on this chip a plain copy is fastest
@@ -67,7 +68,7 @@ __global__ __launch_bounds__(DISPATCH_BLOCK) void dispatch_rows(const u32x4* __r
 
 // The plan of a few slots and the move in one launch: a token's block finds the rows of its own slots by counting, over all slots,
 // those that come before them in the order (local expert, slot).  The block behind the movers adds the row counts up to offsets.
-// Bound by its launch and by the latency of two reads, of the slots and of inv's place in them.
+// Bound by its launch and by the latency of one read of the slots: a lane per own slot, and counts by ballots.
 constexpr int FEW_SLOTS = 2048;
 
 template <bool BF16, bool SCALED>
@@ -76,28 +77,42 @@ __global__ __launch_bounds__(DISPATCH_BLOCK) void plan_and_dispatch(const u32x4*
                                                                     int e_lo, int e_cnt, int cap, int32_t* __restrict__ offsets,
                                                                     int32_t* __restrict__ perm, int32_t* __restrict__ inv,
                                                                     int32_t* __restrict__ status, u32x4* __restrict__ xp) {
-  constexpr int WAVES = DISPATCH_BLOCK / WAVE, KEYS = FEW_SLOTS / DISPATCH_BLOCK;
+  constexpr int WAVES = DISPATCH_BLOCK / WAVE, KEYS = FEW_SLOTS / DISPATCH_BLOCK, BATCH = 4, ELSEWHERE = 0x7FFFFFFF;
   __shared__ int32_t hist[MOE_MAX_LOCAL];
   __shared__ int32_t before[WAVES][MOE_MAX_TOPK];
   const int tid = threadIdx.x, lane = tid & (WAVE - 1), wave = tid / WAVE;
   const int n_slots = T * k, t = blockIdx.x / n_seg;
-  const auto local = [&](int s) {         // index of a slot's expert if it is local, else a number beyond them
+  const auto key_of = [&](int s) {        // place of a slot in the order; beyond all others if its expert is not local
     const int le = topk_idx[s] - e_lo;
-    return le >= 0 && le < e_cnt ? le : 0x7FFFFFFF;
+    return le >= 0 && le < e_cnt ? le * FEW_SLOTS + s : ELSEWHERE;
   };
+  const int seg = blockIdx.x - t * n_seg, c = seg * DISPATCH_BLOCK + tid;
+  u32x4 v = {0, 0, 0, 0};
+  if (t < T && c < row_vecs) v = __builtin_nontemporal_load(x + (size_t)t * row_vecs + c);
+  int key[KEYS];
+#pragma unroll
+  for (int b = 0; b < KEYS; b += BATCH)
+    if (b * DISPATCH_BLOCK < n_slots)     // (uniform)
+#pragma unroll
+      for (int i = b; i < b + BATCH; ++i) {
+        const int s = i * DISPATCH_BLOCK + tid;
+        key[i] = s < n_slots ? key_of(s) : ELSEWHERE;
+      }
   if (t == T) {
     for (int i = tid; i < e_cnt; i += DISPATCH_BLOCK) hist[i] = 0;
     __syncthreads();
-    for (int s = tid; s < n_slots; s += DISPATCH_BLOCK) {
-      const int le = local(s);
-      if (le < e_cnt) atomicAdd(&hist[le], 1);
-    }
+#pragma unroll
+    for (int b = 0; b < KEYS; b += BATCH)
+      if (b * DISPATCH_BLOCK < n_slots)
+#pragma unroll
+        for (int i = b; i < b + BATCH; ++i)
+          if (key[i] != ELSEWHERE) atomicAdd(&hist[key[i] / FEW_SLOTS], 1);
     __syncthreads();
     if (wave == 0) {
       int sum = 0;
       for (int e0 = 0; e0 < e_cnt; e0 += WAVE) {
-        const int v = e0 + lane < e_cnt ? hist[e0 + lane] : 0, incl = wave_scan(v);
-        if (e0 + lane < e_cnt) offsets[e0 + lane] = min(sum + incl - v, cap);
+        const int n = e0 + lane < e_cnt ? hist[e0 + lane] : 0, incl = wave_scan(n);
+        if (e0 + lane < e_cnt) offsets[e0 + lane] = min(sum + incl - n, cap);
         sum += __builtin_amdgcn_readlane(incl, WAVE - 1);
       }
       if (lane == 0) {
@@ -107,43 +122,36 @@ __global__ __launch_bounds__(DISPATCH_BLOCK) void plan_and_dispatch(const u32x4*
     }
     return;
   }
-  const int seg = blockIdx.x - t * n_seg, c = seg * DISPATCH_BLOCK + tid;
-  u32x4 v = {0, 0, 0, 0};
-  if (c < row_vecs) v = __builtin_nontemporal_load(x + (size_t)t * row_vecs + c);
-  int key[KEYS];
-#pragma unroll
-  for (int i = 0; i < KEYS; ++i) {
-    const int s = i * DISPATCH_BLOCK + tid;
-    key[i] = s < n_slots ? local(s) : 0x7FFFFFFF;
-  }
-  for (int j = 0; j < k; ++j) {
-    const int mine = t * k + j, le = local(mine);
-    if (le >= e_cnt) continue;            // (uniform)
+  const int slot = t * k + lane, own = lane < k ? key_of(slot) : ELSEWHERE;
+  const float scale = SCALED && lane < k ? row_scale[slot] : 1.f;
+  const unsigned long long locals = __ballot(own != ELSEWHERE);
+  int row = 0;                            // of slot `lane`
+  for (unsigned long long m = locals; m; m &= m - 1) {
+    const int j = __builtin_ctzll(m), mine = __builtin_amdgcn_readlane(own, j);
     int n = 0;
 #pragma unroll
-    for (int i = 0; i < KEYS; ++i) n += key[i] < le || (key[i] == le && i * DISPATCH_BLOCK + tid < mine) ? 1 : 0;
-    n = wave_sum(n);
-    if (lane == 0) before[wave][j] = n;
-  }
-  __syncthreads();
-  const auto row_of = [&](int j) {        // -1: the slot's expert is elsewhere, or its row beyond the capacity
-    if (local(t * k + j) >= e_cnt) return -1;
-    int row = 0;
+    for (int b = 0; b < KEYS; b += BATCH)
+      if (b * DISPATCH_BLOCK < n_slots)
 #pragma unroll
-    for (int w = 0; w < WAVES; ++w) row += before[w][j];
-    return row < cap ? row : -1;
-  };
-  if (seg == 0 && tid < k) {
-    const int row = row_of(tid);
-    inv[t * k + tid] = row;
-    if (row >= 0) perm[row] = t * k + tid;
+        for (int i = b; i < b + BATCH; ++i) n += __popcll(__ballot(key[i] < mine));
+    row = lane == j ? n : row;
   }
-  if (c >= row_vecs) return;
-  for (int j = 0; j < k; ++j) {
-    const int row = row_of(j);
-    if (row < 0) continue;
-    const u32x4 o = SCALED ? scale_vec<BF16>(v, row_scale[(size_t)t * k + j]) : v;
-    __builtin_nontemporal_store(o, xp + (size_t)row * row_vecs + c);
+  if (lane < k) before[wave][lane] = row;
+  __syncthreads();
+  if (own != ELSEWHERE) {
+    row = 0;
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) row += before[w][lane];
+  }
+  if (own == ELSEWHERE || row >= cap) row = -1;
+  if (seg == 0 && tid < k) {
+    inv[slot] = row;
+    if (row >= 0) perm[row] = slot;
+  }
+  for (unsigned long long m = __ballot(row >= 0); m; m &= m - 1) {
+    const int j = __builtin_ctzll(m);
+    const u32x4 o = SCALED ? scale_vec<BF16>(v, __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(scale), j))) : v;
+    if (c < row_vecs) __builtin_nontemporal_store(o, xp + (size_t)__builtin_amdgcn_readlane(row, j) * row_vecs + c);
   }
 }
 
@@ -218,10 +226,11 @@ int launch_dispatch_rows(const void* x, int dtype, int T, int d, int k, const in
   return MOE_OK;
 }
 
-// Every block reads all slots: up to 2^20 reads in all.  Forward in a captured graph, us, two launches / one (one launch less is 4 to 5
-// us of the host's time as well): 4 tokens, k = 8, d = 4096 55.9 / 53.9; 64 tokens 83.5 / 83.0; 250 tokens (2^21 reads) 166.4 / 166.4;
-// 128, 8, 7168 (2^20) 299.1 / 299.2; 256, 8, 7168 (2^22) 321 / 325.  Training step of 256 tokens, k = 2, d = 128, fp32 101.6 / 87.2
-// (with the shared launches of expert_f32.hip).
+// Every block reads all slots: up to 2^20 reads in all.  Plan and move in a captured graph, us, two launches / one (one launch less is 4
+// to 5 us of the host's time as well): 4 tokens, k = 8, d = 4096, 16 of 128 experts local 5.5 / 2.7, all local 5.7 / 3.6; 64, 8, 4096, all on
+// eight experts 6.2 / 4.4; 724, 2, 1024, 8 of 8 6.4 / 4.8; 128, 8, 7168 (2^20), 64 of 64 8.1 / 7.0; 200, 8, 2048, 256 of 256 8.7 / 7.2.  (Counting
+// slot by slot with a reduction each made the local ones of k = 8 slower than two launches: 6.3, 7.1 and 9.2.)  Where the line lies was measured
+// with that: forward of 250 tokens (2^21 reads) 166.4 / 166.4; 256, 8, 7168 (2^22) 321 / 325.
 bool plan_and_dispatch_fits(int T, int k, int d, int dtype) {
   const long long slots = (long long)T * k, n_seg = ((dtype == MOE_BF16 ? d / 8 : d / 4) + DISPATCH_BLOCK - 1) / DISPATCH_BLOCK;
   return T > 0 && slots <= FEW_SLOTS && T * n_seg * slots <= (1 << 20);
