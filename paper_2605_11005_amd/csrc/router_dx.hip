@@ -10,7 +10,9 @@
 //   T = 4096, d = 2048, E = 64      18.6 / 13.9 / 5      T = 16384, d = 4096, E = 128   67 / 51 / 41     T = 30000, d = 7168, E = 128  215 / 203 / 132
 //   T = 9001, d = 2880, E = 128     35 / 30 / 16         T = 16384, d = 7168, E = 256  125 / 97 / 72     T = 4096, d = 7168, E = 192   38 / 34 / 18
 //   T = 64, d = 4096, E = 96        19 / 10              T = 8192, d = 4096, E = 96    151 / 30 / 21     T = 30000, d = 7168, E = 32  3191 / 187 / 132
-// Old values fetched a tile ahead changed nothing.  (Up to 64 tokens of 32 experts are up to 1 us slower than a block per token.)
+// Small batches of 32 experts, a block per token / now: T = 1, d = 512 4.2 / 3.6; 32, 512 4.4 / 4.0; 64, 512 4.5 / 4.5; 128, 512 4.5 / 4.7; 400, 512 4.7 / 4.7;
+// 64, 2048 5.3 / 4.7; 200, 2048 6.6 / 5.0: no line in T is drawn for the 0.2 us between 100 and 400 tokens of d <= 512.
+// Old values fetched a tile ahead changed nothing.
 #include "common.h"
 #include "kernels.h"
 
@@ -132,51 +134,49 @@ __global__ __launch_bounds__(NT, 2) void router_dx_stream(const void* __restrict
         for (int b = 0; b < 4; ++b) acc[b][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[b][k % NK], f, acc[b][t], 0, 0, 0);
       }
     if (more) publish(buf ^ 1);
+    // The terms of an infinite dlogit are no sum of it, and an empty term makes NaN of an infinite weight: outputs whose sums are no
+    // numbers are formed in plain fp32, by the lanes that hold some.
+    float probe = 0.f;
     if constexpr (SPLIT) {
 #pragma unroll
-      for (int b = 0; b < 4; ++b)
-#pragma unroll
-        for (int t = 0; t < TG; ++t) acc[b][t] *= DL_UNSCALE;
-      // The terms of an infinite dlogit are no sum of it, and an empty term makes NaN of an infinite weight: sums that are no numbers
-      // are formed again, in plain fp32.
-      float probe = 0.f;
-#pragma unroll
       for (int n = 0; n < 16 * TG; ++n) probe += acc[n >> 2 & 3][n >> 4][n & 3] * 0.f;
-      if (probe != 0.f) {
-#pragma unroll 1
-        for (int n = 0; n < 16 * TG; ++n) {
-          const int t = n >> 4, b = n >> 2 & 3, token = t0 + 16 * t + i;
-          float sum = 0.f;
-#pragma unroll
-          for (int o = 0; o < 16 * TG; ++o) sum = o == n ? acc[o >> 2 & 3][o >> 4][o & 3] : sum;
-          if (!active || token >= T || fabsf(sum) < INFINITY) continue;
-          const float* row = (const float*)dl + (size_t)token * S::E;
-          const bf16_t* weights = wr + (size_t)(c0 + 8 * (4 * (b >> 1) + g) + 4 * (b & 1) + (n & 3)) * S::E;
-          sum = 0.f;
-          for (int e = 0; e < S::E; ++e) sum += row[e] * bf16_to_f32(weights[e]);
-          int place = n;
-          asm volatile("" : "+s"(place));      // (compared again: the comparisons above would be kept)
-#pragma unroll
-          for (int o = 0; o < 16 * TG; ++o) acc[o >> 2 & 3][o >> 4][o & 3] = o == place ? sum : acc[o >> 2 & 3][o >> 4][o & 3];
-        }
-      }
     }
+    if (SPLIT && probe != 0.f) {
+#pragma unroll 1
+      for (int n = 0; n < 16 * TG; ++n) {
+        const int t = n >> 4, b = n >> 2 & 3, token = t0 + 16 * t + i;
+        if (!active || token >= T) continue;
+        float sum = 0.f;
 #pragma unroll
-    for (int t = 0; t < TG; ++t)
-#pragma unroll
-      for (int j = 0; j < 2; ++j) {
-        float x[8];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) { x[r] = acc[2 * j][t][r]; x[4 + r] = acc[2 * j + 1][t][r]; }
-        if (accumulate) {
-          const uint32_t u[4] = {old[t][j].x, old[t][j].y, old[t][j].z, old[t][j].w};
-#pragma unroll
-          for (int r = 0; r < 4; ++r) { x[2 * r] += bf16lo(u[r]); x[2 * r + 1] += bf16hi(u[r]); }
+        for (int o = 0; o < 16 * TG; ++o) sum = o == n ? acc[o >> 2 & 3][o >> 4][o & 3] : sum;
+        const int col = c0 + 8 * (4 * (b >> 1) + g) + 4 * (b & 1) + (n & 3);
+        if (fabsf(sum) < INFINITY) {
+          sum *= DL_UNSCALE;
+        } else {
+          sum = 0.f;
+          for (int e = 0; e < S::E; ++e) sum += ((const float*)dl)[(size_t)token * S::E + e] * bf16_to_f32(wr[(size_t)col * S::E + e]);
         }
-        if (active && t0 + 16 * t + i < T)
-          *reinterpret_cast<uint4*>(rows + (size_t)(16 * t + i) * d + 32 * j) =
-              make_uint4(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7]));
+        bf16_t* const out = dx + (size_t)token * d + col;
+        *out = (bf16_t)pack_bf16x2(accumulate ? bf16_to_f32(*out) + sum : sum, 0.f);
       }
+    } else {
+#pragma unroll
+      for (int t = 0; t < TG; ++t)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+          float x[8];
+#pragma unroll
+          for (int r = 0; r < 8; ++r) x[r] = acc[2 * j + (r >> 2)][t][r & 3] * (SPLIT ? DL_UNSCALE : 1.f);
+          if (accumulate) {
+            const uint32_t u[4] = {old[t][j].x, old[t][j].y, old[t][j].z, old[t][j].w};
+#pragma unroll
+            for (int r = 0; r < 4; ++r) { x[2 * r] += bf16lo(u[r]); x[2 * r + 1] += bf16hi(u[r]); }
+          }
+          if (active && t0 + 16 * t + i < T)
+            *reinterpret_cast<uint4*>(rows + (size_t)(16 * t + i) * d + 32 * j) =
+                make_uint4(pack_bf16x2(x[0], x[1]), pack_bf16x2(x[2], x[3]), pack_bf16x2(x[4], x[5]), pack_bf16x2(x[6], x[7]));
+        }
+    }
     __syncthreads();
   }
 }
@@ -184,17 +184,7 @@ __global__ __launch_bounds__(NT, 2) void router_dx_stream(const void* __restrict
 template <int NK, bool SPLIT>
 int launch(const void* dl, const bf16_t* wr, bf16_t* dx, int T, int d, int accumulate, hipStream_t s) {
   constexpr int LDS = 2 * Shape<NK, SPLIT>::BUFFER;
-  if (LDS > 64 * 1024) {      // a per-device attribute of the kernel
-    static bool attr_set[64] = {};
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return MOE_EHIP;
-    if (!attr_set[dev]) {
-      if (hipFuncSetAttribute(reinterpret_cast<const void*>(&router_dx_stream<NK, SPLIT>), hipFuncAttributeMaxDynamicSharedMemorySize,
-                              LDS) != hipSuccess)
-        return MOE_EHIP;
-      attr_set[dev] = true;
-    }
-  }
+  static_assert(LDS <= 64 * 1024, "more needs an opt-in");
   // two blocks per CU, and as many walks on every XCD: with the 18 that d = 7168 would allow two XCDs have three (T = 30000, E = 128:
   // 261 us)
   const int n_cols = (d + COLS - 1) / COLS, n_tiles = (T + Shape<NK, SPLIT>::TOKENS - 1) / Shape<NK, SPLIT>::TOKENS;
