@@ -349,9 +349,10 @@ def test_router_backward_at_block_edges(T, d, E, streams):
 
 # router_dx.hip: rounded dlogits (E = 64, 128, 192, 256) and three terms of them (32, 96, 160); one token, tiles of 32 and 64 tokens with one
 # more or less, several tiles and ranges per block; wavefronts past the last column.  Against the products of what the kernel is given
-# (bf16 dlogits where E % 64 == 0), 2**-8 for the one rounding of a result, bit for bit without the products
+# (bf16 dlogits where E % 64 == 0), 2**-8 for the one rounding of a result, bit for bit without the products.  E = 320, 512 and 1024 are the
+# grouped GEMM's
 @pytest.mark.parametrize("T,d,E", [(1, 64, 32), (33, 192, 96), (65, 320, 32), (127, 256, 160), (31, 64, 64), (64, 576, 128), (129, 448, 192),
-                                   (20011, 64, 96), (9001, 512, 64), (33, 320, 256)])
+                                   (20011, 64, 96), (9001, 512, 64), (33, 320, 256), (1, 64, 320), (300, 576, 512), (129, 448, 1024)])
 def test_router_input_gradient_stream(T, d, E):
     print(f"case router-dx-{T}-{d}-{E}", flush=True)
     g = torch.Generator(device="cuda").manual_seed(T + d + E)
