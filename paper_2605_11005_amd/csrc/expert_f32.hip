@@ -451,13 +451,15 @@ __global__ __launch_bounds__(NT, BUFS == 2 ? 2 : Traits<MODE>::BLOCKS) void gemm
   gemm_tile<MODE, BUFS>(p, blockIdx.x, lds);
 }
 
-// Two GEMMs that do not depend on each other in one launch, the first one's tiles, which take longer, in blocks [0, first).
+// Two GEMMs that do not depend on each other in one launch, one of them in blocks [0, first), the other behind it.
 template <int M1, int M2, int BUFS>
 __global__ __launch_bounds__(NT, BUFS == 2 ? 2 : (Traits<M1>::BLOCKS < Traits<M2>::BLOCKS ? Traits<M1>::BLOCKS : Traits<M2>::BLOCKS))
-void gemm_f32_pair(Args p1, Args p2, int first) {
+void gemm_f32_pair(Args p1, Args p2, int first, int m2_first) {
   __shared__ __align__(16) char lds[BUFS * (Traits<M1>::BUFFER > Traits<M2>::BUFFER ? Traits<M1>::BUFFER : Traits<M2>::BUFFER)];
-  if ((int)blockIdx.x < first) gemm_tile<M1, BUFS>(p1, blockIdx.x, lds);
-  else gemm_tile<M2, BUFS>(p2, blockIdx.x - first, lds);
+  const bool in_first = (int)blockIdx.x < first;
+  const int block = in_first ? blockIdx.x : blockIdx.x - first;
+  if (in_first != (m2_first != 0)) gemm_tile<M1, BUFS>(p1, block, lds);
+  else gemm_tile<M2, BUFS>(p2, block, lds);
 }
 
 // Two LDS buffers while at most two blocks share a CU: nothing else fills the gaps there.  The sums and their order are the same.
@@ -480,14 +482,14 @@ int launch(const Args& p, long long m_tiles, hipStream_t s) {
 }
 
 template <int M1, int M2>
-int launch_pair(const Args& p1, long long m_tiles1, const Args& p2, long long m_tiles2, hipStream_t s) {
-  const long long first = tile_blocks(p1, m_tiles1), blocks = first + tile_blocks(p2, m_tiles2);
+int launch_pair(const Args& p1, long long m_tiles1, const Args& p2, long long m_tiles2, bool m2_first, hipStream_t s) {
+  const long long n1 = tile_blocks(p1, m_tiles1), n2 = tile_blocks(p2, m_tiles2), blocks = n1 + n2;
   if (blocks >= (1ll << 31)) {
     const int rc = launch<M1>(p1, m_tiles1, s);
     return rc ? rc : launch<M2>(p2, m_tiles2, s);
   }
   const auto kernel = use_two(blocks) ? gemm_f32_pair<M1, M2, 2> : gemm_f32_pair<M1, M2, 1>;
-  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(NT), 0, s, p1, p2, (int)first);
+  hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(NT), 0, s, p1, p2, (int)(m2_first ? n2 : n1), m2_first ? 1 : 0);
   HIP_CHECK_LAUNCH();
   return MOE_OK;
 }
@@ -539,16 +541,21 @@ int launch_expert_bwd_f32(const float* xp, const float* h1, const float* h3, con
   // several (T = 1500, d = 520, f = 776, 16 experts, k = 2: 568 and 1872 blocks for 768 places), and a small GEMM is little more
   // than its launch, its first loads and its last stores.  Training steps, us, four launches / two (T, d, f, experts, k): 1500, 520,
   // 776, 16, 2 292 / 265; 309, 736, 792, 32, 2 399 / 361; 261, 120, 992, 12, 4 176 / 157; 126, 336, 808, 8, 4 153 / 131.
+  // The longer tiles come first: a gradient's contract the rows of an expert, of which the capacity tells the average, dA's d and dX's f
+  // twice into one output.  Backward, us, four launches / dA and dX first / gradients first (d, f, experts, rows of each): 1024, 1024, 1, 3000
+  // 340 / 350 / 297; 1024, 1024, 2, 3000 572 / 598 / 547; 1024, 1024, 1, 1000 143 / 110 / 119; 512, 512, 8, 2000 406 / 398 / 383; 512, 512, 8,
+  // 500 127 / 113 / 113; 1024, 1024, 8, 400 344 / 325 / 346; 520, 776, 16, 190 176 / 152 / 160; 512, 256, 32, 3000 / (1 + e) 336 / 346 / 326.
+  const auto gradients_first = [&](int contraction) { return 5ll * cap > 6ll * e_cnt * contraction; };
   const long long wt = (long long)e_cnt * ((f + TM - 1) / TM), vt = (long long)e_cnt * ((d + TM - 1) / TM);
   if (cap == 0) {
     if ((rc = launch<WG>(w, wt, s))) return rc;
     return launch<WGD>(v, vt, s);
   }
   if (a_in) {
-    if ((rc = launch_pair<DA, WG>(g, mtb, w, wt, s))) return rc;
+    if ((rc = launch_pair<DA, WG>(g, mtb, w, wt, gradients_first(d), s))) return rc;
   } else {
     if ((rc = launch<DA>(g, mtb, s))) return rc;
     if ((rc = launch<WG>(w, wt, s))) return rc;
   }
-  return launch_pair<DX, WGD>(x, mtb, v, vt, s);
+  return launch_pair<DX, WGD>(x, mtb, v, vt, gradients_first(f), s);
 }

@@ -175,7 +175,8 @@ def test_fp32_experts_with_one_and_two_buffers(d, f, rows):
 
 
 # dA and dW2 share a launch where the forward's activation is kept, dX and dW1|dW3 always do: blocks beyond the tiles of the first GEMM,
-# one and two LDS buffers (the capacity decides), experts without rows, and the same bits as dA and dW2 in launches of their own
+# one and two LDS buffers and either GEMM first (the capacity decides), experts without rows, and the same bits as dA and dW2 in launches of
+# their own
 @pytest.mark.parametrize("d,f,rows", [(4, 4, [1]), (68, 132, [65, 0, 3, 64]), (200, 520, [40, 0, 129, 7] * 4)])
 def test_fp32_gradients_that_share_launches(d, f, rows):
     print(f"case fp32-shared-{d}-{f}", flush=True)
