@@ -8,10 +8,12 @@
 // Input gradient alone (where E % 64 == 0 with the pass that rounds the dlogits), us; before, on 256x256 tiles or, E = 32 and 96, in
 // plain fp32 products, / now / dx read and written at 6.5 TB/s:
 //   T = 4096, d = 2048, E = 64      18.6 / 13.9 / 5      T = 16384, d = 4096, E = 128   67 / 51 / 41     T = 30000, d = 7168, E = 128  215 / 203 / 132
-//   T = 9001, d = 2880, E = 128     35 / 30 / 16         T = 16384, d = 7168, E = 256  125 / 97 / 72     T = 4096, d = 7168, E = 192   38 / 34 / 18
+//   T = 9001, d = 2880, E = 128     35 / 30 / 16         T = 16384, d = 7168, E = 256  125 / 97 / 72     T = 4096, d = 7168, E = 192   39 / 32 / 18
 //   T = 64, d = 4096, E = 96        19 / 10              T = 8192, d = 4096, E = 96    151 / 30 / 21     T = 30000, d = 7168, E = 32  3191 / 187 / 132
 // Small batches of 32 experts, a block per token / now: T = 1, d = 512 4.2 / 3.6; 32, 512 4.4 / 4.0; 64, 512 4.5 / 4.5; 128, 512 4.5 / 4.7; 400, 512 4.7 / 4.7;
 // 64, 2048 5.3 / 4.7; 200, 2048 6.6 / 5.0: no line in T is drawn for the 0.2 us between 100 and 400 tokens of d <= 512.
+// Long rows leave few walks: T = 600, d = 16384, E = 64 19.5 / 15.8, 128 20.1 / 21.5, 192 21.0 / 19.8 (with tiles of 64 tokens, whose registers
+// did not suffice, 24.0), 256 22.4 / 22.2.
 // Old values fetched a tile ahead changed nothing.
 #include "common.h"
 #include "kernels.h"
@@ -27,7 +29,7 @@ constexpr int NT = 256, COLS = 256, WAVE_COLS = 64;
 template <int NK, bool SPLIT> struct Shape {
   static constexpr int E = 32 * NK, PLANES = SPLIT ? 3 : 1;
   static constexpr int ROW = (PLANES * E * 2 + 127) / 128 * 128;       // bytes of a token in LDS
-  static constexpr int TG = NK == 8 || (SPLIT && NK > 1) ? 2 : 4;      // groups of 16 tokens in a tile: what registers and LDS hold
+  static constexpr int TG = NK >= 6 || (SPLIT && NK > 1) ? 2 : 4;      // groups of 16 tokens in a tile: what registers and LDS hold
   static constexpr int TOKENS = 16 * TG, BUFFER = TOKENS * ROW;
   // place of 16-byte chunk c of a token: sixteen lanes that read one chunk of consecutive tokens must cover 256 distinct bytes
   static __device__ __forceinline__ int swizzle(int token, int c) { return ROW % 256 ? c ^ ((token >> 1) & 7) : c ^ (token & 15); }
