@@ -76,7 +76,8 @@ int moe_route(const float* logits, int T, int E, int k, int gate_mode, int e_lo,
  *   perm    [cap]     int32  out: perm[r] = flat slot s = t*k + j held by row r; rows are
  *                            sorted by (local expert, s) -- a stable counting sort, so the
  *                            result is unique and reproducible.  Entries [R,cap) untouched.
- *   inv     [T,k]     int32  out: row of slot (t,j), or -1 if its expert is not local.
+ *   inv     [T,k]     int32  out: row of slot (t,j), or -1 if its expert is not local; not in
+ *                            topk_idx's place, which is read until the plan is done.
  * With reuse_plan == 1 the three arrays are inputs (as written by an earlier call) and
  * topk_idx may be NULL.
  * Row move: xp[inv[t,j], :] = x[t, :] * (row_scale ? row_scale[t,j] : 1) for every local
@@ -246,10 +247,11 @@ int moe_gate_bwd(const float* logits, const int32_t* topk_idx, const float* dgat
  *   dwr, dx of type dtype; dlogits [T,E] float.  dwr_accumulate / dx_accumulate: 0 overwrite,
  *   1 add to the existing contents (dx_accumulate = 1 adds the router term to the gradient that
  *   the expert path left in dx).  Either output may be NULL to skip it.
- *   bf16: dlogits is rounded to bf16 for the matrix cores when E % 64 == 0 and d % 64 == 0
- *   (fp32 accumulation over T in fixed-size chunks, chunk sums added in fp32).  Other shapes keep
- *   all 24 bits of dlogits: as fp32, or for the weight gradient of up to 42 experts as three bf16
- *   terms on the matrix cores.  ws: moe_workspace_bytes(MOE_WS_ROUTER).
+ *   bf16 with d % 64 == 0 and E % 64 == 0: dlogits is rounded to bf16 for the matrix cores.  Other
+ *   shapes keep all 24 bits of dlogits, as fp32 or as three bf16 terms on the matrix cores; only the
+ *   weight gradient of up to 42 experts may lose bits of dlogits below 2^-109.  All sums are fp32; those
+ *   over T are formed in ranges of tokens that depend on the sizes alone and are added in ascending
+ *   order, so results are bit-reproducible from run to run.  ws: moe_workspace_bytes(MOE_WS_ROUTER).
  */
 int moe_router_bwd(const void* x, const void* wr, const float* dlogits, int dtype, int T, int d, int E,
                    void* dwr, int dwr_accumulate, void* dx, int dx_accumulate, void* ws, size_t ws_bytes,
@@ -260,8 +262,8 @@ int moe_router_bwd(const void* x, const void* wr, const float* dlogits, int dtyp
  * MFMA roofline and of the row movers against HBM bandwidth).  Apart from per-device caches of
  * constants (CU count, the kernels' LDS opt-in attribute, the address of the built-in plan scratch)
  * this is the library's only process-wide state, and it is off by default.  While enabled, every kernel launch of the
- * entry points above is bracketed by a pair of hipEvents recorded on the call's stream
- * (a few microseconds of host work per launch; no synchronisation).
+ * entry points above except the fp32 expert GEMMs is bracketed by a pair of hipEvents recorded on the call's stream
+ * (a few microseconds of host work per launch; no synchronisation).  The launches of one plan count as one.
  *   moe_profile_enable(on)   on != 0: create the event pool (first time) and start recording
  *                            from an empty log; on == 0: stop recording.
  *   moe_profile_read(kernel, &total_ms, &launches)
@@ -273,7 +275,10 @@ int moe_router_bwd(const void* x, const void* wr, const float* dlogits, int dtyp
  * The pool holds MOE_PROFILE_MAX_EVENTS launches; later launches are not recorded.
  * Not thread-safe: enable, run and read from one host thread.
  */
-enum { MOE_K_ROUTE = 0, MOE_K_PLAN = 1, MOE_K_DISPATCH = 2, MOE_K_COMBINE = 3, MOE_K_UP = 4,
+enum { MOE_K_ROUTE = 0,
+       /* a dispatch of up to 2048 slots may make its plan in the launch that moves the rows: it is
+        * booked as MOE_K_DISPATCH, and MOE_K_PLAN has no launch */
+       MOE_K_PLAN = 1, MOE_K_DISPATCH = 2, MOE_K_COMBINE = 3, MOE_K_UP = 4,
        MOE_K_DOWN = 5, MOE_K_DA = 6, MOE_K_DX = 7, MOE_K_WG = 8, MOE_K_WGD = 9, MOE_K_ROUTER_FWD = 10,
        MOE_K_COMBINE_BWD = 11, MOE_K_GATE_BWD = 12, MOE_K_ROUTER_DW = 13, MOE_K_ROUTER_DX = 14,
        MOE_K_WGRAD_REDUCE = 15,   /* sum of the fp32 partial tiles of weight gradients cut along the rows */

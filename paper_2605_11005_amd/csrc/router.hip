@@ -2,13 +2,14 @@
 // gradient of the gate weights in one pass over dy), gradient through the gate weights to the
 // logits, and the router's backward GEMMs.
 //
-// bf16 with d % 64 == 0 runs on the matrix cores: the logits of E % 8 == 0 experts and the weight gradient of up to 128 (42
-// where the dlogits stay fp32) through the kernels of expert_small.hip while launch_router_fwd's and launch_router_bwd's
-// rules on sizes and workspace allow, larger ones and the input gradient of E % 64 == 0 through the grouped-GEMM kernel of
-// expert_bf16.hip.  Every other shape (fp32, odd expert counts) takes
-// the plain LDS-tiled FMA kernels below, which accept any size.  The contraction over the tokens (dWr) is
-// always split into fixed chunks whose fp32 sums are added in ascending order, so the result
-// does not depend on scheduling.
+// bf16 with d % 64 == 0 runs on the matrix cores:
+//   logits           E % 8 == 0: expert_small.hip; many tokens of E % 64 == 0 the grouped-GEMM kernel of expert_bf16.hip (launch_router_fwd)
+//   weight gradient  32, 64, 96, 128, 160, 192 and 256 experts: router_dw.hip where router_dw_ranges says so; else up to 128 experts (42
+//                    where the dlogits stay fp32) expert_small.hip, other E % 64 == 0 the grouped GEMM (launch_router_bwd)
+//   input gradient   32, 96, 160 and E % 64 == 0 experts up to 256: router_dx.hip; E % 64 == 0 beyond: the grouped GEMM
+// Every other shape (fp32, odd expert counts) takes the plain kernels below, which accept any size.  The contraction over the tokens
+// (dWr) is always split into ranges that depend on the sizes alone, whose fp32 sums are added in ascending order, so the result does
+// not depend on scheduling.
 #include "common.h"
 #include "kernels.h"
 
