@@ -150,7 +150,8 @@ __global__ __launch_bounds__(NT, NE == 2 || NE == 3 ? 2 : 1) void router_dw_stre
   }
   if (probe == 0.f) return;
   // Zeros that stand for no product, a dlogit's empty terms and the overlap of the last piece, make NaN of an infinite x, and an
-  // infinite dlogit's terms are no sum.  Sums that are no numbers are formed again, in plain fp32.
+  // infinite dlogit's terms are no sum.  Sums that are no numbers are formed again, in plain fp32, where that can be the reason.
+  if (PLANES == 1 && (T % PIECE == 0 || (first + n) * PIECE < T)) return;
   const int end = min(T, (first + n) * PIECE);
 #pragma unroll 1
   for (int i = 0; i < 2 * S::BLOCKS * 16; ++i) {
