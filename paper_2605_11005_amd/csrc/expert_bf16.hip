@@ -1489,13 +1489,17 @@ __device__ __forceinline__ bool few_rows_pay(const int32_t* __restrict__ off, in
 
 // Forward GEMM of a call whose capacity leaves open which kernel pays: the row counts decide, in every block alike.
 template <int MODE>
-__global__ __launch_bounds__(NT, 1) void gg_or_few(GArgs p, int d, int f) {
+__global__ __launch_bounds__(NT, 1) void gg_or_few(GArgs p, int d, int f, int cached) {
   if (few_rows_pay(p.off, p.e_cnt, d, f)) {
     SArgs q = {};
     q.A = p.A0; q.lda = p.lda; q.B0 = p.B0; q.B1 = p.B1; q.ldb = p.ldb; q.b_es = p.b_es;
     q.C0 = p.C0; q.C1 = p.C1; q.C2 = p.C2; q.ldc = p.ldc; q.off = p.off; q.e_cnt = p.e_cnt; q.N = p.N; q.K = p.K;
     const RaggedTiles<ROWS> list(q.off, q.e_cnt, threadIdx.x & 63);
-    for (int b = blockIdx.x; few_rows_tile<MODE == UP, NW_TILES>(q, list, reinterpret_cast<u32x4*>(smem), b); b += gridDim.x) {}
+    u32x4* const lds = reinterpret_cast<u32x4*>(smem);
+    if (list.total > cached)
+      for (int b = blockIdx.x; few_rows_tile<MODE == UP, NW_TILES, true>(q, list, lds, b); b += gridDim.x) {}
+    else
+      for (int b = blockIdx.x; few_rows_tile<MODE == UP, NW_TILES, false>(q, list, lds, b); b += gridDim.x) {}
     return;
   }
   gg_body<MODE, true>(p);
@@ -1613,7 +1617,7 @@ int launch_gg_or_few(const GArgs& a, int d, int f, hipStream_t s) {
     attr_set[dev] = true;
   }
   ProfScope prof(MOE_K_UP + MODE, s);
-  hipLaunchKernelGGL(gg_or_few<MODE>, dim3(device_cu_count()), dim3(NT), SMEM_BYTES, s, a, d, f);
+  hipLaunchKernelGGL(gg_or_few<MODE>, dim3(device_cu_count()), dim3(NT), SMEM_BYTES, s, a, d, f, cached_tiles(d, f));
   HIP_CHECK_LAUNCH();
   return MOE_OK;
 }

@@ -25,9 +25,20 @@ struct SArgs {
   int rows, e_cnt, N, K;
   long xstep;                             // elements from a row's piece to its next piece
   int n_experts;                          // RW: rows are (plane, expert), expert fastest
+  int cached;                             // UP, DOWN: most row tiles whose weights are read through the Infinity Cache (cached_tiles)
   int range;                              // RL, RW: pieces of the contraction per range (grid z); range z's sums go to F + z * rows * N
                                           // narrow_router: rows per block; UP, DOWN: most tiles that are halved
 };
+
+// Weights that a call reads once and that do not stay in the Infinity Cache (256 MB) until the next call are loaded nontemporally:
+// such loads leave the cache alone, and memory then delivers up to 13 % more (strips of 128 bytes of 1.9 GB: 6.3 -> 7.1 TB/s).  While
+// the active experts' weights fit, a call made again finds them there.  Up and down projection, us, loads as usual / nontemporal:
+//   2.8 GB of weights   7168, 2048, 32 experts of one row   326 + 167 / 291 + 153     of 128 rows by 1/r  329 + 169 / 300 + 155
+//   604 MB              4096, 1536, 16 of 16 rows           88 + 42 / 79 + 39         four of them, 151 MB, again  29 + 14 / 39 + 16
+//   796 MB              2880, 2880, 16 of 16 rows           97 + 57 / 84 + 52
+// The line is at what fits: at 302 MB (8 experts of the second shape) it is 46 + 22 / 44 + 21, and at 138 MB that have not been read just
+// before 22 + 16 / 21 + 15.  In row tiles, which count an expert once per 64 rows:
+inline int cached_tiles(int d, int f) { return (int)((256ll << 20) / (6ll * d * f)); }
 
 // Loads go through a buffer descriptor: a wave-uniform base and a 32-bit byte offset per lane (64-bit addresses per lane limit
 // a CU's address path, see lds_load16 in common.h).  A descriptor of length
@@ -44,11 +55,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t descriptor(const bf16_t* base,
 struct Piece {
   u32x4 w[8];
   // row: bytes per weight row; voff: this lane's offset
-  template <int FIRST, int END>
+  template <int FIRST, int END, bool STREAM = false>
   __device__ __forceinline__ void load(const bf16_t* base, bool in, int row, int voff) {      // rows FIRST .. END - 1 of the eight
+    constexpr int NT = STREAM ? 2 : 0;      // "nt": the line is used once
     const __amdgpu_buffer_rsrc_t d = descriptor(base, in);
 #pragma unroll
-    for (int r = FIRST; r < END; ++r) w[r] = __builtin_amdgcn_raw_buffer_load_b128(d, voff, r * row, 0);
+    for (int r = FIRST; r < END; ++r) w[r] = __builtin_amdgcn_raw_buffer_load_b128(d, voff, r * row, NT);
   }
   __device__ __forceinline__ bf16x8 operand(int j) const {      // column j of the block, its eight k
     u32x4 f;
@@ -81,7 +93,7 @@ constexpr int STEPS = 4;                   // of 32 k, per round
 template <int NW> constexpr int STEP_PLACES = KP * 32 * NW / 8;
 template <int NW> constexpr int WEIGHT_PLACES = STEPS * STEP_PLACES<NW>;
 constexpr int ROW_PLACES = STEPS * ROWS / 16 * WAVE;
-template <bool DUAL, int TG, int NW>
+template <bool DUAL, int TG, int NW, bool STREAM>
 __device__ __forceinline__ void expert_tile(const SArgs& p, u32x4* lds, int e, int row0, int row_end, int n0, int tid) {
   constexpr int DEPTH = 2, XS = STEPS / NW;           // XS: steps of the rows per wavefront
   constexpr int CHUNKS = (DUAL ? 2 : 4) * NW;         // of 8 columns, in a row of a wavefront's piece
@@ -105,7 +117,7 @@ __device__ __forceinline__ void expert_tile(const SArgs& p, u32x4* lds, int e, i
     const int wk = STEPS * round + wk0;           // (steps is even: of a round there are four, two or none)
     // rows past the contraction repeat its last ones (their steps are not multiplied)
     const int woff = min(8 * kg, max(8, KP * (steps - wk)) - 8) * 2 * (int)p.ldb + wcol;
-    w[S].template load<4 * H, 4 * H + 4>(b + (wk < steps ? (long)wk * KP : 0) * p.ldb, wk < steps, 2 * (int)p.ldb, woff);
+    w[S].template load<4 * H, 4 * H + 4, STREAM>(b + (wk < steps ? (long)wk * KP : 0) * p.ldb, wk < steps, 2 * (int)p.ldb, woff);
     if (H) {
 #pragma unroll
       for (int q = 0; q < XS; ++q) {
@@ -210,16 +222,16 @@ __device__ __forceinline__ void expert_tile(const SArgs& p, u32x4* lds, int e, i
 
 // Tile b of a launch over all experts; false: the list is shorter.
 template <int NW> constexpr int FEW_ROWS_PLACES = 2 * (WEIGHT_PLACES<NW> + ROW_PLACES);      // LDS, 16 bytes each
-template <bool DUAL, int NW>
+template <bool DUAL, int NW, bool STREAM>
 __device__ __forceinline__ bool few_rows_tile(const SArgs& p, const RaggedTiles<ROWS>& list, u32x4* lds, int b) {
   constexpr int WIDTH = (DUAL ? 16 : 32) * NW;
   const int tid = threadIdx.x;
   int e, mt, nt;
   if (!list.tile((p.N + WIDTH - 1) / WIDTH, b, e, mt, nt)) return false;
   const int row0 = p.off[e] + mt * ROWS, row_end = min(p.off[e + 1], row0 + ROWS), rows = row_end - row0;
-  if (rows <= 16) expert_tile<DUAL, 1, NW>(p, lds, e, row0, row_end, nt * WIDTH, tid);
-  else if (rows <= 32) expert_tile<DUAL, 2, NW>(p, lds, e, row0, row_end, nt * WIDTH, tid);
-  else expert_tile<DUAL, 4, NW>(p, lds, e, row0, row_end, nt * WIDTH, tid);
+  if (rows <= 16) expert_tile<DUAL, 1, NW, STREAM>(p, lds, e, row0, row_end, nt * WIDTH, tid);
+  else if (rows <= 32) expert_tile<DUAL, 2, NW, STREAM>(p, lds, e, row0, row_end, nt * WIDTH, tid);
+  else expert_tile<DUAL, 4, NW, STREAM>(p, lds, e, row0, row_end, nt * WIDTH, tid);
   return true;
 }
 
