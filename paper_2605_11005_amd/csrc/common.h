@@ -112,16 +112,24 @@ __device__ __forceinline__ float silu_grad_f(float z, float* ds) {
 // Written as inline assembly so that the compiler's wait-count pass does not serialise later
 // LDS reads against these loads; the kernel waits for them itself (s_waitcnt vmcnt) before
 // the barrier that publishes a tile.
+// STREAM: the line is used once ("nt").
+template <bool STREAM = false>
 __device__ __forceinline__ void lds_load16(const bf16_t* sbase, uint32_t voff_bytes, uint32_t lds_wave_base) {
   // make the uniformity of the base explicit so that it is allocated to an SGPR pair
   const uint64_t u = (uint64_t)sbase;
   const uint64_t ub = ((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32)) << 32) |
                       (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u);
   sbase = (const bf16_t*)ub;
-  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
-               :
-               : "s"(lds_wave_base), "v"(voff_bytes), "s"(sbase)
-               : "memory", "m0");
+  if (STREAM)
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2 nt"
+                 :
+                 : "s"(lds_wave_base), "v"(voff_bytes), "s"(sbase)
+                 : "memory", "m0");
+  else
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2"
+                 :
+                 : "s"(lds_wave_base), "v"(voff_bytes), "s"(sbase)
+                 : "memory", "m0");
 }
 __device__ __forceinline__ uint32_t lds_addr(const void* p) {
   return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;

@@ -110,6 +110,7 @@ struct GArgs {
   int accumulate;
   int save_h;
   int pair_first;                         // another GEMM follows in this launch and fills the last round
+  int stream;                             // UP, DOWN: the experts' weights do not fit the Infinity Cache
 };
 
 template <int MODE> struct Traits {
@@ -138,8 +139,9 @@ struct KcIssue {
       voff[j] = (uint32_t)(r * ld * 2 + c * 16);
     }
   }
+  template <bool STREAM>
   __device__ __forceinline__ void issue1(int j, uint32_t oper_lds, int wave, long kofs) const {
-    lds_load16(base + kofs, voff[j], oper_lds + (4 * wave + j) * 1024);
+    lds_load16<STREAM>(base + kofs, voff[j], oper_lds + (4 * wave + j) * 1024);
   }
 };
 
@@ -190,12 +192,12 @@ struct TrIssue {
     coff = (uint32_t)(n * 2);
   }
   // load j of the k-tile whose first source row is k0 (rows above k_last_rel clamped if CLAMP)
-  template <bool CLAMP>
+  template <bool CLAMP, bool STREAM = false>
   __device__ __forceinline__ void issue1(int j, uint32_t oper_lds, int wave, int lane, long k0, int k_last_rel) const {
     const int id = 4 * wave + j;
     int kr = 4 * (id & 7) + (lane >> 4);
     if (CLAMP && kr > k_last_rel) kr = k_last_rel;
-    lds_load16(src + k0 * ld, (uint32_t)(kr * ld * 2) + coff, oper_lds + id * 1024);
+    lds_load16<STREAM>(src + k0 * ld, (uint32_t)(kr * ld * 2) + coff, oper_lds + id * 1024);
   }
 };
 
@@ -950,6 +952,13 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
   int e = 0, lo = 0, hi = 0, n0 = 0;
   int piece = -1;         // ragged-K modes: index of the fp32 partial tile to write, or -1
   int krange = 0;         // RL: which range of a cut contraction
+  // Weights that one tile reads, of a layer whose weights do not fit the Infinity Cache, are loaded nontemporally, as in few_rows.h:
+  // decode of 128 tokens at the DSv3-like share 301 -> 280 us, prefill of 2047 at the GPT-OSS-like share 242 -> 237, training step of
+  // 1936 tokens at the former 1616 -> 1586.  (Of layers that fit, the backward finds them: Qwen-like share 821 against 829.  In every
+  // tile, which drops panels that tiles share, steps take 1 to 3 % longer; in dA and dX, whose weights are read 64 bytes of a row at a
+  // time, up to 7 % even in tiles that share nothing.)  A loop of its own: a branch at every load costs 2 %.
+  constexpr bool ONCE = MODE == UP || MODE == DOWN;
+  bool once = false;      // no other tile reads this one's weights
   int nk0 = 0, nk = 0;    // k-tiles in segment 0 / in total
   int row0 = 0;           // first output row (global row for ragged-M, i for the weight gradients)
   int row_end = 0;        // one past the last valid output row
@@ -979,13 +988,14 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
     const long kofs = (long)(seg1 ? kt0 - nk0 : kt0) * BK + (seg1 ? p.A1 - p.A0 : 0);
     ia_kp.issue1(q, smem_base + (pj & 1) * (2 * OPER_BYTES), wave, kofs);
   };
-  auto issue_b = [&](int kt, int j) {
+  auto issue_b = [&](int kt, int j, auto once_tag) {
+    constexpr bool STREAM = decltype(once_tag)::value != 0;
     if (kt > nk - 1) kt = nk - 1;
     const uint32_t st = smem_base + B_REGION + (kt & (NSTAGE - 1)) * OPER_BYTES;
     const bool seg1 = MODE == DX && kt >= nk0;
     const int k0 = (seg1 ? kt - nk0 : kt) * BK;
-    if (TR::B_TRANS) ib_tr.template issue1<false>(j, st, wave, lane, k0, 0);
-    else ib_kc.issue1(j, st, wave, k0 + (seg1 ? p.B1 - p.B0 : 0));
+    if (TR::B_TRANS) ib_tr.template issue1<false, STREAM>(j, st, wave, lane, k0, 0);
+    else ib_kc.template issue1<STREAM>(j, st, wave, k0 + (seg1 ? p.B1 - p.B0 : 0));
   };
   auto issue_tile = [&](int kt) {
 #pragma unroll
@@ -1005,9 +1015,9 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
     // Within an expert, tiles are ordered in bands of 8 m-tiles, n-tile next, m-tile inside the
     // band fastest: 32 consecutive tiles (one chunk) then form an 8 x 4 block that shares 8 A
     // panels and 4 B panels through one XCD's L2.
-    int mt, nt;
+    int mt, nt, mte;
     {
-      int li, mte;
+      int li;
       const int a = find_position(tile_start, e_cnt, L, pos_hint);
       pos_hint = a;
       li = __builtin_amdgcn_readfirstlane(L - tile_start[a]);
@@ -1041,6 +1051,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
       krange = nt / n_tiles_cols;
       nt -= krange * n_tiles_cols;
     }
+    if (ONCE) once = p.stream && mte == 1;
     n0 = nt * TR::BN_EFF;
     if (TR::RAGGED_K) {
       row0 = mt * BM;
@@ -1062,10 +1073,14 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
       if (PAIR) {       // what the k loop's iterations -2 and -1 would have issued, in its order
 #pragma unroll
         for (int q = 0; q < 8; ++q) issue_a_pair(0, q);
+        auto first_b = [&](auto tag) {
 #pragma unroll
-        for (int t = 0; t < 3; ++t)
+          for (int t = 0; t < 3; ++t)
 #pragma unroll
-          for (int j = 0; j < 4; ++j) issue_b(t, j);
+            for (int j = 0; j < 4; ++j) issue_b(t, j, tag);
+        };
+        if (ONCE && once) first_b(IntC<1>{});
+        else first_b(IntC<0>{});
 #pragma unroll
         for (int q = 0; q < 4; ++q) issue_a_pair(1, q);
       } else {
@@ -1207,7 +1222,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
     // .. B(2j+1) | B(2j+2) A(j+1)a | A(j+1)b B(2j+3) | B(2j+4) A(j+2)a | ..: at the barrier of
     // an even iteration 2j (tile 2j+1 must have landed) the 12 loads after B(2j+1) may remain,
     // at the barrier of an odd one the 8 after A(j+1)b.
-    auto k_loop_pair = [&](auto mv_tag) {
+    auto k_loop_pair = [&](auto mv_tag, auto once_tag) {
       constexpr int MV = decltype(mv_tag)::value;
       auto live = [](int o) { return MV == 4 || (MV == 2 && o <= 5); };
       auto iteration = [&](int kt, auto odd_tag) {
@@ -1222,7 +1237,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
           }
           if (m < 4 * MV) mfma_one(0, m + 1);
           if ((m & 3) == 2) {
-            if (ODD) issue_b(kt + 3, m >> 2);
+            if (ODD) issue_b(kt + 3, m >> 2, once_tag);
             else issue_a_pair((kt >> 1) + 1, 4 + (m >> 2));
           }
           __builtin_amdgcn_sched_barrier(0);
@@ -1238,7 +1253,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
           if (m < 4 * MV) mfma_one(1, m + 1);
           if ((m & 3) == 2) {
             if (ODD) issue_a_pair((kt >> 1) + 2, m >> 2);
-            else issue_b(kt + 3, m >> 2);
+            else issue_b(kt + 3, m >> 2, once_tag);
           }
           __builtin_amdgcn_sched_barrier(0);
         }
@@ -1254,9 +1269,13 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
     } else {
       const int rows_left = row_end - (row0 + wm * 128);
       const int mv = rows_left > 64 ? 4 : (rows_left > 0 ? 2 : 0);
-      if (mv == 4) k_loop_pair(IntC<4>{});
-      else if (mv == 2) k_loop_pair(IntC<2>{});
-      else k_loop_pair(IntC<0>{});
+      auto rows_loop = [&](auto once_tag) {
+        if (mv == 4) k_loop_pair(IntC<4>{}, once_tag);
+        else if (mv == 2) k_loop_pair(IntC<2>{}, once_tag);
+        else k_loop_pair(IntC<0>{}, once_tag);
+      };
+      if (ONCE && once) rows_loop(IntC<1>{});
+      else rows_loop(IntC<0>{});
     }
     asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
     if (tid == 0) *next_q = my_ticket;
@@ -1687,15 +1706,15 @@ int launch_expert_fwd_bf16(const void* xp, int cap, int d, int f, int e_cnt, con
   int32_t* sched = sched_area(a_ws, (size_t)cap * f * 2);
   hipLaunchKernelGGL(zero_words, dim3(1), dim3(64), 0, s, sched, 32);
   HIP_CHECK_LAUNCH();
-  GArgs u = {};
+  GArgs u = {}, w = {};
   u.A0 = u.A1 = (const bf16_t*)xp; u.lda = d;
   u.B0 = (const bf16_t*)w1; u.B1 = (const bf16_t*)w3; u.ldb = f; u.b_es = (long)d * f;
   u.C0 = (bf16_t*)h1; u.C1 = (bf16_t*)h3; u.C2 = act; u.ldc = f;
+  u.stream = w.stream = cached_tiles(d, f) < e_cnt;
   u.off = offsets; u.sched = sched; u.e_cnt = e_cnt; u.N = f; u.K = d; u.save_h = (h1 && h3) ? 1 : 0;
   const bool decide = route == COUNTS_DECIDE;
   int rc = decide ? launch_gg_or_few<UP>(u, d, f, s) : launch_gg<UP>(u, s);
   if (rc) return rc;
-  GArgs w = {};
   w.A0 = w.A1 = act; w.lda = f;
   w.B0 = w.B1 = (const bf16_t*)w2; w.ldb = d; w.b_es = (long)f * d;
   w.C0 = (bf16_t*)o; w.ldc = d;
