@@ -4,10 +4,15 @@ Every function takes torch CUDA tensors (device memory) and forwards their data 
 the sizes and torch's current HIP stream to the C entry point of the same name.  There is
 no fallback: if libmoe_mi355x.so is missing or a call returns an error code, MoeError is
 raised.
+
+A call whose arguments are all as they should be is checked and made by csrc/marshal.cpp
+(_marshal.so), which costs the host a fifth of the time; any other is left to the checks here.
 """
 from __future__ import annotations
 
 import ctypes
+import importlib.machinery
+import importlib.util
 import os
 
 MOE_F32, MOE_BF16 = 0, 1
@@ -16,12 +21,16 @@ WS_DISPATCH, WS_EXPERT_FWD, WS_EXPERT_BWD, WS_ROUTER = 0, 1, 2, 3
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB = None
+_MARSHAL = None
 
 EXPORTS = ("moe_route", "moe_dispatch", "moe_dispatch_static", "moe_expert_fwd", "moe_expert_bwd", "moe_combine",
            "moe_router_fwd", "moe_combine_bwd", "moe_gate_bwd", "moe_router_bwd",
            "moe_profile_enable", "moe_profile_read", "moe_profile_stats", "moe_probe_mfma_bf16", "moe_probe_mfma_fed_bf16",
            "moe_probe_copy", "moe_probe_stream",
            "moe_workspace_bytes", "moe_error_string")
+# what csrc/marshal.cpp calls, in its order
+_MARSHALLED = ("moe_route", "moe_dispatch", "moe_dispatch_static", "moe_expert_fwd", "moe_expert_bwd", "moe_combine", "moe_router_fwd",
+               "moe_combine_bwd", "moe_gate_bwd", "moe_router_bwd")
 
 
 class MoeError(RuntimeError):
@@ -77,6 +86,22 @@ def load_library():
     return lib
 
 
+def _marshal():
+    """The native marshalling, bound to the library's entry points."""
+    global _MARSHAL
+    if _MARSHAL is None:
+        import torch  # noqa: F401  (its libraries come first)
+        lib, path = load_library(), os.path.join(_HERE, "_marshal.so")
+        if not os.path.exists(path):
+            raise MoeError(f"{path} not found: build it first (python -c 'import __graft_entry__ as g; g.build()')")
+        loader = importlib.machinery.ExtensionFileLoader("_marshal", path)
+        module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_marshal", path, loader=loader))
+        loader.exec_module(module)
+        module.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _MARSHALLED))
+        _MARSHAL = module
+    return _MARSHAL
+
+
 def _check(rc: int, name: str):
     if rc != 0:
         raise MoeError(f"{name} failed: {load_library().moe_error_string(rc).decode()} (code {rc})")
@@ -116,6 +141,9 @@ def moe_workspace_bytes(which, dtype, T, k, d, f, e_cnt, cap) -> int:
 
 
 def moe_route(logits, k, gate_mode, e_lo, e_cnt, topk_idx, topk_w, counts):
+    rc = _marshal().route(logits, k, gate_mode, e_lo, e_cnt, topk_idx, topk_w, counts)
+    if rc >= 0:
+        return _check(rc, "moe_route")
     import torch
     T, E = logits.shape
     _need(logits, torch.float32, name="logits")
@@ -127,6 +155,9 @@ def moe_route(logits, k, gate_mode, e_lo, e_cnt, topk_idx, topk_w, counts):
 
 
 def moe_dispatch(x, k, topk_idx, row_scale, e_lo, e_cnt, offsets, perm, inv, reuse_plan, xp, ws):
+    rc = _marshal().dispatch(x, k, topk_idx, row_scale, e_lo, e_cnt, offsets, perm, inv, reuse_plan, xp, ws)
+    if rc >= 0:
+        return _check(rc, "moe_dispatch")
     import torch
     T, d = x.shape
     cap = xp.shape[0]
@@ -145,6 +176,9 @@ def moe_dispatch(x, k, topk_idx, row_scale, e_lo, e_cnt, offsets, perm, inv, reu
 
 def moe_dispatch_static(x, k, topk_idx, row_scale, e_lo, e_cnt, offsets, perm, inv, xp, status=None):
     """moe_dispatch (plan + row move) on the library's built-in plan scratch: no workspace argument."""
+    rc = _marshal().dispatch_static(x, k, topk_idx, row_scale, e_lo, e_cnt, offsets, perm, inv, xp, status)
+    if rc >= 0:
+        return _check(rc, "moe_dispatch_static")
     import torch
     T, d = x.shape
     cap = xp.shape[0]
@@ -162,6 +196,9 @@ def moe_dispatch_static(x, k, topk_idx, row_scale, e_lo, e_cnt, offsets, perm, i
 
 
 def moe_expert_fwd(xp, offsets, w1, w3, w2, h1, h3, o, ws, a=None):
+    rc = _marshal().expert_fwd(xp, offsets, w1, w3, w2, h1, h3, o, ws, a)
+    if rc >= 0:
+        return _check(rc, "moe_expert_fwd")
     import torch
     cap, d = xp.shape
     e_cnt, _, f = w1.shape
@@ -176,6 +213,9 @@ def moe_expert_fwd(xp, offsets, w1, w3, w2, h1, h3, o, ws, a=None):
 
 
 def moe_expert_bwd(xp, h1, h3, d_o, offsets, w1, w3, w2, dxp, dw1, dw3, dw2, accumulate, ws, a=None):
+    rc = _marshal().expert_bwd(xp, h1, h3, d_o, offsets, w1, w3, w2, dxp, dw1, dw3, dw2, accumulate, ws, a)
+    if rc >= 0:
+        return _check(rc, "moe_expert_bwd")
     import torch
     cap, d = xp.shape
     e_cnt, _, f = w1.shape
@@ -192,6 +232,9 @@ def moe_expert_bwd(xp, h1, h3, d_o, offsets, w1, w3, w2, dxp, dw1, dw3, dw2, acc
 
 
 def moe_combine(o, inv, topk_w, y):
+    rc = _marshal().combine(o, inv, topk_w, y)
+    if rc >= 0:
+        return _check(rc, "moe_combine")
     import torch
     T, k = inv.shape
     d = o.shape[1]
@@ -202,6 +245,9 @@ def moe_combine(o, inv, topk_w, y):
 
 
 def moe_router_fwd(x, wr, logits, ws):
+    rc = _marshal().router_fwd(x, wr, logits, ws)
+    if rc >= 0:
+        return _check(rc, "moe_router_fwd")
     import torch
     T, d = x.shape
     E = wr.shape[1]
@@ -212,6 +258,9 @@ def moe_router_fwd(x, wr, logits, ws):
 
 
 def moe_combine_bwd(dy, o, inv, topk_w, d_o, dgate):
+    rc = _marshal().combine_bwd(dy, o, inv, topk_w, d_o, dgate)
+    if rc >= 0:
+        return _check(rc, "moe_combine_bwd")
     import torch
     T, k = inv.shape
     d = dy.shape[1]
@@ -225,6 +274,9 @@ def moe_combine_bwd(dy, o, inv, topk_w, d_o, dgate):
 
 
 def moe_gate_bwd(logits, topk_idx, dgate, gate_mode, dlogits):
+    rc = _marshal().gate_bwd(logits, topk_idx, dgate, gate_mode, dlogits)
+    if rc >= 0:
+        return _check(rc, "moe_gate_bwd")
     import torch
     T, E = logits.shape
     k = topk_idx.shape[1]
@@ -235,6 +287,9 @@ def moe_gate_bwd(logits, topk_idx, dgate, gate_mode, dlogits):
 
 
 def moe_router_bwd(x, wr, dlogits, dwr, dwr_accumulate, dx, dx_accumulate, ws):
+    rc = _marshal().router_bwd(x, wr, dlogits, dwr, dwr_accumulate, dx, dx_accumulate, ws)
+    if rc >= 0:
+        return _check(rc, "moe_router_bwd")
     import torch
     T, d = x.shape
     E = wr.shape[1]

@@ -1,0 +1,86 @@
+"""The native marshalling (csrc/marshal.cpp) makes the calls that binding.py's own checks and ctypes would make, on torch's current stream,
+and leaves every other call to them."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import gpu_layer, make_inputs
+from paper_2605_11005_amd import binding as B
+from paper_2605_11005_amd import workloads as W
+from paper_2605_11005_amd.layer import MoeLayerBuffers, run_backward, run_backward_router, run_forward, run_forward_router
+
+
+class NotTaken:
+    def __getattr__(self, name):
+        return lambda *args: -1
+
+
+class Taken:
+    """The native marshalling; counts the calls it made."""
+    calls = 0
+
+    def __getattr__(self, name):
+        def call(*args):
+            rc = getattr(NATIVE, name)(*args)
+            Taken.calls += rc >= 0
+            return rc
+        return call
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("wl", [W.TINY, W.QWEN.scaled(name="marshal-bf16", T=40, d=192, f=128, E=16, e_cnt=8, k=2)])
+def test_native_calls_equal_those_of_ctypes(wl, monkeypatch):
+    global NATIVE
+    print(f"case marshal-{wl.name}", flush=True)
+    NATIVE = B._marshal()
+    inp = make_inputs(wl)
+    dev, _ = gpu_layer(wl, inp)
+    g = torch.Generator(device="cuda").manual_seed(1)
+    dev["wr"] = torch.randn((wl.d, wl.E), generator=g, device="cuda", dtype=dev["x"].dtype) * wl.d ** -0.5
+    results = []
+    for marshal in (Taken(), NotTaken()):
+        monkeypatch.setattr(B, "_MARSHAL", marshal)
+        buf = MoeLayerBuffers(wl, cap=wl.T * wl.k, router=True)
+        status = torch.full((1,), 7, dtype=torch.int32, device="cuda")
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            run_forward(wl, dev, buf)
+            run_backward(wl, dev, buf)
+            run_forward_router(wl, dev, buf)
+            run_backward_router(wl, dev, buf)
+            B.moe_dispatch_static(dev["x"], wl.k, buf.topk_idx, None, wl.e_lo, wl.e_cnt, buf.offsets, buf.perm, buf.inv, buf.xp, status)
+        side.synchronize()
+        rows = int(buf.offsets[-1])
+        names = ("topk_idx", "topk_w", "counts", "offsets", "inv", "y", "dx", "dw1", "dw3", "dw2", "logits", "dgate", "dlogits", "dwr")
+        results.append([getattr(buf, n).clone() for n in names] + [buf.xp[:rows].clone(), buf.o[:rows].clone(), status])
+    # the forward's and the backward's four and three calls, the router's five and five, the static plan
+    assert Taken.calls == 18
+    Taken.calls = 0
+    assert int(results[0][-1]) == 0 and all(torch.equal(a, b) for a, b in zip(*results))
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("fault", ["dtype", "shape", "strides", "host", "array", "integer", "code"])
+def test_refused_calls_are_refused_alike(fault, monkeypatch):
+    native = B._marshal()
+    logits = torch.randn((6, 8), device="cuda")
+    idx, w, counts = torch.empty((6, 2), dtype=torch.int32, device="cuda"), torch.empty((6, 2), device="cuda"), torch.empty(8, dtype=torch.int32, device="cuda")
+    args = dict(logits=logits, k=2, gate_mode=0, e_lo=0, e_cnt=8, topk_idx=idx, topk_w=w, counts=counts)
+    args.update({"dtype": dict(topk_w=w.double()), "shape": dict(counts=counts[:7]), "strides": dict(logits=torch.randn((8, 6), device="cuda").t()),
+                 "host": dict(topk_idx=idx.cpu()), "array": dict(counts=np.zeros(8, np.int32)), "integer": dict(gate_mode=0.5),
+                 "code": dict(gate_mode=9)}[fault])
+    errors = []
+    for marshal in (native, NotTaken()):
+        monkeypatch.setattr(B, "_MARSHAL", marshal)
+        with pytest.raises(Exception) as e:
+            B.moe_route(**args)
+        errors.append((type(e.value), str(e.value)))
+    assert errors[0] == errors[1]
+
+
+def test_host_tensors_are_left_to_the_checks():
+    t = torch.zeros((4, 8))
+    assert B._marshal().route(t, 2, 0, 0, 8, t, t, t) == -1 and B._marshal().combine(None, None, None, None) == -1 and B._marshal().combine() == -1
+    with pytest.raises(B.MoeError, match="contiguous device tensor"):
+        B.moe_route(t, 2, 0, 0, 8, t, t, t)
