@@ -43,8 +43,30 @@ enum { UP, DOWN, DA, DX, WG, WGD };
 constexpr int PITCH_KC = 36, PITCH_MN = 68;
 constexpr int HALF = TK / 4;      // steps whose fragments are held at a time: half of a k-tile
 
-// The loads below are unconditional (clamped addresses); what lies past the end of the contraction becomes zero on the
-// way to LDS, rows and columns past the end repeat the last ones (their products are never stored).
+// Loads go through a buffer descriptor that begins at the k-tile and ends with the operand's last valid element: a lane's offset in a
+// tile never changes, so that a k-tile's addresses are a few 32-bit scalar instructions instead of two 64-bit multiplications per
+// load on the vector unit, which the splitting keeps busy.  Training steps (T, d, f, experts, k), us: 1500, 520, 776, 16, 2 256 -> 247; 2579, 592,
+// 880, 12, 2 470 -> 452; 1128, 452, 880, 32, 4 380 -> 366; 265, 712, 144, 4, 1 115 -> 113; 256, 128, 256, 8, 2 84.4 -> 83.6.  (With 64-bit
+// scalar bounds, whose comparisons are vector instructions, the small ones took 1 to 2 % longer than before.)
+// What lies past the end of the contraction becomes zero on the way to LDS; rows and columns past the end repeat the last ones (their
+// products are never stored).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_descriptor(const float* base, int words) {
+  uint64_t b = (uint64_t)base;
+  int bytes = 4 * max(0, words);          // (past the last k-tile: zeros, and memory is not touched)
+  asm("" : "+s"(b), "+s"(bytes));         // both are wave-uniform: keep them in scalar registers
+  return __builtin_amdgcn_make_buffer_rsrc((void*)b, 0, bytes, 0x00027000);
+}
+typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ float4 tile_load(__amdgpu_buffer_rsrc_t d, int voff) {
+  return __builtin_bit_cast(float4, __builtin_amdgcn_raw_buffer_load_b128(d, voff, 0, 0));
+}
+// a pointer that is the same in all lanes, in scalar registers
+__device__ __forceinline__ const float* uniform(const float* q) {
+  const uint64_t u = (uint64_t)q;
+  return (const float*)(((uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((int)(u >> 32)) << 32) |
+                        (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)u));
+}
+
 __device__ __forceinline__ float4 keep(float4 v, bool in) {
   return make_float4(in ? v.x : 0.f, in ? v.y : 0.f, in ? v.z : 0.f, in ? v.w : 0.f);
 }
@@ -104,14 +126,26 @@ struct OperKC {
   }
   const float* base;
   long ld;
-  int rows, K;
-  __device__ __forceinline__ void load(float4* v, int k0, int tid) const {
+  int rows, K, voff[2];
+  int left;                // of the contraction
+  __device__ __forceinline__ void setup(const float* base_, long ld_, int rows_, int K_, int tid) {
+    base = uniform(base_);
+    ld = ld_;
+    K = K_;
+    rows = __builtin_amdgcn_readfirstlane(min(rows_, TM));
+    left = K;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int idx = tid + NT * i;
-      const int r = min(idx >> 3, rows - 1), k = min(k0 + 4 * (idx & 7), K - 4);
-      v[i] = *reinterpret_cast<const float4*>(base + (size_t)r * ld + k);
+      voff[i] = 4 * (min(idx >> 3, rows - 1) * (int)ld + 4 * (idx & 7));
     }
+  }
+  __device__ __forceinline__ void load(float4* v) {      // k-tiles in order
+    const __amdgpu_buffer_rsrc_t d = tile_descriptor(base, (rows - 1) * (int)ld + left);
+    base += TK;
+    left -= TK;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) v[i] = tile_load(d, voff[i]);
   }
   __device__ __forceinline__ void store(const float4* v, float* s, int k0, int tid) const {
 #pragma unroll
@@ -155,14 +189,26 @@ struct OperMN {
   }
   const float* base;
   long ld;
-  int cols, K;
-  __device__ __forceinline__ void load(float4* v, int k0, int tid) const {
+  int cols, K, voff[2];
+  int left;                // of the contraction
+  __device__ __forceinline__ void setup(const float* base_, long ld_, int cols_, int K_, int tid) {
+    base = uniform(base_);
+    ld = ld_;
+    cols = cols_;
+    K = __builtin_amdgcn_readfirstlane(K_);
+    left = K;
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
       const int idx = tid + NT * i;
-      const int k = min(k0 + (idx >> 4), K - 1), c = min(4 * (idx & 15), cols - 4);
-      v[i] = *reinterpret_cast<const float4*>(base + (size_t)k * ld + c);
+      voff[i] = 4 * ((idx >> 4) * (int)ld + min(4 * (idx & 15), cols - 4));
     }
+  }
+  __device__ __forceinline__ void load(float4* v) {      // k-tiles in order
+    const __amdgpu_buffer_rsrc_t d = tile_descriptor(base, (min(left, TK) - 1) * (int)ld + cols);
+    base += TK * ld;
+    left -= TK;
+#pragma unroll
+    for (int i = 0; i < 2; ++i) v[i] = tile_load(d, voff[i]);
   }
   __device__ __forceinline__ void store(const float4* v, float* s, int k0, int tid) const {
 #pragma unroll
@@ -242,18 +288,16 @@ __device__ __forceinline__ void gemm_tile(const Args& p, int block, char* lds) {
   auto setup = [&](int seg) {
     if constexpr (RAGGED_K) {
       const size_t first = p.off[e];
-      a.base = p.A[0] + first * p.lda + row0; a.ld = p.lda; a.cols = p.M - row0; a.K = K;
+      a.setup(p.A[0] + first * p.lda + row0, p.lda, p.M - row0, K, tid);
 #pragma unroll
-      for (int i = 0; i < NB; ++i) { b[i].base = p.B[i] + first * p.ldb + col0; b[i].ld = p.ldb; b[i].cols = p.N - col0; b[i].K = K; }
+      for (int i = 0; i < NB; ++i) b[i].setup(p.B[i] + first * p.ldb + col0, p.ldb, p.N - col0, K, tid);
     } else {
-      a.base = p.A[seg] + (size_t)row0 * p.lda; a.ld = p.lda; a.rows = row_end - row0; a.K = K;
+      a.setup(p.A[seg] + (size_t)row0 * p.lda, p.lda, row_end - row0, K, tid);
 #pragma unroll
       for (int i = 0; i < NB; ++i) {
         const float* w = p.B[DUAL ? i : seg] + (size_t)e * p.b_es;
-        b[i].ld = p.ldb;
-        b[i].K = K;
-        if constexpr (MODE == DA || MODE == DX) { b[i].base = w + (size_t)col0 * p.ldb; b[i].rows = p.N - col0; }
-        else { b[i].base = w + col0; b[i].cols = p.N - col0; }
+        if constexpr (MODE == DA || MODE == DX) b[i].setup(w + (size_t)col0 * p.ldb, p.ldb, p.N - col0, K, tid);
+        else b[i].setup(w + col0, p.ldb, p.N - col0, K, tid);
       }
     }
   };
@@ -277,12 +321,10 @@ __device__ __forceinline__ void gemm_tile(const Args& p, int block, char* lds) {
     const auto first_k = [&](int kt) { return (MODE == DX && kt >= nk1 ? kt - nk1 : kt) * TK; };
     auto fetch = [&](int kt, auto set) {
       constexpr int S = decltype(set)::value;
-      if (kt > nk - 1) kt = nk - 1;                // (surplus loads at the end, never multiplied)
       if (MODE == DX && kt == nk1) setup(1);       // the second half of the k-tiles is the second segment
-      const int k0 = first_k(kt);
-      a.load(va[S], k0, tid);
+      a.load(va[S]);                               // (past the last one: never multiplied)
 #pragma unroll
-      for (int i = 0; i < NB; ++i) b[i].load(vb[S][i], k0, tid);
+      for (int i = 0; i < NB; ++i) b[i].load(vb[S][i]);
     };
     auto publish = [&](int kt, auto set) {
       constexpr int S = decltype(set)::value;
