@@ -15,22 +15,24 @@
 // cost one instruction per 16 columns and 32 k.
 //   * UP, DOWN: four wavefronts that share the loads and multiply 32 columns each, every output one chain of sums over
 //     ascending k (expert_tile);
-//   * RL, RW: eight wavefronts that share the contraction, wavefront w the 32-deep pieces w, w + 8, .., two to four of them in
-//     flight; the eight partial results are added in LDS in ascending order (router_tile);
+//   * RL: eight wavefronts that share the contraction, wavefront w the units of 64 k w, w + 8, .., one or two of them in flight; the
+//     eight partial results are added in LDS in ascending order (router_logits);
+//   * RW: the same with 32-deep pieces, two to four of them in flight (router_tile);
 //   * RL with 8 to 56 experts: eight wavefronts with an eighth of the contraction each, eight sums per output (narrow_router).
 #include "few_rows.h"
 #include "kernels.h"
+#include <utility>
 
 namespace {
 
-enum { UP, DOWN, RL, RW };
+enum { UP, DOWN };
 
 constexpr int NW_ROUTER = 8;              // wavefronts per block
 constexpr int RPITCH = COLS + 4;          // partial results in LDS: [wavefront][16 rows][RPITCH]
 
-// RL, RW: up to 16 * TG rows against COLS columns.  Wavefront w multiplies the pieces w, w + NW, .. of all columns, and the
+// RW: up to 16 * TG rows against COLS columns.  Wavefront w multiplies the pieces w, w + NW, .. of all columns, and the
 // partial results are added in LDS in ascending order of the wavefronts.
-template <int MODE, int TG>
+template <int TG>
 __device__ __forceinline__ void router_tile(const SArgs& p, float* red, int row0, int row_end, int n0, int first, int pieces, int tid) {
   constexpr int NW = NW_ROUTER;
   constexpr int DEPTH = TG == 1 ? 4 : (TG == 2 ? 3 : 2);        // pieces in flight
@@ -56,7 +58,7 @@ __device__ __forceinline__ void router_tile(const SArgs& p, float* red, int row0
       constexpr int S = decltype(slot)::value;
       const bool in = idx < n;
       const long piece = in ? first + wave + NW * idx : 0;
-      const long k = MODE == RW ? min(piece * KP, (long)p.K - KP) : piece * KP;      // RW: the last piece ends at the last token
+      const long k = min(piece * KP, (long)p.K - KP);               // the last piece ends at the last token
       w[S].template load<0, 8>(b0 + k * p.ldb, in, 2 * (int)p.ldb, woff);
       const __amdgpu_buffer_rsrc_t dx = descriptor(xrow + piece * p.xstep, in);
 #pragma unroll
@@ -64,23 +66,27 @@ __device__ __forceinline__ void router_tile(const SArgs& p, float* red, int row0
       __builtin_amdgcn_sched_barrier(0);  // pieces stay in order: waiting for one must not wait for the next
     };
     static_for<DEPTH>([&](auto s) { load(s, decltype(s)::value); });
-    for (int idx = 0; idx < n; idx += DEPTH)
+    auto multiply = [&](auto slot) {
+      constexpr int S = decltype(slot)::value;
+#pragma unroll
+      for (int j = 0; j < 8; ++j) {
+        const bf16x8 f = w[S].operand(j);
+#pragma unroll
+        for (int t = 0; t < TG; ++t) acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, x[S][t], acc[t][j], 0, 0, 0);
+      }
+    };
+    int idx = 0;
+    for (; idx + DEPTH < n; idx += DEPTH)
       static_for<DEPTH>([&](auto s) {
-        constexpr int S = decltype(s)::value;
-        if (idx + S < n) {
-#pragma unroll
-          for (int j = 0; j < 8; ++j) {
-            const bf16x8 f = w[S].operand(j);
-#pragma unroll
-            for (int t = 0; t < TG; ++t) acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f, x[S][t], acc[t][j], 0, 0, 0);
-          }
-        }
-        load(s, idx + DEPTH + S);
+        multiply(s);
+        load(s, idx + DEPTH + decltype(s)::value);
       });
+    static_for<DEPTH>([&](auto s) {       // the last ones are on their way
+      if (idx + decltype(s)::value < n) multiply(s);
+    });
   }
   // Add the partial results up, 16 rows at a time.  Element r of acc[t][j] belongs to row 16t + i and lane group 4g + r of
   // the loads: column 8 * (4g + r) + j.
-  constexpr int PER = 16 * COLS / (NW * WAVE);                  // columns per thread
 #pragma unroll
   for (int t = 0; t < TG; ++t) {
     if (t > 0) __syncthreads();
@@ -92,32 +98,175 @@ __device__ __forceinline__ void router_tile(const SArgs& p, float* red, int row0
         *reinterpret_cast<f32x4*>(mine + 8 * (4 * g + r) + 4 * h) =
             f32x4{acc[t][4 * h][r], acc[t][4 * h + 1][r], acc[t][4 * h + 2][r], acc[t][4 * h + 3][r]};
     __syncthreads();
-    if (MODE == RW) {                                           // [column][expert], one plane after the other; rows fastest
-      const int r = tid & 15, row = row0 + 16 * t + r;
-      if (row < row_end) {
-        const int plane = row / p.n_experts;
-        float* out = p.F + (size_t)plane * p.N * p.n_experts + (row - plane * p.n_experts);
-        for (int c = tid >> 4; c < COLS && n0 + c < p.N; c += NW * WAVE / 16) {
-          float v = 0.f;
+    const int r = tid & 15, row = row0 + 16 * t + r;            // [column][expert], one plane after the other; rows fastest
+    if (row >= row_end) continue;
+    const int plane = row / p.n_experts;
+    float* out = p.F + (size_t)plane * p.N * p.n_experts + (row - plane * p.n_experts);
+    for (int c = tid >> 4; c < COLS && n0 + c < p.N; c += NW * WAVE / 16) {
+      float v = 0.f;
 #pragma unroll
-          for (int wv = 0; wv < NW; ++wv) v += red[(wv * 16 + r) * RPITCH + c];
-          out[(size_t)(n0 + c) * p.n_experts] = v;
-        }
-      }
-      continue;
+      for (int wv = 0; wv < NW; ++wv) v += red[(wv * 16 + r) * RPITCH + c];
+      out[(size_t)(n0 + c) * p.n_experts] = v;
     }
-    const int rr = tid / (COLS / PER), col = n0 + PER * (tid % (COLS / PER));      // row of the group, this thread's first column
-    const int row = row0 + 16 * t + rr;
+  }
+}
+
+// RL: 16 * TG tokens against 16 * CL experts.  Wavefront w multiplies the units of 64 k w, w + NW, .., and the partial results are
+// added in LDS in ascending order of the wavefronts: neither TG nor CL changes a bit.  PAIRS, where the contraction may also be cut (E % 64
+// == 0, 16 by 64): the products of a unit's halves start from zero and are added as ordinary fp32 sums, since a chain of matrix instructions
+// does not round to nearest.  Relative error, 128 experts per block and three ranges or more / chains / pairs: T = 300, d = 7168, E = 512
+// 11.4e-8 / 18.0e-8 / 10.0e-8; T = 128, 4096, 128 9.0e-8 / 9.4e-8 / 8.8e-8.
+// What bounds it is how a CU fetches x and the weights, at 60 to 85 GB/s.  Operands of x loaded where the instruction wants them, 16
+// tokens by 64 bytes, touch a line with every lane of 16 and ask memory for half lines; so a load takes whole lines, 128 bytes of
+// eight tokens, and the wavefront's own LDS turns them round.  And nothing is asked for past the end: eight pieces of void loads
+// were 1.5 us.  Calls one after the other, us, operands loaded directly, pieces of 32 k, 128 experts per block / this:
+//   T = 2047, d = 2880, E = 128 12.9 / 8.7    4096, 2048, 64 9.6 / 7.2      9001, 2880, 128 29.2 / 23.6    16384, 2048, 128 24.0 / 21.6
+//   T = 128, d = 4096, E = 128 10.4 / 7.3     4096, 7168, 256 44.5 / 32.5   8192, 4096, 64 25.8 / 21.6     1200, 4096, 192 16.5 / 11.1
+template <int CL>
+struct RouterPiece {                      // 32 k of the weights: a lane holds CL columns of eight rows
+  typedef unsigned int vec __attribute__((ext_vector_type(CL / 2)));
+  vec w[8];
+  __device__ __forceinline__ void load(const bf16_t* base, bool in, int row, int voff) {
+    const __amdgpu_buffer_rsrc_t d = descriptor(base, in);
+#pragma unroll
+    for (int r = 0; r < 8; ++r) {
+      if constexpr (CL == 8) w[r] = __builtin_amdgcn_raw_buffer_load_b128(d, voff, r * row, 0);
+      else w[r] = __builtin_amdgcn_raw_buffer_load_b64(d, voff, r * row, 0);
+    }
+  }
+  __device__ __forceinline__ bf16x8 operand(int j) const {      // column j of the lane's, its eight k
+    u32x4 f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) f[q] = __builtin_amdgcn_perm(w[2 * q + 1][j >> 1], w[2 * q][j >> 1], (j & 1) ? 0x07060302u : 0x05040100u);
+    return __builtin_bit_cast(bf16x8, f);
+  }
+};
+
+template <int TG, int CL, bool PAIRS>
+__global__ __launch_bounds__(NW_ROUTER * WAVE) void router_logits(SArgs p) {
+  constexpr int NW = NW_ROUTER, WIDTH = 16 * CL, PITCH = WIDTH + 4;
+  constexpr int DEPTH = TG >= 2 && CL == 8 ? 1 : 2;                  // units in flight: what the registers hold
+  constexpr int UNIT = 128 * TG;                                // 16-byte places of a wavefront's unit of x
+  constexpr int SUM_PLACES = NW * 16 * PITCH / 4;
+  __shared__ u32x4 lds[NW * UNIT > SUM_PLACES ? NW * UNIT : SUM_PLACES];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int i = lane & 15, g = lane >> 4;
+  const int row0 = blockIdx.x * 16 * TG, rows = min(p.rows - row0, 16 * TG), n0 = blockIdx.y * WIDTH;
+  const int first = blockIdx.z * p.range, units = min(p.range, p.K / 64 - first);
+  const int n = (units - wave + NW - 1) / NW;                   // units of this wavefront
+  f32x4 acc[TG][CL];
+#pragma unroll
+  for (int t = 0; t < TG; ++t)
+#pragma unroll
+    for (int j = 0; j < CL; ++j) acc[t][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  {
+    const bf16_t* const b0 = p.B0 + n0;
+    const bf16_t* const xrow = p.A + (size_t)row0 * p.lda;
+    const int woff = 2 * (8 * g * (int)p.ldb + min(CL * i, p.N - n0 - CL));       // columns past the end repeat the last ones
+    const int xoff = 2 * ((lane >> 3) * (int)p.lda + 8 * (lane & 7));
+    RouterPiece<CL> w[DEPTH][2];
+    u32x4 x[DEPTH][2 * TG];
+    auto load_x = [&](auto slot, int idx) {       // rows past the end are zeros: the descriptor ends there
+      const bool in = idx < n;
+      const int k = in ? 64 * (first + wave + NW * idx) : 0;
+      uint64_t base = (uint64_t)(xrow + k);
+      int bytes = in ? 2 * (rows * (int)p.lda - k) : 0, eight = 16 * (int)p.lda;
+      asm("" : "+s"(base), "+s"(bytes), "+s"(eight));           // (the offsets are formed again each time: no registers are kept for them)
+      const __amdgpu_buffer_rsrc_t d = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00027000);
+#pragma unroll
+      for (int q = 0; q < 2 * TG; ++q) x[decltype(slot)::value][q] = __builtin_amdgcn_raw_buffer_load_b128(d, xoff + q * eight, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);  // loads stay in order: waiting for one must not wait for the next
+    };
+    auto load_w = [&](auto slot, auto half, int idx) {
+      const bool in = idx < n;
+      const long k = in ? 64 * (first + wave + NW * idx) + 32 * decltype(half)::value : 0;
+      w[decltype(slot)::value][decltype(half)::value].load(b0 + k * p.ldb, in, 2 * (int)p.ldb, woff);
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    // token r's chunk c (eight k) of a unit: the 8 chunks of a token and the same chunk of 8 tokens are on different banks
+    u32x4* const mine = lds + wave * UNIT;
+    const auto at = [](int r, int c) { return 8 * r + (c ^ (r & 7)); };
+    auto unit = [&](auto slot, int idx, auto more) {
+      constexpr int S = decltype(slot)::value;
+      constexpr bool MORE = decltype(more)::value;
+#pragma unroll
+      for (int q = 0; q < 2 * TG; ++q) mine[at(8 * q + (lane >> 3), lane & 7)] = x[S][q];
+      __builtin_amdgcn_wave_barrier();    // LDS serves a wavefront's accesses in order
+      if constexpr (MORE) load_x(slot, idx + DEPTH);
+      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
+      bf16x8 f[2][TG];
+      auto read = [&](auto half) {
+        constexpr int H = decltype(half)::value;
+#pragma unroll
+        for (int t = 0; t < TG; ++t) f[H][t] = __builtin_bit_cast(bf16x8, mine[at(16 * t + i, 4 * H + g)]);
+      };
+      if constexpr (PAIRS) {
+        read(Int<0>{});
+        read(Int<1>{});
+#pragma unroll
+        for (int j = 0; j < CL; ++j) {
+          const bf16x8 c0 = w[S][0].operand(j), c1 = w[S][1].operand(j);
+#pragma unroll
+          for (int t = 0; t < TG; ++t)
+            acc[t][j] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(c0, f[0][t], zero, 0, 0, 0) +
+                         __builtin_amdgcn_mfma_f32_16x16x32_bf16(c1, f[1][t], zero, 0, 0, 0);
+        }
+        if constexpr (MORE) {
+          load_w(slot, Int<0>{}, idx + DEPTH);
+          load_w(slot, Int<1>{}, idx + DEPTH);
+        }
+      } else {
+        static_for<2>([&](auto half) {
+          constexpr int H = decltype(half)::value;
+          read(half);
+#pragma unroll
+          for (int j = 0; j < CL; ++j) {
+            const bf16x8 c = w[S][H].operand(j);
+#pragma unroll
+            for (int t = 0; t < TG; ++t) acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c, f[H][t], acc[t][j], 0, 0, 0);
+          }
+          if constexpr (MORE) load_w(slot, half, idx + DEPTH);
+        });
+      }
+      __builtin_amdgcn_wave_barrier();
+    };
+    static_for<DEPTH>([&](auto s) {
+      load_x(s, decltype(s)::value);
+      load_w(s, Int<0>{}, decltype(s)::value);
+      load_w(s, Int<1>{}, decltype(s)::value);
+    });
+    int idx = 0;
+    for (; idx + DEPTH < n; idx += DEPTH) static_for<DEPTH>([&](auto s) { unit(s, idx + decltype(s)::value, Int<1>{}); });
+    static_for<DEPTH>([&](auto s) {       // the last ones are on their way
+      if (idx + decltype(s)::value < n) unit(s, idx + decltype(s)::value, Int<0>{});
+    });
+  }
+  // Element r of acc[t][j] belongs to token 16t + i and lane group 4g + r of the loads: column CL * (4g + r) + j.
+  float* const red = reinterpret_cast<float*>(lds);             // [wavefront][16 tokens][PITCH]
+  float* const out = p.F + ((size_t)blockIdx.z * p.rows + row0) * p.N;
+  constexpr int PER = 16 * WIDTH / (NW * WAVE);                 // columns per thread
+  const int rr = tid / (WIDTH / PER), cc = PER * (tid % (WIDTH / PER));
+#pragma unroll
+  for (int t = 0; t < TG; ++t) {
+    __syncthreads();
+    float* const mine = red + (wave * 16 + i) * PITCH;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int h = 0; h < CL / 4; ++h)
+        *reinterpret_cast<f32x4*>(mine + CL * (4 * g + r) + 4 * h) =
+            f32x4{acc[t][4 * h][r], acc[t][4 * h + 1][r], acc[t][4 * h + 2][r], acc[t][4 * h + 3][r]};
+    __syncthreads();
     float v[PER];
 #pragma unroll
     for (int k = 0; k < PER; ++k) v[k] = 0.f;
 #pragma unroll
     for (int wv = 0; wv < NW; ++wv)
 #pragma unroll
-      for (int k = 0; k < PER; ++k) v[k] += red[(wv * 16 + rr) * RPITCH + col - n0 + k];
-    if (row >= row_end || col >= p.N) continue;
+      for (int k = 0; k < PER; ++k) v[k] += red[(wv * 16 + rr) * PITCH + cc + k];
+    if (16 * t + rr >= rows || n0 + cc >= p.N) continue;
 #pragma unroll
-    for (int k = 0; k < PER; ++k) p.F[(size_t)row * p.ldc + col + k] = v[k];
+    for (int k = 0; k < PER; ++k) out[(size_t)(16 * t + rr) * p.N + n0 + cc + k] = v[k];
   }
 }
 
@@ -264,13 +413,13 @@ __global__ __launch_bounds__(NW_TILES * WAVE) void small_rows(SArgs p) {
 }
 
 // grid = (row blocks of 16 * TG, column blocks, ranges of the contraction)
-template <int MODE, int TG>
-__global__ __launch_bounds__(NW_ROUTER * WAVE) void small_rows_router(SArgs p) {
+template <int TG>
+__global__ __launch_bounds__(NW_ROUTER * WAVE) void router_dw_few(SArgs p) {
   __shared__ __align__(16) float red[NW_ROUTER * 16 * RPITCH];
   const int row0 = blockIdx.x * 16 * TG, first = blockIdx.z * p.range;
   p.F += (size_t)blockIdx.z * p.rows * p.N;
-  router_tile<MODE, TG>(p, red, row0, min(p.rows, row0 + 16 * TG), blockIdx.y * COLS, first,
-                        min(p.range, (p.K + KP - 1) / KP - first), threadIdx.x);
+  router_tile<TG>(p, red, row0, min(p.rows, row0 + 16 * TG), blockIdx.y * COLS, first,
+                  min(p.range, (p.K + KP - 1) / KP - first), threadIdx.x);
 }
 
 template <int MODE>
@@ -293,14 +442,14 @@ int launch_expert_fwd_small(const void* xp, int cap, int d, int f, int e_cnt, co
   SArgs u = {};
   u.A = (const bf16_t*)xp; u.lda = d;
   u.B0 = (const bf16_t*)w1; u.B1 = (const bf16_t*)w3; u.ldb = f; u.b_es = (long)d * f;
-  u.C0 = (bf16_t*)h1; u.C1 = (bf16_t*)h3; u.C2 = (bf16_t*)a; u.ldc = f; u.xstep = KP;
+  u.C0 = (bf16_t*)h1; u.C1 = (bf16_t*)h3; u.C2 = (bf16_t*)a; u.ldc = f;
   u.off = offsets; u.e_cnt = e_cnt; u.N = f; u.K = d; u.cached = cached_tiles(d, f);
   int rc = launch_small<UP>(u, cap, MOE_K_UP, s);
   if (rc) return rc;
   SArgs w = {};
   w.A = (const bf16_t*)a; w.lda = f;
   w.B0 = (const bf16_t*)w2; w.ldb = d; w.b_es = (long)f * d;
-  w.C0 = (bf16_t*)o; w.ldc = d; w.xstep = KP;
+  w.C0 = (bf16_t*)o; w.ldc = d;
   w.off = offsets; w.e_cnt = e_cnt; w.N = d; w.K = f; w.cached = u.cached;
   return launch_small<DOWN>(w, cap, MOE_K_DOWN, s);
 }
@@ -337,29 +486,40 @@ int launch_router_fwd_small(const void* x, const void* wr, int T, int d, int E, 
   SArgs p = {};
   p.A = (const bf16_t*)x; p.lda = d;
   p.B0 = (const bf16_t*)wr; p.ldb = E;
-  p.ldc = E; p.rows = T; p.e_cnt = 1; p.N = E; p.K = d; p.xstep = KP;
-  const int cols = (E + COLS - 1) / COLS, cus = device_cu_count(), pieces = d / KP;
-  // As few rows per block as make at most one block per CU: the weights are read once per block, and a second round of
-  // blocks nearly doubles the time.  16 / 32 / 64 rows per block, us:
-  //   E = 128:  T = 3000, d = 2048 10.2 / 12.4 / 14.7    5000, 2048 19.1 / 13.3 / 17.4    9001, 2048 28.4 / 24.7 / 17.8
-  //             T = 5000, d = 7168 51.6 / 34.2 / 27.0    9001, 7168 75.5 / 64.7 / 46.7
-  const int tg = (long long)(T + 15) / 16 * cols <= cus ? 1 : ((long long)(T + 31) / 32 * cols <= cus ? 2 : 4);
-  const int row_blocks = (T + 16 * tg - 1) / (16 * tg);
-  // A handful of blocks cannot draw the weights fast enough, so it is cut along the contraction (at least two pieces per
-  // wavefront); the second launch that adds the ranges up pays from three ranges on.
+  p.rows = T; p.N = E; p.K = d;
+  // Tokens (16 tg) and experts (16 cl) of a block: the fewest bytes per block that make at most one block per CU; a second round
+  // of blocks nearly doubles the time.  16 x 64 / 16 x 128 / 32 x 64 / 32 x 128 / 64 x 64 / 64 x 128, us:
+  //   T = 2047, d = 2880, E = 128 11.0 / 12.2 / 12.0 / -    / - / -           3500, 2048, 72  14.2 / 9.7 / 10.8 / 10.6 / 12.6 / 13.6
+  //   T = 8000, d = 2880, E = 128 37 / 30 / 27 / 20.4 / 22.1 / 25.1           9001, 2880, 128 44 / 40 / 35 / 33 / 34 / 25.6
+  //   T = 8192, d = 4096, E = 64  29 / 30 / 23.6 / 24.2 / 26.2 / 27.4         16384, 2048, 64 31 / 33 / 24 / 25 / 20.4 / 21.2
+  const int cus = device_cu_count(), units = d / 64;
+  int tg, cl, cols, row_blocks;
+  for (const auto& shape : {std::pair<int, int>{1, 4}, {1, 8}, {2, 4}, {2, 8}, {4, 4}, {4, 8}}) {
+    tg = shape.first, cl = shape.second;
+    cols = (E + 16 * cl - 1) / (16 * cl), row_blocks = (T + 16 * tg - 1) / (16 * tg);
+    if ((long long)row_blocks * cols <= cus) break;
+  }
+  // Where that leaves CUs idle the contraction is cut, at 12 units or more per range.  The launch that adds the ranges up costs what
+  // some 28 units do.  Whole / 2 / 4 / 8 ranges, us:
+  //   d = 2048, E = 64, T = 1024 6.2 / 6.9 / 7.8 / 12    d = 2880, E = 128, T = 256 8.1 / 8.2 / 7.3 / 8.7
+  //   d = 4096, E = 128, T = 4 9.7 / 8.2 / 7.0 / 7.4     T = 300 10.1 / 8.6 / 7.5 / 11     d = 7168, E = 256, T = 8 16 / 12 / 8.5 / 7.8
   int n = cus / (cols * row_blocks);
   if (n > max_ranges) n = max_ranges;
-  if (n > pieces / (2 * NW_ROUTER)) n = pieces / (2 * NW_ROUTER);
-  if (n < 3) n = 1;
-  p.range = (pieces + n - 1) / n;
-  n = (pieces + p.range - 1) / p.range;
+  if (n > units / 12) n = units / 12;
+  if (n < 2 || units - units / n < 28) n = 1;
+  p.range = (units + n - 1) / n;
+  n = (units + p.range - 1) / p.range;
   p.F = n > 1 ? partials : logits;
   *ranges = n;
   const dim3 grid(row_blocks, cols, n), block(NW_ROUTER * WAVE);
   ProfScope prof(MOE_K_ROUTER_FWD, s);
-  if (tg == 4) hipLaunchKernelGGL((small_rows_router<RL, 4>), grid, block, 0, s, p);
-  else if (tg == 2) hipLaunchKernelGGL((small_rows_router<RL, 2>), grid, block, 0, s, p);
-  else hipLaunchKernelGGL((small_rows_router<RL, 1>), grid, block, 0, s, p);
+  if (tg == 1 && cl == 4 && E % 64 == 0) hipLaunchKernelGGL((router_logits<1, 4, true>), grid, block, 0, s, p);
+  else if (tg == 1 && cl == 4) hipLaunchKernelGGL((router_logits<1, 4, false>), grid, block, 0, s, p);
+  else if (tg == 1) hipLaunchKernelGGL((router_logits<1, 8, false>), grid, block, 0, s, p);
+  else if (tg == 2 && cl == 4) hipLaunchKernelGGL((router_logits<2, 4, false>), grid, block, 0, s, p);
+  else if (tg == 2) hipLaunchKernelGGL((router_logits<2, 8, false>), grid, block, 0, s, p);
+  else if (cl == 4) hipLaunchKernelGGL((router_logits<4, 4, false>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((router_logits<4, 8, false>), grid, block, 0, s, p);
   HIP_CHECK_LAUNCH();
   return MOE_OK;
 }
@@ -385,9 +545,9 @@ int launch_router_dw_small(const void* x, const void* dl_pieces, int planes, int
   *sums = n * planes;
   const dim3 grid(row_blocks, cols, n), block(NW_ROUTER * WAVE);
   ProfScope prof(MOE_K_ROUTER_DW, s);
-  if (tg == 4) hipLaunchKernelGGL((small_rows_router<RW, 4>), grid, block, 0, s, p);
-  else if (tg == 2) hipLaunchKernelGGL((small_rows_router<RW, 2>), grid, block, 0, s, p);
-  else hipLaunchKernelGGL((small_rows_router<RW, 1>), grid, block, 0, s, p);
+  if (tg == 4) hipLaunchKernelGGL((router_dw_few<4>), grid, block, 0, s, p);
+  else if (tg == 2) hipLaunchKernelGGL((router_dw_few<2>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((router_dw_few<1>), grid, block, 0, s, p);
   HIP_CHECK_LAUNCH();
   return MOE_OK;
 }

@@ -19,14 +19,14 @@ struct SArgs {
   const bf16_t* A; long lda;
   const bf16_t* B0; const bf16_t* B1; long ldb, b_es;
   bf16_t* C0; bf16_t* C1; bf16_t* C2;     // UP: h1, h3 (both or neither), a; DOWN: o in C0
-  float* F;                               // RL
+  float* F;                               // RL, RW
   long ldc;
-  const int32_t* off;                     // NULL (RL): one expert of `rows` rows
+  const int32_t* off;                     // UP, DOWN
   int rows, e_cnt, N, K;
-  long xstep;                             // elements from a row's piece to its next piece
+  long xstep;                             // RW: elements from a row's piece to its next piece
   int n_experts;                          // RW: rows are (plane, expert), expert fastest
   int cached;                             // UP, DOWN: most row tiles whose weights are read through the Infinity Cache (cached_tiles)
-  int range;                              // RL, RW: pieces of the contraction per range (grid z); range z's sums go to F + z * rows * N
+  int range;                              // RL, RW: units or pieces of the contraction per range (grid z); range z's sums go to F + z * rows * N
                                           // narrow_router: rows per block; UP, DOWN: most tiles that are halved
 };
 

@@ -605,6 +605,28 @@ def test_logits_of_few_experts(E, d, bound):
     assert torch.equal(logits(torch.cat([x[100:], x])), torch.cat([whole[100:], whole]))
 
 
+# logits of 64 experts and more: blocks of 16, 32 and 64 tokens by 64 and 128 experts, the contraction whole and cut; one unit of 64, fewer
+# units than wavefronts, units that are no multiple of them.  The longest chains of matrix instructions are off by 1.8e-7 of the logits' norm
+# (d = 7168; 4.2e-8 to 1.2e-7 at these d), and no batch may be further off
+@pytest.mark.parametrize("d,E", [(64, 64), (192, 72), (832, 128), (2880, 128), (640, 136), (4096, 192), (2112, 520)])
+def test_logits_of_many_experts(d, E):
+    print(f"case many-experts-{E}-{d}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(E + d)
+    x = torch.randn((9001, d), generator=g, device="cuda", dtype=torch.bfloat16)
+    wr = torch.randn((d, E), generator=g, device="cuda", dtype=torch.bfloat16).mul_(d ** -0.5)
+    ref = x.double() @ wr.double()
+    whole = None
+    for T in (9001, 1, 15, 33, 300, 1500, 2700, 4000, 7000):
+        out = torch.full((T + 64, E), float("nan"), device="cuda")
+        ws = torch.empty(B.moe_workspace_bytes(B.WS_ROUTER, B.MOE_BF16, T, 1, d, 0, E, 0), dtype=torch.uint8, device="cuda")
+        B.moe_router_fwd(x[:T], wr, out[:T], ws)
+        assert out[T:].isnan().all()
+        assert float((out[:T].double() - ref[:T]).norm() / ref[:T].norm()) < 1.8e-7
+        whole = out if whole is None else whole
+        if E % 64:                                 # a token's logits do not depend on the batch
+            assert torch.equal(out[:T], whole[:T])
+
+
 # a plan that does not fit its buffers, with the kernels for few rows: the rows that fit are those of the whole plan
 def test_few_rows_with_more_rows_than_the_capacity():
     wl = W.QWEN.scaled(name="few-rows-overflow", T=40, d=128, f=192, E=8, e_cnt=8, k=4)
