@@ -540,7 +540,7 @@ int launch_router_fwd(const void* x, const void* wr, int dtype, int T, int d, in
     int splits = 1;
     // The streaming kernel reads the weights once per 64 tokens.  Up to a block of 64 tokens by 128 experts per CU it is the
     // faster one (whole calls, streaming / big tiles, us: T = 16384, d = 4096, E = 128 32 / 52; 8192, 4096, 256 31 / 56; 16384,
-    // 2048, 64 18 / 34); beyond that it depends (32768, 4096, 128 75 / 89; 12000, 4096, 256 57 / 62; 32768, 7168, 256 271 / 161).
+    // 2048, 64 18 / 34; since then 14 to 22 % off the streaming side, one after the other 44 -> 37, 36 -> 29, 21 -> 18); beyond that it depends (32768, 4096, 128 75 / 89; 12000, 4096, 256 57 / 62; 32768, 7168, 256 271 / 161).
     const bool stream = !mfma_shape(dtype, T, d, E) || (long long)tiles(T, 64) * tiles(E, 128) <= device_cu_count();
     int rc;
     if (stream) {
