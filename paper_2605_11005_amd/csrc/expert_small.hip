@@ -15,13 +15,11 @@
 // cost one instruction per 16 columns and 32 k.
 //   * UP, DOWN: four wavefronts that share the loads and multiply 32 columns each, every output one chain of sums over
 //     ascending k (expert_tile);
-//   * RL: eight wavefronts that share the contraction, wavefront w the units of 64 k w, w + 8, .., one or two of them in flight; the
-//     eight partial results are added in LDS in ascending order (router_logits);
-//   * RW: the same with 32-deep pieces, two to four of them in flight (router_tile);
+//   * RL, RW: eight wavefronts that share the contraction, wavefront w the 32-deep pieces w, w + 8, .., two to four of them in flight; the
+//     eight partial results are added in LDS in ascending order (router_logits, router_tile);
 //   * RL with 8 to 56 experts: eight wavefronts with an eighth of the contraction each, eight sums per output (narrow_router).
 #include "few_rows.h"
 #include "kernels.h"
-#include <utility>
 
 namespace {
 
@@ -111,17 +109,18 @@ __device__ __forceinline__ void router_tile(const SArgs& p, float* red, int row0
   }
 }
 
-// RL: 16 * TG tokens against 16 * CL experts.  Wavefront w multiplies the units of 64 k w, w + NW, .., and the partial results are
-// added in LDS in ascending order of the wavefronts: neither TG nor CL changes a bit.  PAIRS, where the contraction may also be cut (E % 64
-// == 0, 16 by 64): the products of a unit's halves start from zero and are added as ordinary fp32 sums, since a chain of matrix instructions
-// does not round to nearest.  Relative error, 128 experts per block and three ranges or more / chains / pairs: T = 300, d = 7168, E = 512
-// 11.4e-8 / 18.0e-8 / 10.0e-8; T = 128, 4096, 128 9.0e-8 / 9.4e-8 / 8.8e-8.
+// RL: 16 * TG tokens against 16 * CL experts.  Wavefront w multiplies the pieces w, w + NW, .. of 32 k in one chain, and the partial
+// results are added in LDS in ascending order of the wavefronts, so that neither TG nor CL changes a bit.  (Relative error of the logits,
+// T, d, E: 2047, 2880, 128 11.8e-8; 1000, 7168, 256 18.0e-8; 300, 7168, 512 in three ranges 11.4e-8.)
 // What bounds it is how a CU fetches x and the weights, at 60 to 85 GB/s.  Operands of x loaded where the instruction wants them, 16
-// tokens by 64 bytes, touch a line with every lane of 16 and ask memory for half lines; so a load takes whole lines, 128 bytes of
-// eight tokens, and the wavefront's own LDS turns them round.  And nothing is asked for past the end: eight pieces of void loads
-// were 1.5 us.  Calls one after the other, us, operands loaded directly, pieces of 32 k, 128 experts per block / this:
-//   T = 2047, d = 2880, E = 128 12.9 / 8.7    4096, 2048, 64 9.6 / 7.2      9001, 2880, 128 29.2 / 23.6    16384, 2048, 128 24.0 / 21.6
-//   T = 128, d = 4096, E = 128 10.4 / 7.3     4096, 7168, 256 44.5 / 32.5   8192, 4096, 64 25.8 / 21.6     1200, 4096, 192 16.5 / 11.1
+// tokens by 64 bytes, touch a line with every lane of 16 and ask memory for half lines, so LDS turns them round:
+//   * 16 tokens: four lanes load a token's 64 bytes, and a wavefront hands them over to itself;
+//   * 32 and 64 tokens: wavefronts 2r and 2r + 1, whose pieces are the halves of the same 128 bytes, load whole lines of half of the tokens
+//     each, for a barrier per piece (24.7 us for 26.4 without, T = 9001, d = 2880, E = 128; with 16 tokens 7.5 for 7.2, T = 4, 4096, 128).
+// And nothing is asked for past the end: eight pieces of void loads were 1.5 us.  Calls in a captured graph, us, operands loaded
+// directly by blocks of 128 experts / this:
+//   T = 2047, d = 2880, E = 128 17.9 / 11.0    4096, 2048, 64 11.6 / 9.1    9001, 2880, 128 30.0 / 24.7     16384, 2048, 128 24.5 / 21.8
+//   T = 128, d = 4096, E = 128 10.4 / 7.6      4, 4096, 128 8.9 / 6.3       4096, 7168, 256 43.8 / 37.2     8192, 4096, 64 25.6 / 19.9
 template <int CL>
 struct RouterPiece {                      // 32 k of the weights: a lane holds CL columns of eight rows
   typedef unsigned int vec __attribute__((ext_vector_type(CL / 2)));
@@ -142,18 +141,21 @@ struct RouterPiece {                      // 32 k of the weights: a lane holds C
   }
 };
 
-template <int TG, int CL, bool PAIRS>
+template <int TG, int CL>
 __global__ __launch_bounds__(NW_ROUTER * WAVE) void router_logits(SArgs p) {
   constexpr int NW = NW_ROUTER, WIDTH = 16 * CL, PITCH = WIDTH + 4;
-  constexpr int DEPTH = TG >= 2 && CL == 8 ? 1 : 2;                  // units in flight: what the registers hold
-  constexpr int UNIT = 128 * TG;                                // 16-byte places of a wavefront's unit of x
-  constexpr int SUM_PLACES = NW * 16 * PITCH / 4;
-  __shared__ u32x4 lds[NW * UNIT > SUM_PLACES ? NW * UNIT : SUM_PLACES];
+  constexpr bool SHARED = TG > 1;                               // two wavefronts load lines of x together
+  // pieces in flight: more gain nothing (16 by 64: two 6.3 us, four 7.1, T = 4, d = 4096, E = 128; 32 by 128: two 24.0, three 25.1, T = 5000)
+  constexpr int DEPTH = TG == 1 ? (CL == 8 ? 4 : 2) : (CL == 8 ? 2 : (TG == 2 ? 4 : 3));
+  constexpr int BUFFER = NW * 64 * TG;                          // 16-byte places of a piece of all wavefronts
+  constexpr int X_PLACES = SHARED ? 2 * BUFFER : BUFFER, SUM_PLACES = NW * 16 * PITCH / 4;
+  __shared__ u32x4 lds[X_PLACES > SUM_PLACES ? X_PLACES : SUM_PLACES];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int i = lane & 15, g = lane >> 4;
+  const int i = lane & 15, g = lane >> 4, odd = wave & 1;
   const int row0 = blockIdx.x * 16 * TG, rows = min(p.rows - row0, 16 * TG), n0 = blockIdx.y * WIDTH;
-  const int first = blockIdx.z * p.range, units = min(p.range, p.K / 64 - first);
-  const int n = (units - wave + NW - 1) / NW;                   // units of this wavefront
+  const int first = blockIdx.z * p.range, pieces = min(p.range, p.K / KP - first);
+  const int n = (pieces - wave + NW - 1) / NW;                  // pieces of this wavefront
+  const int steps = SHARED ? (pieces + NW - 1) / NW : n;        // SHARED: the same in all of them
   f32x4 acc[TG][CL];
 #pragma unroll
   for (int t = 0; t < TG; ++t)
@@ -163,82 +165,63 @@ __global__ __launch_bounds__(NW_ROUTER * WAVE) void router_logits(SArgs p) {
     const bf16_t* const b0 = p.B0 + n0;
     const bf16_t* const xrow = p.A + (size_t)row0 * p.lda;
     const int woff = 2 * (8 * g * (int)p.ldb + min(CL * i, p.N - n0 - CL));       // columns past the end repeat the last ones
-    const int xoff = 2 * ((lane >> 3) * (int)p.lda + 8 * (lane & 7));
-    RouterPiece<CL> w[DEPTH][2];
-    u32x4 x[DEPTH][2 * TG];
-    auto load_x = [&](auto slot, int idx) {       // rows past the end are zeros: the descriptor ends there
-      const bool in = idx < n;
-      const int k = in ? 64 * (first + wave + NW * idx) : 0;
+    const int xoff = SHARED ? 2 * ((8 * odd + (lane >> 3)) * (int)p.lda + 8 * (lane & 7)) : 2 * ((lane >> 2) * (int)p.lda + 8 * (lane & 3));
+    RouterPiece<CL> w[DEPTH];
+    u32x4 x[DEPTH][TG];
+    // Rows past the end are zeros: the descriptor ends there.  (SHARED: behind an odd number of pieces a line's second half is what
+    // follows in memory, which its wavefront does not multiply.)
+    auto load_x = [&](auto slot, int idx) {
+      const int piece = NW * idx + (SHARED ? wave - odd : wave);
+      const bool in = piece < pieces;
+      const int k = in ? KP * (first + piece) : 0;
       uint64_t base = (uint64_t)(xrow + k);
-      int bytes = in ? 2 * (rows * (int)p.lda - k) : 0, eight = 16 * (int)p.lda;
-      asm("" : "+s"(base), "+s"(bytes), "+s"(eight));           // (the offsets are formed again each time: no registers are kept for them)
+      int bytes = in ? 2 * (rows * (int)p.lda - k) : 0, sixteen = 32 * (int)p.lda;
+      asm("" : "+s"(base), "+s"(bytes), "+s"(sixteen));         // (the offsets are formed again each time: no registers are kept for them)
       const __amdgpu_buffer_rsrc_t d = __builtin_amdgcn_make_buffer_rsrc((void*)base, 0, bytes, 0x00027000);
 #pragma unroll
-      for (int q = 0; q < 2 * TG; ++q) x[decltype(slot)::value][q] = __builtin_amdgcn_raw_buffer_load_b128(d, xoff + q * eight, 0, 0);
+      for (int t = 0; t < TG; ++t) x[decltype(slot)::value][t] = __builtin_amdgcn_raw_buffer_load_b128(d, xoff + t * sixteen, 0, 0);
       __builtin_amdgcn_sched_barrier(0);  // loads stay in order: waiting for one must not wait for the next
     };
-    auto load_w = [&](auto slot, auto half, int idx) {
+    auto load_w = [&](auto slot, int idx) {
       const bool in = idx < n;
-      const long k = in ? 64 * (first + wave + NW * idx) + 32 * decltype(half)::value : 0;
-      w[decltype(slot)::value][decltype(half)::value].load(b0 + k * p.ldb, in, 2 * (int)p.ldb, woff);
+      const long k = in ? KP * (first + wave + NW * idx) : 0;
+      w[decltype(slot)::value].load(b0 + k * p.ldb, in, 2 * (int)p.ldb, woff);
       __builtin_amdgcn_sched_barrier(0);
     };
-    // token r's chunk c (eight k) of a unit: the 8 chunks of a token and the same chunk of 8 tokens are on different banks
-    u32x4* const mine = lds + wave * UNIT;
-    const auto at = [](int r, int c) { return 8 * r + (c ^ (r & 7)); };
-    auto unit = [&](auto slot, int idx, auto more) {
+    // token r's chunk c (eight k): the chunks of a token and the same chunk of eight tokens are on different banks
+    const auto at = [](int r, int c) { return SHARED ? 8 * r + (c ^ (r & 7)) : 4 * r + (c ^ ((r >> 1) & 3)); };
+    auto step = [&](auto slot, int idx, auto more) {
       constexpr int S = decltype(slot)::value;
       constexpr bool MORE = decltype(more)::value;
+      u32x4* const mine = lds + (SHARED ? (idx & 1) * BUFFER + (wave >> 1) * 128 * TG : wave * 64 * TG);
 #pragma unroll
-      for (int q = 0; q < 2 * TG; ++q) mine[at(8 * q + (lane >> 3), lane & 7)] = x[S][q];
-      __builtin_amdgcn_wave_barrier();    // LDS serves a wavefront's accesses in order
+      for (int t = 0; t < TG; ++t)
+        mine[SHARED ? at(16 * t + 8 * odd + (lane >> 3), lane & 7) : at(16 * t + (lane >> 2), lane & 3)] = x[S][t];
       if constexpr (MORE) load_x(slot, idx + DEPTH);
-      const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
-      bf16x8 f[2][TG];
-      auto read = [&](auto half) {
-        constexpr int H = decltype(half)::value;
+      if constexpr (SHARED) __syncthreads();              // (two buffers: the next piece is written while this one is read)
+      else __builtin_amdgcn_wave_barrier();               // LDS serves a wavefront's accesses in order
+      if (!SHARED || idx < n) {
+        bf16x8 f[TG];
 #pragma unroll
-        for (int t = 0; t < TG; ++t) f[H][t] = __builtin_bit_cast(bf16x8, mine[at(16 * t + i, 4 * H + g)]);
-      };
-      if constexpr (PAIRS) {
-        read(Int<0>{});
-        read(Int<1>{});
+        for (int t = 0; t < TG; ++t) f[t] = __builtin_bit_cast(bf16x8, mine[at(16 * t + i, SHARED ? 4 * odd + g : g)]);
 #pragma unroll
         for (int j = 0; j < CL; ++j) {
-          const bf16x8 c0 = w[S][0].operand(j), c1 = w[S][1].operand(j);
+          const bf16x8 c = w[S].operand(j);
 #pragma unroll
-          for (int t = 0; t < TG; ++t)
-            acc[t][j] += __builtin_amdgcn_mfma_f32_16x16x32_bf16(c0, f[0][t], zero, 0, 0, 0) +
-                         __builtin_amdgcn_mfma_f32_16x16x32_bf16(c1, f[1][t], zero, 0, 0, 0);
+          for (int t = 0; t < TG; ++t) acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c, f[t], acc[t][j], 0, 0, 0);
         }
-        if constexpr (MORE) {
-          load_w(slot, Int<0>{}, idx + DEPTH);
-          load_w(slot, Int<1>{}, idx + DEPTH);
-        }
-      } else {
-        static_for<2>([&](auto half) {
-          constexpr int H = decltype(half)::value;
-          read(half);
-#pragma unroll
-          for (int j = 0; j < CL; ++j) {
-            const bf16x8 c = w[S][H].operand(j);
-#pragma unroll
-            for (int t = 0; t < TG; ++t) acc[t][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(c, f[H][t], acc[t][j], 0, 0, 0);
-          }
-          if constexpr (MORE) load_w(slot, half, idx + DEPTH);
-        });
       }
-      __builtin_amdgcn_wave_barrier();
+      if constexpr (MORE) load_w(slot, idx + DEPTH);
+      if constexpr (!SHARED) __builtin_amdgcn_wave_barrier();
     };
     static_for<DEPTH>([&](auto s) {
       load_x(s, decltype(s)::value);
-      load_w(s, Int<0>{}, decltype(s)::value);
-      load_w(s, Int<1>{}, decltype(s)::value);
+      load_w(s, decltype(s)::value);
     });
     int idx = 0;
-    for (; idx + DEPTH < n; idx += DEPTH) static_for<DEPTH>([&](auto s) { unit(s, idx + decltype(s)::value, Int<1>{}); });
+    for (; idx + DEPTH < steps; idx += DEPTH) static_for<DEPTH>([&](auto s) { step(s, idx + decltype(s)::value, Int<1>{}); });
     static_for<DEPTH>([&](auto s) {       // the last ones are on their way
-      if (idx + decltype(s)::value < n) unit(s, idx + decltype(s)::value, Int<0>{});
+      if (idx + decltype(s)::value < steps) step(s, idx + decltype(s)::value, Int<0>{});
     });
   }
   // Element r of acc[t][j] belongs to token 16t + i and lane group 4g + r of the loads: column CL * (4g + r) + j.
@@ -487,39 +470,46 @@ int launch_router_fwd_small(const void* x, const void* wr, int T, int d, int E, 
   p.A = (const bf16_t*)x; p.lda = d;
   p.B0 = (const bf16_t*)wr; p.ldb = E;
   p.rows = T; p.N = E; p.K = d;
-  // Tokens (16 tg) and experts (16 cl) of a block: the fewest bytes per block that make at most one block per CU; a second round
-  // of blocks nearly doubles the time.  16 x 64 / 16 x 128 / 32 x 64 / 32 x 128 / 64 x 64 / 64 x 128, us:
-  //   T = 2047, d = 2880, E = 128 11.0 / 12.2 / 12.0 / -    / - / -           3500, 2048, 72  14.2 / 9.7 / 10.8 / 10.6 / 12.6 / 13.6
-  //   T = 8000, d = 2880, E = 128 37 / 30 / 27 / 20.4 / 22.1 / 25.1           9001, 2880, 128 44 / 40 / 35 / 33 / 34 / 25.6
-  //   T = 8192, d = 4096, E = 64  29 / 30 / 23.6 / 24.2 / 26.2 / 27.4         16384, 2048, 64 31 / 33 / 24 / 25 / 20.4 / 21.2
-  const int cus = device_cu_count(), units = d / 64;
-  int tg, cl, cols, row_blocks;
-  for (const auto& shape : {std::pair<int, int>{1, 4}, {1, 8}, {2, 4}, {2, 8}, {4, 4}, {4, 8}}) {
-    tg = shape.first, cl = shape.second;
-    cols = (E + 16 * cl - 1) / (16 * cl), row_blocks = (T + 16 * tg - 1) / (16 * tg);
-    if ((long long)row_blocks * cols <= cus) break;
-  }
-  // Where that leaves CUs idle the contraction is cut, at 12 units or more per range.  The launch that adds the ranges up costs what
-  // some 28 units do.  Whole / 2 / 4 / 8 ranges, us:
-  //   d = 2048, E = 64, T = 1024 6.2 / 6.9 / 7.8 / 12    d = 2880, E = 128, T = 256 8.1 / 8.2 / 7.3 / 8.7
-  //   d = 4096, E = 128, T = 4 9.7 / 8.2 / 7.0 / 7.4     T = 300 10.1 / 8.6 / 7.5 / 11     d = 7168, E = 256, T = 8 16 / 12 / 8.5 / 7.8
-  int n = cus / (cols * row_blocks);
+  const int cus = device_cu_count(), pieces = d / KP;
+  // A handful of blocks cannot draw the weights fast enough, so the contraction is cut, at two pieces or more per wavefront; the second
+  // launch, which adds the ranges up, pays from three ranges on.  Where it is cut decides the bits, so it follows from blocks of 128
+  // experts, by as few tokens as make at most one block per CU, whatever the blocks are.
+  const int cut_cols = (E + COLS - 1) / COLS;
+  const int cut_rows = (long long)(T + 15) / 16 * cut_cols <= cus ? 16 : ((long long)(T + 31) / 32 * cut_cols <= cus ? 32 : 64);
+  int n = cus / (cut_cols * ((T + cut_rows - 1) / cut_rows));
   if (n > max_ranges) n = max_ranges;
-  if (n > units / 12) n = units / 12;
-  if (n < 2 || units - units / n < 28) n = 1;
-  p.range = (units + n - 1) / n;
-  n = (units + p.range - 1) / p.range;
+  if (n > pieces / (2 * NW_ROUTER)) n = pieces / (2 * NW_ROUTER);
+  if (n < 3) n = 1;
+  p.range = (pieces + n - 1) / n;
+  n = (pieces + p.range - 1) / p.range;
   p.F = n > 1 ? partials : logits;
   *ranges = n;
+  // Tokens (16 tg) and experts (16 cl) of a block: the first of the list with at most one block per CU; a second round of blocks nearly
+  // doubles the time.  32 by 64 comes before 16 by 128 where the experts fill blocks of 128: it asks for a third less per block; where
+  // they do not, the half empty blocks of 128 ask for less.
+  // 16 x 64 / 32 x 64 / 16 x 128 / 64 x 64 / 32 x 128 / 64 x 128, us:
+  //   E = 128   T = 2047, d = 2880 11.0 / 13.4 / 15.5 / 17.4 / 17.6 / -    3000, 2048 13.1 / 11.0 / 11.6 / 14.1 / 13.2 / -
+  //             T = 4096, d = 4096 23 / 17.1 / 19.8 / 22.4 / 22.2 / -      5000, 4096 - / 31 / - / 25.1 / 24.1 / 29.5
+  //             T = 8000, d = 2880 - / 26 / - / 20.7 / 19.8 / 24.2         9001, 2880 - / 35 / - / 33 / 35 / 24.6
+  //   E = 192   T = 1500, d = 4096 21.7 / 17.5 / 16.2 / 22.5 / 18.3 / -    3000, 2048 16.7 / 18.0 / 15.4 / 14.7 / 11.7 / -
+  //   E = 72    T = 3500, d = 2048 13.8 / 11.3 / 9.8 / 14.7 / 11.4 / -     7000, 2048 - / 19.6 / - / 17.2 / 12.3 / 16.1
+  //   E = 64    T = 8192, d = 4096 - / 19.9 / - / 26.1 / 20.3 / 26.5       16384, 2048 - / 23.0 / - / 19.1 / 23.6 / 19.8
+  static constexpr struct { int tg, cl; bool full; } shapes[] = {{1, 4, false}, {2, 4, true}, {1, 8, false}, {2, 4, false}, {2, 8, false}, {4, 4, false}, {4, 8, false}};
+  int tg = 0, cl = 0, cols = 0, row_blocks = 0;
+  for (const auto& b : shapes) {
+    if (b.full && E % COLS) continue;
+    tg = b.tg, cl = b.cl;
+    cols = (E + 16 * cl - 1) / (16 * cl), row_blocks = (T + 16 * tg - 1) / (16 * tg);
+    if ((long long)row_blocks * cols * n <= cus) break;
+  }
   const dim3 grid(row_blocks, cols, n), block(NW_ROUTER * WAVE);
   ProfScope prof(MOE_K_ROUTER_FWD, s);
-  if (tg == 1 && cl == 4 && E % 64 == 0) hipLaunchKernelGGL((router_logits<1, 4, true>), grid, block, 0, s, p);
-  else if (tg == 1 && cl == 4) hipLaunchKernelGGL((router_logits<1, 4, false>), grid, block, 0, s, p);
-  else if (tg == 1) hipLaunchKernelGGL((router_logits<1, 8, false>), grid, block, 0, s, p);
-  else if (tg == 2 && cl == 4) hipLaunchKernelGGL((router_logits<2, 4, false>), grid, block, 0, s, p);
-  else if (tg == 2) hipLaunchKernelGGL((router_logits<2, 8, false>), grid, block, 0, s, p);
-  else if (cl == 4) hipLaunchKernelGGL((router_logits<4, 4, false>), grid, block, 0, s, p);
-  else hipLaunchKernelGGL((router_logits<4, 8, false>), grid, block, 0, s, p);
+  if (tg == 1 && cl == 4) hipLaunchKernelGGL((router_logits<1, 4>), grid, block, 0, s, p);
+  else if (tg == 1) hipLaunchKernelGGL((router_logits<1, 8>), grid, block, 0, s, p);
+  else if (tg == 2 && cl == 4) hipLaunchKernelGGL((router_logits<2, 4>), grid, block, 0, s, p);
+  else if (tg == 2) hipLaunchKernelGGL((router_logits<2, 8>), grid, block, 0, s, p);
+  else if (cl == 4) hipLaunchKernelGGL((router_logits<4, 4>), grid, block, 0, s, p);
+  else hipLaunchKernelGGL((router_logits<4, 8>), grid, block, 0, s, p);
   HIP_CHECK_LAUNCH();
   return MOE_OK;
 }

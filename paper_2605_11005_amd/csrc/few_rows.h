@@ -26,7 +26,7 @@ struct SArgs {
   long xstep;                             // RW: elements from a row's piece to its next piece
   int n_experts;                          // RW: rows are (plane, expert), expert fastest
   int cached;                             // UP, DOWN: most row tiles whose weights are read through the Infinity Cache (cached_tiles)
-  int range;                              // RL, RW: units or pieces of the contraction per range (grid z); range z's sums go to F + z * rows * N
+  int range;                              // RL, RW: pieces of the contraction per range (grid z); range z's sums go to F + z * rows * N
                                           // narrow_router: rows per block; UP, DOWN: most tiles that are halved
 };
 
