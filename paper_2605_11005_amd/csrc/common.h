@@ -59,6 +59,7 @@ struct RaggedTiles {
   int e_cnt, lane;
   int n, incl;         // row tiles of expert `lane`, and of all up to it
   int total;           // row tiles of all experts
+  int active;          // experts that have rows
   __device__ __forceinline__ int scan(int e, int& rows) const {
     rows = e < e_cnt ? (off[e + 1] - off[e] + TM - 1) / TM : 0;
     return wave_scan(rows);
@@ -66,9 +67,11 @@ struct RaggedTiles {
   __device__ __forceinline__ RaggedTiles(const int32_t* __restrict__ off_, int e_cnt_, int lane_) : off(off_), e_cnt(e_cnt_), lane(lane_) {
     incl = scan(lane, n);
     total = __builtin_amdgcn_readlane(incl, WAVE - 1);
+    active = __popcll(__ballot(n > 0));
     for (int base = WAVE; base < e_cnt; base += WAVE) {
       int m;
       total += __builtin_amdgcn_readlane(scan(base + lane, m), WAVE - 1);
+      active += __popcll(__ballot(m > 0));
     }
   }
   // the tile of workgroup b; false for a surplus one

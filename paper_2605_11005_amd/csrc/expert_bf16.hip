@@ -1518,13 +1518,9 @@ __global__ __launch_bounds__(NT, 1) void gg_or_few(GArgs p, int d, int f, int ca
   if (few_rows_pay(p.off, p.e_cnt, d, f)) {
     SArgs q = {};
     q.A = p.A0; q.lda = p.lda; q.B0 = p.B0; q.B1 = p.B1; q.ldb = p.ldb; q.b_es = p.b_es;
-    q.C0 = p.C0; q.C1 = p.C1; q.C2 = p.C2; q.ldc = p.ldc; q.off = p.off; q.e_cnt = p.e_cnt; q.N = p.N; q.K = p.K;
+    q.C0 = p.C0; q.C1 = p.C1; q.C2 = p.C2; q.ldc = p.ldc; q.off = p.off; q.e_cnt = p.e_cnt; q.N = p.N; q.K = p.K; q.cached = cached;
     const RaggedTiles<ROWS> list(q.off, q.e_cnt, threadIdx.x & 63);
-    u32x4* const lds = reinterpret_cast<u32x4*>(smem);
-    if (list.total > cached)
-      for (int b = blockIdx.x; few_rows_tile<MODE == UP, NW_TILES, true>(q, list, lds, b); b += gridDim.x) {}
-    else
-      for (int b = blockIdx.x; few_rows_tile<MODE == UP, NW_TILES, false>(q, list, lds, b); b += gridDim.x) {}
+    for (int b = blockIdx.x; few_rows_tile<MODE == UP, NW_TILES>(q, list, reinterpret_cast<u32x4*>(smem), b); b += gridDim.x) {}
     return;
   }
   gg_body<MODE, true>(p);
@@ -1642,7 +1638,7 @@ int launch_gg_or_few(const GArgs& a, int d, int f, hipStream_t s) {
     attr_set[dev] = true;
   }
   ProfScope prof(MOE_K_UP + MODE, s);
-  hipLaunchKernelGGL(gg_or_few<MODE>, dim3(device_cu_count()), dim3(NT), SMEM_BYTES, s, a, d, f, cached_tiles(d, f));
+  hipLaunchKernelGGL(gg_or_few<MODE>, dim3(device_cu_count()), dim3(NT), SMEM_BYTES, s, a, d, f, cached_experts(d, f));
   HIP_CHECK_LAUNCH();
   return MOE_OK;
 }
@@ -1710,7 +1706,7 @@ int launch_expert_fwd_bf16(const void* xp, int cap, int d, int f, int e_cnt, con
   u.A0 = u.A1 = (const bf16_t*)xp; u.lda = d;
   u.B0 = (const bf16_t*)w1; u.B1 = (const bf16_t*)w3; u.ldb = f; u.b_es = (long)d * f;
   u.C0 = (bf16_t*)h1; u.C1 = (bf16_t*)h3; u.C2 = act; u.ldc = f;
-  u.stream = w.stream = cached_tiles(d, f) < e_cnt;
+  u.stream = w.stream = cached_experts(d, f) < e_cnt;
   u.off = offsets; u.sched = sched; u.e_cnt = e_cnt; u.N = f; u.K = d; u.save_h = (h1 && h3) ? 1 : 0;
   const bool decide = route == COUNTS_DECIDE;
   int rc = decide ? launch_gg_or_few<UP>(u, d, f, s) : launch_gg<UP>(u, s);

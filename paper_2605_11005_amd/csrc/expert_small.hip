@@ -386,13 +386,8 @@ __global__ __launch_bounds__(NW_TILES * WAVE) void small_rows(SArgs p) {
   __shared__ u32x4 lds[FEW_ROWS_PLACES<NW_TILES>];
   const int n_cols = (p.N + TILE_COLS<MODE> - 1) / TILE_COLS<MODE>;
   const RaggedTiles<ROWS> list(p.off, p.e_cnt, threadIdx.x & 63);
-  if (list.total * n_cols > p.range) {
-    if (list.total > p.cached) few_rows_tile<MODE == UP, NW_TILES, true>(p, list, lds, blockIdx.x);
-    else few_rows_tile<MODE == UP, NW_TILES, false>(p, list, lds, blockIdx.x);
-  } else if (threadIdx.x < NW_HALF * WAVE) {
-    if (list.total > p.cached) few_rows_tile<MODE == UP, NW_HALF, true>(p, list, lds, blockIdx.x);
-    else few_rows_tile<MODE == UP, NW_HALF, false>(p, list, lds, blockIdx.x);
-  }
+  if (list.total * n_cols > p.range) few_rows_tile<MODE == UP, NW_TILES>(p, list, lds, blockIdx.x);
+  else if (threadIdx.x < NW_HALF * WAVE) few_rows_tile<MODE == UP, NW_HALF>(p, list, lds, blockIdx.x);
 }
 
 // grid = (row blocks of 16 * TG, column blocks, ranges of the contraction)
@@ -426,7 +421,7 @@ int launch_expert_fwd_small(const void* xp, int cap, int d, int f, int e_cnt, co
   u.A = (const bf16_t*)xp; u.lda = d;
   u.B0 = (const bf16_t*)w1; u.B1 = (const bf16_t*)w3; u.ldb = f; u.b_es = (long)d * f;
   u.C0 = (bf16_t*)h1; u.C1 = (bf16_t*)h3; u.C2 = (bf16_t*)a; u.ldc = f;
-  u.off = offsets; u.e_cnt = e_cnt; u.N = f; u.K = d; u.cached = cached_tiles(d, f);
+  u.off = offsets; u.e_cnt = e_cnt; u.N = f; u.K = d; u.cached = cached_experts(d, f);
   int rc = launch_small<UP>(u, cap, MOE_K_UP, s);
   if (rc) return rc;
   SArgs w = {};

@@ -2,6 +2,7 @@
 // expert_bf16.hip.
 #pragma once
 #include "common.h"
+#include "stream_rule.h"
 
 namespace {
 
@@ -25,20 +26,10 @@ struct SArgs {
   int rows, e_cnt, N, K;
   long xstep;                             // RW: elements from a row's piece to its next piece
   int n_experts;                          // RW: rows are (plane, expert), expert fastest
-  int cached;                             // UP, DOWN: most row tiles whose weights are read through the Infinity Cache (cached_tiles)
+  int cached;                             // UP, DOWN: cached_experts
   int range;                              // RL, RW: pieces of the contraction per range (grid z); range z's sums go to F + z * rows * N
                                           // narrow_router: rows per block; UP, DOWN: most tiles that are halved
 };
-
-// Weights that a call reads once and that do not stay in the Infinity Cache (256 MB) until the next call are loaded nontemporally:
-// such loads leave the cache alone, and memory then delivers up to 13 % more (strips of 128 bytes of 1.9 GB: 6.3 -> 7.1 TB/s).  While
-// the active experts' weights fit, a call made again finds them there.  Up and down projection, us, loads as usual / nontemporal:
-//   2.8 GB of weights   7168, 2048, 32 experts of one row   326 + 167 / 291 + 153     of 128 rows by 1/r  329 + 169 / 300 + 155
-//   604 MB              4096, 1536, 16 of 16 rows           88 + 42 / 79 + 39         four of them, 151 MB, again  29 + 14 / 39 + 16
-//   796 MB              2880, 2880, 16 of 16 rows           97 + 57 / 84 + 52
-// The line is at what fits: at 302 MB (8 experts of the second shape) it is 46 + 22 / 44 + 21, and at 138 MB that have not been read just
-// before 22 + 16 / 21 + 15.  In row tiles, which count an expert once per 64 rows:
-inline int cached_tiles(int d, int f) { return (int)((256ll << 20) / (6ll * d * f)); }
 
 // Loads go through a buffer descriptor: a wave-uniform base and a 32-bit byte offset per lane (64-bit addresses per lane limit
 // a CU's address path, see lds_load16 in common.h).  A descriptor of length
@@ -219,19 +210,24 @@ __device__ __forceinline__ void expert_tile(const SArgs& p, u32x4* lds, int e, i
   }
 }
 
-
 // Tile b of a launch over all experts; false: the list is shorter.
 template <int NW> constexpr int FEW_ROWS_PLACES = 2 * (WEIGHT_PLACES<NW> + ROW_PLACES);      // LDS, 16 bytes each
 template <bool DUAL, int NW, bool STREAM>
+__device__ __forceinline__ void sized_tile(const SArgs& p, u32x4* lds, int e, int row0, int row_end, int n0, int tid) {
+  const int rows = row_end - row0;
+  if (rows <= 16) expert_tile<DUAL, 1, NW, STREAM>(p, lds, e, row0, row_end, n0, tid);
+  else if (rows <= 32) expert_tile<DUAL, 2, NW, STREAM>(p, lds, e, row0, row_end, n0, tid);
+  else expert_tile<DUAL, 4, NW, STREAM>(p, lds, e, row0, row_end, n0, tid);
+}
+template <bool DUAL, int NW>
 __device__ __forceinline__ bool few_rows_tile(const SArgs& p, const RaggedTiles<ROWS>& list, u32x4* lds, int b) {
   constexpr int WIDTH = (DUAL ? 16 : 32) * NW;
   const int tid = threadIdx.x;
   int e, mt, nt;
   if (!list.tile((p.N + WIDTH - 1) / WIDTH, b, e, mt, nt)) return false;
-  const int row0 = p.off[e] + mt * ROWS, row_end = min(p.off[e + 1], row0 + ROWS), rows = row_end - row0;
-  if (rows <= 16) expert_tile<DUAL, 1, NW, STREAM>(p, lds, e, row0, row_end, nt * WIDTH, tid);
-  else if (rows <= 32) expert_tile<DUAL, 2, NW, STREAM>(p, lds, e, row0, row_end, nt * WIDTH, tid);
-  else expert_tile<DUAL, 4, NW, STREAM>(p, lds, e, row0, row_end, nt * WIDTH, tid);
+  const int first = p.off[e], end = p.off[e + 1], row0 = first + mt * ROWS, row_end = min(end, row0 + ROWS);
+  if (stream_weights(list.active, p.cached, end - first, ROWS)) sized_tile<DUAL, NW, true>(p, lds, e, row0, row_end, nt * WIDTH, tid);
+  else sized_tile<DUAL, NW, false>(p, lds, e, row0, row_end, nt * WIDTH, tid);
   return true;
 }
 
