@@ -110,7 +110,7 @@ struct GArgs {
   int accumulate;
   int save_h;
   int pair_first;                         // another GEMM follows in this launch and fills the last round
-  int stream;                             // UP, DOWN: the experts' weights do not fit the Infinity Cache
+  int cached;                             // UP, DOWN: cached_experts
 };
 
 template <int MODE> struct Traits {
@@ -952,13 +952,16 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
   int e = 0, lo = 0, hi = 0, n0 = 0;
   int piece = -1;         // ragged-K modes: index of the fp32 partial tile to write, or -1
   int krange = 0;         // RL: which range of a cut contraction
-  // Weights that one tile reads, of a layer whose weights do not fit the Infinity Cache, are loaded nontemporally, as in few_rows.h:
+  // Weights that one tile reads, of a layer whose active experts' weights do not fit the Infinity Cache, are loaded nontemporally (stream_rule.h):
   // decode of 128 tokens at the DSv3-like share 301 -> 280 us, prefill of 2047 at the GPT-OSS-like share 242 -> 237, training step of
   // 1936 tokens at the former 1616 -> 1586.  (Of layers that fit, the backward finds them: Qwen-like share 821 against 829.  In every
   // tile, which drops panels that tiles share, steps take 1 to 3 % longer; in dA and dX, whose weights are read 64 bytes of a row at a
   // time, up to 7 % even in tiles that share nothing.)  A loop of its own: a branch at every load costs 2 %.
   constexpr bool ONCE = MODE == UP || MODE == DOWN;
   bool once = false;      // no other tile reads this one's weights
+  int active = 0;         // experts that have rows, of a layer that does not fit as a whole
+  if (ONCE && e_cnt > p.cached)
+    for (int base = 0; base < e_cnt; base += WAVE) active += __popcll(__ballot(rows_at(base + lane) > 0));
   int nk0 = 0, nk = 0;    // k-tiles in segment 0 / in total
   int row0 = 0;           // first output row (global row for ragged-M, i for the weight gradients)
   int row_end = 0;        // one past the last valid output row
@@ -1015,9 +1018,9 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
     // Within an expert, tiles are ordered in bands of 8 m-tiles, n-tile next, m-tile inside the
     // band fastest: 32 consecutive tiles (one chunk) then form an 8 x 4 block that shares 8 A
     // panels and 4 B panels through one XCD's L2.
-    int mt, nt, mte;
+    int mt, nt;
     {
-      int li;
+      int li, mte;
       const int a = find_position(tile_start, e_cnt, L, pos_hint);
       pos_hint = a;
       li = __builtin_amdgcn_readfirstlane(L - tile_start[a]);
@@ -1051,7 +1054,7 @@ __device__ __forceinline__ void gg_body(const GArgs& p) {
       krange = nt / n_tiles_cols;
       nt -= krange * n_tiles_cols;
     }
-    if (ONCE) once = p.stream && mte == 1;
+    if (ONCE) once = stream_weights(active, p.cached, hi - lo, BM);
     n0 = nt * TR::BN_EFF;
     if (TR::RAGGED_K) {
       row0 = mt * BM;
@@ -1514,11 +1517,11 @@ __device__ __forceinline__ bool few_rows_pay(const int32_t* __restrict__ off, in
 
 // Forward GEMM of a call whose capacity leaves open which kernel pays: the row counts decide, in every block alike.
 template <int MODE>
-__global__ __launch_bounds__(NT, 1) void gg_or_few(GArgs p, int d, int f, int cached) {
+__global__ __launch_bounds__(NT, 1) void gg_or_few(GArgs p, int d, int f) {
   if (few_rows_pay(p.off, p.e_cnt, d, f)) {
     SArgs q = {};
     q.A = p.A0; q.lda = p.lda; q.B0 = p.B0; q.B1 = p.B1; q.ldb = p.ldb; q.b_es = p.b_es;
-    q.C0 = p.C0; q.C1 = p.C1; q.C2 = p.C2; q.ldc = p.ldc; q.off = p.off; q.e_cnt = p.e_cnt; q.N = p.N; q.K = p.K; q.cached = cached;
+    q.C0 = p.C0; q.C1 = p.C1; q.C2 = p.C2; q.ldc = p.ldc; q.off = p.off; q.e_cnt = p.e_cnt; q.N = p.N; q.K = p.K; q.cached = p.cached;
     const RaggedTiles<ROWS> list(q.off, q.e_cnt, threadIdx.x & 63);
     for (int b = blockIdx.x; few_rows_tile<MODE == UP, NW_TILES>(q, list, reinterpret_cast<u32x4*>(smem), b); b += gridDim.x) {}
     return;
@@ -1638,7 +1641,7 @@ int launch_gg_or_few(const GArgs& a, int d, int f, hipStream_t s) {
     attr_set[dev] = true;
   }
   ProfScope prof(MOE_K_UP + MODE, s);
-  hipLaunchKernelGGL(gg_or_few<MODE>, dim3(device_cu_count()), dim3(NT), SMEM_BYTES, s, a, d, f, cached_experts(d, f));
+  hipLaunchKernelGGL(gg_or_few<MODE>, dim3(device_cu_count()), dim3(NT), SMEM_BYTES, s, a, d, f);
   HIP_CHECK_LAUNCH();
   return MOE_OK;
 }
@@ -1706,7 +1709,7 @@ int launch_expert_fwd_bf16(const void* xp, int cap, int d, int f, int e_cnt, con
   u.A0 = u.A1 = (const bf16_t*)xp; u.lda = d;
   u.B0 = (const bf16_t*)w1; u.B1 = (const bf16_t*)w3; u.ldb = f; u.b_es = (long)d * f;
   u.C0 = (bf16_t*)h1; u.C1 = (bf16_t*)h3; u.C2 = act; u.ldc = f;
-  u.stream = w.stream = cached_experts(d, f) < e_cnt;
+  u.cached = w.cached = cached_experts(d, f);
   u.off = offsets; u.sched = sched; u.e_cnt = e_cnt; u.N = f; u.K = d; u.save_h = (h1 && h3) ? 1 : 0;
   const bool decide = route == COUNTS_DECIDE;
   int rc = decide ? launch_gg_or_few<UP>(u, d, f, s) : launch_gg<UP>(u, s);
