@@ -5,8 +5,9 @@ the sizes and torch's current HIP stream to the C entry point of the same name. 
 no fallback: if libmoe_mi355x.so is missing or a call returns an error code, MoeError is
 raised.
 
-A call whose arguments are all as they should be is checked and made by csrc/marshal.cpp
-(_marshal.so), which costs the host a fifth of the time; any other is left to the checks here.
+A call whose arguments are all as they should be is checked and made by csrc/marshal.cpp, which
+costs the host a fifth of the time; any other is left to the checks here, and all are where that
+extension was not built for this Python and torch.
 """
 from __future__ import annotations
 
@@ -14,6 +15,8 @@ import ctypes
 import importlib.machinery
 import importlib.util
 import os
+import sys
+import warnings
 
 MOE_F32, MOE_BF16 = 0, 1
 GATE_SOFTMAX_RENORM, GATE_SIGMOID_RENORM, GATE_SOFTMAX = 0, 1, 2
@@ -86,18 +89,31 @@ def load_library():
     return lib
 
 
+def marshal_path() -> str:
+    import torch
+    return os.path.join(_HERE, f"_marshal.{sys.implementation.cache_tag}.torch-{torch.__version__}.so")
+
+
+class _ChecksHere:
+    """In the native marshalling's place where it cannot be loaded: takes no call."""
+
+    def __getattr__(self, name):
+        return lambda *args: -1
+
+
 def _marshal():
     """The native marshalling, bound to the library's entry points."""
     global _MARSHAL
     if _MARSHAL is None:
-        import torch  # noqa: F401  (its libraries come first)
-        lib, path = load_library(), os.path.join(_HERE, "_marshal.so")
-        if not os.path.exists(path):
-            raise MoeError(f"{path} not found: build it first (python -c 'import __graft_entry__ as g; g.build()')")
-        loader = importlib.machinery.ExtensionFileLoader("_marshal", path)
-        module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_marshal", path, loader=loader))
-        loader.exec_module(module)
-        module.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _MARSHALLED))
+        path, lib = marshal_path(), load_library()      # (torch's libraries come first)
+        try:
+            loader = importlib.machinery.ExtensionFileLoader("_marshal", path)
+            module = importlib.util.module_from_spec(importlib.util.spec_from_file_location("_marshal", path, loader=loader))
+            loader.exec_module(module)
+            module.bind(*(ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _MARSHALLED))
+        except ImportError as e:
+            warnings.warn(f"calls take the host longer without their native marshalling, which __graft_entry__.build() builds: {e}", RuntimeWarning)
+            module = _ChecksHere()
         _MARSHAL = module
     return _MARSHAL
 
