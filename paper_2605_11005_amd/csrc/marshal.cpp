@@ -11,6 +11,8 @@
 
 #include <cstring>
 #include <initializer_list>
+#include <optional>
+#include <utility>
 
 #include "../../include/moe.h"
 
@@ -104,21 +106,24 @@ moe_stream_t stream() { return (moe_stream_t)c10::hip::getCurrentHIPStream().str
 constexpr auto F32 = at::kFloat;
 constexpr auto I32 = at::kInt;
 
-// f(args) marshals and returns the call to make; the interpreter's lock is not held while it enqueues.
+// f(args) marshals and returns the call to make; the interpreter's lock is not held while it enqueues.  Only marshalling may end in "not
+// taken": the call itself is made once, and what it might throw leaves as it would leave ctypes.
 template <typename F>
 PyObject* take(PyObject* const* v, Py_ssize_t n, F f) {
-  int rc = NOT_TAKEN;
+  std::optional<decltype(f(std::declval<Args&>()))> call;
   try {
     Args a{v, n};
-    auto call = f(a);
+    auto made = f(a);
     if (a.at != n) refuse();
-    Py_BEGIN_ALLOW_THREADS
-    rc = call();
-    Py_END_ALLOW_THREADS
+    call.emplace(std::move(made));
   } catch (...) {
     PyErr_Clear();
-    rc = NOT_TAKEN;
+    return PyLong_FromLong(NOT_TAKEN);
   }
+  int rc;
+  Py_BEGIN_ALLOW_THREADS
+  rc = (*call)();
+  Py_END_ALLOW_THREADS
   return PyLong_FromLong(rc);
 }
 
