@@ -6,8 +6,8 @@ no fallback: if libmoe_mi355x.so is missing or a call returns an error code, Moe
 raised.
 
 A call whose arguments are all as they should be is checked and made by csrc/marshal.cpp, which
-costs the host a fifth of the time; any other is left to the checks here, and all are where that
-extension was not built for this Python and torch.
+takes the host less than half of the time (figures there); any other is left to the checks
+here, and all are where that extension was not built for this Python and torch.
 """
 from __future__ import annotations
 

@@ -48,11 +48,13 @@ constexpr int HALF = TK / 4;      // steps whose fragments are held at a time: h
 // load on the vector unit, which the splitting keeps busy.  Training steps (T, d, f, experts, k), us: 1500, 520, 776, 16, 2 256 -> 247; 2579, 592,
 // 880, 12, 2 470 -> 452; 1128, 452, 880, 32, 4 380 -> 366; 265, 712, 144, 4, 1 115 -> 113; 256, 128, 256, 8, 2 84.4 -> 83.6.  (With 64-bit
 // scalar bounds, whose comparisons are vector instructions, the small ones took 1 to 2 % longer than before.)
-// What lies past the end of the contraction becomes zero on the way to LDS; rows and columns past the end repeat the last ones (their
-// products are never stored).
+// Past the end of the contraction a load of an operand whose columns are contiguous returns zeros; one whose k is contiguous returns what
+// follows in memory up to the tile's last valid element, the next rows' beginnings, also in the k-tiles past the last one.  So mask() and
+// keep() make that part zero on the way to LDS (the k-tiles past the last one are not multiplied); rows and columns past the end repeat the last
+// ones (their products are never stored).  32 bits hold 64 rows: the entry points take d and f up to 4.2 million in fp32.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_descriptor(const float* base, int words) {
   uint64_t b = (uint64_t)base;
-  int bytes = 4 * max(0, words);          // (past the last k-tile: zeros, and memory is not touched)
+  int bytes = 4 * max(0, words);
   asm("" : "+s"(b), "+s"(bytes));         // both are wave-uniform: keep them in scalar registers
   return __builtin_amdgcn_make_buffer_rsrc((void*)b, 0, bytes, 0x00027000);
 }

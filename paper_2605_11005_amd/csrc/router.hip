@@ -539,8 +539,14 @@ int launch_router_fwd(const void* x, const void* wr, int dtype, int T, int d, in
     const int room = mfma_shape(dtype, T, d, E) ? router_fwd_splits(T, d, E) : 1;      // what the workspace holds
     int splits = 1;
     // The streaming kernel reads the weights once per 64 tokens.  Up to a block of 64 tokens by 128 experts per CU it is the
-    // faster one (whole calls, streaming / big tiles, us: T = 16384, d = 4096, E = 128 32 / 52; 8192, 4096, 256 31 / 56; 16384,
-    // 2048, 64 18 / 34; since then 14 to 22 % off the streaming side, one after the other 44 -> 37, 36 -> 29, 21 -> 18); beyond that it depends (32768, 4096, 128 75 / 89; 12000, 4096, 256 57 / 62; 32768, 7168, 256 271 / 161).
+    // faster one; beyond that it depends, mostly on d.  Calls one after the other (and with other memory written in between), streaming / big
+    // tiles, us:
+    //   within  T = 8192, d = 2048, E = 128 12.0 / 34.9 (22.8 / 43.7)    16384, 4096, 128 27.9 / 50.9 (56.4 / 73.4)    16384, 2048, 64 15.1 / 33.1 (33.8 / 49.3)
+    //           8192, 4096, 256 27.6 / 55.6 (43.8 / 71.0)                16384, 7168, 128 44.5 / 68.9 (88.4 / 110.7)   8192, 7168, 256 43.0 / 65.1 (64.2 / 83.5)
+    //   beyond  T = 20000, d = 4096, E = 128 47.1 / 55.0 (91.5 / 86.3)   32768, 4096, 128 67.6 / 83.4 (114.5 / 143.2)  32768, 2048, 64 30.7 / 44.0 (59.1 / 69.2)
+    //           12000, 4096, 256 51.0 / 59.8 (70.7 / 79.1)               12000, 7168, 256 81.9 / 72.9 (110.7 / 107.3)  32768, 7168, 256 230 / 152 (262 / 182)
+    // The two add a logit's products in different orders, so this line also decides bits; it has stayed where the two met before the
+    // streaming kernel loaded x through LDS.
     const bool stream = !mfma_shape(dtype, T, d, E) || (long long)tiles(T, 64) * tiles(E, 128) <= device_cu_count();
     int rc;
     if (stream) {
