@@ -1523,7 +1523,7 @@ __global__ __launch_bounds__(NT, 1) void gg_or_few(GArgs p, int d, int f) {
     q.A = p.A0; q.lda = p.lda; q.B0 = p.B0; q.B1 = p.B1; q.ldb = p.ldb; q.b_es = p.b_es;
     q.C0 = p.C0; q.C1 = p.C1; q.C2 = p.C2; q.ldc = p.ldc; q.off = p.off; q.e_cnt = p.e_cnt; q.N = p.N; q.K = p.K; q.cached = p.cached;
     const RaggedTiles<ROWS> list(q.off, q.e_cnt, threadIdx.x & 63);
-    for (int b = blockIdx.x; few_rows_tile<MODE == UP, NW_TILES>(q, list, reinterpret_cast<u32x4*>(smem), b); b += gridDim.x) {}
+    for (int b = blockIdx.x; few_rows_tile<MODE == UP, NW_TILES, true>(q, list, reinterpret_cast<u32x4*>(smem), b); b += gridDim.x) {}
     return;
   }
   gg_body<MODE, true>(p);

@@ -210,7 +210,7 @@ __device__ __forceinline__ void expert_tile(const SArgs& p, u32x4* lds, int e, i
   }
 }
 
-// Tile b of a launch over all experts; false: the list is shorter.
+// Tile b of a launch over all experts; false: the list is shorter.  MAY_STREAM: the experts may not fit the Infinity Cache (stream_rule.h).
 template <int NW> constexpr int FEW_ROWS_PLACES = 2 * (WEIGHT_PLACES<NW> + ROW_PLACES);      // LDS, 16 bytes each
 template <bool DUAL, int NW, bool STREAM>
 __device__ __forceinline__ void sized_tile(const SArgs& p, u32x4* lds, int e, int row0, int row_end, int n0, int tid) {
@@ -219,14 +219,14 @@ __device__ __forceinline__ void sized_tile(const SArgs& p, u32x4* lds, int e, in
   else if (rows <= 32) expert_tile<DUAL, 2, NW, STREAM>(p, lds, e, row0, row_end, n0, tid);
   else expert_tile<DUAL, 4, NW, STREAM>(p, lds, e, row0, row_end, n0, tid);
 }
-template <bool DUAL, int NW>
+template <bool DUAL, int NW, bool MAY_STREAM>
 __device__ __forceinline__ bool few_rows_tile(const SArgs& p, const RaggedTiles<ROWS>& list, u32x4* lds, int b) {
   constexpr int WIDTH = (DUAL ? 16 : 32) * NW;
   const int tid = threadIdx.x;
   int e, mt, nt;
   if (!list.tile((p.N + WIDTH - 1) / WIDTH, b, e, mt, nt)) return false;
   const int first = p.off[e], end = p.off[e + 1], row0 = first + mt * ROWS, row_end = min(end, row0 + ROWS);
-  if (stream_weights(list.active, p.cached, end - first, ROWS)) sized_tile<DUAL, NW, true>(p, lds, e, row0, row_end, nt * WIDTH, tid);
+  if (MAY_STREAM && stream_weights(list.active, p.cached, end - first, ROWS)) sized_tile<DUAL, NW, true>(p, lds, e, row0, row_end, nt * WIDTH, tid);
   else sized_tile<DUAL, NW, false>(p, lds, e, row0, row_end, nt * WIDTH, tid);
   return true;
 }
